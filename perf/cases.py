@@ -72,12 +72,13 @@ def draw(rng: random.Random):
         top = min(1 << 20, (1 << 33) * 144 // (D * (2 * M + K)))
         return dict(kind=kind, K=K, M=M, D=D, S=_log_int(rng, 1024, top), mod=mod, snr=snr)
     if kind == "train":
-        P = _log_int(rng, 64, 2048)
+        P = _log_int(rng, 64, 1536)
         return dict(kind=kind, K=rng.randint(2, 16), M=_log_int(rng, 8, 64), P=P, W=rng.randint(8, 32),
-                    cap=_log_int(rng, 64, 2048), mod=mod, snr=snr)
+                    cap=_log_int(rng, max(64, P // 2), 2048), mod=mod, snr=snr)
     if kind == "pocs":
-        return dict(kind=kind, K=rng.randint(2, 8), M=_log_int(rng, 8, 32), P=_log_int(rng, 64, 512),
-                    W=rng.randint(8, 32), cap=_log_int(rng, 64, 1024), mod=mod, snr=snr, cycles=rng.randint(2, 4),
+        P = _log_int(rng, 64, 512)
+        return dict(kind=kind, K=rng.randint(2, 8), M=_log_int(rng, 8, 32), P=P,
+                    W=rng.randint(8, 32), cap=_log_int(rng, max(64, P // 2), 1024), mod=mod, snr=snr, cycles=rng.randint(2, 4),
                     radius=round(rng.uniform(1.0, 6.0), 2))
     if kind == "batch_mixed":
         return dict(kind=kind, detectors=_log_int(rng, 4, 64), pmin=64, pmax=_log_int(rng, 128, 2048),
@@ -85,7 +86,7 @@ def draw(rng: random.Random):
     if kind == "batch_array":
         P = _log_int(rng, 512, 4096)
         return dict(kind=kind, detectors=rng.randint(2, 4), K=rng.randint(9, 16), M=rng.randint(33, 64), P=P,
-                    W=rng.randint(16, 32), cap=rng.randint(512, 4096), S=_log_int(rng, 4096, 131072), mod="qam16",
+                    W=rng.randint(16, 32), cap=rng.randint(max(512, P // 2), 4096), S=_log_int(rng, 4096, 131072), mod="qam16",
                     snr=snr)
     return dict(kind=kind, n=_log_int(rng, 2, 64), K=rng.randint(2, 8), M=_log_int(rng, 4, 16),
                 P=_log_int(rng, 32, 512), S=_log_int(rng, 128, 4096), W=rng.randint(4, 32),
@@ -185,7 +186,9 @@ def _unrolled_inputs(c, seed):
     insts = [_instance(seed, 100 + b, c["K"], c["M"], c["P"], c["S"], "qpsk", c["snr"]) for b in range(c["n"])]
     data = [torch.stack([i[k] for i in insts]).contiguous() for k in ("rx_pilot", "sym_pilot", "rx", "sym")]
     om = 0.5 + torch.rand(c["W"], generator=_gen(seed, 5), device="cuda")
-    return data, torch.cat([torch.tensor([0.7, 0.05, 1.0], device="cuda"), om])
+    # over-relaxed, with a wide slab: at mu = 1 the first projection of a pass
+    # ends exactly on the threshold, where the loss has no derivative
+    return data, torch.cat([torch.tensor([0.7, 0.2, 1.3], device="cuda"), om])
 
 
 # The arrays of a batch's detectors are views of one tensor each, every one
@@ -504,6 +507,7 @@ def exact(c, seed):
             for p, v in zip(_PARTS, m + [soft.cpu()]):
                 views[p][b].copy_(v)
         return [whole[p] for p in _PARTS]
-    if c["n"] * c["passes"] * c["P"] ** 2 * c["K"] > 5_000_000 or c["passes"] * c["P"] > 1500:
+    steps = 2 * c["P"] * c["passes"]
+    if steps > 3000 or steps * c["n"] * 2 * c["P"] * c["W"] > 4e9:     # its tape would not be held
         return None
     return _exact_unrolled(c, seed)
