@@ -214,10 +214,22 @@ struct UnrolledArgs {
   size_t inst_bytes;
   size_t off_G, off_D, off_ck, off_st, off_sc, off_tx, off_th, off_adj, off_X, off_fbar, off_lpart, off_spart,
       off_gpart;
-  int n, P, T, M2, M2P, K, KP, S, W, WP, passes, E;
+  // blocked form only: diagonal of K, coefficient totals after the passes,
+  // cbar0 and the taped cbar (off_G, off_D: K and H [TP][TP])
+  size_t off_kd, off_cst, off_cb0, off_tcb;
+  int n, P, T, TP, M2, M2P, K, KP, S, W, WP, passes, E;
   float wl, wg;
   float inv_count;          // 1 / (n * S * K)
 };
+// The blocked form (unrolled_blocked.hip) covers windows of at most 33
+// samples: a wave holds two 32-sample blocks, and the window must end in one
+// and start in the other.  Wider windows run member by member.
+constexpr int kGradParts = 3 + APSM_MAX_WINDOW;   // doubles of one (pass, step range): sigma, eps, mu, omega
+bool unrolled_in_blocks(int W);
+int unrolled_padded_steps(int T);                 // TP
+int unrolled_grad_chunks(int T);                  // step ranges of the gradient parts
+hipError_t launch_unrolled_passes(const UnrolledArgs& a, hipStream_t stream);
+hipError_t launch_unrolled_reverse(const UnrolledArgs& a, float* grad, const float* upstream, hipStream_t stream);
 size_t unrolled_pass_lds(const UnrolledArgs& a);
 size_t unrolled_reverse_lds(const UnrolledArgs& a);
 hipError_t launch_unrolled_forward(const UnrolledArgs& a, float* loss, hipStream_t stream);

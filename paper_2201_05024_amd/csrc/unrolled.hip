@@ -710,14 +710,18 @@ __global__ __launch_bounds__(kT) void unr_grad_kernel(UnrolledArgs a, float* gra
 
 template <int KP>
 hipError_t forward_k(const UnrolledArgs& a, float* loss, hipStream_t s) {
-  hipLaunchKernelGGL(unr_gram_kernel, dim3((a.T + 15) / 16, (a.T + 15) / 16, a.n), dim3(kT), 0, s, a);
-  constexpr int NT = seq_threads<KP>();
-  const size_t lds = unrolled_pass_lds(a);
-  auto pk = unr_pass_kernel<KP, NT, false>;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pk),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(pk, dim3(a.n), dim3(NT), lds, s, a, 0, a.passes);
+  if (unrolled_in_blocks(a.W)) {
+    if (hipError_t e = launch_unrolled_passes(a, s); e != hipSuccess) return e;
+  } else {
+    hipLaunchKernelGGL(unr_gram_kernel, dim3((a.T + 15) / 16, (a.T + 15) / 16, a.n), dim3(kT), 0, s, a);
+    constexpr int NT = seq_threads<KP>();
+    const size_t lds = unrolled_pass_lds(a);
+    auto pk = unr_pass_kernel<KP, NT, false>;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(pk),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(pk, dim3(a.n), dim3(NT), lds, s, a, 0, a.passes);
+  }
   const dim3 gv((2 * a.S + kT - 1) / kT, a.n);
   if (a.M2 <= 16) hipLaunchKernelGGL((unr_val_fwd_kernel<KP, 16>), gv, dim3(kT), 0, s, a);
   else if (a.M2 <= 32) hipLaunchKernelGGL((unr_val_fwd_kernel<KP, 32>), gv, dim3(kT), 0, s, a);
@@ -729,12 +733,14 @@ hipError_t forward_k(const UnrolledArgs& a, float* loss, hipStream_t s) {
 
 template <int KP>
 hipError_t backward_k(const UnrolledArgs& a, float* grad, const float* upstream, hipStream_t s) {
-  hipLaunchKernelGGL(unr_zero_gpart_kernel, dim3(a.n), dim3(kT), 0, s, a);
+  const bool blocks = unrolled_in_blocks(a.W);
+  if (!blocks) hipLaunchKernelGGL(unr_zero_gpart_kernel, dim3(a.n), dim3(kT), 0, s, a);
   const dim3 gb((a.T + 63) / 64 + 1, a.n);
   if (a.M2 <= 16) hipLaunchKernelGGL((unr_val_bwd_kernel<KP, 16>), gb, dim3(kT), 0, s, a);
   else if (a.M2 <= 32) hipLaunchKernelGGL((unr_val_bwd_kernel<KP, 32>), gb, dim3(kT), 0, s, a);
   else if (a.M2 <= 64) hipLaunchKernelGGL((unr_val_bwd_kernel<KP, 64>), gb, dim3(kT), 0, s, a);
   else hipLaunchKernelGGL((unr_val_bwd_kernel<KP, 128>), gb, dim3(kT), 0, s, a);
+  if (blocks) return launch_unrolled_reverse(a, grad, upstream, s);
   constexpr int NT = seq_threads<KP>();
   const size_t lds_p = unrolled_pass_lds(a);
   const size_t lds_r = unrolled_reverse_lds(a);

@@ -23,6 +23,7 @@ UnrolledArgs layout(const apsm_unrolled_t* u) {
   a.n = u->n_inst;
   a.P = u->P;
   a.T = 2 * u->P;
+  a.TP = unrolled_padded_steps(a.T);
   a.M2 = u->M2;
   a.M2P = (u->M2 + 3) / 4 * 4;
   a.K = u->K;
@@ -40,19 +41,30 @@ UnrolledArgs layout(const apsm_unrolled_t* u) {
   const size_t NC = (a.passes + a.E - 1) / a.E;
   const size_t Sr = 2 * (size_t)a.S;
   size_t o = 0;
-  a.off_G = o;     o = align256(o + T * T * 4);
-  a.off_D = o;     o = align256(o + T * T * 4);
-  a.off_ck = o;    o = align256(o + NC * SW * 4);
+  const bool blocks = unrolled_in_blocks(a.W);
+  const size_t TT = blocks ? (size_t)a.TP * a.TP : T * T;
+  const size_t tape = (size_t)a.E * T * a.W * (blocks ? (size_t)a.K : KP) * 4;
+  a.off_G = o;     o = align256(o + TT * 4);
+  a.off_D = o;     o = align256(o + TT * 4);
+  a.off_ck = o;    o = align256(o + NC * (blocks ? T * KP : SW) * 4);
   a.off_st = o;    o = align256(o + SW * 4);
-  a.off_sc = o;    o = align256(o + SW * 4);
-  a.off_tx = o;    o = align256(o + (size_t)a.E * T * a.W * KP * 4);
-  a.off_th = o;    o = align256(o + (size_t)a.E * T * a.W * KP * 4);
+  if (blocks) {
+    a.off_kd = o;  o = align256(o + (size_t)a.TP * 4);
+    a.off_cst = o; o = align256(o + T * KP * 4);
+    a.off_cb0 = o; o = align256(o + T * KP * 4);
+    a.off_tcb = o; o = align256(o + tape);
+  } else {
+    a.off_sc = o;  o = align256(o + SW * 4);
+  }
+  a.off_tx = o;    o = align256(o + tape);
+  a.off_th = o;    o = align256(o + tape);
   a.off_adj = o;   o = align256(o + SW * 4);
   a.off_X = o;     o = align256(o + T * KP * 4);
   a.off_fbar = o;  o = align256(o + Sr * KP * 4);
   a.off_lpart = o; o = align256(o + (Sr + 255) / 256 * 4);
   a.off_spart = o; o = align256(o + (T + 63) / 64 * 4);
-  a.off_gpart = o; o = align256(o + (4 + APSM_MAX_WINDOW) * 8);
+  a.off_gpart = o;
+  o = align256(o + (blocks ? (size_t)a.passes * unrolled_grad_chunks(a.T) * kGradParts : 4 + APSM_MAX_WINDOW) * 8);
   a.inst_bytes = o;
   return a;
 }

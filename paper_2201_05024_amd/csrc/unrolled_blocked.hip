@@ -1,0 +1,573 @@
+// Unrolled training in blocks (windows of at most 33 samples): the forward
+// passes, their re-runs with the tape and the reverse sweep as one kind of
+// sweep over 32-sample blocks (window_sweep.h).
+//
+// Nothing leaves the dictionary here, so a filter is its coefficient totals
+// C[d][k] alone: f_k(r_i) = sum_d K_id C_dk with K = wL r_i.r_d + wG G_id (w =
+// wL sum_d C_d r_d and alpha = wG C at the end).  A step adds c_j to C_j of
+// the window members and sum_j K_ij c_j to every prediction e_i still of use.
+// The taped sigma sums h_i = sum_d wG C_d G_id D_id move the same way with
+// H = wG G D.  The adjoint is again such a recursion: with X_j the step
+// adjoints xbar summed by sample, cbar_i = wL wbar.r_i + wG abar_i = cbar0_i +
+// sum_d K_id X_d (cbar0 from the validation loss), and a step adds
+// sum_j K_ij xbar_j.  Per step the reverse sweep needs x alone (for the
+// active set); it leaves cbar of the members on the tape, and the gradient
+// parts are sums over the tape, taken by a grid-wide kernel in a fixed order
+// that does not depend on the checkpoint interval.
+//
+// One workgroup per (instance, up to four users): four waves run a user each,
+// four evaluate the next block's members against the whole expansion.
+// Bound: the serial chain of a step, about 75 VALU instructions of one wave
+// (window rows 3: 48 of them the matrix-vector product).
+#include "apsm_internal.h"
+#include "window_sweep.h"
+
+namespace apsm {
+namespace {
+
+using namespace sweep;
+
+enum { kForward = 0, kTape = 1, kReverse = 2 };
+
+__device__ __forceinline__ float comp(const float* rx, int M2, int n, int m) {
+  const int M = M2 >> 1;
+  const float* src = rx + (size_t)(n >> 1) * M2;
+  if ((n & 1) == 0) return src[m];
+  return m < M ? src[m + M] : -src[m - M];
+}
+
+template <class T>
+__device__ __forceinline__ T* part_of(const UnrolledArgs& a, int b, size_t off) {
+  return reinterpret_cast<T*>(static_cast<unsigned char*>(a.ws) + (size_t)b * a.inst_bytes + off);
+}
+
+// K, H = wG G D [TP][TP] (zero past T) and the diagonal of K, 16 x 16 pairs
+// per workgroup.
+__global__ __launch_bounds__(256) void unb_gram_kernel(UnrolledArgs a) {
+  __shared__ float ri[16][APSM_MAX_M2 + 1], rj[16][APSM_MAX_M2 + 1];
+  const int b = blockIdx.z, TP = a.TP;
+  const float* rx = a.rx_pilot + (size_t)b * a.P * a.M2;
+  const int i0 = blockIdx.y * 16, j0 = blockIdx.x * 16;
+  for (int e = threadIdx.x; e < 16 * a.M2; e += 256) {
+    const int r = e / a.M2, m = e - r * a.M2;
+    ri[r][m] = i0 + r < a.T ? comp(rx, a.M2, i0 + r, m) : 0.0f;
+    rj[r][m] = j0 + r < a.T ? comp(rx, a.M2, j0 + r, m) : 0.0f;
+  }
+  __syncthreads();
+  const int ti = threadIdx.x / 16, tj = threadIdx.x % 16;
+  const int i = i0 + ti, j = j0 + tj;
+  float d = 0.0f, dot = 0.0f;
+  for (int m = 0; m < a.M2; ++m) {
+    const float x = ri[ti][m], y = rj[tj][m], t = x - y;
+    d = fmaf(t, t, d);
+    dot = fmaf(x, y, dot);
+  }
+  const bool in = i < a.T && j < a.T;
+  const float sigma = a.theta[0];
+  const float g = expf(-d * (1.0f / (2.0f * sigma * sigma)));
+  const float k = in ? fmaf(a.wl, dot, a.wg * g) : 0.0f;
+  part_of<float>(a, b, a.off_G)[(size_t)i * TP + j] = k;
+  part_of<float>(a, b, a.off_D)[(size_t)i * TP + j] = in ? a.wg * (g * d) : 0.0f;
+  if (i == j) part_of<float>(a, b, a.off_kd)[i] = k;
+}
+
+// LDS of a sweep, in floats.
+struct SweepLds {
+  int coef, panel, part, stage, ikn, om, qs, xs, total;
+  int panel_floats;      // one block's panels (K, and H with the tape)
+};
+__host__ __device__ inline SweepLds sweep_lds(int mode, int TP, int W) {
+  const int n2 = mode == kTape ? 2 : 1;
+  SweepLds l{};
+  int o = 0;
+  l.coef = o;  o += TP * kSerial;
+  l.part = o;  o += n2 * kPartFloats;
+  l.stage = o; o += kBlk * kSerial;
+  l.ikn = o;   o += kBlk;
+  l.om = o;    o += 64;
+  l.qs = o;    o += 64;
+  l.xs = o;    o += mode == kReverse ? 2 * kBlk * kSerial * W + 64 : 0;
+  l.panel = o; o += 2 * n2 * kPanelFloats;   // this block's and the one before
+  l.total = o;
+  l.panel_floats = n2 * kPanelFloats;
+  return l;
+}
+
+// One lane's state of a user's recursion.
+struct Lane {
+  float e, h;      // running prediction (cbar in the reverse sweep), sigma sum
+  float C;         // coefficients (xbar) not yet in the expansion
+  float b, ikn;    // target, -1 / kappa(r, r) (0 where that is not positive)
+  int d;           // sample, -1 for none
+};
+
+// 16 steps (or the fewer of the sequence's end) whose newest members lie in
+// row A of the wave; n0 the first of them, cnt their number.
+template <int MODE, int NRW, int A>
+__device__ __forceinline__ void sweep_row(Lane& s, const float* kreg, const float* hreg, int n0, int cnt, int W,
+                                          float eps, float qsW, const float* om, const float* qs, const float* xs,
+                                          int xstep, float* tx, float* th, size_t tstep, int lane) {
+#pragma clang fp contract(off)
+  if (cnt <= 0) return;
+  constexpr int DIR = MODE == kReverse ? -1 : 1;
+  int n = MODE == kReverse ? n0 + cnt - 1 : n0;
+  int age = (16 * A + n - n0 - lane) & 63;   // 33..63: not yet a member
+  float wv = om[age];
+  float xv = 0.0f;
+  if constexpr (MODE == kReverse) xv = xs[(n - n0) * xstep + age];
+  for (int it = 0; it < cnt; ++it, n += DIR) {
+    // weight of each lane's member (0 outside the window); the next step's
+    // reads are issued here, a step ahead of their use
+    const float q = n + 1 < W ? qs[n + 1] : qsW;
+    float t = (wv * q) * s.ikn;
+    const int cur = age;
+    const float xcur = xv;
+    age = (age + DIR) & 63;
+    wv = om[age];
+    if constexpr (MODE == kReverse) {
+      const int nx = it + 1 < cnt ? n - 1 - n0 : 0;
+      xv = xs[nx * xstep + age];
+    }
+    float c;
+    if constexpr (MODE == kReverse) {
+      // adjoint of the active members: xbar = -mu q cbar / kappa
+      t = fabsf(xcur) - eps > 0.0f ? t : 0.0f;
+      c = s.e * t;
+      if (cur < W) tx[(size_t)n * tstep + cur] = s.e;
+    } else {
+      const float x = s.e - s.b;
+      c = slab_residual(x, eps) * t;
+      if constexpr (MODE == kTape) {
+        if (cur < W) {
+          tx[(size_t)n * tstep + cur] = x;
+          th[(size_t)n * tstep + cur] = s.h;
+        }
+      }
+    }
+    s.C += c;
+    const Rows rows = broadcast_rows(c);
+    s.e += window_product<A, NRW>(rows, kreg);
+    if constexpr (MODE == kTape) s.h += window_product<A, NRW>(rows, hreg);
+  }
+}
+
+// Passes [p0, p1) of one instance and one group of at most four users.
+// Forward: from zero (p0 = 0), writing a checkpoint of C at every pass p % E
+// == 0 and C at the end.  Tape: from checkpoint p0 / E, writing x and h of
+// the window members of every step.  Reverse: passes p1 - 1 .. p0 backwards,
+// X carried in the workspace, writing cbar of the members.
+template <int MODE, int NRW>
+__global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int p0, int p1, int ku) {
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  constexpr bool REV = MODE == kReverse, TAPE = MODE == kTape;
+  const int inst = blockIdx.y, k0 = blockIdx.x * ku;
+  const int nu = a.K - k0 < ku ? a.K - k0 : ku;
+  const int T = a.T, TP = a.TP, W = a.W, K = a.K, KP = a.KP, NB = TP / kBlk;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int il = lane & 31;
+  const bool upper = lane >= 32;
+  const float* Km = part_of<float>(a, inst, a.off_G);
+  const float* Hm = part_of<float>(a, inst, a.off_D);
+  const float* kd = part_of<float>(a, inst, a.off_kd);
+  const float* cb0 = part_of<float>(a, inst, a.off_cb0);
+  float* const ck = part_of<float>(a, inst, a.off_ck);
+  const float* sym = a.sym_pilot + (size_t)inst * a.P * K * 2;
+  const SweepLds L = sweep_lds(MODE, TP, W);
+  float* const coef = lds + L.coef;
+  float* const panel = lds + L.panel;
+  float* const part = lds + L.part;
+  float* const stage = lds + L.stage;
+  float* const ikn = lds + L.ikn;
+  float* const om = lds + L.om;
+  float* const qs = lds + L.qs;
+  const float eps = a.theta[1], mu = a.theta[2];
+  if (tid < 64) {
+    om[tid] = tid < W ? a.theta[3 + tid] : 0.0f;
+    float z = 0.0f;                         // qs[l] = mu / (omega_0 + .. + omega_{l-1})
+    for (int s = 0; s < tid; ++s) z += s < W ? a.theta[3 + s] : 0.0f;
+    qs[tid] = tid > 0 ? mu / z : 0.0f;
+  }
+  float* const xg = part_of<float>(a, inst, a.off_X);
+  const float* src = REV ? xg : p0 == 0 ? nullptr : ck + (size_t)(p0 / a.E) * T * KP;
+  // lanes without a sample multiply what the panels hold by zero
+  for (int e = tid; e < 2 * L.panel_floats; e += kThreads) panel[e] = 0.0f;
+  for (int e = tid; e < TP * kSerial; e += kThreads) {
+    const int d = e >> 2, u = e & 3;
+    coef[e] = src && d < T && u < nu ? src[(size_t)d * KP + k0 + u] : 0.0f;
+  }
+  __syncthreads();
+  const float qsW = qs[W];
+
+  // What the block q entering at iteration i needs: its kernel panel, targets (or
+  // cbar0) and diagonal, the sums of its members over the expansion.
+  // In the reverse sweep also the taped x of the block stepped through then.
+  const int ht = tid - 64 * kSerial;        // helper thread
+  auto prepare = [&](int i, int p) {
+    const int q = REV ? NB - 1 - i : i, st = q + 1;
+    float* const pan = panel + (i & 1) * L.panel_floats;
+    if (q >= 0) {
+      for (int e = ht; e < kBlk * (kPanelCols / 4); e += 64 * kHelpers) {
+        const int r = e / (kPanelCols / 4), c4 = e - r * (kPanelCols / 4);
+        const int blk = REV ? q + 2 - (c4 >> 3) : q - 2 + (c4 >> 3);
+        floatx4 v = {0.0f, 0.0f, 0.0f, 0.0f}, vh = v;
+        if (blk >= 0 && blk < NB) {
+          const size_t o = (size_t)(kBlk * q + r) * TP + kBlk * blk + 4 * (c4 & 7);
+          v = *reinterpret_cast<const floatx4*>(Km + o);
+          if constexpr (TAPE) vh = *reinterpret_cast<const floatx4*>(Hm + o);
+        }
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+          pan[r * kPanelStr + 4 * c4 + x] = v[x];
+          if constexpr (TAPE) pan[kPanelFloats + r * kPanelStr + 4 * c4 + x] = vh[x];
+        }
+      }
+      if (ht < kBlk * kSerial) {
+        const int n = kBlk * q + (ht >> 2), uu = ht & 3;
+        float v = 0.0f;
+        if (n < T && uu < nu)
+          v = REV ? cb0[(size_t)n * KP + k0 + uu] : sym[((size_t)(n >> 1) * K + k0 + uu) * 2 + (n & 1)];
+        stage[ht] = v;
+      } else if (ht < kBlk * kSerial + kBlk) {
+        const float kj = kd[kBlk * q + ht - kBlk * kSerial];
+        ikn[ht - kBlk * kSerial] = kj > 0.0f ? -1.0f / kj : 0.0f;
+      }
+      BlockSums s;
+#pragma unroll
+      for (int v = 0; v < 8; ++v) s.v[v] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+      block_accumulate(s, Km + kBlk * q, TP, coef, TP, wave - kSerial, kHelpers, lane);
+      block_store(s, part, wave - kSerial, lane);
+      if constexpr (TAPE) {
+#pragma unroll
+        for (int v = 0; v < 8; ++v) s.v[v] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        block_accumulate(s, Hm + kBlk * q, TP, coef, TP, wave - kSerial, kHelpers, lane);
+        block_store(s, part + kPartFloats, wave - kSerial, lane);
+      }
+    }
+    if (REV && st >= 0 && st < NB) {
+      // taped x of the block's steps, [step][user][age]
+      float* dst = lds + L.xs + (st & 1) * kBlk * kSerial * W;
+      const int steps = T - kBlk * st < kBlk ? T - kBlk * st : kBlk;
+      const float* tx = part_of<float>(a, inst, a.off_tx) + (size_t)((p - p0) * T + kBlk * st) * K * W;
+      for (int e = ht; e < steps * nu * W; e += 64 * kHelpers) {
+        const int t = e / (nu * W), r = e - t * nu * W;
+        dst[t * kSerial * W + r] = tx[(size_t)t * K * W + k0 * W + r];
+      }
+    }
+  };
+
+  // Roles: the waves of users run the recursion, the helper waves prepare
+  // the next block; both keep to the same barriers (two per block, one per
+  // pass).  Separate loops, so that neither role's registers are live in the
+  // other.
+  const int nit = REV ? NB + 1 : NB;
+  if (wave < kSerial) {
+    const int u = wave;
+    const bool active = u < nu;
+    const int k = k0 + (active ? u : 0);
+    if (active) __builtin_amdgcn_s_setprio(3);
+    float kreg[64], hreg[TAPE ? 64 : 1];
+    Lane s{};
+    for (int pi = 0; pi < p1 - p0; ++pi) {
+      const int p = REV ? p1 - 1 - pi : p0 + pi;
+      s = Lane{};
+      s.d = -1;
+      float* const tw = part_of<float>(a, inst, REV ? a.off_tcb : a.off_tx) + ((size_t)(p - p0) * T * K + k) * W;
+      float* const thw = TAPE ? part_of<float>(a, inst, a.off_th) + ((size_t)(p - p0) * T * K + k) * W : nullptr;
+      for (int i = 0; i < nit; ++i) {
+        const int q = REV ? NB - 1 - i : i;   // block entering
+        const int st = REV ? q + 1 : q;       // block stepped through
+        __syncthreads();
+        if (active) {
+          // the lower half's block goes into the expansion, the upper half
+          // moves down, q's members come in with their sums and corrections
+          const float* pn = panel + (i & 1) * L.panel_floats;
+          const float* pv = panel + ((i + 1) & 1) * L.panel_floats;
+          float e = 0.0f, h = 0.0f, g = 0.0f, ik = 0.0f;
+          if (q >= 0) {
+            e = pending_sum(pn, s.C, lane);
+            if constexpr (TAPE) h = pending_sum(pn + kPanelFloats, s.C, lane);
+            float sum = 0.0f, sumh = 0.0f;
+#pragma unroll
+            for (int w = 0; w < kHelpers; ++w) {
+              sum += part[(w * kBlk + il) * kSerial + u];
+              if constexpr (TAPE) sumh += part[kPartFloats + (w * kBlk + il) * kSerial + u];
+            }
+            g = stage[il * kSerial + u];
+            ik = ikn[il];
+            e = sum + e;
+            if constexpr (REV) e = g + e;
+            h = sumh + h;
+          }
+          if (!upper && s.d >= 0) coef[s.d * kSerial + u] += s.C;
+          // (swaps outside the selects: they need every lane)
+          const int du = __float_as_int(upper_half(__int_as_float(s.d)));
+          const float eu = upper_half(s.e), Cu = upper_half(s.C), iu = upper_half(s.ikn);
+          s.e = upper ? e : eu;
+          s.C = upper ? 0.0f : Cu;
+          s.ikn = upper ? ik : iu;
+          s.d = !upper ? du : q >= 0 ? kBlk * q + il : -1;
+          if constexpr (TAPE) {
+            const float hu = upper_half(s.h);
+            s.h = upper ? h : hu;
+          }
+          if constexpr (!REV) {
+            const float bu = upper_half(s.b);
+            s.b = upper ? g : bu;
+          }
+          load_matrix(pn, pv, lane, kreg);
+          if constexpr (TAPE) load_matrix(pn + kPanelFloats, pv + kPanelFloats, lane, hreg);
+        }
+        __syncthreads();
+        if (active && st >= 0 && st < NB) {
+          const int n0 = kBlk * st, rem = T - n0;
+          const int c0 = rem < 16 ? rem : 16, c1 = rem < 16 ? 0 : rem < 32 ? rem - 16 : 16;
+          const float* xs = lds + L.xs + (st & 1) * kBlk * kSerial * W + u * W;
+          const size_t ts = (size_t)K * W;
+#define APSM_SWEEP_ROW(A, n, c)                                                                       \
+  sweep_row<MODE, NRW, A>(s, kreg, hreg, n, c, W, eps, qsW, om, qs, xs + ((n) - n0) * kSerial * W, \
+                          kSerial * W, tw, thw, ts, lane)
+          // forward the steps' block is the upper half, in reverse the lower
+          if constexpr (REV) {
+            APSM_SWEEP_ROW(1, n0 + 16, c1);
+            APSM_SWEEP_ROW(0, n0, c0);
+          } else {
+            APSM_SWEEP_ROW(2, n0, c0);
+            APSM_SWEEP_ROW(3, n0 + 16, c1);
+          }
+#undef APSM_SWEEP_ROW
+        }
+      }
+      // the pass ends: what is pending goes into the expansion
+      if (active && s.d >= 0) coef[s.d * kSerial + u] += s.C;
+      __syncthreads();
+    }
+  } else {
+    for (int pi = 0; pi < p1 - p0; ++pi) {
+      const int p = REV ? p1 - 1 - pi : p0 + pi;
+      if (MODE == kForward && p % a.E == 0) {
+        float* dst = ck + (size_t)(p / a.E) * T * KP;
+        for (int e = ht; e < T * kSerial; e += 64 * kHelpers)
+          if ((e & 3) < nu) dst[(size_t)(e >> 2) * KP + k0 + (e & 3)] = coef[e];
+      }
+      prepare(0, p);
+      for (int i = 0; i < nit; ++i) {
+        __syncthreads();
+        __syncthreads();
+        if (i + 1 < nit) prepare(i + 1, p);
+      }
+      __syncthreads();
+    }
+  }
+  if (MODE == kTape) return;
+  float* dst = REV ? xg : part_of<float>(a, inst, a.off_cst);
+  for (int e = tid; e < T * kSerial; e += kThreads)
+    if ((e & 3) < nu) dst[(size_t)(e >> 2) * KP + k0 + (e & 3)] = coef[e];
+}
+
+// The filter for the validation kernels: w = wL sum_d C_d r_d (workgroup k),
+// alpha = wG C.
+__global__ __launch_bounds__(256) void unb_state_kernel(UnrolledArgs a) {
+  __shared__ float red[256];
+  const int k = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
+  const float* C = part_of<float>(a, b, a.off_cst);
+  float* w = part_of<float>(a, b, a.off_st);
+  float* alpha = w + a.K * a.M2P;
+  const float* rx = a.rx_pilot + (size_t)b * a.P * a.M2;
+  // component m by the threads m, m + MW, ..: each a share of the samples
+  int MW = 1;
+  while (MW < a.M2) MW <<= 1;
+  const int m = tid & (MW - 1), part = tid / MW, np = 256 / MW;
+  float acc = 0.0f;
+  if (m < a.M2)
+    for (int d = part; d < a.T; d += np) acc = fmaf(C[(size_t)d * a.KP + k], comp(rx, a.M2, d, m), acc);
+  red[tid] = acc;
+  __syncthreads();
+  if (part == 0 && m < a.M2P) {
+    float sum = 0.0f;
+    for (int q = 0; q < np; ++q) sum += red[q * MW + m];
+    w[k * a.M2P + m] = m < a.M2 ? a.wl * sum : 0.0f;
+  }
+  for (int d = tid; d < a.T; d += 256) alpha[(size_t)d * a.KP + k] = a.wg * C[(size_t)d * a.KP + k];
+  if (k == 0)                               // padded users
+    for (int e = tid; e < a.T * (a.KP - a.K); e += 256)
+      alpha[(size_t)(e / (a.KP - a.K)) * a.KP + a.K + e % (a.KP - a.K)] = 0.0f;
+}
+
+// cbar0_ik = wL wbar_k . r_i + wG abar0_ik; X starts from zero.
+__global__ __launch_bounds__(256) void unb_adjoint_start_kernel(UnrolledArgs a) {
+  __shared__ float wb[APSM_MAX_K * APSM_MAX_M2];
+  const int b = blockIdx.y;
+  const float* wbar = part_of<float>(a, b, a.off_adj);
+  const float* abar = wbar + a.K * a.M2P;
+  for (int e = threadIdx.x; e < a.K * a.M2P; e += 256) wb[e] = wbar[e];
+  __syncthreads();
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= a.T) return;
+  const float* rx = a.rx_pilot + (size_t)b * a.P * a.M2;
+  float* cb0 = part_of<float>(a, b, a.off_cb0);
+  float* X = part_of<float>(a, b, a.off_X);
+  float acc[APSM_MAX_K];
+#pragma unroll
+  for (int k = 0; k < APSM_MAX_K; ++k) acc[k] = 0.0f;
+  for (int m = 0; m < a.M2; ++m) {
+    const float x = comp(rx, a.M2, i, m);
+#pragma unroll
+    for (int k = 0; k < APSM_MAX_K; ++k)
+      if (k < a.K) acc[k] = fmaf(wb[k * a.M2P + m], x, acc[k]);
+  }
+#pragma unroll
+  for (int k = 0; k < APSM_MAX_K; ++k)
+    if (k < a.K) {
+      cb0[(size_t)i * a.KP + k] = fmaf(a.wl, acc[k], a.wg * abar[(size_t)i * a.KP + k]);
+      X[(size_t)i * a.KP + k] = 0.0f;
+    }
+}
+
+// Gradient parts of pass p0 + blockIdx.y, steps 256 blockIdx.x .., from the
+// tape (x, h, cbar): sigma (times sigma^3), eps, mu, omega.  A thread keeps
+// one window position; the sums over positions of a step are taken within
+// its group of WP lanes.
+constexpr int kGradSteps = 256;
+__global__ __launch_bounds__(256) void unb_gradient_kernel(UnrolledArgs a, int p0) {
+#pragma clang fp contract(off)
+  __shared__ double red[256];
+  __shared__ float om[64], zs[65];
+  const int b = blockIdx.z, p = p0 + blockIdx.y, tid = threadIdx.x;
+  const int W = a.W, WP = a.WP, K = a.K, T = a.T;
+  if (tid < 64) om[tid] = tid < W ? a.theta[3 + tid] : 0.0f;
+  if (tid <= W) {
+    float z = 0.0f;
+    for (int s = 0; s < tid; ++s) z += a.theta[3 + s];
+    zs[tid] = z;
+  }
+  __syncthreads();
+  const float eps = a.theta[1], mu = a.theta[2];
+  const float* kd = part_of<float>(a, b, a.off_kd);
+  const size_t base = (size_t)blockIdx.y * T * K * W;
+  const float* tx = part_of<float>(a, b, a.off_tx) + base;
+  const float* th = part_of<float>(a, b, a.off_th) + base;
+  const float* tc = part_of<float>(a, b, a.off_tcb) + base;
+  const int s = tid & (WP - 1), g = tid / WP, ng = 256 / WP;
+  const int nlo = blockIdx.x * kGradSteps, nhi = nlo + kGradSteps < T ? nlo + kGradSteps : T;
+  double gs = 0.0, ge = 0.0, gm = 0.0, go = 0.0;
+  for (int r = nlo * K + g; r - g < nhi * K; r += ng) {
+    const int n = r / K;                    // (step, user) pair r
+    const int Lw = n + 1 < W ? n + 1 : W;
+    const bool on = r < nhi * K && s < Lw;
+    float qp = 0.0f, q = 0.0f, Z = 1.0f;
+    if (on) {
+      const size_t o = (size_t)r * W + s;
+      const float x = tx[o], h = th[o], cb = tc[o], kjj = kd[n - s];
+      Z = zs[Lw];
+      q = om[s] / Z;
+      const float mag = fabsf(x) - eps;
+      const bool act = mag > 0.0f && kjj > 0.0f;
+      const float beta = act ? -copysignf(mag, x) / kjj : 0.0f;
+      const float bb = mu * q * cb;
+      gm += (double)(q * beta * cb);
+      qp = mu * beta * cb;
+      if (act) {
+        ge += (double)((x > 0.0f ? bb : -bb) / kjj);
+        gs += (double)(-bb / kjj) * (double)h;
+      }
+    }
+    float qq = qp * q;
+    for (int off = WP >> 1; off > 0; off >>= 1) qq += __shfl_xor(qq, off);
+    if (on) go += (double)((qp - qq) / Z);
+  }
+  double* out = part_of<double>(a, b, a.off_gpart) + ((size_t)p * gridDim.x + blockIdx.x) * kGradParts;
+  const double parts[3] = {gs, ge, gm};
+  for (int v = 0; v < 3; ++v) {
+    red[tid] = parts[v];
+    __syncthreads();
+    for (int o = 128; o > 0; o >>= 1) {
+      if (tid < o) red[tid] += red[tid + o];
+      __syncthreads();
+    }
+    if (tid == 0) out[v] = red[0];
+    __syncthreads();
+  }
+  red[tid] = go;
+  __syncthreads();
+  if (tid < W) {
+    double t = 0.0;
+    for (int v = 0; v < ng; ++v) t += red[v * WP + tid];
+    out[3 + tid] = t;
+  }
+}
+
+// grad = upstream * (sum over instances, passes and step ranges of the
+// parts, in a fixed order); sigma gets the validation part and 1/sigma^3.
+// One workgroup per gradient component.
+__global__ __launch_bounds__(256) void unb_grad_sum_kernel(UnrolledArgs a, float* grad, const float* upstream) {
+  __shared__ double red[256];
+  const int q = blockIdx.x, tid = threadIdx.x;
+  const int nch = (a.T + kGradSteps - 1) / kGradSteps, per = a.passes * nch, nib = (a.T + 63) / 64;
+  double acc = 0.0;
+  for (int e = tid; e < a.n * per; e += 256)
+    acc += part_of<double>(a, e / per, a.off_gpart)[(size_t)(e % per) * kGradParts + q];
+  if (q == 0)
+    for (int e = tid; e < a.n * nib; e += 256) acc += (double)part_of<float>(a, e / nib, a.off_spart)[e % nib];
+  red[tid] = acc;
+  __syncthreads();
+  for (int o = 128; o > 0; o >>= 1) {
+    if (tid < o) red[tid] += red[tid + o];
+    __syncthreads();
+  }
+  if (tid == 0) {
+    double v = red[0];
+    if (q == 0) {
+      const double sg = a.theta[0];
+      v /= sg * sg * sg;
+    }
+    grad[q] = (float)(v * (upstream ? (double)upstream[0] : 1.0));
+  }
+}
+
+template <int MODE, int NRW>
+hipError_t launch_sweep_w(const UnrolledArgs& a, int p0, int p1, hipStream_t s) {
+  auto kern = unb_sweep_kernel<MODE, NRW>;
+  const size_t bytes = sweep_lds(MODE, a.TP, a.W).total * sizeof(float);
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e != hipSuccess) return e;
+  const int groups = (a.K + kSerial - 1) / kSerial, ku = (a.K + groups - 1) / groups;
+  hipLaunchKernelGGL(kern, dim3(groups, a.n), dim3(kThreads), bytes, s, a, p0, p1, ku);
+  return hipGetLastError();
+}
+
+template <int MODE>
+hipError_t launch_sweep(const UnrolledArgs& a, int p0, int p1, hipStream_t s) {
+  return window_rows(a.W) == 2 ? launch_sweep_w<MODE, 2>(a, p0, p1, s) : launch_sweep_w<MODE, 3>(a, p0, p1, s);
+}
+
+}  // namespace
+
+bool unrolled_in_blocks(int W) { return W <= kMaxWindow; }
+int unrolled_padded_steps(int T) { return (T + kBlk - 1) / kBlk * kBlk; }
+int unrolled_grad_chunks(int T) { return (T + kGradSteps - 1) / kGradSteps; }
+
+hipError_t launch_unrolled_passes(const UnrolledArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(unb_gram_kernel, dim3(a.TP / 16, a.TP / 16, a.n), dim3(256), 0, s, a);
+  hipError_t e = launch_sweep<kForward>(a, 0, a.passes, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(unb_state_kernel, dim3(a.K, a.n), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_unrolled_reverse(const UnrolledArgs& a, float* grad, const float* upstream, hipStream_t s) {
+  hipLaunchKernelGGL(unb_adjoint_start_kernel, dim3((a.T + 255) / 256, a.n), dim3(256), 0, s, a);
+  const int nseg = (a.passes + a.E - 1) / a.E;
+  for (int sgm = nseg - 1; sgm >= 0; --sgm) {
+    const int p0 = sgm * a.E;
+    const int p1 = p0 + a.E < a.passes ? p0 + a.E : a.passes;
+    hipError_t e = launch_sweep<kTape>(a, p0, p1, s);
+    if (e == hipSuccess) e = launch_sweep<kReverse>(a, p0, p1, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(unb_gradient_kernel, dim3(unrolled_grad_chunks(a.T), p1 - p0, a.n), dim3(256), 0, s, a, p0);
+  }
+  hipLaunchKernelGGL(unb_grad_sum_kernel, dim3(3 + a.W), dim3(256), 0, s, a, grad, upstream);
+  return hipGetLastError();
+}
+
+}  // namespace apsm

@@ -1,0 +1,220 @@
+// Device pieces of the blocked window recursion, shared by the training and
+// the unrolled-training kernels.
+//
+// The windowed projections are serial in the steps n, but what is serial is
+// small: of everything a step touches, only the window members' coefficients
+// change.  Samples are taken in blocks of 32.  At the start of a block the
+// predictions f(r_i) of its 32 members are evaluated at once against the
+// whole expansion (a matrix product, done by other waves while the previous
+// block runs); inside the block every step's update is applied to all
+// members of the block and of the one before it, so a member entering the
+// window has its prediction ready.  With W <= 33 these are 64 samples, one
+// per lane of a wave: one wave runs the recursion of one user with no
+// barrier and no LDS exchange inside a block.  A step is: projection
+// coefficient c of each lane (zero outside the window), then
+// e_l += sum_j K_lj c_j with the 64 x 64 kernel matrix in registers, the
+// coefficients brought to the lanes by row broadcasts (permlane swaps) and
+// DPP row rotations inside v_fmac_f32.
+//
+// The entering block is in the upper half of the wave, the block adjacent to
+// it in the lower half; from block to block the upper half moves down.
+// Register k[16 s + r] of lane l is the kernel value of lane l's sample and
+// the one of lane 16 s + ((l - r) & 15).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+namespace apsm {
+namespace sweep {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+constexpr int kBlk = 32;                   // samples per block
+constexpr int kPanelCols = 96;             // kernel panel of a block: [block leaving | adjacent block | itself]
+constexpr int kPanelStr = 97;              // its row stride in LDS (odd: the diagonal reads of load_matrix spread over banks)
+constexpr int kPanelFloats = kBlk * kPanelStr;
+constexpr int kMaxWindow = 33;             // a window ends inside a block and reaches at most into the one before
+constexpr int kSerial = 4;                 // recursion waves of a workgroup (one user each, one per SIMD)
+constexpr int kHelpers = 4;                // waves evaluating the next block's members meanwhile
+constexpr int kThreads = 64 * (kSerial + kHelpers);
+constexpr int kPartFloats = kHelpers * kBlk * kSerial;
+
+// Rows of 16 lanes a window of W samples can touch.
+__host__ __device__ constexpr int window_rows(int W) { return W <= 17 ? 2 : 3; }
+
+#define APSM_FMAC(i, r) "v_fmac_f32_dpp %0, %1, %" #i " row_ror:" #r " row_mask:0xf bank_mask:0xf\n\t"
+#define APSM_FMAC_ROW                                                                                     \
+  APSM_FMAC(3, 1) APSM_FMAC(4, 2) APSM_FMAC(5, 3) APSM_FMAC(6, 4) APSM_FMAC(7, 5) APSM_FMAC(8, 6)         \
+  APSM_FMAC(9, 7) APSM_FMAC(10, 8) APSM_FMAC(11, 9) APSM_FMAC(12, 10) APSM_FMAC(13, 11) APSM_FMAC(14, 12) \
+  APSM_FMAC(15, 13) APSM_FMAC(16, 14) APSM_FMAC(17, 15)
+#define APSM_ROW_IN(x, k)                                                                              \
+  "v"(x), "v"((k)[0]), "v"((k)[1]), "v"((k)[2]), "v"((k)[3]), "v"((k)[4]), "v"((k)[5]), "v"((k)[6]),  \
+      "v"((k)[7]), "v"((k)[8]), "v"((k)[9]), "v"((k)[10]), "v"((k)[11]), "v"((k)[12]), "v"((k)[13]),  \
+      "v"((k)[14]), "v"((k)[15])
+
+// acc (+)= sum_r k[r] * (x of the lane r places back in its 16-lane row).
+// The compiler does not fold the rotation into the FMA (it emits a move and
+// an FMA, twice the instructions).  The leading s_nop covers the two wait
+// states a DPP read needs after the write of x.
+__device__ __forceinline__ void row_mul(float& acc, float x, const float* k) {
+  asm("s_nop 1\n\tv_mul_f32_e32 %0, %1, %2\n\t" APSM_FMAC_ROW : "=&v"(acc) : APSM_ROW_IN(x, k));
+}
+__device__ __forceinline__ void row_fma(float& acc, float x, const float* k) {
+  asm("s_nop 1\n\tv_fmac_f32_e32 %0, %1, %2\n\t" APSM_FMAC_ROW : "+v"(acc) : APSM_ROW_IN(x, k));
+}
+
+// The four 16-lane rows of x, each broadcast to every row.
+struct Rows {
+  float r[4];
+};
+__device__ __forceinline__ Rows broadcast_rows(float x) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  const auto p = __builtin_amdgcn_permlane32_swap(a[0], a[0], false, false);
+  const auto q = __builtin_amdgcn_permlane32_swap(a[1], a[1], false, false);
+  return {{__uint_as_float(p[0]), __uint_as_float(q[0]), __uint_as_float(p[1]), __uint_as_float(q[1])}};
+}
+
+// sum_j K_lj c_j over the rows A, A - 1, .. (mod 4; NRW of them) that the
+// window ending in row A touches.
+template <int A, int NRW>
+__device__ __forceinline__ float window_product(const Rows& c, const float* k) {
+  float acc;
+  row_mul(acc, c.r[A], k + 16 * A);
+  row_fma(acc, c.r[(A + 3) & 3], k + 16 * ((A + 3) & 3));
+  if constexpr (NRW > 2) row_fma(acc, c.r[(A + 2) & 3], k + 16 * ((A + 2) & 3));
+  return acc;
+}
+
+// The residual of eqn:beta: sign(x) max(|x| - eps, 0), 0 for a NaN.
+__device__ __forceinline__ float slab_residual(float x, float eps) {
+  const float m = fabsf(x) - eps;
+  return m > 0.0f ? copysignf(m, x) : 0.0f;
+}
+
+// Corrections of the entering block's members for the coefficients C pending
+// in the lanes, which the expansion does not hold yet: the lower half of the
+// wave has those of the block about to leave (panel columns 0..31), the
+// upper half those of the adjacent block (columns 32..63).  Both halves get
+// the sum for member lane % 32.
+__device__ __forceinline__ float pending_sum(const float* panel, float C, int lane) {
+  const float* row = panel + (lane & 31) * kPanelStr + (lane & 32);
+  float kf[32];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int jj = (lane - r) & 15;
+    kf[r] = row[jj];
+    kf[16 + r] = row[16 + jj];
+  }
+  const auto y = __builtin_amdgcn_permlane16_swap(__float_as_uint(C), __float_as_uint(C), false, false);
+  float f;
+  row_mul(f, __uint_as_float(y[0]), kf);
+  row_fma(f, __uint_as_float(y[1]), kf + 16);
+  const auto z = __builtin_amdgcn_permlane32_swap(__float_as_uint(f), __float_as_uint(f), false, false);
+  return __uint_as_float(z[0]) + __uint_as_float(z[1]);
+}
+
+// The upper half's value in both halves.
+__device__ __forceinline__ float upper_half(float x) {
+  const auto z = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(z[1]);
+}
+
+// The register matrix once the entering block holds the upper half and the
+// adjacent one the lower half: panel is the entering block's, prev the
+// adjacent block's own.
+__device__ __forceinline__ void load_matrix(const float* panel, const float* prev, int lane, float* k) {
+  const int il = lane & 31;
+  const bool fresh = lane >= 32;
+  // against the adjacent block's members: panel[il][32 + jj] (entering) or prev[il][64 + jj]
+  const float* a = (fresh ? panel + 32 : prev + 64) + il * kPanelStr;
+  // against the entering block's: panel[il][64 + jj] or, transposed, panel[jj][32 + il]
+  const float* b = fresh ? panel + il * kPanelStr + 64 : panel + 32 + il;
+  const int str = fresh ? 1 : kPanelStr;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int jj = (lane - r) & 15;
+    k[r] = a[jj];
+    k[16 + r] = a[16 + jj];
+    k[32 + r] = b[jj * str];
+    k[48 + r] = b[(jj + 16) * str];
+  }
+}
+
+// Evaluation of a block's 32 members against the entries d in [0, n) by the
+// helper waves, four users at a time, on v_mfma_f32_4x4x1_16b_f32: its 16
+// blocks take 16 entries, rows four members, columns the users.  vals: the
+// kernel values, entry d's 32 members contiguous at vals + d * stride
+// (16-byte aligned); coef: [n][4] coefficients (LDS or global); n a multiple
+// of 16.  Helper hw takes every NH-th group of 16 entries; its sums over them go
+// to part[hw][member][user].
+struct BlockSums {
+  floatx4 v[8];
+};
+
+template <class Coef>
+__device__ __forceinline__ void block_accumulate(BlockSums& a, const float* vals, size_t stride, const Coef* coef,
+                                                 int n, int hw, int nh, int lane) {
+  const int b = lane >> 2, r = lane & 3;
+  constexpr int U = 4;                     // groups in flight
+  int d0 = 16 * hw;
+  for (; d0 + 16 * nh * (U - 1) < n; d0 += 16 * nh * U) {
+    floatx4 x[U][2];
+    float c[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      const int d = d0 + 16 * nh * q;
+      const float* p = vals + (size_t)(d + b) * stride + 8 * r;
+      x[q][0] = *reinterpret_cast<const floatx4*>(p);
+      x[q][1] = *reinterpret_cast<const floatx4*>(p + 4);
+      c[q] = coef[(size_t)d * 4 + lane];
+    }
+#pragma unroll
+    for (int q = 0; q < U; ++q)
+#pragma unroll
+      for (int v = 0; v < 8; ++v)
+        a.v[v] = __builtin_amdgcn_mfma_f32_4x4x1f32(x[q][v >> 2][v & 3], c[q], a.v[v], 0, 0, 0);
+  }
+  for (; d0 < n; d0 += 16 * nh) {
+    const float* p = vals + (size_t)(d0 + b) * stride + 8 * r;
+    const floatx4 x0 = *reinterpret_cast<const floatx4*>(p), x1 = *reinterpret_cast<const floatx4*>(p + 4);
+    const float c = coef[(size_t)d0 * 4 + lane];
+#pragma unroll
+    for (int v = 0; v < 8; ++v)
+      a.v[v] = __builtin_amdgcn_mfma_f32_4x4x1f32(v < 4 ? x0[v & 3] : x1[v & 3], c, a.v[v], 0, 0, 0);
+  }
+}
+
+// Sums over the 16 blocks (lane bits 2..5): accumulator (v, r) is member
+// 8 r + v.  Half swaps, then row swaps, each adding two values into one and
+// leaving the pair on the two sides; the last two bits by row rotations.
+__device__ __forceinline__ void block_store(const BlockSums& a, float* part, int hw, int lane) {
+  float q[32];
+#pragma unroll
+  for (int v = 0; v < 8; ++v)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) q[4 * v + r] = a.v[v][r];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(q[i]), __float_as_uint(q[i + 16]), false, false);
+    q[i] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(q[i]), __float_as_uint(q[i + 8]), false, false);
+    q[i] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    q[i] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(q[i]), 0x128, 0xF, 0xF, true));
+    q[i] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(q[i]), 0x124, 0xF, 0xF, true));
+  }
+  if ((lane & 12) == 0) {
+    const int row = lane >> 4, u = lane & 3;
+    const int v0 = 4 * (row >> 1) + 2 * (row & 1);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) part[(hw * kBlk + 8 * (i & 3) + v0 + (i >> 2)) * kSerial + u] = q[i];
+  }
+}
+
+}  // namespace sweep
+}  // namespace apsm

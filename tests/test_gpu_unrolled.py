@@ -133,3 +133,17 @@ def test_unrolled_full_batch_checkpoint_invariance():
     assert np.all(np.isfinite(g5)) and np.isfinite(L5)
     assert L5 == L20
     np.testing.assert_array_equal(g5, g20)
+
+
+@pytest.mark.parametrize("K,P,W", [(1, 1, 1), (4, 8, 16), (5, 16, 17), (3, 17, 18), (8, 33, 32), (16, 49, 33), (2, 40, 34)])
+def test_unrolled_block_edges(K, P, W):
+    """Windows and sequence lengths at the edges of the 32-sample blocks: one
+    block, whole blocks and remainders, windows of two and of three lane rows,
+    the widest the blocks hold (33) and the first past it (34)."""
+    announce(f"unrolled blocks: K={K} P={P} W={W}")
+    host, dev = make(2, K, 4, P, 20, seed=1000 + W)
+    theta = [0.7, 0.2, 1.3] + list(np.linspace(1.0, 0.4, W))
+    L, g = gpu_loss_grad(theta, dev, 3, 2)
+    L_ref, g_ref = U.loss_and_grad(theta, host, 3)
+    assert abs(L - L_ref) <= 1e-4 * L_ref, (L, L_ref)
+    assert_grad_close(g, g_ref)
