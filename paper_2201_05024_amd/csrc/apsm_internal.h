@@ -215,8 +215,8 @@ struct UnrolledArgs {
   size_t off_G, off_D, off_ck, off_st, off_sc, off_tx, off_th, off_adj, off_X, off_fbar, off_lpart, off_spart,
       off_gpart;
   // blocked form only: diagonal of K, coefficient totals after the passes,
-  // cbar0 and the taped cbar (off_G, off_D: K and H [TP][TP])
-  size_t off_kd, off_cst, off_cb0, off_tcb;
+  // cbar0, the taped cbar and the register images (off_G, off_D: K and H)
+  size_t off_kd, off_cst, off_cb0, off_tcb, off_img;
   int n, P, T, TP, M2, M2P, K, KP, S, W, WP, passes, E;
   float wl, wg;
   float inv_count;          // 1 / (n * S * K)
@@ -227,6 +227,7 @@ struct UnrolledArgs {
 constexpr int kGradParts = 3 + APSM_MAX_WINDOW;   // doubles of one (pass, step range): sigma, eps, mu, omega
 bool unrolled_in_blocks(int W);
 int unrolled_padded_steps(int T);                 // TP
+size_t unrolled_image_bytes(int T);
 int unrolled_grad_chunks(int T);                  // step ranges of the gradient parts
 hipError_t launch_unrolled_passes(const UnrolledArgs& a, hipStream_t stream);
 hipError_t launch_unrolled_reverse(const UnrolledArgs& a, float* grad, const float* upstream, hipStream_t stream);

@@ -53,6 +53,7 @@ UnrolledArgs layout(const apsm_unrolled_t* u) {
     a.off_cst = o; o = align256(o + T * KP * 4);
     a.off_cb0 = o; o = align256(o + T * KP * 4);
     a.off_tcb = o; o = align256(o + tape);
+    a.off_img = o; o = align256(o + unrolled_image_bytes(a.T));
   } else {
     a.off_sc = o;  o = align256(o + SW * 4);
   }

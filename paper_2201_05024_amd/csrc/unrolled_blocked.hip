@@ -29,6 +29,15 @@ using namespace sweep;
 
 enum { kForward = 0, kTape = 1, kReverse = 2 };
 
+// Helper waves of a sweep: they read a strip of the kernel matrix (128 KiB
+// at T = 1024) per block while the block before takes about 6 us, which is a
+// matter of loads in flight: 64 x 20 x 1024 steps forward took 6.9 ms with 4,
+// 4.9 ms with 8.  With the tape (two strips, 156 registers) 12 waves fit a CU,
+// else 16; the forward passes keep to the tape's number, so that a re-run
+// sums in the same order and gives the same bits.
+constexpr int helpers(int mode) { return mode == kReverse ? 12 : 8; }
+constexpr int part_floats(int mode) { return helpers(mode) * kBlk * kSerial; }
+
 __device__ __forceinline__ float comp(const float* rx, int M2, int n, int m) {
   const int M = M2 >> 1;
   const float* src = rx + (size_t)(n >> 1) * M2;
@@ -41,8 +50,14 @@ __device__ __forceinline__ T* part_of(const UnrolledArgs& a, int b, size_t off) 
   return reinterpret_cast<T*>(static_cast<unsigned char*>(a.ws) + (size_t)b * a.inst_bytes + off);
 }
 
-// K, H = wG G D [TP][TP] (zero past T) and the diagonal of K, 16 x 16 pairs
-// per workgroup.
+// Where K_ij and H_ij live: the 32 columns of a block together, [block][i][32],
+// so that a block's members against every entry are one contiguous stretch.
+__host__ __device__ __forceinline__ size_t pair_at(int TP, int i, int j) {
+  return ((size_t)(j >> 5) * TP + i) * kBlk + (j & 31);
+}
+
+// K, H = wG G D of all pairs (zero past T) and the diagonal of K, 16 x 16
+// pairs per workgroup.
 __global__ __launch_bounds__(256) void unb_gram_kernel(UnrolledArgs a) {
   __shared__ float ri[16][APSM_MAX_M2 + 1], rj[16][APSM_MAX_M2 + 1];
   const int b = blockIdx.z, TP = a.TP;
@@ -66,30 +81,64 @@ __global__ __launch_bounds__(256) void unb_gram_kernel(UnrolledArgs a) {
   const float sigma = a.theta[0];
   const float g = expf(-d * (1.0f / (2.0f * sigma * sigma)));
   const float k = in ? fmaf(a.wl, dot, a.wg * g) : 0.0f;
-  part_of<float>(a, b, a.off_G)[(size_t)i * TP + j] = k;
-  part_of<float>(a, b, a.off_D)[(size_t)i * TP + j] = in ? a.wg * (g * d) : 0.0f;
+  part_of<float>(a, b, a.off_G)[pair_at(TP, i, j)] = k;
+  part_of<float>(a, b, a.off_D)[pair_at(TP, i, j)] = in ? a.wg * (g * d) : 0.0f;
   if (i == j) part_of<float>(a, b, a.off_kd)[i] = k;
+}
+
+// Register images of every entering block: K forward, H forward, K backward
+// (in that order, [3][TP / 32 + 1][kImage], block q at q + 1).  The adjacent
+// block is the one before (forward) or after (backward), the one leaving the
+// next in that direction.  Backward, block -1 "enters" when block 0 is
+// stepped through.
+__global__ __launch_bounds__(256) void unb_image_kernel(UnrolledArgs a) {
+  const int b = blockIdx.z, kind = blockIdx.y, q = (int)blockIdx.x - 1, TP = a.TP, NB = TP / kBlk;
+  const int dir = kind == 2 ? 1 : -1;
+  const float* m = part_of<float>(a, b, kind == 1 ? a.off_D : a.off_G);
+  float* out = part_of<float>(a, b, a.off_img) + ((size_t)kind * (NB + 1) + q + 1) * kImage;
+  for (int e = threadIdx.x; e < kImage / 4; e += 256) {
+    const bool mat = e < kMatrixImage / 4;
+    const int f = mat ? e : e - kMatrixImage / 4, l = f & 63;
+    floatx4 v;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      const int r = 4 * (f >> 6) + x;
+      int bi, bj, j;
+      if (mat) {
+        const int pl = matrix_lane(l, r);
+        bi = l < 32 ? q + dir : q;
+        bj = pl < 32 ? q + dir : q;
+        j = pl & 31;
+      } else {
+        const int c = pending_col(l, r);
+        bi = q;
+        bj = c < 32 ? q + 2 * dir : q + dir;
+        j = c & 31;
+      }
+      const bool in = bi >= 0 && bi < NB && bj >= 0 && bj < NB;
+      v[x] = in ? m[pair_at(TP, kBlk * bi + (l & 31), kBlk * bj + j)] : 0.0f;
+    }
+    *reinterpret_cast<floatx4*>(out + 4 * e) = v;
+  }
 }
 
 // LDS of a sweep, in floats.
 struct SweepLds {
-  int coef, panel, part, stage, ikn, om, qs, xs, total;
-  int panel_floats;      // one block's panels (K, and H with the tape)
+  int coef, image, part, stage, ikn, om, qs, xs, total;
 };
 __host__ __device__ inline SweepLds sweep_lds(int mode, int TP, int W) {
   const int n2 = mode == kTape ? 2 : 1;
   SweepLds l{};
   int o = 0;
   l.coef = o;  o += TP * kSerial;
-  l.part = o;  o += n2 * kPartFloats;
+  l.part = o;  o += n2 * part_floats(mode);
   l.stage = o; o += kBlk * kSerial;
   l.ikn = o;   o += kBlk;
   l.om = o;    o += 64;
   l.qs = o;    o += 64;
-  l.xs = o;    o += mode == kReverse ? 2 * kBlk * kSerial * W + 64 : 0;
-  l.panel = o; o += 2 * n2 * kPanelFloats;   // this block's and the one before
+  l.xs = o;    o += mode == kReverse ? (2 * kBlk * kSerial * W + 64) / 4 * 4 : 0;
+  l.image = o; o += n2 * kImage;            // every offset a multiple of four floats: float4 reads
   l.total = o;
-  l.panel_floats = n2 * kPanelFloats;
   return l;
 }
 
@@ -157,10 +206,16 @@ __device__ __forceinline__ void sweep_row(Lane& s, const float* kreg, const floa
 // the window members of every step.  Reverse: passes p1 - 1 .. p0 backwards,
 // X carried in the workspace, writing cbar of the members.
 template <int MODE, int NRW>
-__global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int p0, int p1, int ku) {
+__global__ __launch_bounds__(64 * (kSerial + helpers(MODE))) void unb_sweep_kernel(UnrolledArgs a, int p0, int p1,
+                                                                                   int groups, int ku) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
   constexpr bool REV = MODE == kReverse, TAPE = MODE == kTape;
-  const int inst = blockIdx.y, k0 = blockIdx.x * ku;
+  constexpr int kHelpers = helpers(MODE), kThreads = 64 * (kSerial + kHelpers), kPartFloats = part_floats(MODE);
+  // workgroups go round the eight XCDs: the user groups of an instance, which
+  // read the same strips, are eight apart, on one XCD and its L2
+  const int inst = (int)(blockIdx.x / (8 * groups)) * 8 + (blockIdx.x & 7);
+  const int k0 = (int)((blockIdx.x >> 3) % groups) * ku;
+  if (inst >= a.n) return;
   const int nu = a.K - k0 < ku ? a.K - k0 : ku;
   const int T = a.T, TP = a.TP, W = a.W, K = a.K, KP = a.KP, NB = TP / kBlk;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -169,12 +224,13 @@ __global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int
   const float* Km = part_of<float>(a, inst, a.off_G);
   const float* Hm = part_of<float>(a, inst, a.off_D);
   const float* kd = part_of<float>(a, inst, a.off_kd);
+  const float* img = part_of<float>(a, inst, a.off_img) + (REV ? (size_t)2 * (NB + 1) * kImage : 0);
   const float* cb0 = part_of<float>(a, inst, a.off_cb0);
   float* const ck = part_of<float>(a, inst, a.off_ck);
   const float* sym = a.sym_pilot + (size_t)inst * a.P * K * 2;
   const SweepLds L = sweep_lds(MODE, TP, W);
   float* const coef = lds + L.coef;
-  float* const panel = lds + L.panel;
+  float* const image = lds + L.image;
   float* const part = lds + L.part;
   float* const stage = lds + L.stage;
   float* const ikn = lds + L.ikn;
@@ -189,8 +245,8 @@ __global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int
   }
   float* const xg = part_of<float>(a, inst, a.off_X);
   const float* src = REV ? xg : p0 == 0 ? nullptr : ck + (size_t)(p0 / a.E) * T * KP;
-  // lanes without a sample multiply what the panels hold by zero
-  for (int e = tid; e < 2 * L.panel_floats; e += kThreads) panel[e] = 0.0f;
+  // lanes without a sample multiply what the image holds by zero
+  for (int e = tid; e < (TAPE ? 2 : 1) * kImage; e += kThreads) image[e] = 0.0f;
   for (int e = tid; e < TP * kSerial; e += kThreads) {
     const int d = e >> 2, u = e & 3;
     coef[e] = src && d < T && u < nu ? src[(size_t)d * KP + k0 + u] : 0.0f;
@@ -198,29 +254,17 @@ __global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int
   __syncthreads();
   const float qsW = qs[W];
 
-  // What the block q entering at iteration i needs: its kernel panel, targets (or
-  // cbar0) and diagonal, the sums of its members over the expansion.
+  // What the block q entering at iteration i needs: its register images,
+  // targets (or cbar0) and diagonal, the sums of its members over the
+  // expansion.
   // In the reverse sweep also the taped x of the block stepped through then.
   const int ht = tid - 64 * kSerial;        // helper thread
   auto prepare = [&](int i, int p) {
     const int q = REV ? NB - 1 - i : i, st = q + 1;
-    float* const pan = panel + (i & 1) * L.panel_floats;
+    lds_copy(img + (size_t)(q + 1) * kImage, image, kImage, wave - kSerial, kHelpers, lane);
+    if constexpr (TAPE)
+      lds_copy(img + (size_t)(NB + q + 2) * kImage, image + kImage, kImage, wave - kSerial, kHelpers, lane);
     if (q >= 0) {
-      for (int e = ht; e < kBlk * (kPanelCols / 4); e += 64 * kHelpers) {
-        const int r = e / (kPanelCols / 4), c4 = e - r * (kPanelCols / 4);
-        const int blk = REV ? q + 2 - (c4 >> 3) : q - 2 + (c4 >> 3);
-        floatx4 v = {0.0f, 0.0f, 0.0f, 0.0f}, vh = v;
-        if (blk >= 0 && blk < NB) {
-          const size_t o = (size_t)(kBlk * q + r) * TP + kBlk * blk + 4 * (c4 & 7);
-          v = *reinterpret_cast<const floatx4*>(Km + o);
-          if constexpr (TAPE) vh = *reinterpret_cast<const floatx4*>(Hm + o);
-        }
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
-          pan[r * kPanelStr + 4 * c4 + x] = v[x];
-          if constexpr (TAPE) pan[kPanelFloats + r * kPanelStr + 4 * c4 + x] = vh[x];
-        }
-      }
       if (ht < kBlk * kSerial) {
         const int n = kBlk * q + (ht >> 2), uu = ht & 3;
         float v = 0.0f;
@@ -234,12 +278,12 @@ __global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int
       BlockSums s;
 #pragma unroll
       for (int v = 0; v < 8; ++v) s.v[v] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-      block_accumulate(s, Km + kBlk * q, TP, coef, TP, wave - kSerial, kHelpers, lane);
+      block_accumulate(s, Km + (size_t)q * TP * kBlk, kBlk, coef, TP, wave - kSerial, kHelpers, lane);
       block_store(s, part, wave - kSerial, lane);
       if constexpr (TAPE) {
 #pragma unroll
         for (int v = 0; v < 8; ++v) s.v[v] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-        block_accumulate(s, Hm + kBlk * q, TP, coef, TP, wave - kSerial, kHelpers, lane);
+        block_accumulate(s, Hm + (size_t)q * TP * kBlk, kBlk, coef, TP, wave - kSerial, kHelpers, lane);
         block_store(s, part + kPartFloats, wave - kSerial, lane);
       }
     }
@@ -248,11 +292,24 @@ __global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int
       float* dst = lds + L.xs + (st & 1) * kBlk * kSerial * W;
       const int steps = T - kBlk * st < kBlk ? T - kBlk * st : kBlk;
       const float* tx = part_of<float>(a, inst, a.off_tx) + (size_t)((p - p0) * T + kBlk * st) * K * W;
-      for (int e = ht; e < steps * nu * W; e += 64 * kHelpers) {
-        const int t = e / (nu * W), r = e - t * nu * W;
-        dst[t * kSerial * W + r] = tx[(size_t)t * K * W + k0 * W + r];
+      const int total = steps * nu * W;
+      for (int e0 = ht; e0 < total; e0 += 64 * kHelpers * 8) {
+        float v[8];                         // eight loads in flight
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+          const int e = e0 + 64 * kHelpers * x, ec = e < total ? e : e0;
+          const int t = ec / (nu * W), r = ec - t * nu * W;
+          v[x] = tx[(size_t)t * K * W + k0 * W + r];
+        }
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+          const int e = e0 + 64 * kHelpers * x;
+          const int t = e / (nu * W), r = e - t * nu * W;
+          if (e < total) dst[t * kSerial * W + r] = v[x];
+        }
       }
     }
+    lds_copy_wait();
   };
 
   // Roles: the waves of users run the recursion, the helper waves prepare
@@ -280,12 +337,10 @@ __global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int
         if (active) {
           // the lower half's block goes into the expansion, the upper half
           // moves down, q's members come in with their sums and corrections
-          const float* pn = panel + (i & 1) * L.panel_floats;
-          const float* pv = panel + ((i + 1) & 1) * L.panel_floats;
           float e = 0.0f, h = 0.0f, g = 0.0f, ik = 0.0f;
           if (q >= 0) {
-            e = pending_sum(pn, s.C, lane);
-            if constexpr (TAPE) h = pending_sum(pn + kPanelFloats, s.C, lane);
+            e = pending_sum(image + kMatrixImage, s.C, lane);
+            if constexpr (TAPE) h = pending_sum(image + kImage + kMatrixImage, s.C, lane);
             float sum = 0.0f, sumh = 0.0f;
 #pragma unroll
             for (int w = 0; w < kHelpers; ++w) {
@@ -314,8 +369,8 @@ __global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int
             const float bu = upper_half(s.b);
             s.b = upper ? g : bu;
           }
-          load_matrix(pn, pv, lane, kreg);
-          if constexpr (TAPE) load_matrix(pn + kPanelFloats, pv + kPanelFloats, lane, hreg);
+          load_image<64>(image, lane, kreg);
+          if constexpr (TAPE) load_image<64>(image + kImage, lane, hreg);
         }
         __syncthreads();
         if (active && st >= 0 && st < NB) {
@@ -532,7 +587,8 @@ hipError_t launch_sweep_w(const UnrolledArgs& a, int p0, int p1, hipStream_t s) 
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   if (e != hipSuccess) return e;
   const int groups = (a.K + kSerial - 1) / kSerial, ku = (a.K + groups - 1) / groups;
-  hipLaunchKernelGGL(kern, dim3(groups, a.n), dim3(kThreads), bytes, s, a, p0, p1, ku);
+  hipLaunchKernelGGL(kern, dim3((a.n + 7) / 8 * 8 * groups), dim3(64 * (kSerial + helpers(MODE))), bytes, s, a, p0, p1,
+                     groups, ku);
   return hipGetLastError();
 }
 
@@ -545,10 +601,12 @@ hipError_t launch_sweep(const UnrolledArgs& a, int p0, int p1, hipStream_t s) {
 
 bool unrolled_in_blocks(int W) { return W <= kMaxWindow; }
 int unrolled_padded_steps(int T) { return (T + kBlk - 1) / kBlk * kBlk; }
+size_t unrolled_image_bytes(int T) { return (size_t)3 * (unrolled_padded_steps(T) / kBlk + 1) * kImage * sizeof(float); }
 int unrolled_grad_chunks(int T) { return (T + kGradSteps - 1) / kGradSteps; }
 
 hipError_t launch_unrolled_passes(const UnrolledArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(unb_gram_kernel, dim3(a.TP / 16, a.TP / 16, a.n), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(unb_image_kernel, dim3(a.TP / kBlk + 1, 3, a.n), dim3(256), 0, s, a);
   hipError_t e = launch_sweep<kForward>(a, 0, a.passes, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(unb_state_kernel, dim3(a.K, a.n), dim3(256), 0, s, a);

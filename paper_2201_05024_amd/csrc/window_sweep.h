@@ -30,14 +30,15 @@ namespace sweep {
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBlk = 32;                   // samples per block
-constexpr int kPanelCols = 96;             // kernel panel of a block: [block leaving | adjacent block | itself]
-constexpr int kPanelStr = 97;              // its row stride in LDS (odd: the diagonal reads of load_matrix spread over banks)
-constexpr int kPanelFloats = kBlk * kPanelStr;
+// Register images of an entering block, as the lanes read them: float4 g of
+// lane l at 4 (64 g + l).  Matrix image: the 64 x 64 values between the block
+// and the adjacent one; pending image: its members' values against the block
+// leaving and the adjacent one.
+constexpr int kMatrixImage = 64 * 64;
+constexpr int kPendingImage = 32 * 64;
+constexpr int kImage = kMatrixImage + kPendingImage;
 constexpr int kMaxWindow = 33;             // a window ends inside a block and reaches at most into the one before
 constexpr int kSerial = 4;                 // recursion waves of a workgroup (one user each, one per SIMD)
-constexpr int kHelpers = 4;                // waves evaluating the next block's members meanwhile
-constexpr int kThreads = 64 * (kSerial + kHelpers);
-constexpr int kPartFloats = kHelpers * kBlk * kSerial;
 
 // Rows of 16 lanes a window of W samples can touch.
 __host__ __device__ constexpr int window_rows(int W) { return W <= 17 ? 2 : 3; }
@@ -91,20 +92,31 @@ __device__ __forceinline__ float slab_residual(float x, float eps) {
   return m > 0.0f ? copysignf(m, x) : 0.0f;
 }
 
+// Value r of lane l in the pending image: member l % 32 of the entering block
+// against sample pending_col(l, r) of [block leaving | adjacent block]; in
+// the matrix image: lane l's sample against lane matrix_lane(l, r)'s.
+__host__ __device__ __forceinline__ int pending_col(int l, int r) { return (l & 32) + (r & 16) + ((l - r) & 15); }
+__host__ __device__ __forceinline__ int matrix_lane(int l, int r) { return (r & 48) + ((l - r) & 15); }
+
+template <int N>
+__device__ __forceinline__ void load_image(const float* img, int lane, float* k) {
+#pragma unroll
+  for (int g = 0; g < N / 4; ++g) {
+    const floatx4 v = *reinterpret_cast<const floatx4*>(img + 4 * (64 * g + lane));
+    k[4 * g] = v[0];
+    k[4 * g + 1] = v[1];
+    k[4 * g + 2] = v[2];
+    k[4 * g + 3] = v[3];
+  }
+}
+
 // Corrections of the entering block's members for the coefficients C pending
 // in the lanes, which the expansion does not hold yet: the lower half of the
-// wave has those of the block about to leave (panel columns 0..31), the
-// upper half those of the adjacent block (columns 32..63).  Both halves get
-// the sum for member lane % 32.
-__device__ __forceinline__ float pending_sum(const float* panel, float C, int lane) {
-  const float* row = panel + (lane & 31) * kPanelStr + (lane & 32);
+// wave has those of the block about to leave, the upper half those of the
+// adjacent block.  Both halves get the sum for member lane % 32.
+__device__ __forceinline__ float pending_sum(const float* img, float C, int lane) {
   float kf[32];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int jj = (lane - r) & 15;
-    kf[r] = row[jj];
-    kf[16 + r] = row[16 + jj];
-  }
+  load_image<32>(img, lane, kf);
   const auto y = __builtin_amdgcn_permlane16_swap(__float_as_uint(C), __float_as_uint(C), false, false);
   float f;
   row_mul(f, __uint_as_float(y[0]), kf);
@@ -119,26 +131,17 @@ __device__ __forceinline__ float upper_half(float x) {
   return __uint_as_float(z[1]);
 }
 
-// The register matrix once the entering block holds the upper half and the
-// adjacent one the lower half: panel is the entering block's, prev the
-// adjacent block's own.
-__device__ __forceinline__ void load_matrix(const float* panel, const float* prev, int lane, float* k) {
-  const int il = lane & 31;
-  const bool fresh = lane >= 32;
-  // against the adjacent block's members: panel[il][32 + jj] (entering) or prev[il][64 + jj]
-  const float* a = (fresh ? panel + 32 : prev + 64) + il * kPanelStr;
-  // against the entering block's: panel[il][64 + jj] or, transposed, panel[jj][32 + il]
-  const float* b = fresh ? panel + il * kPanelStr + 64 : panel + 32 + il;
-  const int str = fresh ? 1 : kPanelStr;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int jj = (lane - r) & 15;
-    k[r] = a[jj];
-    k[16 + r] = a[16 + jj];
-    k[32 + r] = b[jj * str];
-    k[48 + r] = b[(jj + 16) * str];
-  }
+typedef __attribute__((address_space(1))) void global_void;
+typedef __attribute__((address_space(3))) void lds_void;
+
+// Copy of n floats (a multiple of 256) from global memory into LDS by the
+// helper waves, a KiB per wave instruction; lds_copy_wait() before the
+// barrier that publishes it.
+__device__ __forceinline__ void lds_copy(const float* src, float* dst, int n, int hw, int nh, int lane) {
+  for (int o = 256 * hw; o < n; o += 256 * nh)
+    __builtin_amdgcn_global_load_lds((global_void*)(src + o + 4 * lane), (lds_void*)(dst + o), 16, 0, 0);
 }
+__device__ __forceinline__ void lds_copy_wait() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
 
 // Evaluation of a block's 32 members against the entries d in [0, n) by the
 // helper waves, four users at a time, on v_mfma_f32_4x4x1_16b_f32: its 16
@@ -155,7 +158,7 @@ template <class Coef>
 __device__ __forceinline__ void block_accumulate(BlockSums& a, const float* vals, size_t stride, const Coef* coef,
                                                  int n, int hw, int nh, int lane) {
   const int b = lane >> 2, r = lane & 3;
-  constexpr int U = 4;                     // groups in flight
+  constexpr int U = 8;                     // groups in flight: 16 KiB a wave, to cover the memory latency
   int d0 = 16 * hw;
   for (; d0 + 16 * nh * (U - 1) < n; d0 += 16 * nh * U) {
     floatx4 x[U][2];
