@@ -167,6 +167,7 @@ typedef struct apsm_params {
  *         same filter re-laid out for the detection kernels (written by
  *         apsm_train and by apsm_model_pack, read by apsm_detect); for
  *         2M <= 64 and K <= 8 it holds the layouts of both detection kernels.
+ *         Training may use it as scratch memory before it packs.
  *         It does not depend on sigma2.
  * sigma2 travels with the call (apsm_detect) rather than in this struct. */
 typedef struct apsm_model {
@@ -216,6 +217,20 @@ int apsm_train(const apsm_params_t* params, int M2, int K, int P,
 int apsm_train_batched(const apsm_params_t* params, int M2, int K, int P, int n_inst,
                        const float* rx_pilot, const float* sym_pilot,
                        const apsm_model_t* models, void* stream);
+
+/* The same as apsm_train_batched with a scratch buffer (DEVICE, any size,
+ * caller-owned, free for other uses once the stream has passed the call):
+ * training computes the kernel values of its steps ahead into it.  Without
+ * one (apsm_train, apsm_train_batched) it works in the models' packed
+ * buffers, a few blocks of steps at a time.  The results are the same; a
+ * buffer of apsm_train_scratch_bytes (pure host function; at most about
+ * APSM_TRAIN_SCRATCH_MAX unless one block of steps needs more; 0 where the
+ * shape has no use for one) is the fastest. */
+#define APSM_TRAIN_SCRATCH_MAX (1u << 30)
+size_t apsm_train_scratch_bytes(const apsm_params_t* params, int M2, int K, int P, int n_inst);
+int apsm_train_scratch(const apsm_params_t* params, int M2, int K, int P, int n_inst,
+                       const float* rx_pilot, const float* sym_pilot, const apsm_model_t* models,
+                       void* scratch, size_t scratch_bytes, void* stream);
 
 /* Detection (Sec. III-B): for every received vector r(s), s = 0..S-1,
  * g_k = f_k(r1) + i f_k(r2) with the frozen filter `model` (read only, except
@@ -358,10 +373,11 @@ int apsm_batch_create(const apsm_params_t* params, const apsm_batch_item_t* item
                       apsm_batch_t** out);
 
 /* Bytes of device workspace the batch needs: job tables, the work-item
- * lists of detection, claim counters and the training kernel rows (for each
- * detector with dict_cap <= 8192: 2P x (dict_cap + window) floats, the
- * Gaussian kernel values of every pilot step against the dictionary entries
- * it sees, computed by one data-parallel launch before training). */
+ * lists of detection, claim counters and the kernel values of training (the
+ * values of every pilot step against the dictionary entries it sees, computed
+ * by one data-parallel launch before training: about 2P x (dict_cap + 256)
+ * floats for each detector with window <= 33 and dict_cap >= 96, else for
+ * dict_cap <= 8192 2P x (dict_cap + window)). */
 size_t apsm_batch_workspace_bytes(const apsm_batch_t* batch);
 
 /* Write the batch's tables into `workspace` (DEVICE, at least

@@ -90,6 +90,11 @@ def library() -> ctypes.CDLL:
         L.apsm_train_batched.argtypes = [ctypes.POINTER(_CParams), i32, i32, i32, i32, vp, vp,
                                          ctypes.POINTER(_CModel), vp]
         L.apsm_train_batched.restype = i32
+        L.apsm_train_scratch_bytes.argtypes = [ctypes.POINTER(_CParams), i32, i32, i32, i32]
+        L.apsm_train_scratch_bytes.restype = ctypes.c_size_t
+        L.apsm_train_scratch.argtypes = [ctypes.POINTER(_CParams), i32, i32, i32, i32, vp, vp,
+                                         ctypes.POINTER(_CModel), vp, ctypes.c_size_t, vp]
+        L.apsm_train_scratch.restype = i32
         L.apsm_detect.argtypes = [ctypes.POINTER(_CModel), f32, i32, vp, vp, vp, i32, vp, vp, vp]
         L.apsm_detect.restype = i32
         L.apsm_get_status.argtypes = [ctypes.POINTER(_CModel), ctypes.POINTER(ctypes.c_int32)]
@@ -375,6 +380,19 @@ def shutdown() -> None:
     library().apsm_shutdown()
 
 
+def _train_scratch(p: _CParams, M2: int, K: int, P: int, n: int, device, stream):
+    """Scratch for apsm_train_scratch from torch's allocator (None where the
+    shape has no use for one), held until `stream` has passed its use."""
+    torch = _torch()
+    nbytes = library().apsm_train_scratch_bytes(ctypes.byref(p), M2, K, P, n)
+    if not nbytes:
+        return None
+    t = torch.empty(nbytes, dtype=torch.uint8, device=device)
+    if stream is not None:
+        t.record_stream(stream)
+    return t
+
+
 def train(rx_pilot, sym_pilot, params: Params, model: Optional[Model] = None, stream=None) -> Model:
     """rx_pilot [P][M2] float32, sym_pilot [P][K][2] float32 (device) -> Model."""
     torch = _torch()
@@ -389,8 +407,10 @@ def train(rx_pilot, sym_pilot, params: Params, model: Optional[Model] = None, st
     model.sigma2 = float(params.sigma2)
     p, keep = params._c()
     m = model._c()
-    rc = library().apsm_train(ctypes.byref(p), M2, K, P, rx_pilot.data_ptr(), sym_pilot.data_ptr(),
-                              ctypes.byref(m), _stream_handle(stream))
+    ws = _train_scratch(p, M2, K, P, 1, rx_pilot.device, stream)
+    rc = library().apsm_train_scratch(ctypes.byref(p), M2, K, P, 1, rx_pilot.data_ptr(), sym_pilot.data_ptr(),
+                                      ctypes.byref(m), ws.data_ptr() if ws is not None else None,
+                                      ws.numel() if ws is not None else 0, _stream_handle(stream))
     del keep
     if rc:
         raise APSMError(rc, "apsm_train")
@@ -434,8 +454,10 @@ def train_batched(rx_pilot, sym_pilot, params: Params, models=None, stream=None)
         m.sigma2 = float(params.sigma2)
     p, keep = params._c()
     arr = (_CModel * n)(*[m._c() for m in models]) if n else None
-    rc = library().apsm_train_batched(ctypes.byref(p), M2, K, P, n, rx_pilot.data_ptr(),
-                                      sym_pilot.data_ptr(), arr, _stream_handle(stream))
+    ws = _train_scratch(p, M2, K, P, n, rx_pilot.device, stream) if n else None
+    rc = library().apsm_train_scratch(ctypes.byref(p), M2, K, P, n, rx_pilot.data_ptr(), sym_pilot.data_ptr(), arr,
+                                      ws.data_ptr() if ws is not None else None,
+                                      ws.numel() if ws is not None else 0, _stream_handle(stream))
     del keep
     if rc:
         raise APSMError(rc, "apsm_train_batched")

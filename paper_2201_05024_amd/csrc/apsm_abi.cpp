@@ -1,6 +1,7 @@
 // Host side of the C ABI: argument validation, parameter folding and dispatch
 // to the kernel launchers.  Validation runs before any HIP call, so a
 // rejected call touches neither the device nor the stream.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <string>
@@ -134,10 +135,62 @@ const char* apsm_last_hip_error(void) { return g_last_hip_error.c_str(); }
 
 namespace apsm {
 
+namespace {
+
+// Training in blocks of detectors of one shape: each with its share of the
+// scratch buffer, or in its model's packed buffer.  False (nothing launched)
+// where a share does not hold one block.
+bool train_blocks(const apsm_params_t* p, const TrainCommon& cm, int M2, int K, int P, int n_inst,
+                  const float* rx_pilot, const float* sym_pilot, const apsm_model_t* models, hipStream_t stream,
+                  void* scratch, size_t scratch_bytes, hipError_t* err) {
+  const int cap = p->dict_cap;
+  const bool continued = p->init == APSM_INIT_CONTINUE;
+  auto up = [](uintptr_t x) { return (x + 255) & ~uintptr_t(255); };
+  auto base = [&](int i) {
+    return scratch ? up(reinterpret_cast<uintptr_t>(scratch)) + (size_t)i * (scratch_bytes / n_inst & ~size_t(255))
+                   : up(reinterpret_cast<uintptr_t>(models[i].packed));
+  };
+  size_t share = scratch_bytes / n_inst & ~size_t(255);
+  if (!scratch) {
+    const size_t packed = packed_model_bytes(M2, K, cap);
+    share = packed;
+    for (int i = 0; i < n_inst; ++i) {
+      const size_t skip = base(i) - reinterpret_cast<uintptr_t>(models[i].packed);
+      share = std::min(share, packed - std::min(packed, skip));
+    }
+  }
+  const int blocks = train_blocks_in(M2, K, P, cap, continued, share);
+  if (blocks < 1) return false;
+  *err = hipSuccess;
+  for (int b0 = 0; b0 < n_inst && *err == hipSuccess; b0 += kMaxBlockJobs) {
+    BlockArgs a{};
+    a.cm = cm;
+    a.n = std::min(n_inst - b0, kMaxBlockJobs);
+    for (int i = 0; i < a.n; ++i) {
+      const int q = b0 + i;
+      BlockJob& j = a.jobs[i];
+      train_block_job(j, P, M2, K, cap, continued, reinterpret_cast<void*>(base(q)));
+      j.rx = rx_pilot + (size_t)q * P * M2;
+      j.sym = sym_pilot + (size_t)q * P * K * 2;
+      j.st = p->set_types ? p->set_types + (size_t)q * P * K * 2 : nullptr;
+      j.dict = models[q].dict;
+      j.alpha = models[q].alpha;
+      j.w = models[q].w;
+      j.state = models[q].state;
+      j.c2 = kLog2e / (2.0f * p->sigma2);
+    }
+    *err = launch_train_blocks(a, blocks, stream);
+  }
+  return true;
+}
+
+}  // namespace
+
 // Shared by apsm_train, apsm_train_batched and apsm_track: every check
 // happens before the first launch.
 int train_impl(const apsm_params_t* p, int M2, int K, int P, int n_inst, const float* rx_pilot,
-               const float* sym_pilot, const apsm_model_t* models, void* stream) {
+               const float* sym_pilot, const apsm_model_t* models, void* stream, void* scratch,
+               size_t scratch_bytes) {
   if (int rc = check_params(p)) return rc;
   if (!rx_pilot || !sym_pilot || !models) return APSM_ERR_INVALID_ARG;
   if (P < 1 || M2 < 2 || (M2 & 1) || K < 1 || n_inst < 0) return APSM_ERR_SHAPE;
@@ -158,7 +211,12 @@ int train_impl(const apsm_params_t* p, int M2, int K, int P, int n_inst, const f
   a.cap = p->dict_cap;
   a.c2 = apsm::kLog2e / (2.0f * p->sigma2);
 
-  for (int b0 = 0; b0 < n_inst; b0 += apsm::kMaxTrainBatch) {
+  hipError_t eb = hipSuccess;
+  const bool in_blocks = n_inst > 0 && train_in_blocks(p->window, p->dict_cap) &&
+                         train_blocks(p, a.cm, M2, K, P, n_inst, rx_pilot, sym_pilot, models, (hipStream_t)stream,
+                                      scratch, scratch_bytes, &eb);
+  if (eb != hipSuccess) return hip_status(eb);
+  for (int b0 = 0; !in_blocks && b0 < n_inst; b0 += apsm::kMaxTrainBatch) {
     const int nb = n_inst - b0 < apsm::kMaxTrainBatch ? n_inst - b0 : apsm::kMaxTrainBatch;
     a.rx = rx_pilot + (size_t)b0 * P * M2;
     a.sym = sym_pilot + (size_t)b0 * P * K * 2;
@@ -198,6 +256,29 @@ int apsm_train_batched(const apsm_params_t* p, int M2, int K, int P, int n_inst,
                        const float* sym_pilot, const apsm_model_t* models, void* stream) {
   if (n_inst == 0) return APSM_OK;
   return train_impl(p, M2, K, P, n_inst, rx_pilot, sym_pilot, models, stream);
+}
+
+size_t apsm_train_scratch_bytes(const apsm_params_t* p, int M2, int K, int P, int n_inst) {
+  if (check_params(p) != APSM_OK || P < 1 || M2 < 2 || (M2 & 1) || K < 1 || n_inst < 1 || M2 > APSM_MAX_M2 ||
+      K > APSM_MAX_K || (long long)P * 2 > (long long)INT32_MAX / 2 || !train_in_blocks(p->window, p->dict_cap))
+    return 0;
+  // all blocks at once where that stays within the bound, else as many as do
+  const bool continued = p->init == APSM_INIT_CONTINUE;
+  const size_t bound = (size_t)APSM_TRAIN_SCRATCH_MAX / n_inst & ~size_t(255);
+  const int blocks = std::max(1, train_blocks_in(M2, K, P, p->dict_cap, continued, bound));
+  const size_t one = (train_blocks_bytes(M2, K, P, p->dict_cap, continued, blocks) + 255) & ~size_t(255);
+  return one * n_inst + 256;
+}
+
+int apsm_train_scratch(const apsm_params_t* p, int M2, int K, int P, int n_inst, const float* rx_pilot,
+                       const float* sym_pilot, const apsm_model_t* models, void* scratch, size_t scratch_bytes,
+                       void* stream) {
+  if (n_inst == 0) return APSM_OK;
+  // the share of each detector starts at the next 256-byte boundary
+  const size_t skip = (256 - (reinterpret_cast<uintptr_t>(scratch) & 255)) & 255;
+  const bool use = scratch && scratch_bytes > skip;
+  return train_impl(p, M2, K, P, n_inst, rx_pilot, sym_pilot, models, stream, use ? scratch : nullptr,
+                    use ? scratch_bytes - skip : 0);
 }
 
 size_t apsm_model_packed_bytes(int M2, int K, int dict_cap) {

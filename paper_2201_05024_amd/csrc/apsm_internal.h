@@ -70,6 +70,33 @@ struct TrainArgs {
   float c2;
 };
 
+// Training in blocks (train_blocked.hip): one detector's job over the blocks
+// of 32 steps [qa, qb).  Its workspace holds a header, the lanes carried from
+// one range of blocks to the next, and per block an image and a strip.
+struct BlockJob {
+  const float* rx;        // [P][M2] pilot vectors, r1 layout
+  const float* sym;       // [P][Kt][2]
+  const uint8_t* st;      // [P][Kt][2] set kinds or null
+  float* dict;            // [M2][cap]
+  float* alpha;           // [cap][Kt]
+  float* w;               // [Kt][M2]
+  int32_t* state;         // [4]
+  int32_t* header;        // [0]: samples the continued model had seen
+  float* carry;
+  float* images;          // [qb - qa] images
+  float* strips;          // [qb - qa][SW][32]: kernel values of the block's members against the entries
+  int P, M2, Kt, cap, ku; // ku: users per workgroup
+  int SW, qa, qb;
+  int write_dict;         // the preparing launch writes the dictionary (not for a continued model)
+  float c2;
+};
+constexpr int kMaxBlockJobs = 16;           // detectors per launch, in the kernel arguments
+struct BlockArgs {
+  TrainCommon cm;
+  BlockJob jobs[kMaxBlockJobs];
+  int n, groups;
+};
+
 struct DetectArgs {
   const float* dict;      // [M2][cap] component-major
   const float* alpha;     // [cap][K]
@@ -134,6 +161,29 @@ hipError_t launch_kernel_rows(const TrainJob* jobs, const int4* items, int n_ite
                               const TrainCommon& cm, hipStream_t stream);
 hipError_t launch_train_rows(const TrainJob* jobs, int n, const TrainCommon& cm, size_t lds_bytes,
                              hipStream_t stream);
+// Training in blocks: windows of at most 33 samples (two blocks in a wave)
+// and capacities of at least 96 (an evicted entry's coefficient is final a
+// block ahead).
+// train_block_job lays a job out in its workspace of train_blocks_bytes bytes
+// (256-byte aligned) for `blocks` blocks at a time, of train_blocks_of(P);
+// launch_train_blocks runs detectors of one shape, all ranges of blocks.
+bool train_in_blocks(int W, int cap);
+int train_blocks_of(int P);
+int train_blocks_in(int M2, int K, int P, int cap, bool continued, size_t bytes);   // blocks a workspace holds
+size_t train_blocks_bytes(int M2, int K, int P, int cap, bool continued, int blocks);
+void train_block_job(BlockJob& j, int P, int M2, int K, int cap, bool continued, void* workspace);
+hipError_t launch_train_blocks(BlockArgs& a, int blocks, hipStream_t stream);
+// The same for a device table of jobs (all blocks at once): items of the
+// preparing launch are (job, unit < train_prepare_units), those of the sweep
+// (job, first user in steps of train_group_users), job < 0 for an empty place.
+int train_prepare_units(const BlockJob& j);
+int train_group_users(int K);
+size_t train_prepare_lds(int M2);
+size_t train_sweep_lds(int M2);
+hipError_t launch_train_prepare_table(const BlockJob* jobs, const int2* items, int n, const TrainCommon& cm,
+                                      size_t lds_bytes, hipStream_t stream);
+hipError_t launch_train_sweep_table(const BlockJob* jobs, const int2* items, int n, const TrainCommon& cm,
+                                    size_t lds_bytes, hipStream_t stream);
 hipError_t launch_detect(const DetectArgs& a, hipStream_t stream);
 // Packed model of the detection kernels (split-FP16 layout for 2M <= 64 and
 // K <= 8, two-contraction layout otherwise): bytes and the packing launch.
@@ -248,7 +298,11 @@ DetectArgs detect_args(const apsm_model_t* model, float sigma2, int S, const flo
                        uint8_t* hard, int modulation, const uint8_t* truth, int64_t* err_count);
 // apsm_train / apsm_train_batched after the argument checks of the public
 // entry points: n_inst detectors of one shape, pilots contiguous per detector.
+// scratch: device workspace shared by the detectors, or null (training in
+// blocks then works in the models' packed buffers, which packing rewrites
+// afterwards, in as many ranges of blocks as their size asks for).
 int train_impl(const apsm_params_t* p, int M2, int K, int P, int n_inst, const float* rx_pilot,
-               const float* sym_pilot, const apsm_model_t* models, void* stream);
+               const float* sym_pilot, const apsm_model_t* models, void* stream, void* scratch = nullptr,
+               size_t scratch_bytes = 0);
 
 }  // namespace apsm

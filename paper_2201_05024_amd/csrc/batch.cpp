@@ -2,10 +2,11 @@
 // tables, the device workspace image, the launch forms of batched detection
 // and their tuning.
 //
-// Planning: every item becomes one training job (one workgroup, its kernel
-// specialisation picked by train_rows_variant, else train_variant), ordered
-// by estimated cost so the longest trainings start first.  Jobs of the rows
-// form get their kernel rows (one step per row) in the workspace, written by
+// Planning: every item becomes one training job, ordered by estimated cost so
+// the longest trainings start first: training in blocks (train_in_blocks: one
+// workgroup per four users), else a job of the rows form (train_rows_variant)
+// or of the table kernel (train_variant).  Jobs of the rows form get their
+// kernel rows (one step per row) in the workspace, written by
 // one data-parallel launch before the training launch.  Every item becomes a
 // packing job and, if it has vectors to detect, a detection job of one of the
 // two detection kernels: split-FP16 with VALU coefficients (2M <= 64, K <= 8)
@@ -29,6 +30,10 @@ struct apsm_batch {
   apsm::TrainCommon cm{};
   std::vector<apsm::TrainJob> tjobs;
   size_t train_lds = 0;
+  std::vector<apsm::BlockJob> bjobs;          // training in blocks; workspace pointers set at bind
+  std::vector<size_t> block_off;              // byte offset of each job's workspace
+  std::vector<int2> prep_items, sweep_items;  // (job, unit) and (job, first user; job < 0: empty place)
+  size_t prep_lds = 0, sweep_lds = 0, block_bytes = 0;
   std::vector<apsm::TrainJob> rjobs;          // rows form; glag/kw set at bind
   std::vector<size_t> rows_off;               // float offset of each rows job's glag (kw follows)
   std::vector<int4> ritems;                   // (rows job, first step, first lag) per kernel-row tile
@@ -44,6 +49,7 @@ struct apsm_batch {
   std::vector<int2> witems;                    // grouped by padded width (one launch each)
   int wbegin[4] = {0, 0, 0, 0};                // items of width class c: [wbegin[c], wbegin[c + 1])
   std::vector<int> train_plain;      // items trained with their own launch
+  size_t off_bj = 0, off_pi = 0, off_si = 0, off_blocks = 0;
   size_t off_t = 0, off_rj = 0, off_ri = 0, off_p = 0, off_pw = 0, off_d = 0, off_i = 0, off_wd = 0, off_wi = 0,
          off_c = 0, off_rows = 0, bytes = 0;
   unsigned char* ws = nullptr;       // bound workspace (device)
@@ -220,6 +226,25 @@ void plan(apsm_batch& b, const apsm_params_t* p) {
   std::stable_sort(order.begin(), order.end(), [&](int a, int c) { return tcost[a] > tcost[c]; });
   for (int i : order) {
     const auto& it = b.items[i];
+    if (train_in_blocks(p->window, it.model.dict_cap)) {
+      BlockJob j{};
+      train_block_job(j, it.P, it.model.M2, it.model.K, it.model.dict_cap, false, nullptr);
+      j.rx = it.rx_pilot;
+      j.sym = it.sym_pilot;
+      j.dict = it.model.dict;
+      j.alpha = it.model.alpha;
+      j.w = it.model.w;
+      j.state = it.model.state;
+      j.c2 = kLog2e / (2.0f * it.sigma2);
+      const int q = (int)b.bjobs.size(), units = train_prepare_units(j);
+      for (int u = 0; u < units; ++u) b.prep_items.push_back(make_int2(q, u));
+      b.block_off.push_back(b.block_bytes);
+      b.block_bytes += align256(train_blocks_bytes(j.M2, j.Kt, it.P, j.cap, false, train_blocks_of(it.P)));
+      b.prep_lds = std::max(b.prep_lds, train_prepare_lds(j.M2));
+      b.sweep_lds = std::max(b.sweep_lds, train_sweep_lds(j.M2));
+      b.bjobs.push_back(j);
+      continue;
+    }
     // users per rows job: all of them, or groups of four when the capacity
     // needs 16 coefficient slots per thread
     const int ku = std::min(it.model.K, train_rows_max_users(it.model.dict_cap));
@@ -266,6 +291,23 @@ void plan(apsm_batch& b, const apsm_params_t* p) {
     b.train_lds = std::max(b.train_lds, train_lds_bytes(p->window, j.M2, j.K, j.cap));
   }
 
+  // Sweeps, longest first; workgroups go round the eight XCDs, so the user
+  // groups of a detector, which read the same kernel values, are placed eight
+  // apart (places a detector with fewer groups leaves are empty).
+  for (size_t q0 = 0; q0 < b.bjobs.size(); q0 += 8) {
+    const size_t q1 = std::min(q0 + 8, b.bjobs.size());
+    bool any = true;
+    for (int g = 0; any; ++g) {
+      any = false;
+      for (size_t q = q0; q < q1; ++q) any = any || g * b.bjobs[q].ku < b.bjobs[q].Kt;
+      if (!any) break;
+      for (size_t q = q0; q < q0 + 8; ++q) {
+        const bool in = q < q1 && g * b.bjobs[q].ku < b.bjobs[q].Kt;
+        b.sweep_items.push_back(make_int2(in ? (int)q : -1, in ? g * b.bjobs[q].ku : 0));
+      }
+    }
+  }
+
   // packing: dual shapes get both packed images
   for (int i = 0; i < n; ++i) {
     const auto& it = b.items[i];
@@ -303,7 +345,10 @@ void plan(apsm_batch& b, const apsm_params_t* p) {
   }
   assign_detection(b);
 
-  b.off_t = 0;
+  b.off_bj = 0;
+  b.off_pi = align256(b.off_bj + b.bjobs.size() * sizeof(BlockJob));
+  b.off_si = align256(b.off_pi + b.prep_items.size() * sizeof(int2));
+  b.off_t = align256(b.off_si + b.sweep_items.size() * sizeof(int2));
   b.off_rj = align256(b.off_t + b.tjobs.size() * sizeof(TrainJob));
   b.off_ri = align256(b.off_rj + b.rjobs.size() * sizeof(TrainJob));
   b.off_p = align256(b.off_ri + b.ritems.size() * sizeof(int4));
@@ -314,7 +359,8 @@ void plan(apsm_batch& b, const apsm_params_t* p) {
   b.off_wi = align256(b.off_wd + max_wj * sizeof(DetJob));
   b.off_c = align256(b.off_wi + max_wi * sizeof(int2));
   b.off_rows = b.off_c + 256;                 // tables end here (the bound image)
-  b.bytes = b.off_rows + b.rows_floats * sizeof(float);
+  b.off_blocks = align256(b.off_rows + b.rows_floats * sizeof(float));
+  b.bytes = b.off_blocks + b.block_bytes;
   b.signature = signature_of(b.items);
   bool pers = true;
   if (tune_get_form(b.signature, &pers)) b.persistent = pers;
@@ -366,7 +412,8 @@ int apsm_batch_create(const apsm_params_t* params, const apsm_batch_item_t* item
   if (!b) return APSM_ERR_INVALID_ARG;
   b->items.assign(items, items + n);
   plan(*b, &pc);
-  if (b->ditems.size() > (size_t)INT32_MAX || b->witems.size() > (size_t)INT32_MAX) {
+  if (b->ditems.size() > (size_t)INT32_MAX || b->witems.size() > (size_t)INT32_MAX ||
+      b->prep_items.size() > (size_t)INT32_MAX) {
     delete b;
     return APSM_ERR_UNSUPPORTED;
   }
@@ -381,6 +428,21 @@ int apsm_batch_bind(apsm_batch_t* b, void* workspace, size_t bytes, void* stream
   if (!workspace || bytes < b->bytes || (reinterpret_cast<uintptr_t>(workspace) & 255)) return APSM_ERR_WORKSPACE;
   // the tables (the kernel rows after them are written on the device)
   std::vector<unsigned char> img(b->off_rows, 0);
+  if (!b->bjobs.empty()) {
+    std::vector<BlockJob> bj = b->bjobs;
+    for (size_t q = 0; q < bj.size(); ++q) {
+      BlockJob at{};
+      train_block_job(at, bj[q].P, bj[q].M2, bj[q].Kt, bj[q].cap, false,
+                      static_cast<unsigned char*>(workspace) + b->off_blocks + b->block_off[q]);
+      bj[q].header = at.header;
+      bj[q].carry = at.carry;
+      bj[q].images = at.images;
+      bj[q].strips = at.strips;
+    }
+    std::memcpy(img.data() + b->off_bj, bj.data(), bj.size() * sizeof(BlockJob));
+    std::memcpy(img.data() + b->off_pi, b->prep_items.data(), b->prep_items.size() * sizeof(int2));
+    std::memcpy(img.data() + b->off_si, b->sweep_items.data(), b->sweep_items.size() * sizeof(int2));
+  }
   if (!b->tjobs.empty()) std::memcpy(img.data() + b->off_t, b->tjobs.data(), b->tjobs.size() * sizeof(TrainJob));
   if (!b->rjobs.empty()) {
     std::vector<TrainJob> rj = b->rjobs;
@@ -409,6 +471,9 @@ int apsm_batch_bind(apsm_batch_t* b, void* workspace, size_t bytes, void* stream
 
 int apsm_batch_kernel_rows(const apsm_batch_t* b, void* stream) {
   if (!b || !b->ws) return APSM_ERR_INVALID_ARG;
+  const hipError_t e = launch_train_prepare_table(at<BlockJob>(b, b->off_bj), at<int2>(b, b->off_pi),
+                                                  (int)b->prep_items.size(), b->cm, b->prep_lds, (hipStream_t)stream);
+  if (e != hipSuccess) return hip_status(e);
   return hip_status(launch_kernel_rows(at<TrainJob>(b, b->off_rj), at<int4>(b, b->off_ri), (int)b->ritems.size(),
                                        b->rows_max_m2, b->cm, (hipStream_t)stream));
 }
@@ -421,7 +486,10 @@ int apsm_batch_train(const apsm_batch_t* b, void* stream) {
 int apsm_batch_train_prepared(const apsm_batch_t* b, void* stream) {
   if (!b || !b->ws) return APSM_ERR_INVALID_ARG;
   hipStream_t s = (hipStream_t)stream;
-  hipError_t e = launch_train_rows(at<TrainJob>(b, b->off_rj), (int)b->rjobs.size(), b->cm, b->rows_lds, s);
+  hipError_t e = launch_train_sweep_table(at<BlockJob>(b, b->off_bj), at<int2>(b, b->off_si),
+                                          (int)b->sweep_items.size(), b->cm, b->sweep_lds, s);
+  if (e == hipSuccess)
+    e = launch_train_rows(at<TrainJob>(b, b->off_rj), (int)b->rjobs.size(), b->cm, b->rows_lds, s);
   if (e == hipSuccess) e = launch_train_table(at<TrainJob>(b, b->off_t), (int)b->tjobs.size(), b->cm, b->train_lds, s);
   for (size_t q = 0; q < b->train_plain.size() && e == hipSuccess; ++q) {
     // shapes outside the table kernel (2M > 64, dictionaries past the rows

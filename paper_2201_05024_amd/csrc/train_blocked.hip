@@ -1,0 +1,865 @@
+// Training in blocks of 32 steps (windows of at most 33 samples, dictionary
+// capacities of at least 96): the window recursion of window_sweep.h with a
+// FIFO dictionary.
+//
+// f_n(x) = wL v_n . x + sum_d alpha_d kappa_G(r_d, x) over the dictionary.  When
+// block q is stepped through, the samples of blocks q - 1 and q are in the
+// lanes of a wave; their coefficients C (alpha = wG C, v += C r) are pending,
+// those of older blocks are in alpha and v.  A member i of the block gets
+//   f(r_i) = sum_{d < 32 (q - 2)} alpha_d kappa_G(r_d, r_i)      (strip, helper waves)
+//          + sum over the pending samples K_id C_d               (pending image)
+//          + wL v . r_i,
+// entries that leave the dictionary by step i left out (an entry of block
+// q - 2 keeps its linear part).  The members already in the window lose an
+// evicted entry's term at its step; its coefficient is final and in alpha a
+// block ahead (capacity >= 96: it is of block q - 3 or older).
+//
+// Two launches.  train_prepare: everything that depends on the received
+// vectors alone, data-parallel: the strips (kernel values of a block's
+// members against the entries, 128 x 128 pairs per workgroup on
+// v_mfma_f32_16x16x4_f32), the blocks' register images, eviction values and
+// diagonals, and the dictionary itself.  train_sweep: one workgroup per
+// detector and up to four users, one wave per user and eight helper waves.
+// Where the workspace does not hold all blocks, the pair of launches is
+// repeated over ranges of blocks, the lanes' state carried in the workspace.
+#include <algorithm>
+
+#include "apsm_internal.h"
+#include "window_sweep.h"
+
+namespace apsm {
+namespace {
+
+using namespace sweep;
+
+constexpr int kHelpers = 8;
+constexpr int kThreads = 64 * (kSerial + kHelpers);
+constexpr int kPartFloats = kHelpers * kBlk * kSerial;
+constexpr int kMinCap = 96;
+
+// A block's image in the workspace: matrix and pending image, -1 / kappa(r, r)
+// of its members, then the [step][lane] eviction values (whole KiB each).
+constexpr int kIknAt = kImage, kEvAt = kIknAt + 256;
+constexpr int kEviction = kBlk * 64;
+constexpr int kTrainImage = kEvAt + kEviction;
+constexpr int kTile = 128;                    // entries and members of a strip tile
+constexpr int kPrepThreads = 512;
+constexpr int kDictSlots = 256;               // slots of a dictionary unit
+
+typedef __attribute__((address_space(1))) float gfloat;
+template <class T>
+__device__ __forceinline__ __attribute__((address_space(1))) T* gmem(T* p) {
+  return (__attribute__((address_space(1))) T*)p;
+}
+
+__host__ __device__ __forceinline__ int blocks_of(int P) { return (2 * P + kBlk - 1) / kBlk; }
+
+// ---- units of the preparing launch: images, strip tiles, dictionary slots
+struct Units {
+  int images, groups, tiles, dict;
+};
+__host__ __device__ inline Units units_of(const BlockJob& j) {
+  Units u;
+  u.images = j.qb - j.qa;
+  u.groups = j.SW > 0 ? (u.images + 3) / 4 : 0;
+  u.tiles = (j.SW + 96 + kTile - 1) / kTile;
+  u.dict = j.write_dict ? (j.cap + kDictSlots - 1) / kDictSlots : 0;
+  return u;
+}
+
+// Vector component m of local sample i: a pilot, an entry of the continued
+// model's ring (i < 0, n0 samples seen), else 0.
+struct Source {
+  const gfloat* rx;
+  const gfloat* dict;
+  int M2, M, T, cap, n0;
+  __device__ __forceinline__ float at(int i, int m) const {
+    if (i >= 0 || n0 == 0) {
+      const bool ok = i >= 0 && i < T && m < M2, odd = (i & 1) != 0;
+      const int ic = ok ? i : 0, mc = m < M2 ? m : 0;
+      const float sg = ok ? (odd && mc >= M ? -1.0f : 1.0f) : 0.0f;
+      return sg * rx[(size_t)(ic >> 1) * M2 + (odd ? (mc < M ? mc + M : mc - M) : mc)];
+    }
+    const int g = n0 + i;
+    return g >= 0 && i >= -cap && m < M2 ? dict[(size_t)m * cap + g % cap] : 0.0f;
+  }
+};
+
+// rows [0, 128) of xs [..][M2R + 4] from samples idx(row), and their squared norms
+template <int M2R, class Idx>
+__device__ __forceinline__ void stage_vectors(const Source& src, Idx&& idx, float* xs, float* xn) {
+  constexpr int STR = M2R + 4, B = 8, N = kTile * M2R;   // STR = 4 (mod 16): conflict-free 16-byte reads
+  for (int e0 = threadIdx.x; e0 < N; e0 += B * kPrepThreads) {
+    float v[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const int e = e0 + u * kPrepThreads, ec = e < N ? e : e0;
+      v[u] = src.at(idx(ec / M2R), ec % M2R);
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const int e = e0 + u * kPrepThreads;
+      if (e < N) xs[(e / M2R) * STR + e % M2R] = v[u];
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < kTile) {
+    const float* x = xs + threadIdx.x * STR;
+    float n4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int m = 0; m < M2R; ++m) n4[m & 3] = fmaf(x[m], x[m], n4[m & 3]);
+    xn[threadIdx.x] = (n4[0] + n4[1]) + (n4[2] + n4[3]);
+  }
+  __syncthreads();
+}
+
+__device__ __forceinline__ float gauss(float c2, float na, float nb, float dot) {
+  return __builtin_amdgcn_exp2f(-c2 * fmaxf(na + nb - 2.0f * dot, 0.0f));
+}
+
+// Strip tile: members 32 (qa + 4 group) .. + 127 against the 128 entries from
+// dlo on.  Wave w has members 16 w .. 16 w + 15 as MFMA columns in registers
+// (lane (c, g): components g Q .. g Q + Q - 1 of member c), the entries are
+// the rows, from LDS four components at a time.
+template <int M2R>
+__device__ __forceinline__ void strip_unit(const BlockJob& j, const Source& src, int group, int tile, float* lds) {
+  constexpr int Q = M2R / 4, STR = M2R + 4;
+  float* xs = lds;
+  float* xn = lds + kTile * STR;
+  const int q0 = j.qa + 4 * group, m0 = kBlk * q0;
+  const int dlo = m0 + 32 - kTile * (tile + 1);
+  const int nold = src.n0 < src.cap ? src.n0 : src.cap;
+  if (dlo + kTile - 1 < -nold - 16 || dlo >= kBlk * (j.qb - 3)) return;   // not read
+  stage_vectors<M2R>(src, [&](int r) { return dlo + r; }, xs, xn);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, c = lane & 15, g = lane >> 4;
+  const int m = m0 + 16 * w + c;
+  float b[Q];
+  float nn = 0.0f;
+#pragma unroll
+  for (int s = 0; s < Q; ++s) {
+    b[s] = src.at(m, g * Q + s);
+    nn = fmaf(b[s], b[s], nn);
+  }
+  nn += __shfl_xor(nn, 16);
+  nn += __shfl_xor(nn, 32);
+  floatx4 acc[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) acc[u] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int s0 = 0; s0 < Q; s0 += 4)
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const floatx4 a4 = *reinterpret_cast<const floatx4*>(xs + (16 * u + c) * STR + g * Q + s0);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[t], b[s0 + t], acc[u], 0, 0, 0);
+    }
+  const int q = q0 + (w >> 1);
+  if (q >= j.qb) return;
+  auto out = gmem(j.strips) + (size_t)(q - j.qa) * j.SW * kBlk + 16 * (w & 1) + c;
+  const int x0 = dlo - kBlk * (q - 2) + j.SW;
+#pragma unroll
+  for (int u = 0; u < 8; ++u)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = 16 * u + 4 * g + i, d = dlo + r, x = x0 + r;
+      if (x < 0 || x >= j.SW) continue;
+      const bool in = d >= -nold && m - d < src.cap;
+      out[(size_t)x * kBlk] = in ? gauss(j.c2, nn, xn[r], acc[u][i]) : 0.0f;
+    }
+}
+
+// Image unit of block q: the 24 tiles of 16 x 16 pairs it needs among the
+// samples of blocks q - 2, q - 1, q and the entries evicted by its steps,
+// three per wave, then the image gathered from them.
+template <int M2R>
+__device__ __forceinline__ void image_unit(const BlockJob& j, const TrainCommon& cm, const Source& src, int q,
+                                           float* lds) {
+  constexpr int Q = M2R / 4, STR = M2R + 4;
+  float* xs = lds;
+  float* xn = xs + kTile * STR;
+  float* k1 = xn + kTile;                  // [32][97] members of q against blocks q - 2, q - 1, q
+  float* k2 = k1 + 32 * 97;                // [32][33] block q - 1 against itself
+  float* ev = k2 + 32 * 33;                // [32][65] evicted entries against the lanes' samples
+  const int n0 = src.n0, cap = src.cap, base = kBlk * (q - 2);
+  stage_vectors<M2R>(src, [&](int r) { return r < 96 ? base + r : kBlk * q + (r - 96) - cap; }, xs, xn);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, c = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int u = 0; u < 3; ++u) {
+    const int t = 3 * w + u;
+    const int rt = t < 12 ? 4 + t / 6 : t < 16 ? 2 + ((t - 12) >> 1) : 6 + ((t - 16) >> 2);
+    const int ct = t < 12 ? t % 6 : t < 16 ? 2 + (t & 1) : 2 + (t & 3);
+    floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int s0 = 0; s0 < Q; s0 += 4) {
+      const floatx4 a4 = *reinterpret_cast<const floatx4*>(xs + (16 * rt + c) * STR + g * Q + s0);
+      const floatx4 b4 = *reinterpret_cast<const floatx4*>(xs + (16 * ct + c) * STR + g * Q + s0);
+#pragma unroll
+      for (int x = 0; x < 4; ++x) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[x], b4[x], acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int ra = 16 * rt + 4 * g + i, rb = 16 * ct + c;
+      const float dot = ra == rb ? xn[ra] : acc[i];
+      const float kg = ra == rb ? 1.0f : gauss(j.c2, xn[ra], xn[rb], dot);
+      const int db = base + rb;            // column's sample
+      if (t < 12) {
+        const int il = ra - 64, lag = base + ra - db;
+        // a pilot's entry gone from the dictionary keeps its linear part; the
+        // linear part of a continued model's entries is in w already
+        float v;
+        if (db >= 0) v = fmaf(cm.wl, dot, lag < cap ? cm.wg * kg : 0.0f);
+        else v = n0 + db >= 0 && lag < cap ? kg : 0.0f;
+        k1[il * 97 + rb] = v;
+      } else if (t < 16) {
+        k2[(ra - 32) * 33 + rb - 32] = fmaf(cm.wl, dot, cm.wg * kg);
+      } else {
+        const int n = kBlk * q + ra - 96;
+        ev[(ra - 96) * 65 + rb - 32] = n0 + n >= cap && db >= 0 && db < n ? kg : 0.0f;
+      }
+    }
+  }
+  __syncthreads();
+  float* out = j.images + (size_t)(q - j.qa) * kTrainImage;
+  for (int e = threadIdx.x; e < kTrainImage / 4; e += kPrepThreads) {
+    floatx4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (e < kImage / 4) {
+      const bool mat = e < kMatrixImage / 4;
+      const int f = mat ? e : e - kMatrixImage / 4, l = f & 63, il = l & 31;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        const int r = 4 * (f >> 6) + x;
+        if (mat) {
+          const int pl = matrix_lane(l, r), jl = pl & 31;
+          v[x] = l >= 32 ? k1[il * 97 + (pl >= 32 ? 64 : 32) + jl] : pl >= 32 ? k1[jl * 97 + 32 + il] : k2[il * 33 + jl];
+        } else {
+          v[x] = k1[il * 97 + pending_col(l, r)];
+        }
+      }
+    } else if (e >= kEvAt / 4) {
+      const int f = 4 * e - kEvAt;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) v[x] = ev[(f >> 6) * 65 + (f & 63) + x];
+    } else if (e < (kIknAt + kBlk) / 4) {
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        const int il = 4 * e - kIknAt + x;
+        const float kjj = k1[il * 97 + 64 + il];
+        v[x] = kBlk * q + il < src.T && kjj > 0.0f ? -1.0f / kjj : 0.0f;
+      }
+    }
+    *reinterpret_cast<floatx4*>(out + 4 * e) = v;
+  }
+}
+
+template <int M2R>
+__host__ __device__ constexpr int prep_floats() {
+  return kTile * (M2R + 4) + kTile + 32 * 97 + 32 * 33 + 32 * 65;
+}
+__host__ __device__ inline int m2r_of(int M2) { return M2 <= 16 ? 16 : M2 <= 32 ? 32 : M2 <= 64 ? 64 : 128; }
+inline int prep_floats_of(int M2) {
+  switch (m2r_of(M2)) {
+    case 16: return prep_floats<16>();
+    case 32: return prep_floats<32>();
+    case 64: return prep_floats<64>();
+    default: return prep_floats<128>();
+  }
+}
+
+// Dictionary slots [s0, s0 + 256): the newest sample of each, zero for
+// unused slots (a continued model keeps what the block did not replace).
+__device__ __forceinline__ void dict_unit(const Source& src, float* dict, int s0) {
+  const int cap = src.cap, T = src.T;
+  const int slot = s0 + (threadIdx.x & (kDictSlots - 1));
+  if (slot >= cap) return;
+  int lag = (src.n0 + T - 1) % cap - slot;
+  if (lag < 0) lag += cap;
+  const int i = T - 1 - lag;
+  if (i < 0 && src.n0 > 0) return;
+  for (int m = threadIdx.x / kDictSlots; m < src.M2; m += kPrepThreads / kDictSlots)
+    gmem(dict)[(size_t)m * cap + slot] = i >= 0 ? src.at(i, m) : 0.0f;
+}
+
+__device__ __forceinline__ Source source_of(const BlockJob& j, int n0) {
+  return {gmem(j.rx), gmem(j.dict), j.M2, j.M2 / 2, 2 * j.P, j.cap, n0};
+}
+
+template <int M2R>
+__device__ __forceinline__ void prepare_unit_w(const BlockJob& j, const TrainCommon& cm, int unit, float* lds) {
+  const Units u = units_of(j);
+  const Source src = source_of(j, cm.init == kInitContinue ? __builtin_amdgcn_readfirstlane(gmem(j.state)[2]) : 0);
+  if (unit == 0 && j.qa == 0 && threadIdx.x == 0) {
+    gmem(j.state)[3] = 0;                   // collects what the users' sweeps find
+    gmem(j.header)[0] = src.n0;             // for the sweeps: the first to end writes the new count
+  }
+  if (unit < u.images) {
+    image_unit<M2R>(j, cm, src, j.qa + unit, lds);
+  } else if ((unit -= u.images) < u.groups * u.tiles) {
+    strip_unit<M2R>(j, src, unit / u.tiles, unit % u.tiles, lds);
+  } else if ((unit -= u.groups * u.tiles) < u.dict) {
+    dict_unit(src, j.dict, unit * kDictSlots);
+  }
+}
+
+__device__ __forceinline__ void prepare_unit(const BlockJob& j, const TrainCommon& cm, int unit, float* lds) {
+  switch (m2r_of(j.M2)) {
+    case 16: prepare_unit_w<16>(j, cm, unit, lds); break;
+    case 32: prepare_unit_w<32>(j, cm, unit, lds); break;
+    case 64: prepare_unit_w<64>(j, cm, unit, lds); break;
+    default: prepare_unit_w<128>(j, cm, unit, lds); break;
+  }
+}
+
+__global__ __launch_bounds__(kPrepThreads) void prepare_kernel(BlockArgs a) {
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  prepare_unit(a.jobs[blockIdx.y], a.cm, blockIdx.x, lds);
+}
+
+__global__ __launch_bounds__(kPrepThreads) void prepare_table_kernel(const BlockJob* jobs, const int2* items,
+                                                                     TrainCommon cm) {
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  const int2 it = items[blockIdx.x];
+  const BlockJob j = jobs[it.x];
+  prepare_unit(j, cm, it.y, lds);
+}
+
+// The dictionary of a continued model, after its training.
+__global__ __launch_bounds__(kPrepThreads) void continued_dict_kernel(BlockArgs a) {
+  const BlockJob& j = a.jobs[blockIdx.y];
+  dict_unit(source_of(j, gmem(j.header)[0]), j.dict, blockIdx.x * kDictSlots);
+}
+
+// ---- sweep
+
+// LDS of a sweep, in floats.  The vectors of four blocks: the entering one's
+// for its linear part, the three before it until they are in v.
+struct SweepLds {
+  int image, ev, part, target, kind, aev, rows, v, flushed, om, qs, total;
+};
+__host__ __device__ inline SweepLds sweep_lds(int M2) {
+  SweepLds l{};
+  const int M2P = m2r_of(M2);
+  int o = 0;
+  l.image = o;   o += kEvAt;
+  l.ev = o;      o += 2 * kEviction + 64;  // this block's and the next one's; read one step past the end
+  l.part = o;    o += kPartFloats;
+  l.target = o;  o += kBlk * kSerial;
+  l.kind = o;    o += kBlk * kSerial;
+  l.aev = o;     o += kBlk * kSerial;
+  l.rows = o;    o += 4 * kBlk * (M2P + 4);
+  l.v = o;       o += kSerial * M2P;
+  l.flushed = o; o += 2 * kBlk * kSerial;
+  l.om = o;      o += 64;
+  l.qs = o;      o += 64;
+  l.total = o;
+  return l;
+}
+
+struct Lane {
+  float e;         // running prediction
+  float C;         // pending coefficient
+  float b, ikn;    // target, -1 / kappa(r, r) (0 where that is not positive)
+  float bad;       // not finite once a residual was not
+  int kind;        // set kind
+  int d;           // sample, negative for none
+};
+
+// 16 steps (or the fewer of the sequence's end) whose newest members lie in
+// row A of the wave; n0 the first of them, t0 its place in the block.  GEN:
+// any set weights, relaxation and set kinds; else position weights and
+// hyperslabs.
+template <bool GEN, int NRW, int A>
+__device__ __forceinline__ void train_row(Lane& s, const float* kreg, int n0, int t0, int cnt, const TrainCommon& cm,
+                                          bool typed, float qsW, const float* om, const float* qs, bool evict,
+                                          const float* ev, float aev, int lane) {
+#pragma clang fp contract(off)
+  if (cnt <= 0) return;
+  const int W = cm.W;
+  const float inv_mu = 1.0f / cm.mu;
+  int age = (16 * A - lane) & 63;           // 33..63: not yet a member
+  float wv = om[age];
+  float kv = evict ? ev[t0 * 64 + lane] : 0.0f;
+  for (int it = 0; it < cnt; ++it) {
+    const int n = n0 + it;
+    const float q = n + 1 < W ? qs[n + 1] : qsW;   // mu / (omega_0 + .. + omega_{L-1})
+    const float wq = wv * q, wcur = wv, kcur = kv;
+    age = (age + 1) & 63;                   // the next step's reads are issued a step ahead
+    wv = om[age];
+    if (evict) {
+      // the members in the window lose the entry that leaves
+      const float a = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(aev), t0 + it));
+      s.e = fmaf(-a, kcur, s.e);
+      kv = ev[(t0 + it + 1) * 64 + lane];   // (past the last step: not used)
+    }
+    const float x = s.e - s.b;
+    s.bad = fmaf(x, 0.0f, s.bad);
+    if constexpr (!GEN) {
+      const float c = slab_residual(x, cm.eps) * (wq * s.ikn);
+      s.C += c;
+      s.e += window_product<A, NRW>(broadcast_rows(c), kreg);
+    } else {
+      float res = slab_residual(x, cm.eps);
+      if (typed) {
+        res = s.kind == kSetPlane   ? x
+              : s.kind == kSetUpper ? fmaxf(x - cm.eps, 0.0f)
+              : s.kind == kSetLower ? fminf(x + cm.eps, 0.0f)
+                                    : res;
+      }
+      const float beta = res * s.ikn;
+      float u;                              // q_j beta_j
+      if (cm.weights != kWeightsPosition) {
+        // proportional to the distance, or uniform over the members violated
+        // by more than 1e-5 (a member that its own projection left on the
+        // boundary stays out, whatever the rounding)
+        const float dist = cm.weights == kWeightsActive ? (fabsf(res) > 1e-5f ? 1.0f : 0.0f) : fabsf(res);
+        const float v = wcur > 0.0f && s.d >= 0 ? dist : 0.0f;
+        const float tot = wave_sum(v);
+        u = tot > 0.0f ? v / tot * beta : 0.0f;
+      } else {
+        u = wq * inv_mu * beta;
+      }
+      const float ku = window_product<A, NRW>(broadcast_rows(u), kreg);
+      float step = cm.mu;
+      if (cm.extrapolate) {
+        // M = sum_j q_j beta_j^2 K_jj / sum_jl u_j K_jl u_l (beta_j K_jj = -residual)
+        const float num = wave_sum(s.ikn != 0.0f ? -u * res : 0.0f);
+        const float den = wave_sum(u != 0.0f ? u * ku : 0.0f);
+        step = cm.mu * (den > 0.0f ? num / den : 1.0f);
+      }
+      s.C += step * u;
+      s.e += step * ku;
+    }
+  }
+}
+
+template <bool GEN, int NRW>
+__device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon& cm, int k0, float* lds) {
+  const int Kt = j.Kt, nu = Kt - k0 < j.ku ? Kt - k0 : j.ku;
+  const int T = 2 * j.P, W = cm.W, M2 = j.M2, M2P = m2r_of(M2), RS = M2P + 4, cap = j.cap, SW = j.SW;
+  const int NB = blocks_of(j.P);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), il = lane & 31;
+  const bool upper = lane >= 32;
+  const SweepLds L = sweep_lds(M2);
+  float* const image = lds + L.image;
+  float* const evict_lds = lds + L.ev;
+  float* const part = lds + L.part;
+  float* const target = lds + L.target;
+  int* const kind = reinterpret_cast<int*>(lds + L.kind);
+  float* const aevict = lds + L.aev;
+  float* const rows = lds + L.rows;
+  float* const vlin = lds + L.v;
+  float* const flushed = lds + L.flushed;
+  float* const om = lds + L.om;
+  float* const qs = lds + L.qs;
+  const auto alpha = gmem(j.alpha);
+  const auto sym = gmem(j.sym);
+  const bool typed = GEN && j.st != nullptr;
+  const int n0 = cm.init == kInitContinue ? __builtin_amdgcn_readfirstlane(gmem(j.header)[0]) : 0;
+  const int nold = n0 < cap ? n0 : cap;
+  const Source src = source_of(j, n0);
+  const bool first = j.qa == 0, last = j.qb == NB;
+  // coefficient of user u of the group in a slot
+  auto cval = [&](int slot, int u) { return u < nu ? alpha[(unsigned)(slot * Kt + k0 + u)] : 0.0f; };
+  auto set_coef = [&](int d, int u, float C) { alpha[(size_t)((n0 + d) % cap) * Kt + k0 + u] = cm.wg * C; };
+
+  if (tid < 64) {
+    // weights past the window are 0; read at constant indices, straight from
+    // the kernel arguments
+    float w = 0.0f, z = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kMaxWindow; ++i) {
+      const float o = i < W ? cm.omega[i] : 0.0f;
+      w = i == tid ? o : w;
+      z += i < tid ? o : 0.0f;
+    }
+    om[tid] = w;
+    qs[tid] = tid > 0 ? cm.mu / z : 0.0f;
+  }
+  // coefficients and linear part at the start: the continued (or carried)
+  // ones, else none and w / wL or 0
+  if (first && cm.init != kInitContinue)
+    for (size_t e = tid; e < (size_t)cap * nu; e += kThreads) alpha[e / nu * Kt + k0 + e % nu] = 0.0f;
+  float* const carry = j.carry;             // per user C [64], e [32]; v [Kt][M2]; -1 / kappa of the last block
+  for (int e = tid; e < kSerial * M2P; e += kThreads) {
+    const int u = e / M2P, m = e - u * M2P;
+    float v = 0.0f;
+    if (u < nu && m < M2) {
+      if (!first) v = carry[(size_t)Kt * 96 + (k0 + u) * M2 + m];
+      else if (cm.init != kInitZero) v = gmem(j.w)[(size_t)(k0 + u) * M2 + m] / cm.wl;
+    }
+    vlin[e] = v;
+  }
+  __syncthreads();
+  const float qsW = qs[W];
+
+  auto rows_of = [&](int q) { return rows + (q & 3) * kBlk * RS; };
+  // element r of block q's vectors [32][M2P] (scalar base, small lane offset)
+  const int rsh = 31 - __builtin_clz(M2P);
+  auto vec_load = [&](int q, int r) -> float {
+    const int i = r >> rsh, m = r & (M2P - 1), M = M2 >> 1;
+    const bool ok = m < M2 && 16 * q + (i >> 1) < j.P, odd = (i & 1) != 0;
+    const gfloat* base = src.rx + (size_t)(16 * q) * M2;
+    const unsigned off = ok ? (unsigned)((i >> 1) * M2 + (odd ? (m < M ? m + M : m - M) : m)) : 0u;
+    const float sg = ok ? (odd && m >= M ? -1.0f : 1.0f) : 0.0f;
+    return sg * base[off];
+  };
+  if (!first) {                             // vectors staged by the launch before
+    for (int e = tid; e < 3 * kBlk * M2P; e += kThreads) {
+      const int q = j.qa - 3 + (e >> (5 + rsh)), r = e & (kBlk * M2P - 1);
+      if (q >= 0) rows_of(q)[(r >> rsh) * RS + (r & (M2P - 1))] = vec_load(q, r);
+    }
+  }
+  // v += sum_i C_i r_i over the 32 samples of block q, their C in
+  // flushed[from ..][user]: output e = (user, component), at most 512
+  auto take_linear = [&](int q, int from, int e) {
+    if (q < 0 || e >= kSerial * M2P) return;
+    const float* r = rows_of(q) + (e & (M2P - 1));
+    const float* f = flushed + from * kSerial + (e >> rsh);
+    float acc = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kBlk; ++i) acc = fmaf(f[i * kSerial], r[i * RS], acc);
+    vlin[e] += acc;
+  };
+
+  if (wave < kSerial) {
+    const int u = wave;
+    const bool active = u < nu;
+    if (active) __builtin_amdgcn_s_setprio(3);
+    float kreg[64];
+    Lane s{};
+    // what is pending at the start: the carried lanes, or the newest entries
+    // of a continued model (their linear part is in v)
+    s.d = kBlk * (j.qa - 2) + lane;
+    if (active) {
+      if (!first) {
+        s.C = carry[(k0 + u) * 96 + lane];
+        s.e = upper ? carry[(k0 + u) * 96 + 64 + il] : 0.0f;
+        if (upper && s.d >= 0 && s.d < T) {
+          s.b = sym[((size_t)(s.d >> 1) * Kt + k0 + u) * 2 + (s.d & 1)];
+          if constexpr (GEN) s.kind = typed ? gmem(j.st)[((size_t)(s.d >> 1) * Kt + k0 + u) * 2 + (s.d & 1)] : 0;
+        }
+      } else if (n0 + s.d >= 0) {
+        s.C = cval((n0 + s.d) % cap, u);
+      }
+      if (!first && upper) s.ikn = carry[(size_t)Kt * (96 + M2) + il];
+    }
+    for (int q = j.qa; q < j.qb; ++q) {
+      __syncthreads();
+      float aev = 0.0f;
+      const bool evict = n0 + kBlk * q + kBlk - 1 >= cap;
+      if (active) {
+        // the lower half's block goes into the expansion, the upper half
+        // moves down, q's members come in
+        const float f = pending_sum(image + kMatrixImage, s.C, lane);
+        float lin = 0.0f;
+        {
+          const int h = upper ? M2P / 2 : 0;
+          const float* r = rows_of(q) + il * RS + h;
+          const float* v = vlin + u * M2P + h;
+          float l4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+          for (int m = 0; m < M2P / 2; m += 4) {
+            const floatx4 a = *reinterpret_cast<const floatx4*>(r + m), b = *reinterpret_cast<const floatx4*>(v + m);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) l4[x] = fmaf(a[x], b[x], l4[x]);
+          }
+          lin = halves_sum((l4[0] + l4[1]) + (l4[2] + l4[3]));
+        }
+        float sum = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kHelpers; ++w) sum += part[(w * kBlk + il) * kSerial + u];
+        const float e = fmaf(cm.wl, lin, sum + f);
+        if (!upper) {
+          flushed[il * kSerial + u] = s.d >= 0 ? s.C : 0.0f;
+          if (s.d >= 0) set_coef(s.d, u, s.C);
+        }
+        // (swaps outside the selects: they need every lane)
+        const float eu = upper_half(s.e), Cu = upper_half(s.C), bu = upper_half(s.b), iu = upper_half(s.ikn);
+        const int du = __float_as_int(upper_half(__int_as_float(s.d)));
+        const float b = target[il * kSerial + u], ik = image[kIknAt + il];
+        s.e = upper ? e : eu;
+        s.C = upper ? 0.0f : Cu;
+        s.b = upper ? b : bu;
+        s.ikn = upper ? ik : iu;
+        s.d = upper ? kBlk * q + il : du;
+        if constexpr (GEN) {
+          const int ku = __float_as_int(upper_half(__int_as_float(s.kind)));
+          s.kind = upper ? kind[il * kSerial + u] : ku;
+        }
+        load_image<64>(image, lane, kreg);
+        aev = aevict[il * kSerial + u];     // lane t: coefficient of the entry step t evicts
+      }
+      __syncthreads();
+      if (active) {
+        const int nb = kBlk * q, rem = T - nb;
+        const float* ev = evict_lds + (q & 1) * kEviction;
+        train_row<GEN, NRW, 2>(s, kreg, nb, 0, rem < 16 ? rem : 16, cm, typed, qsW, om, qs, evict, ev, aev, lane);
+        train_row<GEN, NRW, 3>(s, kreg, nb + 16, 16, rem < 32 ? rem - 16 : 16, cm, typed, qsW, om, qs, evict, ev, aev,
+                               lane);
+      }
+    }
+    if (active) {
+      if (!last) {
+        carry[(k0 + u) * 96 + lane] = s.C;
+        if (upper) carry[(k0 + u) * 96 + 64 + il] = s.e;
+        if (upper && k0 + u == 0) carry[(size_t)Kt * (96 + M2) + il] = s.ikn;
+      }
+      if (__ballot(!(s.bad == 0.0f)) != 0 && lane == 0) atomicOr(j.state + 3, APSM_FLAG_TRAIN_NONFINITE);
+    }
+    __syncthreads();
+    take_linear(j.qb - 3, 0, tid);          // flushed at the last block's start
+    __syncthreads();
+    if (last && active) {
+      // what is pending goes into the expansion
+      const bool in = s.d >= 0 && s.d < T;
+      flushed[lane * kSerial + u] = in ? s.C : 0.0f;
+      if (in) set_coef(s.d, u, s.C);
+    }
+    __syncthreads();
+  } else {
+    const int hw = wave - kSerial, ht = tid - 64 * kSerial, nt = 64 * kHelpers;
+    // what block q needs: image, eviction values, targets, vectors, the sums
+    // of its members over the entries; the block flushed before enters the
+    // linear part.  Loads first, the sums next, stores last: the latencies
+    // of the small pieces pass behind the strip's.
+    auto prepare = [&](int q) {
+      const float* img = j.images + (size_t)(q - j.qa) * kTrainImage;
+      lds_copy(img, image, kEvAt, hw, kHelpers, lane);
+      if (n0 + kBlk * q + kBlk - 1 >= cap)
+        lds_copy(img + kEvAt, evict_lds + (q & 1) * kEviction, kEviction, hw, kHelpers, lane);
+      float tg = 0.0f;
+      int kd = 0;
+      if (ht < kBlk * kSerial) {
+        const int n = kBlk * q + (ht >> 2), u = ht & 3;
+        if (n < T && u < nu) {
+          const size_t at = ((size_t)(n >> 1) * Kt + k0 + u) * 2 + (n & 1);
+          tg = sym[at];
+          if constexpr (GEN) kd = typed ? gmem(j.st)[at] : 0;
+        }
+      }
+      float rv[8];                          // 32 vectors of up to 128 components over 512 threads
+#pragma unroll
+      for (int x = 0; x < 8; ++x) {
+        const int e = ht + x * nt;
+        rv[x] = e < kBlk * M2P ? vec_load(q, e) : 0.0f;
+      }
+      float av = 0.0f;
+      if (ht < kBlk * kSerial) {
+        const int ng = n0 + kBlk * q + (ht >> 2);
+        if (ng >= cap) av = cval(ng % cap, ht & 3);
+      }
+      BlockSums b;
+#pragma unroll
+      for (int v = 0; v < 8; ++v) b.v[v] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+      // entry x of the strip is sample 32 (q - 2) - SW + x; those before the
+      // oldest have no slot (and zero kernel values)
+      const int dlo = kBlk * (q - 2) - SW, bl = lane >> 2, u = lane & 3;
+      const int x0 = -nold - dlo <= 0 ? 0 : (-nold - dlo) & ~15;
+      const int s0 = ((n0 + dlo) % cap + cap) % cap;
+      auto co = [&](int x) -> float {
+        int slot = s0 + x + bl;
+        slot = slot >= cap ? slot - cap : slot;
+        return cval(slot, u);
+      };
+      block_accumulate(b, j.strips + (size_t)(q - j.qa) * SW * kBlk, co, x0, SW, hw, kHelpers, lane);
+      block_store(b, part, hw, lane);
+      if (ht < kBlk * kSerial) {
+        target[ht] = tg;
+        aevict[ht] = av;
+        if constexpr (GEN) kind[ht] = kd;
+      }
+#pragma unroll
+      for (int x = 0; x < 8; ++x) {
+        const int e = ht + x * nt;
+        if (e < kBlk * M2P) rows_of(q)[(e >> rsh) * RS + (e & (M2P - 1))] = rv[x];
+      }
+      if (q > j.qa) take_linear(q - 3, 0, ht);
+      lds_copy_wait();
+    };
+    prepare(j.qa);
+    for (int q = j.qa; q < j.qb; ++q) {
+      __syncthreads();
+      __syncthreads();
+      if (q + 1 < j.qb) prepare(q + 1);
+    }
+    __syncthreads();
+    take_linear(j.qb - 3, 0, tid);
+    __syncthreads();
+    __syncthreads();
+  }
+  if (last) {
+    take_linear(NB - 2, 0, tid);
+    __syncthreads();
+    take_linear(NB - 1, kBlk, tid);
+  }
+  __syncthreads();
+
+  // ---- write back
+  for (int e = tid; e < nu * M2; e += kThreads) {
+    const int u = e / M2, m = e - u * M2;
+    const float v = vlin[u * M2P + m];
+    if (last) gmem(j.w)[(size_t)(k0 + u) * M2 + m] = cm.wl * v;
+    else carry[(size_t)Kt * 96 + (k0 + u) * M2 + m] = v;
+  }
+  if (last && k0 == 0 && tid == 0) {
+    const int Tg = n0 + T;                  // samples seen in all
+    gmem(j.state)[0] = Tg < cap ? Tg : cap;
+    gmem(j.state)[1] = Tg % cap;
+    gmem(j.state)[2] = Tg;
+  }
+}
+
+template <bool GEN, int NRW>
+__global__ __launch_bounds__(kThreads) void sweep_kernel(BlockArgs a) {
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  // workgroups go round the eight XCDs: a detector's user groups, which read
+  // the same strips, are eight apart, on one XCD and its L2
+  const int inst = (int)(blockIdx.x / (8 * a.groups)) * 8 + (blockIdx.x & 7);
+  if (inst >= a.n) return;
+  const BlockJob& j = a.jobs[inst];
+  sweep_body<GEN, NRW>(j, a.cm, (int)((blockIdx.x >> 3) % a.groups) * j.ku, lds);
+}
+
+// items: (job, first user), job < 0 for a place left empty
+template <bool GEN, int NRW>
+__global__ __launch_bounds__(kThreads) void sweep_table_kernel(const BlockJob* jobs, const int2* items,
+                                                               TrainCommon cm) {
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  const int2 it = items[blockIdx.x];
+  if (it.x < 0) return;
+  const BlockJob j = jobs[it.x];
+  sweep_body<GEN, NRW>(j, cm, it.y, lds);
+}
+
+template <class K>
+hipError_t set_lds(K kern, size_t bytes) {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)bytes);
+}
+
+size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
+
+// Workspace of one detector: header, carried lanes, then per block its image
+// and strip.
+size_t head_bytes(int M2, int K) { return align256(256 + ((size_t)K * (96 + M2) + kBlk) * sizeof(float)); }
+size_t block_bytes(int SW) { return ((size_t)kTrainImage + (size_t)SW * kBlk) * sizeof(float); }
+
+template <bool GEN, int NRW>
+hipError_t launch_sweep_args(const BlockArgs& a, size_t bytes, hipStream_t s) {
+  hipError_t e = set_lds(sweep_kernel<GEN, NRW>, bytes);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((sweep_kernel<GEN, NRW>), dim3((a.n + 7) / 8 * 8 * a.groups), dim3(kThreads), bytes, s, a);
+  return hipGetLastError();
+}
+
+bool general(const TrainCommon& cm, bool typed) {
+  return typed || cm.weights != kWeightsPosition || cm.extrapolate != 0;
+}
+
+}  // namespace
+
+bool train_in_blocks(int W, int cap) { return W <= kMaxWindow && cap >= kMinCap; }
+
+// Entries a strip covers: those older than the two blocks in the lanes.
+static int strip_width(int P, int cap, bool continued) {
+  const int by_cap = (std::max(cap - 2 * kBlk - 1, 0) + 15) / 16 * 16;
+  return continued ? by_cap : std::min(by_cap, std::max(0, kBlk * (blocks_of(P) - 3)));
+}
+
+size_t train_blocks_bytes(int M2, int K, int P, int cap, bool continued, int blocks) {
+  return head_bytes(M2, K) + (size_t)std::min(blocks, blocks_of(P)) * block_bytes(strip_width(P, cap, continued));
+}
+
+int train_blocks_of(int P) { return blocks_of(P); }
+
+int train_blocks_in(int M2, int K, int P, int cap, bool continued, size_t bytes) {
+  const size_t head = head_bytes(M2, K), per = block_bytes(strip_width(P, cap, continued));
+  return bytes < head + per ? 0 : (int)std::min<size_t>((bytes - head) / per, blocks_of(P));
+}
+
+void train_block_job(BlockJob& j, int P, int M2, int K, int cap, bool continued, void* workspace) {
+  j.P = P;
+  j.M2 = M2;
+  j.Kt = K;
+  j.cap = cap;
+  const int groups = (K + kSerial - 1) / kSerial;
+  j.ku = (K + groups - 1) / groups;
+  j.SW = strip_width(P, cap, continued);
+  j.qa = 0;
+  j.qb = blocks_of(P);
+  j.write_dict = continued ? 0 : 1;
+  unsigned char* ws = static_cast<unsigned char*>(workspace);
+  j.header = reinterpret_cast<int32_t*>(ws);
+  j.carry = reinterpret_cast<float*>(ws + 256);
+  j.images = reinterpret_cast<float*>(ws + head_bytes(M2, K));
+  j.strips = j.images + (size_t)(j.qb - j.qa) * kTrainImage;
+}
+
+int train_prepare_units(const BlockJob& j) {
+  const Units u = units_of(j);
+  return u.images + u.groups * u.tiles + u.dict;
+}
+
+size_t train_prepare_lds(int M2) { return (size_t)prep_floats_of(M2) * sizeof(float); }
+size_t train_sweep_lds(int M2) { return (size_t)sweep_lds(M2).total * sizeof(float); }
+int train_group_users(int K) { return (K + (K + kSerial - 1) / kSerial - 1) / ((K + kSerial - 1) / kSerial); }
+
+// Detectors of one shape, `blocks` of each held by their workspaces at a
+// time.
+hipError_t launch_train_blocks(BlockArgs& a, int blocks, hipStream_t s) {
+  const BlockJob& j0 = a.jobs[0];
+  const int NB = blocks_of(j0.P);
+  const size_t plds = train_prepare_lds(j0.M2), slds = train_sweep_lds(j0.M2);
+  const bool gen = general(a.cm, j0.st != nullptr);
+  a.groups = (j0.Kt + kSerial - 1) / kSerial;
+  hipError_t e = set_lds(prepare_kernel, plds);
+  for (int q = 0; q < NB && e == hipSuccess; q += blocks) {
+    for (int i = 0; i < a.n; ++i) {
+      BlockJob& j = a.jobs[i];
+      j.qa = q;
+      j.qb = std::min(q + blocks, NB);
+      j.strips = j.images + (size_t)(j.qb - j.qa) * kTrainImage;
+      if (q > 0) j.write_dict = 0;
+    }
+    hipLaunchKernelGGL(prepare_kernel, dim3(train_prepare_units(a.jobs[0]), a.n), dim3(kPrepThreads), plds, s, a);
+    e = hipGetLastError();
+    if (e != hipSuccess) break;
+    if (window_rows(a.cm.W) == 2)
+      e = gen ? launch_sweep_args<true, 2>(a, slds, s) : launch_sweep_args<false, 2>(a, slds, s);
+    else
+      e = gen ? launch_sweep_args<true, 3>(a, slds, s) : launch_sweep_args<false, 3>(a, slds, s);
+  }
+  if (e == hipSuccess && a.cm.init == kInitContinue) {
+    hipLaunchKernelGGL(continued_dict_kernel, dim3((j0.cap + kDictSlots - 1) / kDictSlots, a.n), dim3(kPrepThreads), 0,
+                       s, a);
+    e = hipGetLastError();
+  }
+  return e;
+}
+
+hipError_t launch_train_prepare_table(const BlockJob* jobs, const int2* items, int n, const TrainCommon& cm,
+                                      size_t lds, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  hipError_t e = set_lds(prepare_table_kernel, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(prepare_table_kernel, dim3(n), dim3(kPrepThreads), lds, s, jobs, items, cm);
+  return hipGetLastError();
+}
+
+template <bool GEN, int NRW>
+static hipError_t launch_table(const BlockJob* jobs, const int2* items, int n, const TrainCommon& cm, size_t lds,
+                               hipStream_t s) {
+  hipError_t e = set_lds(sweep_table_kernel<GEN, NRW>, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((sweep_table_kernel<GEN, NRW>), dim3(n), dim3(kThreads), lds, s, jobs, items, cm);
+  return hipGetLastError();
+}
+
+hipError_t launch_train_sweep_table(const BlockJob* jobs, const int2* items, int n, const TrainCommon& cm, size_t lds,
+                                    hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  const bool gen = general(cm, false);
+  if (window_rows(cm.W) == 2)
+    return gen ? launch_table<true, 2>(jobs, items, n, cm, lds, s) : launch_table<false, 2>(jobs, items, n, cm, lds, s);
+  return gen ? launch_table<true, 3>(jobs, items, n, cm, lds, s) : launch_table<false, 3>(jobs, items, n, cm, lds, s);
+}
+
+}  // namespace apsm

@@ -275,15 +275,16 @@ __global__ __launch_bounds__(64 * (kSerial + helpers(MODE))) void unb_sweep_kern
         const float kj = kd[kBlk * q + ht - kBlk * kSerial];
         ikn[ht - kBlk * kSerial] = kj > 0.0f ? -1.0f / kj : 0.0f;
       }
+      auto c4 = [&](int d) { return coef[d * kSerial + lane]; };
       BlockSums s;
 #pragma unroll
       for (int v = 0; v < 8; ++v) s.v[v] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-      block_accumulate(s, Km + (size_t)q * TP * kBlk, kBlk, coef, TP, wave - kSerial, kHelpers, lane);
+      block_accumulate(s, Km + (size_t)q * TP * kBlk, c4, 0, TP, wave - kSerial, kHelpers, lane);
       block_store(s, part, wave - kSerial, lane);
       if constexpr (TAPE) {
 #pragma unroll
         for (int v = 0; v < 8; ++v) s.v[v] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-        block_accumulate(s, Hm + (size_t)q * TP * kBlk, kBlk, coef, TP, wave - kSerial, kHelpers, lane);
+        block_accumulate(s, Hm + (size_t)q * TP * kBlk, c4, 0, TP, wave - kSerial, kHelpers, lane);
         block_store(s, part + kPartFloats, wave - kSerial, lane);
       }
     }

@@ -110,6 +110,12 @@ __device__ __forceinline__ void load_image(const float* img, int lane, float* k)
   }
 }
 
+// The sum of the two halves' values, in both.
+__device__ __forceinline__ float halves_sum(float x) {
+  const auto z = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(z[0]) + __uint_as_float(z[1]);
+}
+
 // Corrections of the entering block's members for the coefficients C pending
 // in the lanes, which the expansion does not hold yet: the lower half of the
 // wave has those of the block about to leave, the upper half those of the
@@ -121,8 +127,19 @@ __device__ __forceinline__ float pending_sum(const float* img, float C, int lane
   float f;
   row_mul(f, __uint_as_float(y[0]), kf);
   row_fma(f, __uint_as_float(y[1]), kf + 16);
-  const auto z = __builtin_amdgcn_permlane32_swap(__float_as_uint(f), __float_as_uint(f), false, false);
-  return __uint_as_float(z[0]) + __uint_as_float(z[1]);
+  return halves_sum(f);
+}
+
+// The sum over the wave, in every lane.
+__device__ __forceinline__ float wave_sum(float x) {
+  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x128, 0xF, 0xF, true));
+  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x124, 0xF, 0xF, true));
+  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x122, 0xF, 0xF, true));
+  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x121, 0xF, 0xF, true));
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
 // The upper half's value in both halves.
@@ -143,33 +160,38 @@ __device__ __forceinline__ void lds_copy(const float* src, float* dst, int n, in
 }
 __device__ __forceinline__ void lds_copy_wait() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
 
-// Evaluation of a block's 32 members against the entries d in [0, n) by the
+// Evaluation of a block's 32 members against the entries [d0, n) by the
 // helper waves, four users at a time, on v_mfma_f32_4x4x1_16b_f32: its 16
 // blocks take 16 entries, rows four members, columns the users.  vals: the
-// kernel values, entry d's 32 members contiguous at vals + d * stride
-// (16-byte aligned); coef: [n][4] coefficients (LDS or global); n a multiple
-// of 16.  Helper hw takes every NH-th group of 16 entries; its sums over them go
-// to part[hw][member][user].
+// kernel values, entry d's 32 members contiguous at vals + 32 d (16-byte
+// aligned); coef(d): this lane's coefficient of the 16 entries from d on
+// (entry lane / 4, user lane % 4); d0 and n multiples of 16.  Helper hw takes
+// every nh-th group of 16 entries; its sums over them go to
+// part[hw][member][user].
 struct BlockSums {
   floatx4 v[8];
 };
 
 template <class Coef>
-__device__ __forceinline__ void block_accumulate(BlockSums& a, const float* vals, size_t stride, const Coef* coef,
-                                                 int n, int hw, int nh, int lane) {
-  const int b = lane >> 2, r = lane & 3;
+__device__ __forceinline__ void block_accumulate(BlockSums& a, const float* vals, Coef&& coef, int d0, int n, int hw,
+                                                 int nh, int lane) {
+  // scalar base per group, one lane offset for all (no address registers)
+  typedef __attribute__((address_space(1))) const floatx4 gvec;
+  typedef __attribute__((address_space(1))) const char gbyte;
+  gbyte* const base = (gbyte*)vals;
+  const unsigned off = (unsigned)((lane >> 2) * kBlk + 8 * (lane & 3)) * 4u;
   constexpr int U = 8;                     // groups in flight: 16 KiB a wave, to cover the memory latency
-  int d0 = 16 * hw;
+  d0 += 16 * hw;
   for (; d0 + 16 * nh * (U - 1) < n; d0 += 16 * nh * U) {
     floatx4 x[U][2];
     float c[U];
 #pragma unroll
     for (int q = 0; q < U; ++q) {
       const int d = d0 + 16 * nh * q;
-      const float* p = vals + (size_t)(d + b) * stride + 8 * r;
-      x[q][0] = *reinterpret_cast<const floatx4*>(p);
-      x[q][1] = *reinterpret_cast<const floatx4*>(p + 4);
-      c[q] = coef[(size_t)d * 4 + lane];
+      gbyte* const p = base + (size_t)d * (kBlk * 4);
+      x[q][0] = *(gvec*)(p + off);
+      x[q][1] = *(gvec*)(p + off + 16);
+      c[q] = coef(d);
     }
 #pragma unroll
     for (int q = 0; q < U; ++q)
@@ -178,9 +200,9 @@ __device__ __forceinline__ void block_accumulate(BlockSums& a, const float* vals
         a.v[v] = __builtin_amdgcn_mfma_f32_4x4x1f32(x[q][v >> 2][v & 3], c[q], a.v[v], 0, 0, 0);
   }
   for (; d0 < n; d0 += 16 * nh) {
-    const float* p = vals + (size_t)(d0 + b) * stride + 8 * r;
-    const floatx4 x0 = *reinterpret_cast<const floatx4*>(p), x1 = *reinterpret_cast<const floatx4*>(p + 4);
-    const float c = coef[(size_t)d0 * 4 + lane];
+    gbyte* const p = base + (size_t)d0 * (kBlk * 4);
+    const floatx4 x0 = *(gvec*)(p + off), x1 = *(gvec*)(p + off + 16);
+    const float c = coef(d0);
 #pragma unroll
     for (int v = 0; v < 8; ++v)
       a.v[v] = __builtin_amdgcn_mfma_f32_4x4x1f32(v < 4 ? x0[v & 3] : x1[v & 3], c, a.v[v], 0, 0, 0);
