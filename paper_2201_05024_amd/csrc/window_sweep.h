@@ -180,32 +180,47 @@ __device__ __forceinline__ void block_accumulate(BlockSums& a, const float* vals
   typedef __attribute__((address_space(1))) const char gbyte;
   gbyte* const base = (gbyte*)vals;
   const unsigned off = (unsigned)((lane >> 2) * kBlk + 8 * (lane & 3)) * 4u;
-  constexpr int U = 8;                     // groups in flight: 16 KiB a wave, to cover the memory latency
-  d0 += 16 * hw;
-  for (; d0 + 16 * nh * (U - 1) < n; d0 += 16 * nh * U) {
+  // rounds of U groups, the next round's loads issued before this round's
+  // products: 8 to 16 KiB in flight a wave, to cover the memory latency; past
+  // the end a valid group is read again, with coefficients 0
+  constexpr int U = 4;
+  struct Round {
     floatx4 x[U][2];
     float c[U];
+  };
+  const int step = 16 * nh;
+  d0 += 16 * hw;
+  if (d0 >= n) return;
+  auto load = [&](Round& r, int d) {
 #pragma unroll
     for (int q = 0; q < U; ++q) {
-      const int d = d0 + 16 * nh * q;
-      gbyte* const p = base + (size_t)d * (kBlk * 4);
-      x[q][0] = *(gvec*)(p + off);
-      x[q][1] = *(gvec*)(p + off + 16);
-      c[q] = coef(d);
+      const bool in = d + step * q < n;
+      const int dq = in ? d + step * q : d;
+      gbyte* const p = base + (size_t)dq * (kBlk * 4);
+      r.x[q][0] = *(gvec*)(p + off);
+      r.x[q][1] = *(gvec*)(p + off + 16);
+      const float c = coef(dq);
+      r.c[q] = in ? c : 0.0f;
     }
+  };
+  auto add = [&](const Round& r) {
 #pragma unroll
     for (int q = 0; q < U; ++q)
 #pragma unroll
       for (int v = 0; v < 8; ++v)
-        a.v[v] = __builtin_amdgcn_mfma_f32_4x4x1f32(x[q][v >> 2][v & 3], c[q], a.v[v], 0, 0, 0);
-  }
-  for (; d0 < n; d0 += 16 * nh) {
-    gbyte* const p = base + (size_t)d0 * (kBlk * 4);
-    const floatx4 x0 = *(gvec*)(p + off), x1 = *(gvec*)(p + off + 16);
-    const float c = coef(d0);
-#pragma unroll
-    for (int v = 0; v < 8; ++v)
-      a.v[v] = __builtin_amdgcn_mfma_f32_4x4x1f32(v < 4 ? x0[v & 3] : x1[v & 3], c, a.v[v], 0, 0, 0);
+        a.v[v] = __builtin_amdgcn_mfma_f32_4x4x1f32(r.x[q][v >> 2][v & 3], r.c[q], a.v[v], 0, 0, 0);
+  };
+  Round r0, r1;
+  load(r0, d0);
+  for (;;) {
+    d0 += step * U;
+    if (d0 < n) load(r1, d0);
+    add(r0);
+    if (d0 >= n) break;
+    d0 += step * U;
+    if (d0 < n) load(r0, d0);
+    add(r1);
+    if (d0 >= n) break;
   }
 }
 
