@@ -32,7 +32,7 @@ namespace {
 
 using namespace sweep;
 
-constexpr int kHelpers = 8;
+constexpr int kHelpers = 8;                  // (the linear part is split over them by components)
 constexpr int kThreads = 64 * (kSerial + kHelpers);
 constexpr int kPartFloats = kHelpers * kBlk * kSerial;
 constexpr int kMinCap = 96;
@@ -358,15 +358,44 @@ struct Lane {
   float e;         // running prediction
   float C;         // pending coefficient
   float b, ikn;    // target, -1 / kappa(r, r) (0 where that is not positive)
-  float bad;       // not finite once a residual was not
+  float bad;       // not finite once a prediction or a target was not
   int kind;        // set kind
   int d;           // sample, negative for none
 };
 
-// 16 steps (or the fewer of the sequence's end) whose newest members lie in
-// row A of the wave; n0 the first of them, t0 its place in the block.  GEN:
+// 16 steps whose newest members lie in row A of the wave, t0 the place of the
+// first in its block, with the window full: position weights, hyperslabs.
+// Bound by the issue of one wave (5 cycles an instruction): with three window
+// rows 48 FMAs of the matrix-vector product and about 18 more, 3 with
+// evictions.
+template <int NRW, int A, bool EV>
+__device__ __forceinline__ void full_row(Lane& s, const float* kreg, int t0, float eps, float qsW, const float* om,
+                                         const float* ev, float aev, int lane) {
+#pragma clang fp contract(off)
+  float w = om[(16 * A - lane) & 63];       // weight of the lane's member (0 outside the window)
+  const float iq = s.ikn * qsW;
+  const float* e0 = ev + t0 * 64 + lane;
+  float kv = EV ? e0[0] : 0.0f;
+#pragma unroll 4
+  for (int it = 0; it < 16; ++it) {
+    const float t = w * iq;
+    w = from_below(w);                      // every member is one step older
+    if constexpr (EV) {
+      // the members in the window lose the entry that leaves; the next
+      // step's values are read a step ahead
+      const float a = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(aev), t0 + it));
+      s.e = fmaf(-a, kv, s.e);
+      kv = e0[(it + 1) * 64];
+    }
+    const float c = slab_residual_pos(s.e - s.b, eps) * t;
+    s.C += c;
+    s.e += window_product<A, NRW>(broadcast_rows(c), kreg);
+  }
+}
+
+// 16 steps, or the fewer of the sequence's end; n0 the first of them.  GEN:
 // any set weights, relaxation and set kinds; else position weights and
-// hyperslabs.
+// hyperslabs (here while the window fills, and at the end).
 template <bool GEN, int NRW, int A>
 __device__ __forceinline__ void train_row(Lane& s, const float* kreg, int n0, int t0, int cnt, const TrainCommon& cm,
                                           bool typed, float qsW, const float* om, const float* qs, bool evict,
@@ -374,30 +403,31 @@ __device__ __forceinline__ void train_row(Lane& s, const float* kreg, int n0, in
 #pragma clang fp contract(off)
   if (cnt <= 0) return;
   const int W = cm.W;
+  if (!GEN && cnt == 16 && n0 + 1 >= W) {
+    if (evict) full_row<NRW, A, true>(s, kreg, t0, cm.eps, qsW, om, ev, aev, lane);
+    else full_row<NRW, A, false>(s, kreg, t0, cm.eps, qsW, om, ev, aev, lane);
+    return;
+  }
   const float inv_mu = 1.0f / cm.mu;
-  int age = (16 * A - lane) & 63;           // 33..63: not yet a member
-  float wv = om[age];
+  float wv = om[(16 * A - lane) & 63];
   float kv = evict ? ev[t0 * 64 + lane] : 0.0f;
   for (int it = 0; it < cnt; ++it) {
     const int n = n0 + it;
     const float q = n + 1 < W ? qs[n + 1] : qsW;   // mu / (omega_0 + .. + omega_{L-1})
     const float wq = wv * q, wcur = wv, kcur = kv;
-    age = (age + 1) & 63;                   // the next step's reads are issued a step ahead
-    wv = om[age];
+    wv = from_below(wv);
     if (evict) {
-      // the members in the window lose the entry that leaves
       const float a = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(aev), t0 + it));
       s.e = fmaf(-a, kcur, s.e);
       kv = ev[(t0 + it + 1) * 64 + lane];   // (past the last step: not used)
     }
     const float x = s.e - s.b;
-    s.bad = fmaf(x, 0.0f, s.bad);
     if constexpr (!GEN) {
-      const float c = slab_residual(x, cm.eps) * (wq * s.ikn);
+      const float c = slab_residual_pos(x, cm.eps) * (wcur * (s.ikn * q));
       s.C += c;
       s.e += window_product<A, NRW>(broadcast_rows(c), kreg);
     } else {
-      float res = slab_residual(x, cm.eps);
+      float res = slab_residual_pos(x, cm.eps);
       if (typed) {
         res = s.kind == kSetPlane   ? x
               : s.kind == kSetUpper ? fmaxf(x - cm.eps, 0.0f)
@@ -492,10 +522,10 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
   const float qsW = qs[W];
 
   auto rows_of = [&](int q) { return rows + (q & 3) * kBlk * RS; };
-  // element r of block q's vectors [32][M2P] (scalar base, small lane offset)
+  // component m of vector i of block q (scalar base, small lane offset)
   const int rsh = 31 - __builtin_clz(M2P);
-  auto vec_load = [&](int q, int r) -> float {
-    const int i = r >> rsh, m = r & (M2P - 1), M = M2 >> 1;
+  auto vec_load = [&](int q, int i, int m) -> float {
+    const int M = M2 >> 1;
     const bool ok = m < M2 && 16 * q + (i >> 1) < j.P, odd = (i & 1) != 0;
     const gfloat* base = src.rx + (size_t)(16 * q) * M2;
     const unsigned off = ok ? (unsigned)((i >> 1) * M2 + (odd ? (m < M ? m + M : m - M) : m)) : 0u;
@@ -505,7 +535,7 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
   if (!first) {                             // vectors staged by the launch before
     for (int e = tid; e < 3 * kBlk * M2P; e += kThreads) {
       const int q = j.qa - 3 + (e >> (5 + rsh)), r = e & (kBlk * M2P - 1);
-      if (q >= 0) rows_of(q)[(r >> rsh) * RS + (r & (M2P - 1))] = vec_load(q, r);
+      if (q >= 0) rows_of(q)[(r >> rsh) * RS + (r & (M2P - 1))] = vec_load(q, r >> rsh, r & (M2P - 1));
     }
   }
   // v += sum_i C_i r_i over the 32 samples of block q, their C in
@@ -550,23 +580,10 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
         // the lower half's block goes into the expansion, the upper half
         // moves down, q's members come in
         const float f = pending_sum(image + kMatrixImage, s.C, lane);
-        float lin = 0.0f;
-        {
-          const int h = upper ? M2P / 2 : 0;
-          const float* r = rows_of(q) + il * RS + h;
-          const float* v = vlin + u * M2P + h;
-          float l4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-          for (int m = 0; m < M2P / 2; m += 4) {
-            const floatx4 a = *reinterpret_cast<const floatx4*>(r + m), b = *reinterpret_cast<const floatx4*>(v + m);
-#pragma unroll
-            for (int x = 0; x < 4; ++x) l4[x] = fmaf(a[x], b[x], l4[x]);
-          }
-          lin = halves_sum((l4[0] + l4[1]) + (l4[2] + l4[3]));
-        }
         float sum = 0.0f;
 #pragma unroll
         for (int w = 0; w < kHelpers; ++w) sum += part[(w * kBlk + il) * kSerial + u];
-        const float e = fmaf(cm.wl, lin, sum + f);
+        const float e = sum + f;
         if (!upper) {
           flushed[il * kSerial + u] = s.d >= 0 ? s.C : 0.0f;
           if (s.d >= 0) set_coef(s.d, u, s.C);
@@ -580,6 +597,7 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
         s.b = upper ? b : bu;
         s.ikn = upper ? ik : iu;
         s.d = upper ? kBlk * q + il : du;
+        s.bad = fmaf(b, 0.0f, s.bad);
         if constexpr (GEN) {
           const int ku = __float_as_int(upper_half(__int_as_float(s.kind)));
           s.kind = upper ? kind[il * kSerial + u] : ku;
@@ -594,6 +612,7 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
         train_row<GEN, NRW, 2>(s, kreg, nb, 0, rem < 16 ? rem : 16, cm, typed, qsW, om, qs, evict, ev, aev, lane);
         train_row<GEN, NRW, 3>(s, kreg, nb + 16, 16, rem < 32 ? rem - 16 : 16, cm, typed, qsW, om, qs, evict, ev, aev,
                                lane);
+        s.bad = fmaf(s.e, 0.0f, s.bad);     // a residual that was not finite leaves its prediction so
       }
     }
     if (active) {
@@ -615,7 +634,9 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
     }
     __syncthreads();
   } else {
-    const int hw = wave - kSerial, ht = tid - 64 * kSerial, nt = 64 * kHelpers;
+    const int hw = wave - kSerial, ht = tid - 64 * kSerial;
+    // components [mlo, mlo + MR) of the vectors and of v are this wave's
+    const int MR = M2P / kHelpers, msh = rsh - 3, mlo = hw * MR;
     // what block q needs: image, eviction values, targets, vectors, the sums
     // of its members over the entries; the block flushed before enters the
     // linear part.  Loads first, the sums next, stores last: the latencies
@@ -635,11 +656,12 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
           if constexpr (GEN) kd = typed ? gmem(j.st)[at] : 0;
         }
       }
-      float rv[8];                          // 32 vectors of up to 128 components over 512 threads
+      // this wave's components of the block's vectors, up to 8 per lane
+      float rv[8];
 #pragma unroll
       for (int x = 0; x < 8; ++x) {
-        const int e = ht + x * nt;
-        rv[x] = e < kBlk * M2P ? vec_load(q, e) : 0.0f;
+        const int e = lane + 64 * x;
+        rv[x] = e < kBlk * MR ? vec_load(q, e >> msh, mlo + (e & (MR - 1))) : 0.0f;
       }
       float av = 0.0f;
       if (ht < kBlk * kSerial) {
@@ -668,10 +690,29 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
       }
 #pragma unroll
       for (int x = 0; x < 8; ++x) {
-        const int e = ht + x * nt;
-        if (e < kBlk * M2P) rows_of(q)[(e >> rsh) * RS + (e & (M2P - 1))] = rv[x];
+        const int e = lane + 64 * x;
+        if (e < kBlk * MR) rows_of(q)[(e >> msh) * RS + mlo + (e & (MR - 1))] = rv[x];
       }
-      if (q > j.qa) take_linear(q - 3, 0, ht);
+      // this wave's components of the linear part: the flushed block enters
+      // v, then v . r of the members joins the wave's sums (the wave reads
+      // what its own lanes wrote: LDS operations of a wave are in order)
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      if (q > j.qa && lane < kSerial * MR) take_linear(q - 3, 0, (lane >> msh) * M2P + mlo + (lane & (MR - 1)));
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      {
+        const int i = lane & 31, u0 = 2 * (lane >> 5);
+        const float* r = rows_of(q) + i * RS + mlo;
+        const float* v = vlin + u0 * M2P + mlo;
+        float l0 = 0.0f, l1 = 0.0f;
+        for (int m = 0; m < MR; m += 2) {
+          const float a = r[m], b2 = r[m + 1];
+          l0 = fmaf(a, v[m], fmaf(b2, v[m + 1], l0));
+          l1 = fmaf(a, v[M2P + m], fmaf(b2, v[M2P + m + 1], l1));
+        }
+        float* p = part + (hw * kBlk + i) * kSerial + u0;
+        p[0] = fmaf(cm.wl, l0, p[0]);
+        p[1] = fmaf(cm.wl, l1, p[1]);
+      }
       lds_copy_wait();
     };
     prepare(j.qa);

@@ -30,13 +30,13 @@ using namespace sweep;
 enum { kForward = 0, kTape = 1, kReverse = 2 };
 
 // Helper waves of a sweep: they read a strip of the kernel matrix (128 KiB
-// at T = 1024) per block while the block before takes about 6 us, which is a
+// at T = 1024) per block while the block before takes about 5 us, which is a
 // matter of loads in flight: 64 x 20 x 1024 steps forward took 6.9 ms with 4,
-// 4.9 ms with 8.  With the tape (two strips, 156 registers) 12 waves fit a CU,
-// else 16; the forward passes keep to the tape's number, so that a re-run
-// sums in the same order and gives the same bits.
-constexpr int helpers(int mode) { return mode == kReverse ? 12 : 8; }
-constexpr int part_floats(int mode) { return helpers(mode) * kBlk * kSerial; }
+// 4.9 ms with 8; 12 in all leave 168 registers a wave.  All modes alike, so
+// that a re-run sums in the same order and gives the same bits.
+constexpr int kHelpers = 8;
+constexpr int kThreads = 64 * (kSerial + kHelpers);
+constexpr int kPartFloats = kHelpers * kBlk * kSerial;
 
 __device__ __forceinline__ float comp(const float* rx, int M2, int n, int m) {
   const int M = M2 >> 1;
@@ -126,17 +126,17 @@ __global__ __launch_bounds__(256) void unb_image_kernel(UnrolledArgs a) {
 struct SweepLds {
   int coef, image, part, stage, ikn, om, qs, xs, total;
 };
-__host__ __device__ inline SweepLds sweep_lds(int mode, int TP, int W) {
+__host__ __device__ inline SweepLds sweep_lds(int mode, int TP) {
   const int n2 = mode == kTape ? 2 : 1;
   SweepLds l{};
   int o = 0;
   l.coef = o;  o += TP * kSerial;
-  l.part = o;  o += n2 * part_floats(mode);
+  l.part = o;  o += n2 * kPartFloats;
   l.stage = o; o += kBlk * kSerial;
   l.ikn = o;   o += kBlk;
   l.om = o;    o += 64;
   l.qs = o;    o += 64;
-  l.xs = o;    o += mode == kReverse ? (2 * kBlk * kSerial * W + 64) / 4 * 4 : 0;
+  l.xs = o;    o += mode == kReverse ? 2 * kBlk * kSerial * 64 : 0;
   l.image = o; o += n2 * kImage;            // every offset a multiple of four floats: float4 reads
   l.total = o;
   return l;
@@ -151,45 +151,46 @@ struct Lane {
 };
 
 // 16 steps (or the fewer of the sequence's end) whose newest members lie in
-// row A of the wave; n0 the first of them, cnt their number.
-template <int MODE, int NRW, int A>
-__device__ __forceinline__ void sweep_row(Lane& s, const float* kreg, const float* hreg, int n0, int cnt, int W,
-                                          float eps, float qsW, const float* om, const float* qs, const float* xs,
-                                          int xstep, float* tx, float* th, size_t tstep, int lane) {
+// row A of the wave; n0 the first of them, cnt their number.  FULL: all 16,
+// with the window full.  xs: the taped x of the steps, [step][user][lane].
+template <int MODE, int NRW, int A, bool FULL>
+__device__ __forceinline__ void sweep_steps(Lane& s, const float* kreg, const float* hreg, int n0, int cnt, int W,
+                                            float eps, float qsW, const float* om, const float* qs, const float* xs,
+                                            float* tx, float* th, size_t tstep, int lane) {
 #pragma clang fp contract(off)
-  if (cnt <= 0) return;
-  constexpr int DIR = MODE == kReverse ? -1 : 1;
-  int n = MODE == kReverse ? n0 + cnt - 1 : n0;
-  int age = (16 * A + n - n0 - lane) & 63;   // 33..63: not yet a member
-  float wv = om[age];
-  float xv = 0.0f;
-  if constexpr (MODE == kReverse) xv = xs[(n - n0) * xstep + age];
-  for (int it = 0; it < cnt; ++it, n += DIR) {
-    // weight of each lane's member (0 outside the window); the next step's
-    // reads are issued here, a step ahead of their use
-    const float q = n + 1 < W ? qs[n + 1] : qsW;
-    float t = (wv * q) * s.ikn;
-    const int cur = age;
-    const float xcur = xv;
-    age = (age + DIR) & 63;
-    wv = om[age];
-    if constexpr (MODE == kReverse) {
-      const int nx = it + 1 < cnt ? n - 1 - n0 : 0;
-      xv = xs[nx * xstep + age];
-    }
+  constexpr bool REV = MODE == kReverse;
+  const int last = FULL ? 15 : cnt - 1;
+  const int t0 = REV ? last : 0;            // first step taken
+  // weight of each lane's member (0 outside the window) and its place on the
+  // tape: from step to step every member's age moves by one, which is the
+  // neighbour lane's
+  float wv = om[(16 * A + t0 - lane) & 63];
+  float at = __int_as_float((16 * A + t0 - lane) & 63);
+  const float iq = s.ikn * qsW;
+  float xv = REV ? xs[t0 * kSerial * 64 + lane] : 0.0f;
+  const int steps = FULL ? 16 : cnt;
+#pragma unroll 4
+  for (int it = 0; it < steps; ++it) {
+    const int t = REV ? last - it : it, n = n0 + t;
+    float w = FULL || n + 1 >= W ? wv * iq : (wv * qs[n + 1]) * s.ikn;
+    const float wq = w;
+    const int age = __float_as_int(at);
+    wv = REV ? from_above(wv) : from_below(wv);
+    if constexpr (MODE != kForward) at = REV ? from_above(at) : from_below(at);
     float c;
-    if constexpr (MODE == kReverse) {
+    if constexpr (REV) {
       // adjoint of the active members: xbar = -mu q cbar / kappa
-      t = fabsf(xcur) - eps > 0.0f ? t : 0.0f;
-      c = s.e * t;
-      if (cur < W) tx[(size_t)n * tstep + cur] = s.e;
+      w = fabsf(xv) - eps > 0.0f ? wq : 0.0f;
+      xv = xs[(t > 0 ? t - 1 : 0) * kSerial * 64 + lane];   // the next step's, a step ahead
+      c = s.e * w;
+      if (age < W) (tx + (size_t)n * tstep)[(unsigned)age] = s.e;
     } else {
       const float x = s.e - s.b;
-      c = slab_residual(x, eps) * t;
+      c = slab_residual(x, eps) * w;
       if constexpr (MODE == kTape) {
-        if (cur < W) {
-          tx[(size_t)n * tstep + cur] = x;
-          th[(size_t)n * tstep + cur] = s.h;
+        if (age < W) {
+          (tx + (size_t)n * tstep)[(unsigned)age] = x;
+          (th + (size_t)n * tstep)[(unsigned)age] = s.h;
         }
       }
     }
@@ -200,17 +201,25 @@ __device__ __forceinline__ void sweep_row(Lane& s, const float* kreg, const floa
   }
 }
 
+template <int MODE, int NRW, int A>
+__device__ __forceinline__ void sweep_row(Lane& s, const float* kreg, const float* hreg, int n0, int cnt, int W,
+                                          float eps, float qsW, const float* om, const float* qs, const float* xs,
+                                          float* tx, float* th, size_t tstep, int lane) {
+  if (cnt == 16 && n0 + 1 >= W)
+    sweep_steps<MODE, NRW, A, true>(s, kreg, hreg, n0, 16, W, eps, qsW, om, qs, xs, tx, th, tstep, lane);
+  else if (cnt > 0)
+    sweep_steps<MODE, NRW, A, false>(s, kreg, hreg, n0, cnt, W, eps, qsW, om, qs, xs, tx, th, tstep, lane);
+}
+
 // Passes [p0, p1) of one instance and one group of at most four users.
 // Forward: from zero (p0 = 0), writing a checkpoint of C at every pass p % E
 // == 0 and C at the end.  Tape: from checkpoint p0 / E, writing x and h of
 // the window members of every step.  Reverse: passes p1 - 1 .. p0 backwards,
 // X carried in the workspace, writing cbar of the members.
 template <int MODE, int NRW>
-__global__ __launch_bounds__(64 * (kSerial + helpers(MODE))) void unb_sweep_kernel(UnrolledArgs a, int p0, int p1,
-                                                                                   int groups, int ku) {
+__global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int p0, int p1, int groups, int ku) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
   constexpr bool REV = MODE == kReverse, TAPE = MODE == kTape;
-  constexpr int kHelpers = helpers(MODE), kThreads = 64 * (kSerial + kHelpers), kPartFloats = part_floats(MODE);
   // workgroups go round the eight XCDs: the user groups of an instance, which
   // read the same strips, are eight apart, on one XCD and its L2
   const int inst = (int)(blockIdx.x / (8 * groups)) * 8 + (blockIdx.x & 7);
@@ -228,7 +237,7 @@ __global__ __launch_bounds__(64 * (kSerial + helpers(MODE))) void unb_sweep_kern
   const float* cb0 = part_of<float>(a, inst, a.off_cb0);
   float* const ck = part_of<float>(a, inst, a.off_ck);
   const float* sym = a.sym_pilot + (size_t)inst * a.P * K * 2;
-  const SweepLds L = sweep_lds(MODE, TP, W);
+  const SweepLds L = sweep_lds(MODE, TP);
   float* const coef = lds + L.coef;
   float* const image = lds + L.image;
   float* const part = lds + L.part;
@@ -289,8 +298,8 @@ __global__ __launch_bounds__(64 * (kSerial + helpers(MODE))) void unb_sweep_kern
       }
     }
     if (REV && st >= 0 && st < NB) {
-      // taped x of the block's steps, [step][user][age]
-      float* dst = lds + L.xs + (st & 1) * kBlk * kSerial * W;
+      // taped x of the block's steps, [step][user][age] there, by lane here
+      float* dst = lds + L.xs + (st & 1) * kBlk * kSerial * 64;
       const int steps = T - kBlk * st < kBlk ? T - kBlk * st : kBlk;
       const float* tx = part_of<float>(a, inst, a.off_tx) + (size_t)((p - p0) * T + kBlk * st) * K * W;
       const int total = steps * nu * W;
@@ -306,7 +315,8 @@ __global__ __launch_bounds__(64 * (kSerial + helpers(MODE))) void unb_sweep_kern
         for (int x = 0; x < 8; ++x) {
           const int e = e0 + 64 * kHelpers * x;
           const int t = e / (nu * W), r = e - t * nu * W;
-          if (e < total) dst[t * kSerial * W + r] = v[x];
+          const int uu = r / W, age = r - uu * W;
+          if (e < total) dst[(t * kSerial + uu) * 64 + ((t - age) & 63)] = v[x];
         }
       }
     }
@@ -377,11 +387,10 @@ __global__ __launch_bounds__(64 * (kSerial + helpers(MODE))) void unb_sweep_kern
         if (active && st >= 0 && st < NB) {
           const int n0 = kBlk * st, rem = T - n0;
           const int c0 = rem < 16 ? rem : 16, c1 = rem < 16 ? 0 : rem < 32 ? rem - 16 : 16;
-          const float* xs = lds + L.xs + (st & 1) * kBlk * kSerial * W + u * W;
+          const float* xs = lds + L.xs + ((st & 1) * kBlk * kSerial + u) * 64;
           const size_t ts = (size_t)K * W;
 #define APSM_SWEEP_ROW(A, n, c)                                                                       \
-  sweep_row<MODE, NRW, A>(s, kreg, hreg, n, c, W, eps, qsW, om, qs, xs + ((n) - n0) * kSerial * W, \
-                          kSerial * W, tw, thw, ts, lane)
+  sweep_row<MODE, NRW, A>(s, kreg, hreg, n, c, W, eps, qsW, om, qs, xs + ((n) - n0) * kSerial * 64, tw, thw, ts, lane)
           // forward the steps' block is the upper half, in reverse the lower
           if constexpr (REV) {
             APSM_SWEEP_ROW(1, n0 + 16, c1);
@@ -583,12 +592,12 @@ __global__ __launch_bounds__(256) void unb_grad_sum_kernel(UnrolledArgs a, float
 template <int MODE, int NRW>
 hipError_t launch_sweep_w(const UnrolledArgs& a, int p0, int p1, hipStream_t s) {
   auto kern = unb_sweep_kernel<MODE, NRW>;
-  const size_t bytes = sweep_lds(MODE, a.TP, a.W).total * sizeof(float);
+  const size_t bytes = sweep_lds(MODE, a.TP).total * sizeof(float);
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   if (e != hipSuccess) return e;
   const int groups = (a.K + kSerial - 1) / kSerial, ku = (a.K + groups - 1) / groups;
-  hipLaunchKernelGGL(kern, dim3((a.n + 7) / 8 * 8 * groups), dim3(64 * (kSerial + helpers(MODE))), bytes, s, a, p0, p1,
+  hipLaunchKernelGGL(kern, dim3((a.n + 7) / 8 * 8 * groups), dim3(kThreads), bytes, s, a, p0, p1,
                      groups, ku);
   return hipGetLastError();
 }

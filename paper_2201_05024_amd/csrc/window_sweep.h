@@ -48,6 +48,11 @@ __host__ __device__ constexpr int window_rows(int W) { return W <= 17 ? 2 : 3; }
   APSM_FMAC(3, 1) APSM_FMAC(4, 2) APSM_FMAC(5, 3) APSM_FMAC(6, 4) APSM_FMAC(7, 5) APSM_FMAC(8, 6)         \
   APSM_FMAC(9, 7) APSM_FMAC(10, 8) APSM_FMAC(11, 9) APSM_FMAC(12, 10) APSM_FMAC(13, 11) APSM_FMAC(14, 12) \
   APSM_FMAC(15, 13) APSM_FMAC(16, 14) APSM_FMAC(17, 15)
+#define APSM_FMAC_AT(i, r) "v_fmac_f32_dpp %0, %3, %" #i " row_ror:" #r " row_mask:0xf bank_mask:0xf\n\t"
+#define APSM_FMAC_ROW_AT                                                                                        \
+  APSM_FMAC_AT(5, 1) APSM_FMAC_AT(6, 2) APSM_FMAC_AT(7, 3) APSM_FMAC_AT(8, 4) APSM_FMAC_AT(9, 5)               \
+  APSM_FMAC_AT(10, 6) APSM_FMAC_AT(11, 7) APSM_FMAC_AT(12, 8) APSM_FMAC_AT(13, 9) APSM_FMAC_AT(14, 10)         \
+  APSM_FMAC_AT(15, 11) APSM_FMAC_AT(16, 12) APSM_FMAC_AT(17, 13) APSM_FMAC_AT(18, 14) APSM_FMAC_AT(19, 15)
 #define APSM_ROW_IN(x, k)                                                                              \
   "v"(x), "v"((k)[0]), "v"((k)[1]), "v"((k)[2]), "v"((k)[3]), "v"((k)[4]), "v"((k)[5]), "v"((k)[6]),  \
       "v"((k)[7]), "v"((k)[8]), "v"((k)[9]), "v"((k)[10]), "v"((k)[11]), "v"((k)[12]), "v"((k)[13]),  \
@@ -63,6 +68,10 @@ __device__ __forceinline__ void row_mul(float& acc, float x, const float* k) {
 __device__ __forceinline__ void row_fma(float& acc, float x, const float* k) {
   asm("s_nop 1\n\tv_fmac_f32_e32 %0, %1, %2\n\t" APSM_FMAC_ROW : "+v"(acc) : APSM_ROW_IN(x, k));
 }
+// The same where x was written well before (no wait states).
+__device__ __forceinline__ void row_fma_ready(float& acc, float x, const float* k) {
+  asm("v_fmac_f32_e32 %0, %1, %2\n\t" APSM_FMAC_ROW : "+v"(acc) : APSM_ROW_IN(x, k));
+}
 
 // The four 16-lane rows of x, each broadcast to every row.
 struct Rows {
@@ -76,20 +85,39 @@ __device__ __forceinline__ Rows broadcast_rows(float x) {
 }
 
 // sum_j K_lj c_j over the rows A, A - 1, .. (mod 4; NRW of them) that the
-// window ending in row A touches.
+// window ending in row A touches.  The broadcast rows are all operands of the
+// first block (the later ones pass through it), so that its leading wait
+// states cover every DPP read.
 template <int A, int NRW>
 __device__ __forceinline__ float window_product(const Rows& c, const float* k) {
   float acc;
-  row_mul(acc, c.r[A], k + 16 * A);
-  row_fma(acc, c.r[(A + 3) & 3], k + 16 * ((A + 3) & 3));
-  if constexpr (NRW > 2) row_fma(acc, c.r[(A + 2) & 3], k + 16 * ((A + 2) & 3));
+  const float x0 = c.r[A];
+  float x1 = c.r[(A + 3) & 3], x2 = c.r[(A + 2) & 3];
+  const float* k0 = k + 16 * A;
+  asm("s_nop 1\n\tv_mul_f32_e32 %0, %3, %4\n\t" APSM_FMAC_ROW_AT
+      : "=&v"(acc), "+v"(x1), "+v"(x2)
+      : APSM_ROW_IN(x0, k0));
+  row_fma_ready(acc, x1, k + 16 * ((A + 3) & 3));
+  if constexpr (NRW > 2) row_fma_ready(acc, x2, k + 16 * ((A + 2) & 3));
   return acc;
+}
+
+// x of the lane one below (lane 0: of lane 63), of the lane one above.
+__device__ __forceinline__ float from_below(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x13C, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float from_above(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x134, 0xF, 0xF, true));
 }
 
 // The residual of eqn:beta: sign(x) max(|x| - eps, 0), 0 for a NaN.
 __device__ __forceinline__ float slab_residual(float x, float eps) {
   const float m = fabsf(x) - eps;
   return m > 0.0f ? copysignf(m, x) : 0.0f;
+}
+// The same for eps >= 0: the median of x - eps, x + eps and 0.
+__device__ __forceinline__ float slab_residual_pos(float x, float eps) {
+  return __builtin_amdgcn_fmed3f(x - eps, x + eps, 0.0f);
 }
 
 // Value r of lane l in the pending image: member l % 32 of the entering block
