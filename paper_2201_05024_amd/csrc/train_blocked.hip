@@ -461,6 +461,142 @@ __device__ __forceinline__ void train_row(Lane& s, const float* kreg, int n0, in
   }
 }
 
+// The helper waves' side of a sweep, eight waves; MR: components of the
+// vectors and of v each has (M2P / 8).
+struct HelperArgs {
+  const BlockJob* j;
+  float *image, *ev, *part, *target;
+  int* kind;
+  float *aev, *rows, *v, *flushed;
+  int k0, nu, n0, hw;
+};
+
+template <bool GEN, int MR>
+__device__ __forceinline__ void helper_role(const HelperArgs& h, const TrainCommon& cm) {
+  constexpr int M2P = kHelpers * MR, RS = M2P + 4, VW = MR < 4 ? MR : 4;
+  const BlockJob& j = *h.j;
+  const int Kt = j.Kt, T = 2 * j.P, M2 = j.M2, cap = j.cap, SW = j.SW, k0 = h.k0, nu = h.nu, n0 = h.n0, hw = h.hw;
+  const int nold = n0 < cap ? n0 : cap, mlo = hw * MR;
+  const int lane = threadIdx.x & 63, ht = threadIdx.x - 64 * kSerial;
+  const bool typed = GEN && j.st != nullptr;
+  const auto alpha = gmem(j.alpha);
+  const auto sym = gmem(j.sym);
+  const auto st = gmem(typed ? j.st : reinterpret_cast<const uint8_t*>(j.sym));
+  const auto rx = gmem(j.rx);
+  auto rows_of = [&](int q) { return h.rows + (q & 3) * kBlk * RS; };
+
+  // What block q needs: image, eviction values, targets, vectors, the sums
+  // of its members over the entries and with the linear part, which takes in
+  // the block flushed before.  Every load is issued ahead of the sums and
+  // unconditionally (clamped addresses; masks and signs are applied where
+  // the values are stored), so that only the strip's are waited for.
+  auto prepare = [&](int q) {
+    const float* img = j.images + (size_t)(q - j.qa) * kTrainImage;
+    lds_copy(img, h.image, kEvAt, hw, kHelpers, lane);
+    if (n0 + kBlk * q + kBlk - 1 >= cap)
+      lds_copy(img + kEvAt, h.ev + (q & 1) * kEviction, kEviction, hw, kHelpers, lane);
+    const int i4 = (ht >> 2) & 31, u4 = ht & 3, uc = u4 < nu ? u4 : 0, n = kBlk * q + i4;
+    const bool member = n < T && u4 < nu;
+    const size_t at = ((size_t)((n < T ? n : 0) >> 1) * Kt + k0 + uc) * 2 + (n & 1);
+    const float tg = sym[at];
+    const int kd = GEN ? st[at] : 0;
+    const bool evicted = n0 + n >= cap && u4 < nu;
+    const float av = alpha[(unsigned)((n0 + n) % cap * Kt + k0 + uc)];
+    float rv[MR / 2];
+    const gfloat* const vec = rx + (size_t)(16 * q) * M2;
+    const int M = M2 >> 1;
+#pragma unroll
+    for (int x = 0; x < MR / 2; ++x) {
+      const int e = lane + 64 * x, i = e / MR, m = mlo + e % MR;
+      const bool ok = m < M2 && 16 * q + (i >> 1) < j.P;
+      rv[x] = vec[ok ? (unsigned)((i >> 1) * M2 + ((i & 1) ? (m < M ? m + M : m - M) : m)) : 0u];
+    }
+    BlockSums b;
+#pragma unroll
+    for (int v = 0; v < 8; ++v) b.v[v] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    // entry x of the strip is sample 32 (q - 2) - SW + x; those before the
+    // oldest have no slot (and zero kernel values)
+    const int dlo = kBlk * (q - 2) - SW, bl = lane >> 2, u = lane & 3, ul = k0 + (u < nu ? u : 0);
+    const int x0 = -nold - dlo <= 0 ? 0 : (-nold - dlo) & ~15;
+    const int s0 = ((n0 + dlo) % cap + cap) % cap;
+    auto co = [&](int x) -> float {
+      int slot = s0 + x + bl;
+      slot = slot >= cap ? slot - cap : slot;
+      return alpha[(unsigned)(slot * Kt + ul)];
+    };
+    block_accumulate(b, j.strips + (size_t)(q - j.qa) * SW * kBlk, co, u < nu, x0, SW, hw, kHelpers, lane);
+    block_store(b, h.part, hw, lane);
+    if (ht < kBlk * kSerial) {
+      h.target[ht] = member ? tg : 0.0f;
+      h.aev[ht] = evicted ? av : 0.0f;
+      if constexpr (GEN) h.kind[ht] = member && typed ? kd : 0;
+    }
+    float* const rq = rows_of(q);
+#pragma unroll
+    for (int x = 0; x < MR / 2; ++x) {
+      const int e = lane + 64 * x, i = e / MR, m = mlo + e % MR;
+      const bool ok = m < M2 && 16 * q + (i >> 1) < j.P;
+      rq[i * RS + m] = !ok ? 0.0f : (i & 1) && m >= M ? -rv[x] : rv[x];
+    }
+    // This wave's components of the linear part: v takes in the flushed
+    // block q - 3, then v . r of the members joins the wave's sums (the wave
+    // reads what its own lanes wrote: LDS operations of a wave are in order).
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (q > j.qa && q >= 3) {
+      // lane: output o = (user, VW components), samples i = group, group + G, ..
+      constexpr int OUT = kSerial * MR / VW, G = 64 / OUT;
+      const int o = lane % OUT, uo = o / (MR / VW), mo = mlo + VW * (o % (MR / VW));
+      const float* r = rows_of(q - 3) + mo;
+      float acc[VW];
+#pragma unroll
+      for (int v = 0; v < VW; ++v) acc[v] = 0.0f;
+#pragma unroll
+      for (int y = 0; y < kBlk / G; ++y) {
+        const int i = lane / OUT + G * y;
+        const float c = h.flushed[i * kSerial + uo];
+#pragma unroll
+        for (int v = 0; v < VW; ++v) acc[v] = fmaf(c, r[i * RS + v], acc[v]);
+      }
+#pragma unroll
+      for (int v = 0; v < VW; ++v) {
+        acc[v] = halves_sum(acc[v]);
+        const auto w = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[v]), __float_as_uint(acc[v]), false, false);
+        acc[v] = __uint_as_float(w[0]) + __uint_as_float(w[1]);
+        if constexpr (G > 4)
+          acc[v] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(acc[v]), 0x128, 0xF, 0xF, true));
+        if constexpr (G > 8)
+          acc[v] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(acc[v]), 0x124, 0xF, 0xF, true));
+      }
+      if (lane < OUT) {
+#pragma unroll
+        for (int v = 0; v < VW; ++v) h.v[uo * M2P + mo + v] += acc[v];
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    {
+      const int i = lane & 31, u0 = 2 * (lane >> 5);
+      const float* r = rq + i * RS + mlo;
+      const float* v = h.v + u0 * M2P + mlo;
+      float l0 = 0.0f, l1 = 0.0f;
+#pragma unroll
+      for (int m = 0; m < MR; ++m) {
+        l0 = fmaf(r[m], v[m], l0);
+        l1 = fmaf(r[m], v[M2P + m], l1);
+      }
+      float* p = h.part + (hw * kBlk + i) * kSerial + u0;
+      p[0] = fmaf(cm.wl, l0, p[0]);
+      p[1] = fmaf(cm.wl, l1, p[1]);
+    }
+    lds_copy_wait();
+  };
+  prepare(j.qa);
+  for (int q = j.qa; q < j.qb; ++q) {
+    __syncthreads();
+    __syncthreads();
+    if (q + 1 < j.qb) prepare(q + 1);
+  }
+}
+
 template <bool GEN, int NRW>
 __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon& cm, int k0, float* lds) {
   const int Kt = j.Kt, nu = Kt - k0 < j.ku ? Kt - k0 : j.ku;
@@ -522,20 +658,11 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
   const float qsW = qs[W];
 
   auto rows_of = [&](int q) { return rows + (q & 3) * kBlk * RS; };
-  // component m of vector i of block q (scalar base, small lane offset)
   const int rsh = 31 - __builtin_clz(M2P);
-  auto vec_load = [&](int q, int i, int m) -> float {
-    const int M = M2 >> 1;
-    const bool ok = m < M2 && 16 * q + (i >> 1) < j.P, odd = (i & 1) != 0;
-    const gfloat* base = src.rx + (size_t)(16 * q) * M2;
-    const unsigned off = ok ? (unsigned)((i >> 1) * M2 + (odd ? (m < M ? m + M : m - M) : m)) : 0u;
-    const float sg = ok ? (odd && m >= M ? -1.0f : 1.0f) : 0.0f;
-    return sg * base[off];
-  };
   if (!first) {                             // vectors staged by the launch before
     for (int e = tid; e < 3 * kBlk * M2P; e += kThreads) {
       const int q = j.qa - 3 + (e >> (5 + rsh)), r = e & (kBlk * M2P - 1);
-      if (q >= 0) rows_of(q)[(r >> rsh) * RS + (r & (M2P - 1))] = vec_load(q, r >> rsh, r & (M2P - 1));
+      if (q >= 0) rows_of(q)[(r >> rsh) * RS + (r & (M2P - 1))] = src.at(kBlk * q + (r >> rsh), r & (M2P - 1));
     }
   }
   // v += sum_i C_i r_i over the 32 samples of block q, their C in
@@ -634,92 +761,12 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
     }
     __syncthreads();
   } else {
-    const int hw = wave - kSerial, ht = tid - 64 * kSerial;
-    // components [mlo, mlo + MR) of the vectors and of v are this wave's
-    const int MR = M2P / kHelpers, msh = rsh - 3, mlo = hw * MR;
-    // what block q needs: image, eviction values, targets, vectors, the sums
-    // of its members over the entries; the block flushed before enters the
-    // linear part.  Loads first, the sums next, stores last: the latencies
-    // of the small pieces pass behind the strip's.
-    auto prepare = [&](int q) {
-      const float* img = j.images + (size_t)(q - j.qa) * kTrainImage;
-      lds_copy(img, image, kEvAt, hw, kHelpers, lane);
-      if (n0 + kBlk * q + kBlk - 1 >= cap)
-        lds_copy(img + kEvAt, evict_lds + (q & 1) * kEviction, kEviction, hw, kHelpers, lane);
-      float tg = 0.0f;
-      int kd = 0;
-      if (ht < kBlk * kSerial) {
-        const int n = kBlk * q + (ht >> 2), u = ht & 3;
-        if (n < T && u < nu) {
-          const size_t at = ((size_t)(n >> 1) * Kt + k0 + u) * 2 + (n & 1);
-          tg = sym[at];
-          if constexpr (GEN) kd = typed ? gmem(j.st)[at] : 0;
-        }
-      }
-      // this wave's components of the block's vectors, up to 8 per lane
-      float rv[8];
-#pragma unroll
-      for (int x = 0; x < 8; ++x) {
-        const int e = lane + 64 * x;
-        rv[x] = e < kBlk * MR ? vec_load(q, e >> msh, mlo + (e & (MR - 1))) : 0.0f;
-      }
-      float av = 0.0f;
-      if (ht < kBlk * kSerial) {
-        const int ng = n0 + kBlk * q + (ht >> 2);
-        if (ng >= cap) av = cval(ng % cap, ht & 3);
-      }
-      BlockSums b;
-#pragma unroll
-      for (int v = 0; v < 8; ++v) b.v[v] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-      // entry x of the strip is sample 32 (q - 2) - SW + x; those before the
-      // oldest have no slot (and zero kernel values)
-      const int dlo = kBlk * (q - 2) - SW, bl = lane >> 2, u = lane & 3;
-      const int x0 = -nold - dlo <= 0 ? 0 : (-nold - dlo) & ~15;
-      const int s0 = ((n0 + dlo) % cap + cap) % cap;
-      auto co = [&](int x) -> float {
-        int slot = s0 + x + bl;
-        slot = slot >= cap ? slot - cap : slot;
-        return cval(slot, u);
-      };
-      block_accumulate(b, j.strips + (size_t)(q - j.qa) * SW * kBlk, co, x0, SW, hw, kHelpers, lane);
-      block_store(b, part, hw, lane);
-      if (ht < kBlk * kSerial) {
-        target[ht] = tg;
-        aevict[ht] = av;
-        if constexpr (GEN) kind[ht] = kd;
-      }
-#pragma unroll
-      for (int x = 0; x < 8; ++x) {
-        const int e = lane + 64 * x;
-        if (e < kBlk * MR) rows_of(q)[(e >> msh) * RS + mlo + (e & (MR - 1))] = rv[x];
-      }
-      // this wave's components of the linear part: the flushed block enters
-      // v, then v . r of the members joins the wave's sums (the wave reads
-      // what its own lanes wrote: LDS operations of a wave are in order)
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      if (q > j.qa && lane < kSerial * MR) take_linear(q - 3, 0, (lane >> msh) * M2P + mlo + (lane & (MR - 1)));
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      {
-        const int i = lane & 31, u0 = 2 * (lane >> 5);
-        const float* r = rows_of(q) + i * RS + mlo;
-        const float* v = vlin + u0 * M2P + mlo;
-        float l0 = 0.0f, l1 = 0.0f;
-        for (int m = 0; m < MR; m += 2) {
-          const float a = r[m], b2 = r[m + 1];
-          l0 = fmaf(a, v[m], fmaf(b2, v[m + 1], l0));
-          l1 = fmaf(a, v[M2P + m], fmaf(b2, v[M2P + m + 1], l1));
-        }
-        float* p = part + (hw * kBlk + i) * kSerial + u0;
-        p[0] = fmaf(cm.wl, l0, p[0]);
-        p[1] = fmaf(cm.wl, l1, p[1]);
-      }
-      lds_copy_wait();
-    };
-    prepare(j.qa);
-    for (int q = j.qa; q < j.qb; ++q) {
-      __syncthreads();
-      __syncthreads();
-      if (q + 1 < j.qb) prepare(q + 1);
+    HelperArgs h{&j, image, evict_lds, part, target, kind, aevict, rows, vlin, flushed, k0, nu, n0, wave - kSerial};
+    switch (M2P) {
+      case 16: helper_role<GEN, 2>(h, cm); break;
+      case 32: helper_role<GEN, 4>(h, cm); break;
+      case 64: helper_role<GEN, 8>(h, cm); break;
+      default: helper_role<GEN, 16>(h, cm); break;
     }
     __syncthreads();
     take_linear(j.qb - 3, 0, tid);

@@ -274,28 +274,25 @@ __global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int
     if constexpr (TAPE)
       lds_copy(img + (size_t)(NB + q + 2) * kImage, image + kImage, kImage, wave - kSerial, kHelpers, lane);
     if (q >= 0) {
-      if (ht < kBlk * kSerial) {
-        const int n = kBlk * q + (ht >> 2), uu = ht & 3;
-        float v = 0.0f;
-        if (n < T && uu < nu)
-          v = REV ? cb0[(size_t)n * KP + k0 + uu] : sym[((size_t)(n >> 1) * K + k0 + uu) * 2 + (n & 1)];
-        stage[ht] = v;
-      } else if (ht < kBlk * kSerial + kBlk) {
-        const float kj = kd[kBlk * q + ht - kBlk * kSerial];
-        ikn[ht - kBlk * kSerial] = kj > 0.0f ? -1.0f / kj : 0.0f;
-      }
+      // targets and diagonal: read here, stored after the sums, so that
+      // nothing waits for them
+      const int n = kBlk * q + ((ht >> 2) & 31), nc = n < T ? n : 0, uu = ht & 3, uc = uu < nu ? uu : 0;
+      const float tv = REV ? cb0[(size_t)nc * KP + k0 + uc] : sym[((size_t)(nc >> 1) * K + k0 + uc) * 2 + (nc & 1)];
+      const float kj = kd[kBlk * q + (ht & 31)];
       auto c4 = [&](int d) { return coef[d * kSerial + lane]; };
       BlockSums s;
 #pragma unroll
       for (int v = 0; v < 8; ++v) s.v[v] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-      block_accumulate(s, Km + (size_t)q * TP * kBlk, c4, 0, TP, wave - kSerial, kHelpers, lane);
+      block_accumulate(s, Km + (size_t)q * TP * kBlk, c4, true, 0, TP, wave - kSerial, kHelpers, lane);
       block_store(s, part, wave - kSerial, lane);
       if constexpr (TAPE) {
 #pragma unroll
         for (int v = 0; v < 8; ++v) s.v[v] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-        block_accumulate(s, Hm + (size_t)q * TP * kBlk, c4, 0, TP, wave - kSerial, kHelpers, lane);
+        block_accumulate(s, Hm + (size_t)q * TP * kBlk, c4, true, 0, TP, wave - kSerial, kHelpers, lane);
         block_store(s, part + kPartFloats, wave - kSerial, lane);
       }
+      if (ht < kBlk * kSerial) stage[ht] = n < T && uu < nu ? tv : 0.0f;
+      if (ht < kBlk) ikn[ht] = kj > 0.0f ? -1.0f / kj : 0.0f;
     }
     if (REV && st >= 0 && st < NB) {
       // taped x of the block's steps, [step][user][age] there, by lane here

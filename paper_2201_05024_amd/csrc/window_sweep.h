@@ -193,7 +193,8 @@ __device__ __forceinline__ void lds_copy_wait() { __builtin_amdgcn_s_waitcnt(0x0
 // blocks take 16 entries, rows four members, columns the users.  vals: the
 // kernel values, entry d's 32 members contiguous at vals + 32 d (16-byte
 // aligned); coef(d): this lane's coefficient of the 16 entries from d on
-// (entry lane / 4, user lane % 4); d0 and n multiples of 16.  Helper hw takes
+// (entry lane / 4, user lane % 4), read whatever `keep` is and counted where
+// it is set; d0 and n multiples of 16.  Helper hw takes
 // every nh-th group of 16 entries; its sums over them go to
 // part[hw][member][user].
 struct BlockSums {
@@ -201,16 +202,18 @@ struct BlockSums {
 };
 
 template <class Coef>
-__device__ __forceinline__ void block_accumulate(BlockSums& a, const float* vals, Coef&& coef, int d0, int n, int hw,
-                                                 int nh, int lane) {
+__device__ __forceinline__ void block_accumulate(BlockSums& a, const float* vals, Coef&& coef, bool keep, int d0,
+                                                 int n, int hw, int nh, int lane) {
   // scalar base per group, one lane offset for all (no address registers)
   typedef __attribute__((address_space(1))) const floatx4 gvec;
   typedef __attribute__((address_space(1))) const char gbyte;
   gbyte* const base = (gbyte*)vals;
   const unsigned off = (unsigned)((lane >> 2) * kBlk + 8 * (lane & 3)) * 4u;
-  // rounds of U groups, the next round's loads issued before this round's
-  // products: 8 to 16 KiB in flight a wave, to cover the memory latency; past
-  // the end a valid group is read again, with coefficients 0
+  // Rounds of U groups, the next round's loads issued before this round's
+  // products: 8 to 16 KiB in flight a wave, to cover the memory latency.
+  // Loads are unconditional (past the end the wave's first group again, its
+  // coefficients replaced by 0 where they are used): a branch around them
+  // makes the compiler wait for them at its end.
   constexpr int U = 4;
   struct Round {
     floatx4 x[U][2];
@@ -219,35 +222,36 @@ __device__ __forceinline__ void block_accumulate(BlockSums& a, const float* vals
   const int step = 16 * nh;
   d0 += 16 * hw;
   if (d0 >= n) return;
+  const int dfirst = d0;
   auto load = [&](Round& r, int d) {
 #pragma unroll
     for (int q = 0; q < U; ++q) {
-      const bool in = d + step * q < n;
-      const int dq = in ? d + step * q : d;
+      const int dq = d + step * q < n ? d + step * q : dfirst;
       gbyte* const p = base + (size_t)dq * (kBlk * 4);
       r.x[q][0] = *(gvec*)(p + off);
       r.x[q][1] = *(gvec*)(p + off + 16);
-      const float c = coef(dq);
-      r.c[q] = in ? c : 0.0f;
+      r.c[q] = coef(dq);
     }
   };
-  auto add = [&](const Round& r) {
+  auto add = [&](const Round& r, int d) {
 #pragma unroll
-    for (int q = 0; q < U; ++q)
+    for (int q = 0; q < U; ++q) {
+      const float c = keep && d + step * q < n ? r.c[q] : 0.0f;
 #pragma unroll
       for (int v = 0; v < 8; ++v)
-        a.v[v] = __builtin_amdgcn_mfma_f32_4x4x1f32(r.x[q][v >> 2][v & 3], r.c[q], a.v[v], 0, 0, 0);
+        a.v[v] = __builtin_amdgcn_mfma_f32_4x4x1f32(r.x[q][v >> 2][v & 3], c, a.v[v], 0, 0, 0);
+    }
   };
   Round r0, r1;
   load(r0, d0);
   for (;;) {
+    load(r1, d0 + step * U);
+    add(r0, d0);
     d0 += step * U;
-    if (d0 < n) load(r1, d0);
-    add(r0);
     if (d0 >= n) break;
+    load(r0, d0 + step * U);
+    add(r1, d0);
     d0 += step * U;
-    if (d0 < n) load(r0, d0);
-    add(r1);
     if (d0 >= n) break;
   }
 }
