@@ -185,33 +185,35 @@ hipError_t launch_train_prepare_table(const BlockJob* jobs, const int2* items, i
 hipError_t launch_train_sweep_table(const BlockJob* jobs, const int2* items, int n, const TrainCommon& cm,
                                     size_t lds_bytes, hipStream_t stream);
 hipError_t launch_detect(const DetectArgs& a, hipStream_t stream);
-// Packed model of the detection kernels (split-FP16 layout for 2M <= 64 and
-// K <= 8, two-contraction layout otherwise): bytes and the packing launch.
+// Packed model of the detection kernels (two-contraction layout, and for
+// 2M <= 64 and K <= 8 the split-FP16 layout before it): bytes and the packing
+// launches.
 size_t packed_model_bytes(int M2, int K, int cap);
 hipError_t launch_pack_model(const float* dict, const float* alpha, const float* w, const int32_t* state, int cap,
                              int M2, int K, void* packed, hipStream_t stream);
 
-// One model to pack in a batched packing launch; variant =
-// detect_batch_variant(M2, K) for the split-FP16 (VALU-coefficient) layout,
-// unused for the two-contraction layout.
+// One model to pack: its split-FP16 image at packed (null if the shape has
+// none), its two-contraction image at wide.
 struct PackJob {
   const float* dict;
   const float* alpha;
   const float* w;
   const int32_t* state;
   unsigned char* packed;
-  int cap, M2, K, variant;
+  unsigned char* wide;
+  int cap, M2, K;
 };
-// Packs jobs[0..n) (device table) in the split-FP16 layout, max_cap the
-// largest capacity among them.
-hipError_t launch_pack_model_batch(const PackJob* jobs, int n, int max_cap, hipStream_t stream);
+PackJob pack_job(const float* dict, const float* alpha, const float* w, const int32_t* state, int cap, int M2, int K,
+                 void* packed);
+// Packs jobs[0..n) (device table) in one launch pair, max_units the largest
+// pack_units among them.
+int pack_units(const PackJob& j);
+hipError_t launch_pack_batch(const PackJob* jobs, int n, int max_units, hipStream_t stream);
 
-// Two-contraction detection (detect_wide.h).  Packing many models in one
-// launch pair (max_threads: the largest wide_pack_threads of the jobs) and
-// detection of many jobs of one padded width (variant = wide_detect_variant)
-// in one launch over (job, item) pairs, item i of a job covering received
-// vectors 128 i .. 128 i + 127 (persistent form with ctr as for
-// launch_detect_batch).
+// Two-contraction detection (detect_wide.h) of many jobs of one padded width
+// (variant = wide_detect_variant) in one launch over (job, item) pairs, item
+// i of a job covering received vectors 128 i .. 128 i + 127 (persistent form
+// with ctr as for launch_detect_batch).
 // Detection kernels: kDetectF16 (split-FP16 distance block, coefficients on
 // VALU; 2M <= 64 and K <= 8) and kDetectWide (both contractions on the
 // matrix cores; every shape).  Shapes both kernels hold ("dual") carry both
@@ -221,10 +223,8 @@ bool detect_dual(int M2, int K);
 int detect_default_kernel(int M2, int K);
 size_t wide_offset(int M2, int K, int cap);
 hipError_t launch_detect_with(const DetectArgs& a, int kernel, hipStream_t stream);
-int wide_pack_threads(int M2, int cap);
 int wide_detect_variant(int M2);
 int wide_detect_items(int S);
-hipError_t launch_pack_wide_batch(const PackJob* jobs, int n, int max_threads, hipStream_t stream);
 hipError_t launch_detect_wide_batch(const DetJob* jobs, const int2* items, int n_items, unsigned int* ctr, int grid,
                                     int variant, hipStream_t stream);
 

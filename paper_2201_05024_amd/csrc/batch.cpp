@@ -40,9 +40,7 @@ struct apsm_batch {
   size_t rows_lds = 0, rows_floats = 0;
   int rows_max_m2 = 0;
   std::vector<apsm::PackJob> pjobs;
-  int pack_max_cap = 0;
-  std::vector<apsm::PackJob> pwjobs;           // two-contraction packing
-  int pack_wide_threads = 0;
+  int pack_max_units = 0;
   std::vector<apsm::DetJob> djobs;
   std::vector<int2> ditems;
   std::vector<apsm::DetJob> wjobs;             // two-contraction detection
@@ -50,7 +48,7 @@ struct apsm_batch {
   int wbegin[4] = {0, 0, 0, 0};                // items of width class c: [wbegin[c], wbegin[c + 1])
   std::vector<int> train_plain;      // items trained with their own launch
   size_t off_bj = 0, off_pi = 0, off_si = 0, off_blocks = 0;
-  size_t off_t = 0, off_rj = 0, off_ri = 0, off_p = 0, off_pw = 0, off_d = 0, off_i = 0, off_wd = 0, off_wi = 0,
+  size_t off_t = 0, off_rj = 0, off_ri = 0, off_p = 0, off_d = 0, off_i = 0, off_wd = 0, off_wi = 0,
          off_c = 0, off_rows = 0, bytes = 0;
   unsigned char* ws = nullptr;       // bound workspace (device)
   bool persistent = true;
@@ -310,25 +308,9 @@ void plan(apsm_batch& b, const apsm_params_t* p) {
 
   // packing: dual shapes get both packed images
   for (int i = 0; i < n; ++i) {
-    const auto& it = b.items[i];
-    PackJob pj{};
-    pj.dict = it.model.dict;
-    pj.alpha = it.model.alpha;
-    pj.w = it.model.w;
-    pj.state = it.model.state;
-    pj.packed = static_cast<unsigned char*>(it.model.packed);
-    pj.cap = it.model.dict_cap;
-    pj.M2 = it.model.M2;
-    pj.K = it.model.K;
-    if (detect_dual(pj.M2, pj.K)) {
-      pj.variant = detect_batch_variant(pj.M2, pj.K);
-      b.pjobs.push_back(pj);
-      b.pack_max_cap = std::max(b.pack_max_cap, pj.cap);
-    }
-    pj.variant = -1;
-    pj.packed += wide_offset(pj.M2, pj.K, pj.cap);
-    b.pwjobs.push_back(pj);
-    b.pack_wide_threads = std::max(b.pack_wide_threads, wide_pack_threads(pj.M2, pj.cap));
+    const auto& m = b.items[i].model;
+    b.pjobs.push_back(pack_job(m.dict, m.alpha, m.w, m.state, m.dict_cap, m.M2, m.K, m.packed));
+    b.pack_max_units = std::max(b.pack_max_units, pack_units(b.pjobs.back()));
   }
 
   // detection tables sized for either kernel choice of every dual shape, so
@@ -352,8 +334,7 @@ void plan(apsm_batch& b, const apsm_params_t* p) {
   b.off_rj = align256(b.off_t + b.tjobs.size() * sizeof(TrainJob));
   b.off_ri = align256(b.off_rj + b.rjobs.size() * sizeof(TrainJob));
   b.off_p = align256(b.off_ri + b.ritems.size() * sizeof(int4));
-  b.off_pw = align256(b.off_p + b.pjobs.size() * sizeof(PackJob));
-  b.off_d = align256(b.off_pw + b.pwjobs.size() * sizeof(PackJob));
+  b.off_d = align256(b.off_p + b.pjobs.size() * sizeof(PackJob));
   b.off_i = align256(b.off_d + max_dj * sizeof(DetJob));
   b.off_wd = align256(b.off_i + max_di * sizeof(int2));
   b.off_wi = align256(b.off_wd + max_wj * sizeof(DetJob));
@@ -455,7 +436,6 @@ int apsm_batch_bind(apsm_batch_t* b, void* workspace, size_t bytes, void* stream
   }
   if (!b->ritems.empty()) std::memcpy(img.data() + b->off_ri, b->ritems.data(), b->ritems.size() * sizeof(int4));
   if (!b->pjobs.empty()) std::memcpy(img.data() + b->off_p, b->pjobs.data(), b->pjobs.size() * sizeof(PackJob));
-  if (!b->pwjobs.empty()) std::memcpy(img.data() + b->off_pw, b->pwjobs.data(), b->pwjobs.size() * sizeof(PackJob));
   if (!b->djobs.empty()) std::memcpy(img.data() + b->off_d, b->djobs.data(), b->djobs.size() * sizeof(DetJob));
   if (!b->ditems.empty()) std::memcpy(img.data() + b->off_i, b->ditems.data(), b->ditems.size() * sizeof(int2));
   if (!b->wjobs.empty()) std::memcpy(img.data() + b->off_wd, b->wjobs.data(), b->wjobs.size() * sizeof(DetJob));
@@ -512,9 +492,7 @@ int apsm_batch_train_prepared(const apsm_batch_t* b, void* stream) {
     e = launch_train(a, s);
   }
   // packing reads the trained models: after every training launch
-  if (e == hipSuccess) e = launch_pack_model_batch(at<PackJob>(b, b->off_p), (int)b->pjobs.size(), b->pack_max_cap, s);
-  if (e == hipSuccess)
-    e = launch_pack_wide_batch(at<PackJob>(b, b->off_pw), (int)b->pwjobs.size(), b->pack_wide_threads, s);
+  if (e == hipSuccess) e = launch_pack_batch(at<PackJob>(b, b->off_p), (int)b->pjobs.size(), b->pack_max_units, s);
   return hip_status(e);
 }
 

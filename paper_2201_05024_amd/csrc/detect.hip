@@ -1,4 +1,4 @@
-// Dispatch of apsm_detect and of model packing.  Two detection kernels:
+// Dispatch of apsm_detect.  Two detection kernels:
 // split-FP16 with the coefficient sums on VALU (2M <= 64 and K <= 8) and
 // the two-contraction kernel with them on the matrix cores (every shape).
 // Shapes both hold ("dual") carry both packed images, so either kernel can
@@ -25,24 +25,6 @@ size_t wide_offset(int M2, int K, int cap) {
 }
 
 size_t packed_model_bytes(int M2, int K, int cap) { return wide_offset(M2, K, cap) + wide::packed_bytes(M2, cap); }
-
-hipError_t launch_pack_model(const float* dict, const float* alpha, const float* w, const int32_t* state, int cap,
-                             int M2, int K, void* packed, hipStream_t stream) {
-  unsigned char* out = static_cast<unsigned char*>(packed);
-  if (detect_dual(M2, K)) {
-    hipError_t e = f16::launch_pack(dict, alpha, state, cap, M2, K, out, stream);
-    if (e != hipSuccess) return e;
-  }
-  return wide::launch_pack(dict, alpha, w, state, cap, M2, K, out + wide_offset(M2, K, cap), stream);
-}
-
-hipError_t launch_pack_model_batch(const PackJob* jobs, int n, int max_cap, hipStream_t stream) {
-  return f16::launch_pack_batch(jobs, n, max_cap, stream);
-}
-
-hipError_t launch_pack_wide_batch(const PackJob* jobs, int n, int max_threads, hipStream_t stream) {
-  return wide::launch_pack_batch(jobs, n, max_threads, stream);
-}
 
 hipError_t launch_detect_with(const DetectArgs& a, int kernel, hipStream_t stream) {
   if (a.M2 > APSM_MAX_M2) return hipErrorInvalidValue;

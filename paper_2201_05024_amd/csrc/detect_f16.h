@@ -100,9 +100,6 @@ __device__ __forceinline__ int scale_exp(float maxabs) {
   return 13 - ex;
 }
 
-hipError_t launch_pack_batch(const PackJob* jobs, int n, int max_cap, hipStream_t stream);
-hipError_t launch_pack(const float* dict, const float* alpha, const int32_t* state, int cap, int M2,
-                       int K, unsigned char* packed, hipStream_t stream);
 hipError_t launch_detect_f16_m16(const DetectArgs& a, const unsigned char* packed, hipStream_t stream);
 hipError_t launch_detect_f16_m32(const DetectArgs& a, const unsigned char* packed, hipStream_t stream);
 hipError_t launch_detect_f16_m64(const DetectArgs& a, const unsigned char* packed, hipStream_t stream);

@@ -401,9 +401,6 @@ __device__ __forceinline__ void detect_wide_tile(const A& a, const unsigned char
   }
 }
 
-hipError_t launch_pack(const float* dict, const float* alpha, const float* w, const int32_t* state, int cap, int M2,
-                       int K, unsigned char* packed, hipStream_t stream);
-hipError_t launch_pack_batch(const PackJob* jobs, int n, int max_cap, hipStream_t stream);
 hipError_t launch_detect(const DetectArgs& a, hipStream_t stream);
 
 }  // namespace wide
