@@ -229,8 +229,8 @@ __device__ __forceinline__ void image_unit(const BlockJob& j, const TrainCommon&
       for (int x = 0; x < 4; ++x) {
         const int r = 4 * (f >> 6) + x;
         if (mat) {
-          const int pl = matrix_lane(l, r), jl = pl & 31;
-          v[x] = l >= 32 ? k1[il * 97 + (pl >= 32 ? 64 : 32) + jl] : pl >= 32 ? k1[jl * 97 + 32 + il] : k2[il * 33 + jl];
+          const int jl = r & 31;
+          v[x] = l >= 32 ? k1[il * 97 + (r >= 32 ? 64 : 32) + jl] : r >= 32 ? k1[jl * 97 + 32 + il] : k2[il * 33 + jl];
         } else {
           v[x] = k1[il * 97 + pending_col(l, r)];
         }
@@ -355,78 +355,54 @@ __host__ __device__ inline SweepLds sweep_lds(int M2) {
 }
 
 struct Lane {
-  float e;         // running prediction
+  float x;         // running prediction less the target
   float C;         // pending coefficient
-  float b, ikn;    // target, -1 / kappa(r, r) (0 where that is not positive)
+  float ikn;       // -1 / kappa(r, r) (0 where that is not positive)
   float bad;       // not finite once a prediction or a target was not
   int kind;        // set kind
   int d;           // sample, negative for none
 };
 
-// 16 steps whose newest members lie in row A of the wave, t0 the place of the
-// first in its block, with the window full: position weights, hyperslabs.
-// Bound by the issue of one wave (5 cycles an instruction): with three window
-// rows 48 FMAs of the matrix-vector product and about 18 more, 3 with
-// evictions.
-template <int NRW, int A, bool EV>
-__device__ __forceinline__ void full_row(Lane& s, const float* kreg, int t0, float eps, float qsW, const float* om,
-                                         const float* ev, float aev, int lane) {
+// The steps whose newest members lie in row A of the wave, t0 the place of
+// the first in its block, n0 its number: 16, or the cnt of the sequence's
+// end.  FULL: all 16, with the window full.  GEN: any set weights, relaxation
+// and set kinds; else position weights and hyperslabs.
+// Bound by the issue of one wave (5 cycles an instruction): with a window of
+// 17 to 32 samples 32 FMAs of the matrix-vector product and about 16 more, 3
+// with evictions.  Unrolled, as the product's registers depend on the place.
+template <bool GEN, int NRW, int A, bool FULL, bool EV>
+__device__ __forceinline__ void steps(Lane& s, const float* kreg, int n0, int t0, int cnt, const TrainCommon& cm,
+                                      bool typed, float qsW, const float* om, const float* qs, const float* ev,
+                                      float aev, int lane) {
 #pragma clang fp contract(off)
+  const int W = cm.W;
   float w = om[(16 * A - lane) & 63];       // weight of the lane's member (0 outside the window)
   const float iq = s.ikn * qsW;
+  const float inv_mu = 1.0f / cm.mu;
   const float* e0 = ev + t0 * 64 + lane;
   float kv = EV ? e0[0] : 0.0f;
-#pragma unroll 4
+#pragma unroll
   for (int it = 0; it < 16; ++it) {
-    const float t = w * iq;
+    if (!FULL && it >= cnt) continue;
+    const int n = n0 + it;
+    const float wc = w;
     w = from_below(w);                      // every member is one step older
     if constexpr (EV) {
       // the members in the window lose the entry that leaves; the next
-      // step's values are read a step ahead
+      // step's values are read a step ahead (past the last step: not used)
       const float a = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(aev), t0 + it));
-      s.e = fmaf(-a, kv, s.e);
+      s.x = fmaf(-a, kv, s.x);
       kv = e0[(it + 1) * 64];
     }
-    const float c = slab_residual_pos(s.e - s.b, eps) * t;
-    s.C += c;
-    s.e += window_product<A, NRW>(broadcast_rows(c), kreg);
-  }
-}
-
-// 16 steps, or the fewer of the sequence's end; n0 the first of them.  GEN:
-// any set weights, relaxation and set kinds; else position weights and
-// hyperslabs (here while the window fills, and at the end).
-template <bool GEN, int NRW, int A>
-__device__ __forceinline__ void train_row(Lane& s, const float* kreg, int n0, int t0, int cnt, const TrainCommon& cm,
-                                          bool typed, float qsW, const float* om, const float* qs, bool evict,
-                                          const float* ev, float aev, int lane) {
-#pragma clang fp contract(off)
-  if (cnt <= 0) return;
-  const int W = cm.W;
-  if (!GEN && cnt == 16 && n0 + 1 >= W) {
-    if (evict) full_row<NRW, A, true>(s, kreg, t0, cm.eps, qsW, om, ev, aev, lane);
-    else full_row<NRW, A, false>(s, kreg, t0, cm.eps, qsW, om, ev, aev, lane);
-    return;
-  }
-  const float inv_mu = 1.0f / cm.mu;
-  float wv = om[(16 * A - lane) & 63];
-  float kv = evict ? ev[t0 * 64 + lane] : 0.0f;
-  for (int it = 0; it < cnt; ++it) {
-    const int n = n0 + it;
-    const float q = n + 1 < W ? qs[n + 1] : qsW;   // mu / (omega_0 + .. + omega_{L-1})
-    const float wq = wv * q, wcur = wv, kcur = kv;
-    wv = from_below(wv);
-    if (evict) {
-      const float a = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(aev), t0 + it));
-      s.e = fmaf(-a, kcur, s.e);
-      kv = ev[(t0 + it + 1) * 64 + lane];   // (past the last step: not used)
-    }
-    const float x = s.e - s.b;
+    float c;
     if constexpr (!GEN) {
-      const float c = slab_residual_pos(x, cm.eps) * (wcur * (s.ikn * q));
+      // weight, mu / (omega_0 + .. + omega_{L-1}), -1 / kappa
+      const float t = FULL || n + 1 >= W ? wc * iq : wc * (s.ikn * qs[n + 1]);
+      c = slab_residual_pos(s.x, cm.eps) * t;
       s.C += c;
-      s.e += window_product<A, NRW>(broadcast_rows(c), kreg);
+      s.x += window_sum<A, NRW>(window_gather<A, NRW>(c, it, lane), kreg, it);
     } else {
+      const float x = s.x;
       float res = slab_residual_pos(x, cm.eps);
       if (typed) {
         res = s.kind == kSetPlane   ? x
@@ -441,13 +417,13 @@ __device__ __forceinline__ void train_row(Lane& s, const float* kreg, int n0, in
         // by more than 1e-5 (a member that its own projection left on the
         // boundary stays out, whatever the rounding)
         const float dist = cm.weights == kWeightsActive ? (fabsf(res) > 1e-5f ? 1.0f : 0.0f) : fabsf(res);
-        const float v = wcur > 0.0f && s.d >= 0 ? dist : 0.0f;
+        const float v = wc > 0.0f && s.d >= 0 ? dist : 0.0f;
         const float tot = wave_sum(v);
         u = tot > 0.0f ? v / tot * beta : 0.0f;
       } else {
-        u = wq * inv_mu * beta;
+        u = wc * (FULL || n + 1 >= W ? qsW : qs[n + 1]) * inv_mu * beta;
       }
-      const float ku = window_product<A, NRW>(broadcast_rows(u), kreg);
+      const float ku = window_sum<A, NRW>(window_gather<A, NRW>(u, it, lane), kreg, it);
       float step = cm.mu;
       if (cm.extrapolate) {
         // M = sum_j q_j beta_j^2 K_jj / sum_jl u_j K_jl u_l (beta_j K_jj = -residual)
@@ -456,8 +432,23 @@ __device__ __forceinline__ void train_row(Lane& s, const float* kreg, int n0, in
         step = cm.mu * (den > 0.0f ? num / den : 1.0f);
       }
       s.C += step * u;
-      s.e += step * ku;
+      s.x += step * ku;
     }
+  }
+}
+
+template <bool GEN, int NRW, int A>
+__device__ __forceinline__ void train_row(Lane& s, const float* kreg, int n0, int t0, int cnt, const TrainCommon& cm,
+                                          bool typed, float qsW, const float* om, const float* qs, bool evict,
+                                          const float* ev, float aev, int lane) {
+  if (cnt <= 0) return;
+  if (!GEN && cnt == 16 && n0 + 1 >= cm.W) {
+    if (evict) steps<GEN, NRW, A, true, true>(s, kreg, n0, t0, 16, cm, typed, qsW, om, qs, ev, aev, lane);
+    else steps<GEN, NRW, A, true, false>(s, kreg, n0, t0, 16, cm, typed, qsW, om, qs, ev, aev, lane);
+  } else if (evict) {
+    steps<GEN, NRW, A, false, true>(s, kreg, n0, t0, cnt, cm, typed, qsW, om, qs, ev, aev, lane);
+  } else {
+    steps<GEN, NRW, A, false, false>(s, kreg, n0, t0, cnt, cm, typed, qsW, om, qs, ev, aev, lane);
   }
 }
 
@@ -644,7 +635,7 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
   // ones, else none and w / wL or 0
   if (first && cm.init != kInitContinue)
     for (size_t e = tid; e < (size_t)cap * nu; e += kThreads) alpha[e / nu * Kt + k0 + e % nu] = 0.0f;
-  float* const carry = j.carry;             // per user C [64], e [32]; v [Kt][M2]; -1 / kappa of the last block
+  float* const carry = j.carry;             // per user C [64], x [32]; v [Kt][M2]; -1 / kappa of the last block
   for (int e = tid; e < kSerial * M2P; e += kThreads) {
     const int u = e / M2P, m = e - u * M2P;
     float v = 0.0f;
@@ -689,11 +680,10 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
     if (active) {
       if (!first) {
         s.C = carry[(k0 + u) * 96 + lane];
-        s.e = upper ? carry[(k0 + u) * 96 + 64 + il] : 0.0f;
-        if (upper && s.d >= 0 && s.d < T) {
-          s.b = sym[((size_t)(s.d >> 1) * Kt + k0 + u) * 2 + (s.d & 1)];
-          if constexpr (GEN) s.kind = typed ? gmem(j.st)[((size_t)(s.d >> 1) * Kt + k0 + u) * 2 + (s.d & 1)] : 0;
-        }
+        s.x = upper ? carry[(k0 + u) * 96 + 64 + il] : 0.0f;
+        if constexpr (GEN)
+          if (upper && s.d >= 0 && s.d < T)
+            s.kind = typed ? gmem(j.st)[((size_t)(s.d >> 1) * Kt + k0 + u) * 2 + (s.d & 1)] : 0;
       } else if (n0 + s.d >= 0) {
         s.C = cval((n0 + s.d) % cap, u);
       }
@@ -716,12 +706,11 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
           if (s.d >= 0) set_coef(s.d, u, s.C);
         }
         // (swaps outside the selects: they need every lane)
-        const float eu = upper_half(s.e), Cu = upper_half(s.C), bu = upper_half(s.b), iu = upper_half(s.ikn);
+        const float xu = upper_half(s.x), Cu = upper_half(s.C), iu = upper_half(s.ikn);
         const int du = __float_as_int(upper_half(__int_as_float(s.d)));
         const float b = target[il * kSerial + u], ik = image[kIknAt + il];
-        s.e = upper ? e : eu;
+        s.x = upper ? e - b : xu;
         s.C = upper ? 0.0f : Cu;
-        s.b = upper ? b : bu;
         s.ikn = upper ? ik : iu;
         s.d = upper ? kBlk * q + il : du;
         s.bad = fmaf(b, 0.0f, s.bad);
@@ -739,13 +728,13 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
         train_row<GEN, NRW, 2>(s, kreg, nb, 0, rem < 16 ? rem : 16, cm, typed, qsW, om, qs, evict, ev, aev, lane);
         train_row<GEN, NRW, 3>(s, kreg, nb + 16, 16, rem < 32 ? rem - 16 : 16, cm, typed, qsW, om, qs, evict, ev, aev,
                                lane);
-        s.bad = fmaf(s.e, 0.0f, s.bad);     // a residual that was not finite leaves its prediction so
+        s.bad = fmaf(s.x, 0.0f, s.bad);     // a residual that was not finite leaves its prediction so
       }
     }
     if (active) {
       if (!last) {
         carry[(k0 + u) * 96 + lane] = s.C;
-        if (upper) carry[(k0 + u) * 96 + 64 + il] = s.e;
+        if (upper) carry[(k0 + u) * 96 + 64 + il] = s.x;
         if (upper && k0 + u == 0) carry[(size_t)Kt * (96 + M2) + il] = s.ikn;
       }
       if (__ballot(!(s.bad == 0.0f)) != 0 && lane == 0) atomicOr(j.state + 3, APSM_FLAG_TRAIN_NONFINITE);
@@ -830,11 +819,12 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 size_t head_bytes(int M2, int K) { return align256(256 + ((size_t)K * (96 + M2) + kBlk) * sizeof(float)); }
 size_t block_bytes(int SW) { return ((size_t)kTrainImage + (size_t)SW * kBlk) * sizeof(float); }
 
-template <bool GEN, int NRW>
-hipError_t launch_sweep_args(const BlockArgs& a, size_t bytes, hipStream_t s) {
-  hipError_t e = set_lds(sweep_kernel<GEN, NRW>, bytes);
+template <int NRW>
+hipError_t launch_sweep_args(const BlockArgs& a, bool gen, size_t bytes, hipStream_t s) {
+  const auto kern = gen ? sweep_kernel<true, NRW> : sweep_kernel<false, NRW>;
+  hipError_t e = set_lds(kern, bytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((sweep_kernel<GEN, NRW>), dim3((a.n + 7) / 8 * 8 * a.groups), dim3(kThreads), bytes, s, a);
+  hipLaunchKernelGGL(kern, dim3((a.n + 7) / 8 * 8 * a.groups), dim3(kThreads), bytes, s, a);
   return hipGetLastError();
 }
 
@@ -910,10 +900,11 @@ hipError_t launch_train_blocks(BlockArgs& a, int blocks, hipStream_t s) {
     hipLaunchKernelGGL(prepare_kernel, dim3(train_prepare_units(a.jobs[0]), a.n), dim3(kPrepThreads), plds, s, a);
     e = hipGetLastError();
     if (e != hipSuccess) break;
-    if (window_rows(a.cm.W) == 2)
-      e = gen ? launch_sweep_args<true, 2>(a, slds, s) : launch_sweep_args<false, 2>(a, slds, s);
-    else
-      e = gen ? launch_sweep_args<true, 3>(a, slds, s) : launch_sweep_args<false, 3>(a, slds, s);
+    switch (window_rows(a.cm.W)) {
+      case kOneRow: e = launch_sweep_args<kOneRow>(a, gen, slds, s); break;
+      case kTwoRows: e = launch_sweep_args<kTwoRows>(a, gen, slds, s); break;
+      default: e = launch_sweep_args<kTwoRowsAndOne>(a, gen, slds, s);
+    }
   }
   if (e == hipSuccess && a.cm.init == kInitContinue) {
     hipLaunchKernelGGL(continued_dict_kernel, dim3((j0.cap + kDictSlots - 1) / kDictSlots, a.n), dim3(kPrepThreads), 0,
@@ -932,12 +923,13 @@ hipError_t launch_train_prepare_table(const BlockJob* jobs, const int2* items, i
   return hipGetLastError();
 }
 
-template <bool GEN, int NRW>
-static hipError_t launch_table(const BlockJob* jobs, const int2* items, int n, const TrainCommon& cm, size_t lds,
-                               hipStream_t s) {
-  hipError_t e = set_lds(sweep_table_kernel<GEN, NRW>, lds);
+template <int NRW>
+static hipError_t launch_table(const BlockJob* jobs, const int2* items, int n, const TrainCommon& cm, bool gen,
+                               size_t lds, hipStream_t s) {
+  const auto kern = gen ? sweep_table_kernel<true, NRW> : sweep_table_kernel<false, NRW>;
+  hipError_t e = set_lds(kern, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((sweep_table_kernel<GEN, NRW>), dim3(n), dim3(kThreads), lds, s, jobs, items, cm);
+  hipLaunchKernelGGL(kern, dim3(n), dim3(kThreads), lds, s, jobs, items, cm);
   return hipGetLastError();
 }
 
@@ -945,9 +937,11 @@ hipError_t launch_train_sweep_table(const BlockJob* jobs, const int2* items, int
                                     hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const bool gen = general(cm, false);
-  if (window_rows(cm.W) == 2)
-    return gen ? launch_table<true, 2>(jobs, items, n, cm, lds, s) : launch_table<false, 2>(jobs, items, n, cm, lds, s);
-  return gen ? launch_table<true, 3>(jobs, items, n, cm, lds, s) : launch_table<false, 3>(jobs, items, n, cm, lds, s);
+  switch (window_rows(cm.W)) {
+    case kOneRow: return launch_table<kOneRow>(jobs, items, n, cm, gen, lds, s);
+    case kTwoRows: return launch_table<kTwoRows>(jobs, items, n, cm, gen, lds, s);
+    default: return launch_table<kTwoRowsAndOne>(jobs, items, n, cm, gen, lds, s);
+  }
 }
 
 }  // namespace apsm

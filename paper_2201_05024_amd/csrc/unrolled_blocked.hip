@@ -105,10 +105,9 @@ __global__ __launch_bounds__(256) void unb_image_kernel(UnrolledArgs a) {
       const int r = 4 * (f >> 6) + x;
       int bi, bj, j;
       if (mat) {
-        const int pl = matrix_lane(l, r);
         bi = l < 32 ? q + dir : q;
-        bj = pl < 32 ? q + dir : q;
-        j = pl & 31;
+        bj = r < 32 ? q + dir : q;
+        j = r & 31;
       } else {
         const int c = pending_col(l, r);
         bi = q;
@@ -159,8 +158,7 @@ __device__ __forceinline__ void sweep_steps(Lane& s, const float* kreg, const fl
                                             float* tx, float* th, size_t tstep, int lane) {
 #pragma clang fp contract(off)
   constexpr bool REV = MODE == kReverse;
-  const int last = FULL ? 15 : cnt - 1;
-  const int t0 = REV ? last : 0;            // first step taken
+  const int t0 = !REV ? 0 : FULL ? 15 : cnt - 1;      // first step taken
   // weight of each lane's member (0 outside the window) and its place on the
   // tape: from step to step every member's age moves by one, which is the
   // neighbour lane's
@@ -168,10 +166,11 @@ __device__ __forceinline__ void sweep_steps(Lane& s, const float* kreg, const fl
   float at = __int_as_float((16 * A + t0 - lane) & 63);
   const float iq = s.ikn * qsW;
   float xv = REV ? xs[t0 * kSerial * 64 + lane] : 0.0f;
-  const int steps = FULL ? 16 : cnt;
-#pragma unroll 4
-  for (int it = 0; it < steps; ++it) {
-    const int t = REV ? last - it : it, n = n0 + t;
+  // (unrolled: the product's registers depend on the step's place)
+#pragma unroll
+  for (int it = 0; it < 16; ++it) {
+    const int t = REV ? 15 - it : it, n = n0 + t;
+    if (!FULL && t >= cnt) continue;
     float w = FULL || n + 1 >= W ? wv * iq : (wv * qs[n + 1]) * s.ikn;
     const float wq = w;
     const int age = __float_as_int(at);
@@ -195,9 +194,9 @@ __device__ __forceinline__ void sweep_steps(Lane& s, const float* kreg, const fl
       }
     }
     s.C += c;
-    const Rows rows = broadcast_rows(c);
-    s.e += window_product<A, NRW>(rows, kreg);
-    if constexpr (MODE == kTape) s.h += window_product<A, NRW>(rows, hreg);
+    const WindowRows rows = window_gather<A, NRW>(c, t, lane);
+    s.e += window_sum<A, NRW>(rows, kreg, t);
+    if constexpr (MODE == kTape) s.h += window_sum<A, NRW>(rows, hreg, t);
   }
 }
 
@@ -601,7 +600,11 @@ hipError_t launch_sweep_w(const UnrolledArgs& a, int p0, int p1, hipStream_t s) 
 
 template <int MODE>
 hipError_t launch_sweep(const UnrolledArgs& a, int p0, int p1, hipStream_t s) {
-  return window_rows(a.W) == 2 ? launch_sweep_w<MODE, 2>(a, p0, p1, s) : launch_sweep_w<MODE, 3>(a, p0, p1, s);
+  switch (window_rows(a.W)) {
+    case kOneRow: return launch_sweep_w<MODE, kOneRow>(a, p0, p1, s);
+    case kTwoRows: return launch_sweep_w<MODE, kTwoRows>(a, p0, p1, s);
+    default: return launch_sweep_w<MODE, kTwoRowsAndOne>(a, p0, p1, s);
+  }
 }
 
 }  // namespace

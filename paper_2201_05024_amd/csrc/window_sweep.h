@@ -13,13 +13,12 @@
 // barrier and no LDS exchange inside a block.  A step is: projection
 // coefficient c of each lane (zero outside the window), then
 // e_l += sum_j K_lj c_j with the 64 x 64 kernel matrix in registers, the
-// coefficients brought to the lanes by row broadcasts (permlane swaps) and
-// DPP row rotations inside v_fmac_f32.
+// coefficients brought to the lanes by permlane swaps and DPP row broadcasts
+// inside v_fmac_f32.
 //
 // The entering block is in the upper half of the wave, the block adjacent to
 // it in the lower half; from block to block the upper half moves down.
-// Register k[16 s + r] of lane l is the kernel value of lane l's sample and
-// the one of lane 16 s + ((l - r) & 15).
+// Register r of lane l is the kernel value of lane l's sample and lane r's.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -40,66 +39,99 @@ constexpr int kImage = kMatrixImage + kPendingImage;
 constexpr int kMaxWindow = 33;             // a window ends inside a block and reaches at most into the one before
 constexpr int kSerial = 4;                 // recursion waves of a workgroup (one user each, one per SIMD)
 
-// Rows of 16 lanes a window of W samples can touch.
-__host__ __device__ constexpr int window_rows(int W) { return W <= 17 ? 2 : 3; }
+// How a step's product runs through the rows of 16 lanes (window_sum): a
+// window ending at place p of row A has members at places <= p of row A,
+// anywhere in row A - 1 and past p in row A - 2.  No two of rows A and A - 2
+// (W <= 32; of A and A - 1 with W <= 16) share a place, so their
+// coefficients, zero outside the window, are summed into one row, and the
+// register of each place is the one of the row its member lies in: 32 (16)
+// FMAs a step.  W = 33 has one member more, at place p of row A - 2.
+enum { kOneRow = 1, kTwoRows = 2, kTwoRowsAndOne = 3 };
+__host__ __device__ constexpr int window_rows(int W) { return W <= 16 ? kOneRow : W <= 32 ? kTwoRows : kTwoRowsAndOne; }
 
-#define APSM_FMAC(i, r) "v_fmac_f32_dpp %0, %1, %" #i " row_ror:" #r " row_mask:0xf bank_mask:0xf\n\t"
-#define APSM_FMAC_ROW                                                                                     \
-  APSM_FMAC(3, 1) APSM_FMAC(4, 2) APSM_FMAC(5, 3) APSM_FMAC(6, 4) APSM_FMAC(7, 5) APSM_FMAC(8, 6)         \
-  APSM_FMAC(9, 7) APSM_FMAC(10, 8) APSM_FMAC(11, 9) APSM_FMAC(12, 10) APSM_FMAC(13, 11) APSM_FMAC(14, 12) \
-  APSM_FMAC(15, 13) APSM_FMAC(16, 14) APSM_FMAC(17, 15)
-#define APSM_FMAC_AT(i, r) "v_fmac_f32_dpp %0, %3, %" #i " row_ror:" #r " row_mask:0xf bank_mask:0xf\n\t"
-#define APSM_FMAC_ROW_AT                                                                                        \
-  APSM_FMAC_AT(5, 1) APSM_FMAC_AT(6, 2) APSM_FMAC_AT(7, 3) APSM_FMAC_AT(8, 4) APSM_FMAC_AT(9, 5)               \
-  APSM_FMAC_AT(10, 6) APSM_FMAC_AT(11, 7) APSM_FMAC_AT(12, 8) APSM_FMAC_AT(13, 9) APSM_FMAC_AT(14, 10)         \
-  APSM_FMAC_AT(15, 11) APSM_FMAC_AT(16, 12) APSM_FMAC_AT(17, 13) APSM_FMAC_AT(18, 14) APSM_FMAC_AT(19, 15)
-#define APSM_ROW_IN(x, k)                                                                              \
-  "v"(x), "v"((k)[0]), "v"((k)[1]), "v"((k)[2]), "v"((k)[3]), "v"((k)[4]), "v"((k)[5]), "v"((k)[6]),  \
-      "v"((k)[7]), "v"((k)[8]), "v"((k)[9]), "v"((k)[10]), "v"((k)[11]), "v"((k)[12]), "v"((k)[13]),  \
-      "v"((k)[14]), "v"((k)[15])
+#define APSM_BCAST(acc, x, i, r) "v_fmac_f32_dpp %" #acc ", %" #x ", %" #i " row_newbcast:" #r " row_mask:0xf bank_mask:0xf\n\t"
+#define APSM_BCAST_MUL(acc, x, i) "v_mul_f32_dpp %" #acc ", %" #x ", %" #i " row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"
 
-// acc (+)= sum_r k[r] * (x of the lane r places back in its 16-lane row).
-// The compiler does not fold the rotation into the FMA (it emits a move and
-// an FMA, twice the instructions).  The leading s_nop covers the two wait
-// states a DPP read needs after the write of x.
-__device__ __forceinline__ void row_mul(float& acc, float x, const float* k) {
-  asm("s_nop 1\n\tv_mul_f32_e32 %0, %1, %2\n\t" APSM_FMAC_ROW : "=&v"(acc) : APSM_ROW_IN(x, k));
-}
-__device__ __forceinline__ void row_fma(float& acc, float x, const float* k) {
-  asm("s_nop 1\n\tv_fmac_f32_e32 %0, %1, %2\n\t" APSM_FMAC_ROW : "+v"(acc) : APSM_ROW_IN(x, k));
-}
-// The same where x was written well before (no wait states).
-__device__ __forceinline__ void row_fma_ready(float& acc, float x, const float* k) {
-  asm("v_fmac_f32_e32 %0, %1, %2\n\t" APSM_FMAC_ROW : "+v"(acc) : APSM_ROW_IN(x, k));
-}
-
-// The four 16-lane rows of x, each broadcast to every row.
-struct Rows {
-  float r[4];
-};
-__device__ __forceinline__ Rows broadcast_rows(float x) {
-  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  const auto p = __builtin_amdgcn_permlane32_swap(a[0], a[0], false, false);
-  const auto q = __builtin_amdgcn_permlane32_swap(a[1], a[1], false, false);
-  return {{__uint_as_float(p[0]), __uint_as_float(q[0]), __uint_as_float(p[1]), __uint_as_float(q[1])}};
-}
-
-// sum_j K_lj c_j over the rows A, A - 1, .. (mod 4; NRW of them) that the
-// window ending in row A touches.  The broadcast rows are all operands of the
-// first block (the later ones pass through it), so that its leading wait
-// states cover every DPP read.
-template <int A, int NRW>
-__device__ __forceinline__ float window_product(const Rows& c, const float* k) {
+// acc = sum_r k[r] * x(place r of the lane's 16-lane row), and the same added
+// to acc.  The leading s_nop covers the two wait states a DPP read needs
+// after the write of x.
+__device__ __forceinline__ float row_sum(float x, const float* k) {
   float acc;
-  const float x0 = c.r[A];
-  float x1 = c.r[(A + 3) & 3], x2 = c.r[(A + 2) & 3];
-  const float* k0 = k + 16 * A;
-  asm("s_nop 1\n\tv_mul_f32_e32 %0, %3, %4\n\t" APSM_FMAC_ROW_AT
-      : "=&v"(acc), "+v"(x1), "+v"(x2)
-      : APSM_ROW_IN(x0, k0));
-  row_fma_ready(acc, x1, k + 16 * ((A + 3) & 3));
-  if constexpr (NRW > 2) row_fma_ready(acc, x2, k + 16 * ((A + 2) & 3));
+  asm("s_nop 1\n\t" APSM_BCAST_MUL(0, 1, 2)
+      APSM_BCAST(0, 1, 3, 1) APSM_BCAST(0, 1, 4, 2) APSM_BCAST(0, 1, 5, 3) APSM_BCAST(0, 1, 6, 4)
+      APSM_BCAST(0, 1, 7, 5) APSM_BCAST(0, 1, 8, 6) APSM_BCAST(0, 1, 9, 7) APSM_BCAST(0, 1, 10, 8)
+      APSM_BCAST(0, 1, 11, 9) APSM_BCAST(0, 1, 12, 10) APSM_BCAST(0, 1, 13, 11) APSM_BCAST(0, 1, 14, 12)
+      APSM_BCAST(0, 1, 15, 13) APSM_BCAST(0, 1, 16, 14) APSM_BCAST(0, 1, 17, 15)
+      : "=&v"(acc)
+      : "v"(x), "v"(k[0]), "v"(k[1]), "v"(k[2]), "v"(k[3]), "v"(k[4]), "v"(k[5]), "v"(k[6]), "v"(k[7]), "v"(k[8]),
+        "v"(k[9]), "v"(k[10]), "v"(k[11]), "v"(k[12]), "v"(k[13]), "v"(k[14]), "v"(k[15]));
   return acc;
+}
+// The same over two rows, place by place, in one accumulator a row.
+__device__ __forceinline__ float two_row_sum(float x, float y, const float* k, const float* l) {
+  float a, b;
+  asm("s_nop 1\n\t" APSM_BCAST_MUL(0, 2, 4) APSM_BCAST_MUL(1, 3, 20)
+      APSM_BCAST(0, 2, 5, 1) APSM_BCAST(1, 3, 21, 1) APSM_BCAST(0, 2, 6, 2) APSM_BCAST(1, 3, 22, 2)
+      APSM_BCAST(0, 2, 7, 3) APSM_BCAST(1, 3, 23, 3) APSM_BCAST(0, 2, 8, 4) APSM_BCAST(1, 3, 24, 4)
+      APSM_BCAST(0, 2, 9, 5) APSM_BCAST(1, 3, 25, 5) APSM_BCAST(0, 2, 10, 6) APSM_BCAST(1, 3, 26, 6)
+      APSM_BCAST(0, 2, 11, 7) APSM_BCAST(1, 3, 27, 7) APSM_BCAST(0, 2, 12, 8) APSM_BCAST(1, 3, 28, 8)
+      APSM_BCAST(0, 2, 13, 9) APSM_BCAST(1, 3, 29, 9) APSM_BCAST(0, 2, 14, 10) APSM_BCAST(1, 3, 30, 10)
+      APSM_BCAST(0, 2, 15, 11) APSM_BCAST(1, 3, 31, 11) APSM_BCAST(0, 2, 16, 12) APSM_BCAST(1, 3, 32, 12)
+      APSM_BCAST(0, 2, 17, 13) APSM_BCAST(1, 3, 33, 13) APSM_BCAST(0, 2, 18, 14) APSM_BCAST(1, 3, 34, 14)
+      APSM_BCAST(0, 2, 19, 15) APSM_BCAST(1, 3, 35, 15)
+      : "=&v"(a), "=&v"(b)
+      : "v"(x), "v"(y), "v"(k[0]), "v"(k[1]), "v"(k[2]), "v"(k[3]), "v"(k[4]), "v"(k[5]), "v"(k[6]), "v"(k[7]),
+        "v"(k[8]), "v"(k[9]), "v"(k[10]), "v"(k[11]), "v"(k[12]), "v"(k[13]), "v"(k[14]), "v"(k[15]), "v"(l[0]),
+        "v"(l[1]), "v"(l[2]), "v"(l[3]), "v"(l[4]), "v"(l[5]), "v"(l[6]), "v"(l[7]), "v"(l[8]), "v"(l[9]), "v"(l[10]),
+        "v"(l[11]), "v"(l[12]), "v"(l[13]), "v"(l[14]), "v"(l[15]));
+  return a + b;
+}
+
+// The sum of the two halves' values, in both.
+__device__ __forceinline__ float halves_sum(float x) {
+  const auto z = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(z[0]) + __uint_as_float(z[1]);
+}
+
+// The coefficients c of a window ending at place `at` of row A, zero outside
+// it, as window_sum takes them: the summed rows, each in all four rows.
+struct WindowRows {
+  float own, other;        // rows A and A - 2, row A - 1 (one row: all in own)
+  float oldest;            // W = 33: the member 32 places back
+};
+template <int A, int NRW>
+__device__ __forceinline__ WindowRows window_gather(float c, int at, int lane) {
+  WindowRows w{0.0f, 0.0f, 0.0f};
+  if constexpr (NRW == kTwoRowsAndOne) {
+    const int old = 16 * ((A + 2) & 3) + at;
+    w.oldest = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(c), old));
+    c = lane == old ? 0.0f : c;
+  }
+  const float h = halves_sum(c);
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(h), __float_as_uint(h), false, false);
+  const float r0 = __uint_as_float(r[0]), r1 = __uint_as_float(r[1]);
+  if constexpr (NRW == kOneRow) {
+    w.own = r0 + r1;
+  } else {
+    w.own = A & 1 ? r1 : r0;
+    w.other = A & 1 ? r0 : r1;
+  }
+  return w;
+}
+
+// sum_j K_lj c_j over the window; k[16 s + r]: the lane's value with lane
+// 16 s + r.  `at` is a constant where the steps are unrolled: the choice of a
+// place's register costs nothing.
+template <int A, int NRW>
+__device__ __forceinline__ float window_sum(const WindowRows& w, const float* k, int at) {
+  constexpr int B = NRW == kOneRow ? (A + 3) & 3 : (A + 2) & 3;    // the older row of the shared places
+  float own[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) own[r] = r <= at ? k[16 * A + r] : k[16 * B + r];
+  if constexpr (NRW == kOneRow) return row_sum(w.own, own);
+  float e = two_row_sum(w.own, w.other, own, k + 16 * ((A + 3) & 3));
+  if constexpr (NRW == kTwoRowsAndOne) e = fmaf(w.oldest, k[16 * B + at], e);
+  return e;
 }
 
 // x of the lane one below (lane 0: of lane 63), of the lane one above.
@@ -122,9 +154,8 @@ __device__ __forceinline__ float slab_residual_pos(float x, float eps) {
 
 // Value r of lane l in the pending image: member l % 32 of the entering block
 // against sample pending_col(l, r) of [block leaving | adjacent block]; in
-// the matrix image: lane l's sample against lane matrix_lane(l, r)'s.
-__host__ __device__ __forceinline__ int pending_col(int l, int r) { return (l & 32) + (r & 16) + ((l - r) & 15); }
-__host__ __device__ __forceinline__ int matrix_lane(int l, int r) { return (r & 48) + ((l - r) & 15); }
+// the matrix image: lane l's sample against lane r's.
+__host__ __device__ __forceinline__ int pending_col(int l, int r) { return (l & 32) + r; }
 
 template <int N>
 __device__ __forceinline__ void load_image(const float* img, int lane, float* k) {
@@ -138,12 +169,6 @@ __device__ __forceinline__ void load_image(const float* img, int lane, float* k)
   }
 }
 
-// The sum of the two halves' values, in both.
-__device__ __forceinline__ float halves_sum(float x) {
-  const auto z = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(z[0]) + __uint_as_float(z[1]);
-}
-
 // Corrections of the entering block's members for the coefficients C pending
 // in the lanes, which the expansion does not hold yet: the lower half of the
 // wave has those of the block about to leave, the upper half those of the
@@ -152,10 +177,7 @@ __device__ __forceinline__ float pending_sum(const float* img, float C, int lane
   float kf[32];
   load_image<32>(img, lane, kf);
   const auto y = __builtin_amdgcn_permlane16_swap(__float_as_uint(C), __float_as_uint(C), false, false);
-  float f;
-  row_mul(f, __uint_as_float(y[0]), kf);
-  row_fma(f, __uint_as_float(y[1]), kf + 16);
-  return halves_sum(f);
+  return halves_sum(two_row_sum(__uint_as_float(y[0]), __uint_as_float(y[1]), kf, kf + 16));
 }
 
 // The sum over the wave, in every lane.
