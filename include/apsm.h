@@ -318,7 +318,9 @@ int apsm_project_ball(const apsm_model_t* model, float sigma2, float w_lin, floa
  *  params     HOST, as for apsm_train (set_types allowed); cycles > 1 needs
  *             w_lin > 0.
  *  cycles     >= 1.
- *  workspace  as for apsm_project_ball.
+ *  workspace  as for apsm_project_ball; where it is larger than the model's
+ *             packed form the training works in it (apsm_train_scratch_bytes,
+ *             of the first cycle's and the continued init), else in that.
  * Asynchronous on `stream`. */
 int apsm_pocs(const apsm_params_t* params, int M2, int K, int P, const float* rx_pilot, const float* sym_pilot,
               const apsm_model_t* model, float radius, int cycles, void* workspace, size_t ws_bytes,

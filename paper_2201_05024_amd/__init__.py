@@ -336,9 +336,20 @@ def pocs(rx_pilot, sym_pilot, params: Params, radius: float, cycles: int, model:
         _check(params.set_types, torch.uint8, (P, K, 2), "set_types")
     if model is None:
         model = Model(M2, K, params.dict_cap, rx_pilot.device, params.sigma2)
-    if workspace is None:
-        workspace = ball_workspace(model)
     cp, keep = params._c()
+    if workspace is None:
+        # room for the training of each cycle as well, the later ones continued
+        sizes = [library().apsm_ball_workspace_bytes(model.M2, model.K, model.dict_cap)]
+        if sizes[0] == 0:
+            raise APSMError(ERR_UNSUPPORTED, "apsm_ball_workspace_bytes")
+        first = cp.init
+        for init in {first, INIT["continue"]} if cycles > 1 else {first}:
+            cp.init = init
+            sizes.append(library().apsm_train_scratch_bytes(ctypes.byref(cp), M2, K, P, 1))
+        cp.init = first
+        workspace = torch.empty(max(sizes), dtype=torch.uint8, device=model.dict.device)
+        if stream is not None:
+            workspace.record_stream(stream)
     m = model._c()
     rc = library().apsm_pocs(ctypes.byref(cp), M2, K, P, rx_pilot.data_ptr(), sym_pilot.data_ptr(),
                              ctypes.byref(m), float(radius), int(cycles), workspace.data_ptr(), workspace.numel(),

@@ -170,9 +170,13 @@ int apsm_pocs(const apsm_params_t* params, int M2, int K, int P, const float* rx
   if (int rc = check_ball(model, params->sigma2, params->w_lin, params->w_gauss, radius, workspace, ws_bytes))
     return rc;
   apsm_params_t pc = *params;
+  // training works in the workspace where that is the larger room: fewer,
+  // longer launches (the ball's use of it and the training's alternate)
+  void* const scratch = ws_bytes > packed_model_bytes(M2, K, model->dict_cap) ? workspace : nullptr;
   for (int c = 0; c < cycles; ++c) {
     if (c > 0) pc.init = APSM_INIT_CONTINUE;
-    if (int rc = train_impl(&pc, M2, K, P, 1, rx_pilot, sym_pilot, model, stream)) return rc;
+    if (int rc = train_impl(&pc, M2, K, P, 1, rx_pilot, sym_pilot, model, stream, scratch, scratch ? ws_bytes : 0))
+      return rc;
     if (int rc = ball_launch(model, params->sigma2, params->w_lin, params->w_gauss, radius, workspace, nullptr,
                              (hipStream_t)stream))
       return rc;

@@ -155,7 +155,7 @@ __device__ __forceinline__ void strip_unit(const BlockJob& j, const Source& src,
     }
   const int q = q0 + (w >> 1);
   if (q >= j.qb) return;
-  auto out = gmem(j.strips) + (size_t)(q - j.qa) * j.SW * kBlk + 16 * (w & 1) + c;
+  auto out = gmem(j.strips) + (size_t)(q - j.qa) * j.SW * kBlk;
   const int x0 = dlo - kBlk * (q - 2) + j.SW;
 #pragma unroll
   for (int u = 0; u < 8; ++u)
@@ -164,7 +164,7 @@ __device__ __forceinline__ void strip_unit(const BlockJob& j, const Source& src,
       const int r = 16 * u + 4 * g + i, d = dlo + r, x = x0 + r;
       if (x < 0 || x >= j.SW) continue;
       const bool in = d >= -nold && m - d < src.cap;
-      out[(size_t)x * kBlk] = in ? gauss(j.c2, nn, xn[r], acc[u][i]) : 0.0f;
+      out[strip_at(x, 16 * (w & 1) + c)] = in ? gauss(j.c2, nn, xn[r], acc[u][i]) : 0.0f;
     }
 }
 
@@ -481,6 +481,14 @@ __device__ __forceinline__ void helper_role(const HelperArgs& h, const TrainComm
   // the block flushed before.  Every load is issued ahead of the sums and
   // unconditionally (clamped addresses; masks and signs are applied where
   // the values are stored), so that only the strip's are waited for.
+  StripRound ahead;
+  // entry x of block q's strip is sample dlo + x; those before the oldest
+  // have no slot (and zero kernel values): the strip from first_entry on
+  auto first_entry = [&](int dlo) { return -nold - dlo <= 0 ? 0 : (-nold - dlo) & ~15; };
+  auto strip_of = [&](int q) { return j.strips + (size_t)(q - j.qa) * SW * kBlk; };
+  auto begin = [&](int q) {
+    strip_begin(ahead, strip_of(q), first_entry(kBlk * (q - 2) - SW), SW, hw, kHelpers, lane);
+  };
   auto prepare = [&](int q) {
     const float* img = j.images + (size_t)(q - j.qa) * kTrainImage;
     lds_copy(img, h.image, kEvAt, hw, kHelpers, lane);
@@ -505,17 +513,16 @@ __device__ __forceinline__ void helper_role(const HelperArgs& h, const TrainComm
     BlockSums b;
 #pragma unroll
     for (int v = 0; v < 8; ++v) b.v[v] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-    // entry x of the strip is sample 32 (q - 2) - SW + x; those before the
-    // oldest have no slot (and zero kernel values)
     const int dlo = kBlk * (q - 2) - SW, bl = lane >> 2, u = lane & 3, ul = k0 + (u < nu ? u : 0);
-    const int x0 = -nold - dlo <= 0 ? 0 : (-nold - dlo) & ~15;
     const int s0 = ((n0 + dlo) % cap + cap) % cap;
     auto co = [&](int x) -> float {
       int slot = s0 + x + bl;
       slot = slot >= cap ? slot - cap : slot;
       return alpha[(unsigned)(slot * Kt + ul)];
     };
-    block_accumulate(b, j.strips + (size_t)(q - j.qa) * SW * kBlk, co, u < nu, x0, SW, hw, kHelpers, lane);
+    block_accumulate(b, ahead, strip_of(q), co, u < nu, first_entry(dlo), SW, hw, kHelpers, lane);
+    lds_copy_wait();                        // (the copies are older than the strip's loads)
+    if (q + 1 < j.qb) begin(q + 1);
     block_store(b, h.part, hw, lane);
     if (ht < kBlk * kSerial) {
       h.target[ht] = member ? tg : 0.0f;
@@ -578,8 +585,8 @@ __device__ __forceinline__ void helper_role(const HelperArgs& h, const TrainComm
       p[0] = fmaf(cm.wl, l0, p[0]);
       p[1] = fmaf(cm.wl, l1, p[1]);
     }
-    lds_copy_wait();
   };
+  begin(j.qa);
   prepare(j.qa);
   for (int q = j.qa; q < j.qb; ++q) {
     __syncthreads();

@@ -53,7 +53,7 @@ __device__ __forceinline__ T* part_of(const UnrolledArgs& a, int b, size_t off) 
 // Where K_ij and H_ij live: the 32 columns of a block together, [block][i][32],
 // so that a block's members against every entry are one contiguous stretch.
 __host__ __device__ __forceinline__ size_t pair_at(int TP, int i, int j) {
-  return ((size_t)(j >> 5) * TP + i) * kBlk + (j & 31);
+  return (size_t)(j >> 5) * TP * kBlk + strip_at(i, j & 31);
 }
 
 // K, H = wG G D of all pairs (zero past T) and the diagonal of K, 16 x 16
@@ -262,11 +262,17 @@ __global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int
   __syncthreads();
   const float qsW = qs[W];
 
+  const int nit = REV ? NB + 1 : NB;
   // What the block q entering at iteration i needs: its register images,
   // targets (or cbar0) and diagonal, the sums of its members over the
   // expansion.
   // In the reverse sweep also the taped x of the block stepped through then.
   const int ht = tid - 64 * kSerial;        // helper thread
+  StripRound ahead;
+  auto begin = [&](int i) {
+    const int q = REV ? NB - 1 - i : i;
+    if (q >= 0) strip_begin(ahead, Km + (size_t)q * TP * kBlk, 0, TP, wave - kSerial, kHelpers, lane);
+  };
   auto prepare = [&](int i, int p) {
     const int q = REV ? NB - 1 - i : i, st = q + 1;
     lds_copy(img + (size_t)(q + 1) * kImage, image, kImage, wave - kSerial, kHelpers, lane);
@@ -282,12 +288,14 @@ __global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int
       BlockSums s;
 #pragma unroll
       for (int v = 0; v < 8; ++v) s.v[v] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-      block_accumulate(s, Km + (size_t)q * TP * kBlk, c4, true, 0, TP, wave - kSerial, kHelpers, lane);
+      block_accumulate(s, ahead, Km + (size_t)q * TP * kBlk, c4, true, 0, TP, wave - kSerial, kHelpers, lane);
+      if constexpr (TAPE)
+        strip_begin(ahead, Hm + (size_t)q * TP * kBlk, 0, TP, wave - kSerial, kHelpers, lane);
       block_store(s, part, wave - kSerial, lane);
       if constexpr (TAPE) {
 #pragma unroll
         for (int v = 0; v < 8; ++v) s.v[v] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-        block_accumulate(s, Hm + (size_t)q * TP * kBlk, c4, true, 0, TP, wave - kSerial, kHelpers, lane);
+        block_accumulate(s, ahead, Hm + (size_t)q * TP * kBlk, c4, true, 0, TP, wave - kSerial, kHelpers, lane);
         block_store(s, part + kPartFloats, wave - kSerial, lane);
       }
       if (ht < kBlk * kSerial) stage[ht] = n < T && uu < nu ? tv : 0.0f;
@@ -317,13 +325,13 @@ __global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int
       }
     }
     lds_copy_wait();
+    begin(i + 1 < nit ? i + 1 : 0);
   };
 
   // Roles: the waves of users run the recursion, the helper waves prepare
   // the next block; both keep to the same barriers (two per block, one per
   // pass).  Separate loops, so that neither role's registers are live in the
   // other.
-  const int nit = REV ? NB + 1 : NB;
   if (wave < kSerial) {
     const int u = wave;
     const bool active = u < nu;
@@ -403,6 +411,7 @@ __global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int
       __syncthreads();
     }
   } else {
+    begin(0);
     for (int pi = 0; pi < p1 - p0; ++pi) {
       const int p = REV ? p1 - 1 - pi : p0 + pi;
       if (MODE == kForward && p % a.E == 0) {

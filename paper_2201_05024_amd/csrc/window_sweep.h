@@ -213,73 +213,88 @@ __device__ __forceinline__ void lds_copy_wait() { __builtin_amdgcn_s_waitcnt(0x0
 // Evaluation of a block's 32 members against the entries [d0, n) by the
 // helper waves, four users at a time, on v_mfma_f32_4x4x1_16b_f32: its 16
 // blocks take 16 entries, rows four members, columns the users.  vals: the
-// kernel values, entry d's 32 members contiguous at vals + 32 d (16-byte
-// aligned); coef(d): this lane's coefficient of the 16 entries from d on
-// (entry lane / 4, user lane % 4), read whatever `keep` is and counted where
-// it is set; d0 and n multiples of 16.  Helper hw takes
-// every nh-th group of 16 entries; its sums over them go to
-// part[hw][member][user].
+// kernel values, strip_at(entry, member) floats on (16-byte aligned): a wave
+// reads a KiB of 16 entries and 16 members with each load.  coef(d): this
+// lane's coefficient of the 16 entries from d on (entry lane / 4, user lane %
+// 4), read whatever `keep` is and counted where it is set; d0 and n multiples
+// of 16.  Helper hw takes every nh-th group of 16 entries; its sums over them
+// go to part[hw][member][user].
+// Bound by the latency of the loads: a strip is read once, from the Infinity
+// Cache or HBM.  Rounds of kRound groups, the next round's loads issued before
+// this round's products, and a block's first round (strip_begin: kernel
+// values only, the coefficients may not be final) as early as the caller can,
+// a block ahead.  Loads are unconditional (past the end the wave's first group
+// again, its coefficients replaced by 0 where they are used): a branch around
+// them makes the compiler wait for them at its end.
 struct BlockSums {
   floatx4 v[8];
 };
+constexpr int kRound = 4;
+struct StripRound {
+  floatx4 x[kRound][2];
+};
+__host__ __device__ __forceinline__ size_t strip_at(int d, int m) {
+  return (size_t)(d & ~15) * kBlk + 256 * (m >> 4) + 16 * (d & 15) + (m & 15);
+}
 
-template <class Coef>
-__device__ __forceinline__ void block_accumulate(BlockSums& a, const float* vals, Coef&& coef, bool keep, int d0,
-                                                 int n, int hw, int nh, int lane) {
-  // scalar base per group, one lane offset for all (no address registers)
+// The round whose first group is at d.
+__device__ __forceinline__ void strip_load(StripRound& r, const float* vals, int d, int first, int n, int step,
+                                           int lane) {
   typedef __attribute__((address_space(1))) const floatx4 gvec;
   typedef __attribute__((address_space(1))) const char gbyte;
+  // scalar base per group, one lane offset for all (no address registers)
   gbyte* const base = (gbyte*)vals;
-  const unsigned off = (unsigned)((lane >> 2) * kBlk + 8 * (lane & 3)) * 4u;
-  // Rounds of U groups, the next round's loads issued before this round's
-  // products: 8 to 16 KiB in flight a wave, to cover the memory latency.
-  // Loads are unconditional (past the end the wave's first group again, its
-  // coefficients replaced by 0 where they are used): a branch around them
-  // makes the compiler wait for them at its end.
-  constexpr int U = 4;
-  struct Round {
-    floatx4 x[U][2];
-    float c[U];
-  };
+#pragma unroll
+  for (int q = 0; q < kRound; ++q) {
+    gbyte* const p = base + (size_t)(d + step * q < n ? d + step * q : first) * (kBlk * 4);
+    r.x[q][0] = *(gvec*)(p + 16u * (unsigned)lane);
+    r.x[q][1] = *(gvec*)(p + 16u * (unsigned)lane + 1024u);
+  }
+}
+__device__ __forceinline__ void strip_begin(StripRound& r, const float* vals, int d0, int n, int hw, int nh, int lane) {
+  d0 += 16 * hw;
+  if (d0 < n) strip_load(r, vals, d0, d0, n, 16 * nh, lane);
+}
+
+template <class Coef>
+__device__ __forceinline__ void block_accumulate(BlockSums& a, StripRound& r0, const float* vals, Coef&& coef,
+                                                 bool keep, int d0, int n, int hw, int nh, int lane) {
   const int step = 16 * nh;
   d0 += 16 * hw;
   if (d0 >= n) return;
-  const int dfirst = d0;
-  auto load = [&](Round& r, int d) {
+  const int first = d0;
+  float c0[kRound], c1[kRound];
+  auto load_coef = [&](float (&c)[kRound], int d) {
 #pragma unroll
-    for (int q = 0; q < U; ++q) {
-      const int dq = d + step * q < n ? d + step * q : dfirst;
-      gbyte* const p = base + (size_t)dq * (kBlk * 4);
-      r.x[q][0] = *(gvec*)(p + off);
-      r.x[q][1] = *(gvec*)(p + off + 16);
-      r.c[q] = coef(dq);
-    }
+    for (int q = 0; q < kRound; ++q) c[q] = coef(d + step * q < n ? d + step * q : first);
   };
-  auto add = [&](const Round& r, int d) {
+  auto add = [&](const StripRound& r, const float (&cr)[kRound], int d) {
 #pragma unroll
-    for (int q = 0; q < U; ++q) {
-      const float c = keep && d + step * q < n ? r.c[q] : 0.0f;
+    for (int q = 0; q < kRound; ++q) {
+      const float c = keep && d + step * q < n ? cr[q] : 0.0f;
 #pragma unroll
       for (int v = 0; v < 8; ++v)
         a.v[v] = __builtin_amdgcn_mfma_f32_4x4x1f32(r.x[q][v >> 2][v & 3], c, a.v[v], 0, 0, 0);
     }
   };
-  Round r0, r1;
-  load(r0, d0);
+  StripRound r1;
+  load_coef(c0, d0);
   for (;;) {
-    load(r1, d0 + step * U);
-    add(r0, d0);
-    d0 += step * U;
+    load_coef(c1, d0 + step * kRound);
+    strip_load(r1, vals, d0 + step * kRound, first, n, step, lane);
+    add(r0, c0, d0);
+    d0 += step * kRound;
     if (d0 >= n) break;
-    load(r0, d0 + step * U);
-    add(r1, d0);
-    d0 += step * U;
+    load_coef(c0, d0 + step * kRound);
+    strip_load(r0, vals, d0 + step * kRound, first, n, step, lane);
+    add(r1, c1, d0);
+    d0 += step * kRound;
     if (d0 >= n) break;
   }
 }
 
 // Sums over the 16 blocks (lane bits 2..5): accumulator (v, r) is member
-// 8 r + v.  Half swaps, then row swaps, each adding two values into one and
+// 16 (v / 4) + 4 r + v % 4.  Half swaps, then row swaps, each adding two values into one and
 // leaving the pair on the two sides; the last two bits by row rotations.
 __device__ __forceinline__ void block_store(const BlockSums& a, float* part, int hw, int lane) {
   float q[32];
@@ -304,9 +319,9 @@ __device__ __forceinline__ void block_store(const BlockSums& a, float* part, int
   }
   if ((lane & 12) == 0) {
     const int row = lane >> 4, u = lane & 3;
-    const int v0 = 4 * (row >> 1) + 2 * (row & 1);
+    const int m0 = 16 * (row >> 1) + 2 * (row & 1);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) part[(hw * kBlk + 8 * (i & 3) + v0 + (i >> 2)) * kSerial + u] = q[i];
+    for (int i = 0; i < 8; ++i) part[(hw * kBlk + m0 + 4 * (i & 3) + (i >> 2)) * kSerial + u] = q[i];
   }
 }
 
