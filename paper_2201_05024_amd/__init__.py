@@ -295,13 +295,22 @@ def linear_mmse(h, n0: float, w=None, stream=None):
     return w[0] if squeeze else w
 
 
+# Room for training that ball_workspace adds at most.
+_BALL_TRAIN_MAX = 64 << 20
+
+
 def ball_workspace(model: "Model"):
-    """A device workspace for project_ball / pocs with this model's shape."""
+    """A device workspace for project_ball / pocs with this model's shape, with
+    room for pocs to train about two dictionaries of samples in one launch
+    (up to 64 MiB: more samples take more launches)."""
     torch = _torch()
     n = library().apsm_ball_workspace_bytes(model.M2, model.K, model.dict_cap)
     if n == 0:
         raise APSMError(ERR_UNSUPPORTED, "apsm_ball_workspace_bytes")
-    return torch.empty(n, dtype=torch.uint8, device=model.dict.device)
+    p, keep = Params(sigma2=model.sigma2, window=1, dict_cap=model.dict_cap, init="continue")._c()
+    t = library().apsm_train_scratch_bytes(ctypes.byref(p), model.M2, model.K, model.dict_cap, 1)
+    del keep
+    return torch.empty(max(n, min(t, _BALL_TRAIN_MAX)), dtype=torch.uint8, device=model.dict.device)
 
 
 def project_ball(model: "Model", radius: float, params: Params, workspace=None, norms=None, stream=None):
