@@ -54,10 +54,10 @@ __host__ __device__ inline bool coef_in_lds(int T, int KP, size_t before) {
 
 __device__ __forceinline__ float comp(const float* rx, int M2, int n, int m) {
   // component m of real sample n: r_{2t} = r1(t), r_{2t+1} = r2(t) = [Im; -Re]
-  const int M = M2 >> 1;
-  const float* src = rx + (size_t)(n >> 1) * M2;
-  if ((n & 1) == 0) return src[m];
-  return m < M ? src[m + M] : -src[m - M];
+  // (one load, no branch: loads of several components stay in flight)
+  const int M = M2 >> 1, odd = n & 1;
+  const float v = rx[(size_t)(n >> 1) * M2 + (odd ? (m < M ? m + M : m - M) : m)];
+  return odd && m >= M ? -v : v;
 }
 
 __device__ __forceinline__ float target(const float* sym, int K, int n, int k) {
@@ -412,13 +412,34 @@ __global__ __launch_bounds__(kT) void unr_val_bwd_kernel(UnrolledArgs a) {
   float* abar = I.adj + K * WS;
   const int nib = (T + 63) / 64;
   if ((int)blockIdx.x == nib) {
-    // wbar_k,m = sum_v fbar_vk v_m
-    for (int e = threadIdx.x; e < K * WS; e += kT) {
-      const int k = e / WS, m = e - k * WS;
+    // wbar_k,m = sum_v fbar_vk v_m: the vectors in NS interleaved parts where
+    // there are threads to spare, 16 terms in flight a thread.  Bound by the
+    // latency of the loads (one term at a time: 2.6 ms at 8192 vectors of 32
+    // components and 6 users, twice what the other workgroups take; 0.13 ms).
+    const int NS = kT / (K * WS) > 1 ? kT / (K * WS) : 1;
+    float* part = &red[0][0];
+    for (int e0 = 0; e0 < K * WS * NS; e0 += kT) {
+      const int e = e0 + threadIdx.x, o = e < K * WS * NS ? e / NS : 0, seg = e % NS;
+      const int k = o / WS, m = o - k * WS, mc = m < M2 ? m : 0;
       float acc = 0.0f;
-      if (m < M2)
-        for (int v = 0; v < Sr; ++v) acc = fmaf(I.fbar[(size_t)v * KP + k], comp(rv, M2, v, m), acc);
-      wbar[e] = acc;
+      for (int v0 = seg; v0 < Sr; v0 += 16 * NS) {
+        float f[16], x[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+          const int v = v0 + q * NS < Sr ? v0 + q * NS : seg;
+          f[q] = I.fbar[(size_t)v * KP + k];
+          x[q] = comp(rv, M2, v, mc);
+        }
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc = fmaf(v0 + q * NS < Sr ? f[q] : 0.0f, x[q], acc);
+      }
+      __syncthreads();
+      part[threadIdx.x] = acc;
+      __syncthreads();
+      if (e < K * WS * NS && seg == 0) {
+        for (int q = 1; q < NS; ++q) acc += part[threadIdx.x + q];
+        wbar[o] = m < M2 ? acc : 0.0f;
+      }
     }
     return;
   }

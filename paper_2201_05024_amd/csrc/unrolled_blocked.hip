@@ -16,9 +16,9 @@
 // that does not depend on the checkpoint interval.
 //
 // One workgroup per (instance, up to four users): four waves run a user each,
-// four evaluate the next block's members against the whole expansion.
-// Bound: the serial chain of a step, about 75 VALU instructions of one wave
-// (window rows 3: 48 of them the matrix-vector product).
+// eight evaluate the next block's members against the whole expansion.
+// Bound: the serial chain of a step, about 46 VALU instructions of one wave
+// (W = 17..32: 32 of them the matrix-vector product).
 #include "apsm_internal.h"
 #include "window_sweep.h"
 
@@ -37,12 +37,12 @@ enum { kForward = 0, kTape = 1, kReverse = 2 };
 constexpr int kHelpers = 8;
 constexpr int kThreads = 64 * (kSerial + kHelpers);
 constexpr int kPartFloats = kHelpers * kBlk * kSerial;
+constexpr int kTapeUsers = kSerial / 2;    // of a taped sweep: a wave for K and one for H each
 
 __device__ __forceinline__ float comp(const float* rx, int M2, int n, int m) {
-  const int M = M2 >> 1;
-  const float* src = rx + (size_t)(n >> 1) * M2;
-  if ((n & 1) == 0) return src[m];
-  return m < M ? src[m + M] : -src[m - M];
+  const int M = M2 >> 1, odd = n & 1;
+  const float v = rx[(size_t)(n >> 1) * M2 + (odd ? (m < M ? m + M : m - M) : m)];
+  return odd && m >= M ? -v : v;
 }
 
 template <class T>
@@ -121,7 +121,7 @@ __global__ __launch_bounds__(256) void unb_image_kernel(UnrolledArgs a) {
   }
 }
 
-// LDS of a sweep, in floats.
+// LDS of a sweep, in floats.  xs: the taped x of two blocks' steps, by lane.
 struct SweepLds {
   int coef, image, part, stage, ikn, om, qs, xs, total;
 };
@@ -132,10 +132,10 @@ __host__ __device__ inline SweepLds sweep_lds(int mode, int TP) {
   l.coef = o;  o += TP * kSerial;
   l.part = o;  o += n2 * kPartFloats;
   l.stage = o; o += kBlk * kSerial;
-  l.ikn = o;   o += kBlk;
+  l.ikn = o;   o += n2 * kBlk;
   l.om = o;    o += 64;
   l.qs = o;    o += 64;
-  l.xs = o;    o += mode == kReverse ? 2 * kBlk * kSerial * 64 : 0;
+  l.xs = o;    o += mode == kForward ? 0 : 2 * kBlk * (mode == kTape ? kTapeUsers : kSerial) * 64;
   l.image = o; o += n2 * kImage;            // every offset a multiple of four floats: float4 reads
   l.total = o;
   return l;
@@ -143,7 +143,7 @@ __host__ __device__ inline SweepLds sweep_lds(int mode, int TP) {
 
 // One lane's state of a user's recursion.
 struct Lane {
-  float e, h;      // running prediction (cbar in the reverse sweep), sigma sum
+  float e;         // running prediction (cbar in the reverse sweep)
   float C;         // coefficients (xbar) not yet in the expansion
   float b, ikn;    // target, -1 / kappa(r, r) (0 where that is not positive)
   int d;           // sample, -1 for none
@@ -151,11 +151,13 @@ struct Lane {
 
 // 16 steps (or the fewer of the sequence's end) whose newest members lie in
 // row A of the wave; n0 the first of them, cnt their number.  FULL: all 16,
-// with the window full.  xs: the taped x of the steps, [step][user][lane].
+// with the window full.  xs: the x of the steps, [step][xstep] by lane
+// (written by the taped sweep, read in reverse); tc: the tape of cbar.
+// Unrolled, as the product's registers depend on the step's place.
 template <int MODE, int NRW, int A, bool FULL>
-__device__ __forceinline__ void sweep_steps(Lane& s, const float* kreg, const float* hreg, int n0, int cnt, int W,
-                                            float eps, float qsW, const float* om, const float* qs, const float* xs,
-                                            float* tx, float* th, size_t tstep, int lane) {
+__device__ __forceinline__ void sweep_steps(Lane& s, const float* kreg, int n0, int cnt, int W, float eps, float qsW,
+                                            const float* om, const float* qs, float* xs, int xstep, float* tc,
+                                            size_t tstep, int lane) {
 #pragma clang fp contract(off)
   constexpr bool REV = MODE == kReverse;
   const int t0 = !REV ? 0 : FULL ? 15 : cnt - 1;      // first step taken
@@ -165,8 +167,7 @@ __device__ __forceinline__ void sweep_steps(Lane& s, const float* kreg, const fl
   float wv = om[(16 * A + t0 - lane) & 63];
   float at = __int_as_float((16 * A + t0 - lane) & 63);
   const float iq = s.ikn * qsW;
-  float xv = REV ? xs[t0 * kSerial * 64 + lane] : 0.0f;
-  // (unrolled: the product's registers depend on the step's place)
+  float xv = REV ? xs[t0 * xstep + lane] : 0.0f;
 #pragma unroll
   for (int it = 0; it < 16; ++it) {
     const int t = REV ? 15 - it : it, n = n0 + t;
@@ -175,50 +176,89 @@ __device__ __forceinline__ void sweep_steps(Lane& s, const float* kreg, const fl
     const float wq = w;
     const int age = __float_as_int(at);
     wv = REV ? from_above(wv) : from_below(wv);
-    if constexpr (MODE != kForward) at = REV ? from_above(at) : from_below(at);
     float c;
     if constexpr (REV) {
+      at = from_above(at);
       // adjoint of the active members: xbar = -mu q cbar / kappa
       w = fabsf(xv) - eps > 0.0f ? wq : 0.0f;
-      xv = xs[(t > 0 ? t - 1 : 0) * kSerial * 64 + lane];   // the next step's, a step ahead
+      xv = xs[(t > 0 ? t - 1 : 0) * xstep + lane];          // the next step's, a step ahead
       c = s.e * w;
-      if (age < W) (tx + (size_t)n * tstep)[(unsigned)age] = s.e;
+      if (age < W) (tc + (size_t)n * tstep)[(unsigned)age] = s.e;
     } else {
       const float x = s.e - s.b;
       c = slab_residual(x, eps) * w;
-      if constexpr (MODE == kTape) {
-        if (age < W) {
-          (tx + (size_t)n * tstep)[(unsigned)age] = x;
-          (th + (size_t)n * tstep)[(unsigned)age] = s.h;
-        }
-      }
+      if constexpr (MODE == kTape) xs[t * xstep + lane] = x;
     }
     s.C += c;
-    const WindowRows rows = window_gather<A, NRW>(c, t, lane);
-    s.e += window_sum<A, NRW>(rows, kreg, t);
-    if constexpr (MODE == kTape) s.h += window_sum<A, NRW>(rows, hreg, t);
+    s.e += window_sum<A, NRW>(window_gather<A, NRW>(c, t, lane), kreg, t);
   }
 }
 
 template <int MODE, int NRW, int A>
-__device__ __forceinline__ void sweep_row(Lane& s, const float* kreg, const float* hreg, int n0, int cnt, int W,
-                                          float eps, float qsW, const float* om, const float* qs, const float* xs,
-                                          float* tx, float* th, size_t tstep, int lane) {
+__device__ __forceinline__ void sweep_row(Lane& s, const float* kreg, int n0, int cnt, int W, float eps, float qsW,
+                                          const float* om, const float* qs, float* xs, int xstep, float* tc,
+                                          size_t tstep, int lane) {
   if (cnt == 16 && n0 + 1 >= W)
-    sweep_steps<MODE, NRW, A, true>(s, kreg, hreg, n0, 16, W, eps, qsW, om, qs, xs, tx, th, tstep, lane);
+    sweep_steps<MODE, NRW, A, true>(s, kreg, n0, 16, W, eps, qsW, om, qs, xs, xstep, tc, tstep, lane);
   else if (cnt > 0)
-    sweep_steps<MODE, NRW, A, false>(s, kreg, hreg, n0, cnt, W, eps, qsW, om, qs, xs, tx, th, tstep, lane);
+    sweep_steps<MODE, NRW, A, false>(s, kreg, n0, cnt, W, eps, qsW, om, qs, xs, xstep, tc, tstep, lane);
+}
+
+// The same steps for the sigma sums, a block behind: x from xs, c from it as
+// the recursion has it, x and h of the members to the tape.
+struct SigmaLane {
+  float h, C, ikn;
+};
+template <int NRW, int A, bool FULL>
+__device__ __forceinline__ void sigma_steps(SigmaLane& s, const float* hreg, int n0, int cnt, int W, float eps,
+                                            float qsW, const float* om, const float* qs, const float* xs, float* tx,
+                                            float* th, size_t tstep, int lane) {
+#pragma clang fp contract(off)
+  float wv = om[(16 * A - lane) & 63];
+  float at = __int_as_float((16 * A - lane) & 63);
+  const float iq = s.ikn * qsW;
+  float xv = xs[lane];
+  tx += (size_t)n0 * tstep;
+  th += (size_t)n0 * tstep;
+#pragma unroll
+  for (int t = 0; t < 16; ++t) {
+    if (!FULL && t >= cnt) continue;
+    const int n = n0 + t;
+    const float x = xv, w = FULL || n + 1 >= W ? wv * iq : (wv * qs[n + 1]) * s.ikn;
+    const int age = __float_as_int(at);
+    wv = from_below(wv);
+    at = from_below(at);
+    xv = xs[(t < 15 ? t + 1 : 15) * kTapeUsers * 64 + lane];      // the next step's, a step ahead
+    const float c = slab_residual(x, eps) * w;
+    if (age < W) {
+      tx[(unsigned)age] = x;
+      th[(unsigned)age] = s.h;
+    }
+    tx += tstep;
+    th += tstep;
+    s.C += c;
+    s.h += window_sum<A, NRW>(window_gather<A, NRW>(c, t, lane), hreg, t);
+  }
+}
+template <int NRW, int A>
+__device__ __forceinline__ void sigma_row(SigmaLane& s, const float* hreg, int n0, int cnt, int W, float eps,
+                                          float qsW, const float* om, const float* qs, const float* xs, float* tx,
+                                          float* th, size_t tstep, int lane) {
+  if (cnt == 16 && n0 + 1 >= W)
+    sigma_steps<NRW, A, true>(s, hreg, n0, 16, W, eps, qsW, om, qs, xs, tx, th, tstep, lane);
+  else if (cnt > 0)
+    sigma_steps<NRW, A, false>(s, hreg, n0, cnt, W, eps, qsW, om, qs, xs, tx, th, tstep, lane);
 }
 
 // Passes [p0, p1) of one instance and one group of at most four users.
 // Forward: from zero (p0 = 0), writing a checkpoint of C at every pass p % E
-// == 0 and C at the end.  Tape: from checkpoint p0 / E, writing x and h of
-// the window members of every step.  Reverse: passes p1 - 1 .. p0 backwards,
-// X carried in the workspace, writing cbar of the members.
+// == 0 and C at the end.  Reverse: passes p1 - 1 .. p0 backwards, X carried
+// in the workspace, writing cbar of the members.
 template <int MODE, int NRW>
 __global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int p0, int p1, int groups, int ku) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
-  constexpr bool REV = MODE == kReverse, TAPE = MODE == kTape;
+  constexpr bool REV = MODE == kReverse;
+  static_assert(MODE != kTape, "unb_tape_kernel");
   // workgroups go round the eight XCDs: the user groups of an instance, which
   // read the same strips, are eight apart, on one XCD and its L2
   const int inst = (int)(blockIdx.x / (8 * groups)) * 8 + (blockIdx.x & 7);
@@ -230,7 +270,6 @@ __global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int
   const int il = lane & 31;
   const bool upper = lane >= 32;
   const float* Km = part_of<float>(a, inst, a.off_G);
-  const float* Hm = part_of<float>(a, inst, a.off_D);
   const float* kd = part_of<float>(a, inst, a.off_kd);
   const float* img = part_of<float>(a, inst, a.off_img) + (REV ? (size_t)2 * (NB + 1) * kImage : 0);
   const float* cb0 = part_of<float>(a, inst, a.off_cb0);
@@ -252,9 +291,9 @@ __global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int
     qs[tid] = tid > 0 ? mu / z : 0.0f;
   }
   float* const xg = part_of<float>(a, inst, a.off_X);
-  const float* src = REV ? xg : p0 == 0 ? nullptr : ck + (size_t)(p0 / a.E) * T * KP;
+  const float* src = REV ? xg : nullptr;
   // lanes without a sample multiply what the image holds by zero
-  for (int e = tid; e < (TAPE ? 2 : 1) * kImage; e += kThreads) image[e] = 0.0f;
+  for (int e = tid; e < kImage; e += kThreads) image[e] = 0.0f;
   for (int e = tid; e < TP * kSerial; e += kThreads) {
     const int d = e >> 2, u = e & 3;
     coef[e] = src && d < T && u < nu ? src[(size_t)d * KP + k0 + u] : 0.0f;
@@ -276,8 +315,6 @@ __global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int
   auto prepare = [&](int i, int p) {
     const int q = REV ? NB - 1 - i : i, st = q + 1;
     lds_copy(img + (size_t)(q + 1) * kImage, image, kImage, wave - kSerial, kHelpers, lane);
-    if constexpr (TAPE)
-      lds_copy(img + (size_t)(NB + q + 2) * kImage, image + kImage, kImage, wave - kSerial, kHelpers, lane);
     if (q >= 0) {
       // targets and diagonal: read here, stored after the sums, so that
       // nothing waits for them
@@ -289,15 +326,7 @@ __global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int
 #pragma unroll
       for (int v = 0; v < 8; ++v) s.v[v] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
       block_accumulate(s, ahead, Km + (size_t)q * TP * kBlk, c4, true, 0, TP, wave - kSerial, kHelpers, lane);
-      if constexpr (TAPE)
-        strip_begin(ahead, Hm + (size_t)q * TP * kBlk, 0, TP, wave - kSerial, kHelpers, lane);
       block_store(s, part, wave - kSerial, lane);
-      if constexpr (TAPE) {
-#pragma unroll
-        for (int v = 0; v < 8; ++v) s.v[v] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-        block_accumulate(s, ahead, Hm + (size_t)q * TP * kBlk, c4, true, 0, TP, wave - kSerial, kHelpers, lane);
-        block_store(s, part + kPartFloats, wave - kSerial, lane);
-      }
       if (ht < kBlk * kSerial) stage[ht] = n < T && uu < nu ? tv : 0.0f;
       if (ht < kBlk) ikn[ht] = kj > 0.0f ? -1.0f / kj : 0.0f;
     }
@@ -337,14 +366,13 @@ __global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int
     const bool active = u < nu;
     const int k = k0 + (active ? u : 0);
     if (active) __builtin_amdgcn_s_setprio(3);
-    float kreg[64], hreg[TAPE ? 64 : 1];
+    float kreg[64];
     Lane s{};
     for (int pi = 0; pi < p1 - p0; ++pi) {
       const int p = REV ? p1 - 1 - pi : p0 + pi;
       s = Lane{};
       s.d = -1;
-      float* const tw = part_of<float>(a, inst, REV ? a.off_tcb : a.off_tx) + ((size_t)(p - p0) * T * K + k) * W;
-      float* const thw = TAPE ? part_of<float>(a, inst, a.off_th) + ((size_t)(p - p0) * T * K + k) * W : nullptr;
+      float* const tc = REV ? part_of<float>(a, inst, a.off_tcb) + ((size_t)(p - p0) * T * K + k) * W : nullptr;
       for (int i = 0; i < nit; ++i) {
         const int q = REV ? NB - 1 - i : i;   // block entering
         const int st = REV ? q + 1 : q;       // block stepped through
@@ -352,21 +380,16 @@ __global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int
         if (active) {
           // the lower half's block goes into the expansion, the upper half
           // moves down, q's members come in with their sums and corrections
-          float e = 0.0f, h = 0.0f, g = 0.0f, ik = 0.0f;
+          float e = 0.0f, g = 0.0f, ik = 0.0f;
           if (q >= 0) {
             e = pending_sum(image + kMatrixImage, s.C, lane);
-            if constexpr (TAPE) h = pending_sum(image + kImage + kMatrixImage, s.C, lane);
-            float sum = 0.0f, sumh = 0.0f;
+            float sum = 0.0f;
 #pragma unroll
-            for (int w = 0; w < kHelpers; ++w) {
-              sum += part[(w * kBlk + il) * kSerial + u];
-              if constexpr (TAPE) sumh += part[kPartFloats + (w * kBlk + il) * kSerial + u];
-            }
+            for (int w = 0; w < kHelpers; ++w) sum += part[(w * kBlk + il) * kSerial + u];
             g = stage[il * kSerial + u];
             ik = ikn[il];
             e = sum + e;
             if constexpr (REV) e = g + e;
-            h = sumh + h;
           }
           if (!upper && s.d >= 0) coef[s.d * kSerial + u] += s.C;
           // (swaps outside the selects: they need every lane)
@@ -376,25 +399,20 @@ __global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int
           s.C = upper ? 0.0f : Cu;
           s.ikn = upper ? ik : iu;
           s.d = !upper ? du : q >= 0 ? kBlk * q + il : -1;
-          if constexpr (TAPE) {
-            const float hu = upper_half(s.h);
-            s.h = upper ? h : hu;
-          }
           if constexpr (!REV) {
             const float bu = upper_half(s.b);
             s.b = upper ? g : bu;
           }
           load_image<64>(image, lane, kreg);
-          if constexpr (TAPE) load_image<64>(image + kImage, lane, hreg);
         }
         __syncthreads();
         if (active && st >= 0 && st < NB) {
           const int n0 = kBlk * st, rem = T - n0;
           const int c0 = rem < 16 ? rem : 16, c1 = rem < 16 ? 0 : rem < 32 ? rem - 16 : 16;
-          const float* xs = lds + L.xs + ((st & 1) * kBlk * kSerial + u) * 64;
+          float* const xs = lds + L.xs + ((st & 1) * kBlk * kSerial + u) * 64;
           const size_t ts = (size_t)K * W;
 #define APSM_SWEEP_ROW(A, n, c)                                                                       \
-  sweep_row<MODE, NRW, A>(s, kreg, hreg, n, c, W, eps, qsW, om, qs, xs + ((n) - n0) * kSerial * 64, tw, thw, ts, lane)
+  sweep_row<MODE, NRW, A>(s, kreg, n, c, W, eps, qsW, om, qs, xs + ((n) - n0) * kSerial * 64, kSerial * 64, tc, ts, lane)
           // forward the steps' block is the upper half, in reverse the lower
           if constexpr (REV) {
             APSM_SWEEP_ROW(1, n0 + 16, c1);
@@ -428,10 +446,189 @@ __global__ __launch_bounds__(kThreads) void unb_sweep_kernel(UnrolledArgs a, int
       __syncthreads();
     }
   }
-  if (MODE == kTape) return;
   float* dst = REV ? xg : part_of<float>(a, inst, a.off_cst);
   for (int e = tid; e < T * kSerial; e += kThreads)
     if ((e & 3) < nu) dst[(size_t)(e >> 2) * KP + k0 + (e & 3)] = coef[e];
+}
+
+// The taped passes [p0, p1) of one instance and one group of at most two
+// users, from checkpoint p0 / E: x and h of the window members of every step.
+// The recursion is the forward sweep's, bit for bit.  The sigma sums need its
+// coefficients but it does not need them: a second wave per user takes them a
+// block behind, from the x it left in LDS, so that neither waits for the
+// other inside a block and no wave holds both matrices (one wave for both
+// steps: 28700 cycles a block of W = 32, ten registers spilled).  A pass has
+// one iteration more than blocks: the helper waves prepare K's block i and
+// H's block i - 1 for iteration i.
+template <int NRW>
+__global__ __launch_bounds__(kThreads) void unb_tape_kernel(UnrolledArgs a, int p0, int p1, int groups, int ku) {
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  const int inst = (int)(blockIdx.x / (8 * groups)) * 8 + (blockIdx.x & 7);
+  const int k0 = (int)((blockIdx.x >> 3) % groups) * ku;
+  if (inst >= a.n) return;
+  const int nu = a.K - k0 < ku ? a.K - k0 : ku;
+  const int T = a.T, TP = a.TP, W = a.W, K = a.K, KP = a.KP, NB = TP / kBlk;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int il = lane & 31;
+  const bool upper = lane >= 32;
+  const float* Km = part_of<float>(a, inst, a.off_G);
+  const float* Hm = part_of<float>(a, inst, a.off_D);
+  const float* kd = part_of<float>(a, inst, a.off_kd);
+  const float* img = part_of<float>(a, inst, a.off_img);
+  const float* sym = a.sym_pilot + (size_t)inst * a.P * K * 2;
+  const SweepLds L = sweep_lds(kTape, TP);
+  float* const coef = lds + L.coef;
+  float* const image = lds + L.image;
+  float* const part = lds + L.part;
+  float* const stage = lds + L.stage;
+  float* const ikn = lds + L.ikn;
+  float* const om = lds + L.om;
+  float* const qs = lds + L.qs;
+  const float eps = a.theta[1], mu = a.theta[2];
+  if (tid < 64) {
+    om[tid] = tid < W ? a.theta[3 + tid] : 0.0f;
+    float z = 0.0f;                         // qs[l] = mu / (omega_0 + .. + omega_{l-1})
+    for (int s = 0; s < tid; ++s) z += s < W ? a.theta[3 + s] : 0.0f;
+    qs[tid] = tid > 0 ? mu / z : 0.0f;
+  }
+  const float* src = p0 == 0 ? nullptr : part_of<float>(a, inst, a.off_ck) + (size_t)(p0 / a.E) * T * KP;
+  for (int e = tid; e < 2 * kImage; e += kThreads) image[e] = 0.0f;
+  for (int e = tid; e < TP * kSerial; e += kThreads) {
+    const int d = e >> 2, u = e & 3;
+    coef[e] = src && d < T && u < nu ? src[(size_t)d * KP + k0 + u] : 0.0f;
+  }
+  __syncthreads();
+  const float qsW = qs[W];
+  const size_t ts = (size_t)K * W;
+  // x of block q's steps and user u, [step][kTapeUsers][64]
+  auto xs_of = [&](int q, int u) { return lds + L.xs + ((q & 1) * kBlk * kTapeUsers + u) * 64; };
+  auto steps_in = [&](int q, int row) {     // of block q's 16-step rows
+    const int rem = T - kBlk * q - 16 * row;
+    return rem < 0 ? 0 : rem < 16 ? rem : 16;
+  };
+
+  if (wave < kTapeUsers) {
+    const int u = wave;
+    const bool active = u < nu;
+    if (active) __builtin_amdgcn_s_setprio(3);
+    float kreg[64];
+    Lane s{};
+    for (int p = p0; p < p1; ++p) {
+      s = Lane{};
+      s.d = -1;
+      for (int i = 0; i <= NB; ++i) {
+        __syncthreads();
+        if (active && i < NB) {
+          const float f = pending_sum(image + kMatrixImage, s.C, lane);
+          float sum = 0.0f;
+#pragma unroll
+          for (int w = 0; w < kHelpers; ++w) sum += part[(w * kBlk + il) * kSerial + u];
+          const float e = sum + f, b = stage[il * kSerial + u], ik = ikn[(i & 1) * kBlk + il];
+          if (!upper && s.d >= 0) coef[s.d * kSerial + u] += s.C;
+          // (swaps outside the selects: they need every lane)
+          const int du = __float_as_int(upper_half(__int_as_float(s.d)));
+          const float eu = upper_half(s.e), Cu = upper_half(s.C), iu = upper_half(s.ikn), bu = upper_half(s.b);
+          s.e = upper ? e : eu;
+          s.C = upper ? 0.0f : Cu;
+          s.ikn = upper ? ik : iu;
+          s.b = upper ? b : bu;
+          s.d = upper ? kBlk * i + il : du;
+          load_image<64>(image, lane, kreg);
+        } else if (active && s.d >= 0) {
+          coef[s.d * kSerial + u] += s.C;   // the pass ends: what is pending goes into the expansion
+        }
+        __syncthreads();
+        if (active && i < NB) {
+          float* const xs = xs_of(i, u);
+          constexpr int XS = kTapeUsers * 64;
+          sweep_row<kTape, NRW, 2>(s, kreg, kBlk * i, steps_in(i, 0), W, eps, qsW, om, qs, xs, XS, nullptr, 0, lane);
+          sweep_row<kTape, NRW, 3>(s, kreg, kBlk * i + 16, steps_in(i, 1), W, eps, qsW, om, qs, xs + 16 * XS, XS,
+                                   nullptr, 0, lane);
+        }
+      }
+    }
+  } else if (wave < kSerial) {
+    const int u = wave - kTapeUsers;
+    const bool active = u < nu;
+    const int k = k0 + (active ? u : 0);
+    if (active) __builtin_amdgcn_s_setprio(3);
+    float hreg[64];
+    for (int p = p0; p < p1; ++p) {
+      const size_t at = ((size_t)(p - p0) * T * K + k) * W;
+      float* const tx = part_of<float>(a, inst, a.off_tx) + at;
+      float* const th = part_of<float>(a, inst, a.off_th) + at;
+      SigmaLane s{};
+      for (int i = 0; i <= NB; ++i) {
+        const int q = i - 1;                // block stepped through
+        __syncthreads();
+        if (active && q >= 0) {
+          // the expansion holds the block that left before q came in, so of
+          // the lanes only the upper half is pending
+          const float f = pending_sum(image + kImage + kMatrixImage, upper ? s.C : 0.0f, lane);
+          float sum = 0.0f;
+#pragma unroll
+          for (int w = 0; w < kHelpers; ++w) sum += part[kPartFloats + (w * kBlk + il) * kSerial + u];
+          const float h = sum + f, ik = ikn[(q & 1) * kBlk + il];
+          const float hu = upper_half(s.h), Cu = upper_half(s.C), iu = upper_half(s.ikn);
+          s.h = upper ? h : hu;
+          s.C = upper ? 0.0f : Cu;
+          s.ikn = upper ? ik : iu;
+          load_image<64>(image + kImage, lane, hreg);
+        }
+        __syncthreads();
+        if (active && q >= 0) {
+          const float* const xs = xs_of(q, u);
+          sigma_row<NRW, 2>(s, hreg, kBlk * q, steps_in(q, 0), W, eps, qsW, om, qs, xs, tx, th, ts, lane);
+          sigma_row<NRW, 3>(s, hreg, kBlk * q + 16, steps_in(q, 1), W, eps, qsW, om, qs, xs + 16 * kTapeUsers * 64,
+                            tx, th, ts, lane);
+        }
+      }
+    }
+  } else {
+    const int ht = tid - 64 * kSerial, hw = wave - kSerial;
+    StripRound ahead;
+    auto begin = [&](const float* m, int q) { strip_begin(ahead, m + (size_t)q * TP * kBlk, 0, TP, hw, kHelpers, lane); };
+    auto c4 = [&](int d) { return coef[d * kSerial + lane]; };
+    auto sums = [&](const float* m, int q, BlockSums& s) {
+#pragma unroll
+      for (int v = 0; v < 8; ++v) s.v[v] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+      block_accumulate(s, ahead, m + (size_t)q * TP * kBlk, c4, true, 0, TP, hw, kHelpers, lane);
+    };
+    auto prepare = [&](int i) {
+      BlockSums s;
+      if (i < NB) {
+        lds_copy(img + (size_t)(i + 1) * kImage, image, kImage, hw, kHelpers, lane);
+        // targets and diagonal: read here, stored after the sums, so that
+        // nothing waits for them
+        const int n = kBlk * i + ((ht >> 2) & 31), nc = n < T ? n : 0, uu = ht & 3, uc = uu < nu ? uu : 0;
+        const float tv = sym[((size_t)(nc >> 1) * K + k0 + uc) * 2 + (nc & 1)];
+        const float kj = kd[kBlk * i + (ht & 31)];
+        sums(Km, i, s);
+        if (i > 0) begin(Hm, i - 1);
+        block_store(s, part, hw, lane);
+        if (ht < kBlk * kSerial) stage[ht] = n < T && uu < nu ? tv : 0.0f;
+        if (ht < kBlk) ikn[(i & 1) * kBlk + ht] = kj > 0.0f ? -1.0f / kj : 0.0f;
+      } else {
+        begin(Hm, i - 1);
+      }
+      if (i > 0) {
+        lds_copy(img + (size_t)(NB + 1 + i) * kImage, image + kImage, kImage, hw, kHelpers, lane);
+        sums(Hm, i - 1, s);
+        block_store(s, part + kPartFloats, hw, lane);
+      }
+      lds_copy_wait();
+      if (i + 1 != NB) begin(Km, i < NB ? i + 1 : 0);
+    };
+    begin(Km, 0);
+    prepare(0);
+    for (int p = p0; p < p1; ++p)
+      for (int i = 0; i <= NB; ++i) {
+        __syncthreads();
+        __syncthreads();
+        if (i < NB) prepare(i + 1);
+        else if (p + 1 < p1) prepare(0);
+      }
+  }
 }
 
 // The filter for the validation kernels: w = wL sum_d C_d r_d (workgroup k),
@@ -596,12 +793,15 @@ __global__ __launch_bounds__(256) void unb_grad_sum_kernel(UnrolledArgs a, float
 
 template <int MODE, int NRW>
 hipError_t launch_sweep_w(const UnrolledArgs& a, int p0, int p1, hipStream_t s) {
-  auto kern = unb_sweep_kernel<MODE, NRW>;
+  void (*kern)(UnrolledArgs, int, int, int, int);
+  if constexpr (MODE == kTape) kern = unb_tape_kernel<NRW>;
+  else kern = unb_sweep_kernel<MODE, NRW>;
   const size_t bytes = sweep_lds(MODE, a.TP).total * sizeof(float);
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   if (e != hipSuccess) return e;
-  const int groups = (a.K + kSerial - 1) / kSerial, ku = (a.K + groups - 1) / groups;
+  const int most = MODE == kTape ? kTapeUsers : kSerial;
+  const int groups = (a.K + most - 1) / most, ku = (a.K + groups - 1) / groups;
   hipLaunchKernelGGL(kern, dim3((a.n + 7) / 8 * 8 * groups), dim3(kThreads), bytes, s, a, p0, p1,
                      groups, ku);
   return hipGetLastError();
