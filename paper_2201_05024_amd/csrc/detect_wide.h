@@ -134,17 +134,72 @@ __device__ __forceinline__ floatx4 mfma(const half8& a, const half8& b, const fl
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
 
+// A stage as one wave's operands, read from the packed model without LDS.
+template <int M2P>
+struct StageRegs {
+  static constexpr int NB = Geo<M2P>::NB;
+  half8 dh[2][2][NB], dl[2][2][NB];          // entries: [32-entry block][row tile][component block]
+  half8 ah[2], al[2];
+  floatx4 n[2][2];
+  __device__ __forceinline__ void load(const unsigned char* packed, int s, int lane) {
+    using G = Geo<M2P>;
+    typedef __attribute__((address_space(1))) const unsigned char gbyte;
+    typedef __attribute__((address_space(1))) const half8 ghalf8;
+    typedef __attribute__((address_space(1))) const floatx4 gfloatx4;
+    gbyte* const st = (gbyte*)(packed + kHeader + G::W_BYTES + (size_t)s * G::STAGE_BYTES);
+    gbyte* const at = st + 16 * lane;
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk) {
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+        for (int jb = 0; jb < NB; ++jb) {
+          gbyte* const fr = at + (((blk * 2 + rt) * NB + jb) * 2) * 1024;
+          dh[blk][rt][jb] = *(ghalf8*)fr;
+          dl[blk][rt][jb] = *(ghalf8*)(fr + 1024);
+        }
+      ah[blk] = *(ghalf8*)(at + G::D_BYTES + blk * 2048);
+      al[blk] = *(ghalf8*)(at + G::D_BYTES + blk * 2048 + 1024);
+      gbyte* const nb = st + G::D_BYTES + G::A_BYTES + blk * 128 + 32 * (lane >> 4);
+      n[blk][0] = *(gfloatx4*)nb;
+      n[blk][1] = *(gfloatx4*)(nb + 16);
+    }
+  }
+};
+
+// FP16 hi and lo parts of a lane's eight kernel values.
+__device__ __forceinline__ void split_kappa(const float (&kap)[8], half8& kh, half8& kl) {
+#pragma unroll
+  for (int i = 0; i < 8; i += 2) {
+    const float2v kv = {kap[i], kap[i + 1]};
+    const half2v hv = __builtin_convertvector(kv, half2v);
+    const float2v rv = {kap[i] - (float)hv[0], kap[i + 1] - (float)hv[1]};
+    const half2v lv = __builtin_convertvector(rv, half2v);
+    kh[i] = hv[0];
+    kh[i + 1] = hv[1];
+    kl[i] = lv[0];
+    kl[i + 1] = lv[1];
+  }
+}
+
 // Detection of work item `item` (received vectors item * kVecPerItem / 2 ..)
 // by the whole workgroup.  A is DetectArgs or DetJob (same field names);
 // buf0 and buf1 are two distinct LDS arrays of Geo<M2P>::STAGE_BYTES bytes
 // each (16-byte aligned), the double buffer of dictionary stages, werr 16
 // counters.  A workgroup may run items back to back on the same LDS when a
 // barrier separates them.
-template <int M2P, class A>
+//
+// NW = 1: one wave and one tile of 16 real vectors (8 received ones) a
+// workgroup, for calls too small to fill the chip otherwise.  It reads the
+// stages into registers, the next one's while it works on this one (no LDS
+// buffers, no barriers), and takes a stage's four chains of distance products
+// in turn, as no other wave of its SIMD covers their latency.  The sums of a
+// vector are in the same order: the outputs are the same bits.
+template <int M2P, int NW = kWaves, class A>
 __device__ __forceinline__ void detect_wide_tile(const A& a, const unsigned char* packed, int item,
                                                  unsigned char* buf0, unsigned char* buf1, unsigned int* werr) {
   using G = Geo<M2P>;
-  constexpr int NB = G::NB, NS = kNS;
+  constexpr int NB = G::NB, NS = NW == 1 ? 1 : kNS;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15, g = lane >> 4;
@@ -166,7 +221,7 @@ __device__ __forceinline__ void detect_wide_tile(const A& a, const unsigned char
   bool bad = false;                        // a non-finite input component or output
 #pragma unroll
   for (int t = 0; t < NS; ++t) {
-    const int v = ((item * kWaves + wave) * NS + t) * 16 + col;
+    const int v = ((item * NW + wave) * NS + t) * 16 + col;
     const int smp = v >> 1, part = v & 1;
     const bool valid = smp < a.S;
     const float* x = a.rx + (size_t)(valid ? smp : 0) * M2;
@@ -214,6 +269,44 @@ __device__ __forceinline__ void detect_wide_tile(const A& a, const unsigned char
   }
   const float mc2 = uniform_f(-a.c2);
   const int nst = (D + kStage - 1) / kStage;
+  if constexpr (NW == 1) {
+    auto work = [&](const StageRegs<M2P>& r) {
+      floatx4 acc1[2][2];
+#pragma unroll
+      for (int jb = 0; jb < NB; ++jb)
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+#pragma unroll
+          for (int blk = 0; blk < 2; ++blk)
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt)
+              acc1[blk][rt] = mfma(p == 1 ? r.dl[blk][rt][jb] : r.dh[blk][rt][jb], p == 2 ? xl[0][jb] : xh[0][jb],
+                                   jb == 0 && p == 0 ? cinit[0] : acc1[blk][rt]);
+#pragma unroll
+      for (int blk = 0; blk < 2; ++blk) {
+        float kap[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          kap[i] = __builtin_amdgcn_exp2f(fmaf(acc1[blk][i >> 2][i & 3], desc[0], mc2 * r.n[blk][i >> 2][i & 3]));
+        half8 kh, kl;
+        split_kappa(kap, kh, kl);
+        acc2[0] = mfma(r.ah[blk], kh, acc2[0]);
+        acc2x[0] = mfma(r.ah[blk], kl, acc2x[0]);
+        acc2x[0] = mfma(r.al[blk], kh, acc2x[0]);
+      }
+    };
+    if (nst > 0) {
+      StageRegs<M2P> r0, r1;
+      r0.load(packed, 0, lane);
+      for (int c = 0; c < nst; c += 2) {
+        r1.load(packed, c + 1 < nst ? c + 1 : c, lane);
+        work(r0);
+        if (c + 1 >= nst) break;
+        r0.load(packed, c + 2 < nst ? c + 2 : c, lane);
+        work(r1);
+      }
+    }
+  } else {
   if (nst > 0) stage_async<M2P>(packed, 0, buf0, wave, lane);
   stage_wait();
   __syncthreads();
@@ -284,17 +377,7 @@ __device__ __forceinline__ void detect_wide_tile(const A& a, const unsigned char
         for (int i = 0; i < 8; ++i)
           kap[i] = __builtin_amdgcn_exp2f(fmaf(acc1[t][i >> 2][i & 3], desc[t], cn[i]));
         half8 kh, kl;
-#pragma unroll
-        for (int i = 0; i < 8; i += 2) {
-          const float2v kv = {kap[i], kap[i + 1]};
-          const half2v hv = __builtin_convertvector(kv, half2v);
-          const float2v rv = {kap[i] - (float)hv[0], kap[i + 1] - (float)hv[1]};
-          const half2v lv = __builtin_convertvector(rv, half2v);
-          kh[i] = hv[0];
-          kh[i + 1] = hv[1];
-          kl[i] = lv[0];
-          kl[i + 1] = lv[1];
-        }
+        split_kappa(kap, kh, kl);
         acc2[t] = mfma(ah, kh, acc2[t]);
         acc2x[t] = mfma(ah, kl, acc2x[t]);
         acc2x[t] = mfma(al, kh, acc2x[t]);
@@ -306,6 +389,7 @@ __device__ __forceinline__ void detect_wide_tile(const A& a, const unsigned char
   for (int c = 0; c < nst; c += 2) {
     stage(buf0, buf1, c);
     if (c + 1 < nst) stage(buf1, buf0, c + 1);
+  }
   }
 
   // ---- linear part (third contraction), outputs, decisions
@@ -334,7 +418,7 @@ __device__ __forceinline__ void detect_wide_tile(const A& a, const unsigned char
       accl = mfma(wh[jb], xl[t][jb], accl);
     }
     const float sl = ldexpf(1.0f, -(e_w + ex[t]));
-    const int v = ((item * kWaves + wave) * NS + t) * 16 + col;
+    const int v = ((item * NW + wave) * NS + t) * 16 + col;
     const int smp = v >> 1, part = v & 1;
     const bool valid = smp < a.S;
     float vals[4];

@@ -111,7 +111,28 @@ __global__ __launch_bounds__(kThreads, batch_waves_per_simd<M2P>()) void detect_
 
 }  // namespace
 
+template <int M2P>
+__global__ __launch_bounds__(64, 1) void detect_wide_small_kernel(DetectArgs a) {
+  __shared__ unsigned int werr[16];
+  detect_wide_tile<M2P, 1>(a, a.packed, blockIdx.x, nullptr, nullptr, werr);
+}
+
 hipError_t launch_detect(const DetectArgs& a, hipStream_t stream) {
+  // Up to six tiles of 16 vectors a CU, one wave a tile: the kernel for large
+  // calls has 16 tiles a workgroup, so few of the CUs run, two waves a SIMD
+  // with two tiles each.  1370 entries of 32 components, 480 tiles: 36.9 ->
+  // 17.3 us.  Past that the dictionary read per tile costs more than the
+  // empty CUs: at 6 a CU 37.9 -> 26.0 (200 to 4000 entries of 32 to 128
+  // components: 3 to 38 % less), at 12 a CU 40.6 -> 43.5 (up to 48 % more).
+  const int tiles = (int)(((long long)2 * a.S + 15) / 16);
+  if (tiles <= 6 * device_cus()) {
+    switch (m2p_wide(a.M2)) {
+      case 32: hipLaunchKernelGGL(detect_wide_small_kernel<32>, dim3(tiles), dim3(64), 0, stream, a); break;
+      case 64: hipLaunchKernelGGL(detect_wide_small_kernel<64>, dim3(tiles), dim3(64), 0, stream, a); break;
+      default: hipLaunchKernelGGL(detect_wide_small_kernel<128>, dim3(tiles), dim3(64), 0, stream, a); break;
+    }
+    return hipGetLastError();
+  }
   const int blocks = (int)(((long long)2 * a.S + kVecPerItem - 1) / kVecPerItem);
   switch (m2p_wide(a.M2)) {
     case 32: hipLaunchKernelGGL(detect_wide_kernel<32>, dim3(blocks), dim3(kThreads), 0, stream, a); break;
