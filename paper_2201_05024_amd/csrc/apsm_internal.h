@@ -222,7 +222,9 @@ enum { kDetectF16 = 0, kDetectWide = 1 };
 bool detect_dual(int M2, int K);
 int detect_default_kernel(int M2, int K);
 size_t wide_offset(int M2, int K, int cap);
-hipError_t launch_detect_with(const DetectArgs& a, int kernel, hipStream_t stream);
+// few: a call of few vectors may take the two-contraction kernel's form for
+// them (not where a batch's kernel, which has none, is timed).
+hipError_t launch_detect_with(const DetectArgs& a, int kernel, hipStream_t stream, bool few = true);
 int wide_detect_variant(int M2);
 int wide_detect_items(int S);
 hipError_t launch_detect_wide_batch(const DetJob* jobs, const int2* items, int n_items, unsigned int* ctr, int grid,

@@ -545,7 +545,7 @@ int apsm_batch_tune(apsm_batch_t* b, void* stream) {
                                      it.err_count);
     float t[2] = {0.0f, 0.0f};
     for (int k = 0; k < 2 && rc == APSM_OK; ++k)
-      time_ms([&] { return hip_status(launch_detect_with(a, k == 0 ? kDetectF16 : kDetectWide, s)); }, &t[k]);
+      time_ms([&] { return hip_status(launch_detect_with(a, k == 0 ? kDetectF16 : kDetectWide, s, false)); }, &t[k]);
     if (rc == APSM_OK) tune_set_kernel(it.model.M2, it.model.K, t[0] < t[1] ? kDetectF16 : kDetectWide);
   }
   if (rc == APSM_OK && !classes.empty()) {

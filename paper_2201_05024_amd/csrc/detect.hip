@@ -26,7 +26,7 @@ size_t wide_offset(int M2, int K, int cap) {
 
 size_t packed_model_bytes(int M2, int K, int cap) { return wide_offset(M2, K, cap) + wide::packed_bytes(M2, cap); }
 
-hipError_t launch_detect_with(const DetectArgs& a, int kernel, hipStream_t stream) {
+hipError_t launch_detect_with(const DetectArgs& a, int kernel, hipStream_t stream, bool few) {
   if (a.M2 > APSM_MAX_M2) return hipErrorInvalidValue;
   if (kernel == kDetectF16 && f16::supported(a.M2, a.K)) {
     const int M2P = f16::m2p_f16(a.M2);
@@ -36,7 +36,7 @@ hipError_t launch_detect_with(const DetectArgs& a, int kernel, hipStream_t strea
   }
   DetectArgs b = a;
   b.packed = a.packed + wide_offset(a.M2, a.K, a.cap);
-  return wide::launch_detect(b, stream);
+  return wide::launch_detect(b, few, stream);
 }
 
 hipError_t launch_detect(const DetectArgs& a, hipStream_t stream) {

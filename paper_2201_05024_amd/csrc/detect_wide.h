@@ -501,7 +501,8 @@ __device__ __forceinline__ void detect_wide_tile(const A& a, const unsigned char
   }
 }
 
-hipError_t launch_detect(const DetectArgs& a, hipStream_t stream);
+// few: small calls may take the one-wave form.
+hipError_t launch_detect(const DetectArgs& a, bool few, hipStream_t stream);
 
 }  // namespace wide
 }  // namespace apsm

@@ -117,7 +117,7 @@ __global__ __launch_bounds__(64, 1) void detect_wide_small_kernel(DetectArgs a) 
   detect_wide_tile<M2P, 1>(a, a.packed, blockIdx.x, nullptr, nullptr, werr);
 }
 
-hipError_t launch_detect(const DetectArgs& a, hipStream_t stream) {
+hipError_t launch_detect(const DetectArgs& a, bool few, hipStream_t stream) {
   // Up to six tiles of 16 vectors a CU, one wave a tile: the kernel for large
   // calls has 16 tiles a workgroup, so few of the CUs run, two waves a SIMD
   // with two tiles each.  1370 entries of 32 components, 480 tiles: 36.9 ->
@@ -125,7 +125,7 @@ hipError_t launch_detect(const DetectArgs& a, hipStream_t stream) {
   // empty CUs: at 6 a CU 37.9 -> 26.0 (200 to 4000 entries of 32 to 128
   // components: 3 to 38 % less), at 12 a CU 40.6 -> 43.5 (up to 48 % more).
   const int tiles = (int)(((long long)2 * a.S + 15) / 16);
-  if (tiles <= 6 * device_cus()) {
+  if (few && tiles <= 6 * device_cus()) {
     switch (m2p_wide(a.M2)) {
       case 32: hipLaunchKernelGGL(detect_wide_small_kernel<32>, dim3(tiles), dim3(64), 0, stream, a); break;
       case 64: hipLaunchKernelGGL(detect_wide_small_kernel<64>, dim3(tiles), dim3(64), 0, stream, a); break;

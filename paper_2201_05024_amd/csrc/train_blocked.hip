@@ -103,13 +103,15 @@ __device__ __forceinline__ void stage_vectors(const Source& src, Idx&& idx, floa
     }
   }
   __syncthreads();
-  if (threadIdx.x < kTile) {
-    const float* x = xs + threadIdx.x * STR;
-    float n4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  // four threads a vector, each every fourth component
+  static_assert(kPrepThreads == 4 * kTile, "a thread per quarter of a vector");
+  const float* x = xs + (threadIdx.x >> 2) * STR + (threadIdx.x & 3);
+  float n = 0.0f;
 #pragma unroll
-    for (int m = 0; m < M2R; ++m) n4[m & 3] = fmaf(x[m], x[m], n4[m & 3]);
-    xn[threadIdx.x] = (n4[0] + n4[1]) + (n4[2] + n4[3]);
-  }
+  for (int m = 0; m < M2R; m += 4) n = fmaf(x[m], x[m], n);
+  n += __shfl_xor(n, 1);
+  n += __shfl_xor(n, 2);
+  if ((threadIdx.x & 3) == 0) xn[threadIdx.x >> 2] = n;
   __syncthreads();
 }
 
@@ -168,6 +170,13 @@ __device__ __forceinline__ void strip_unit(const BlockJob& j, const Source& src,
     }
 }
 
+// LDS of an image unit before the norms: the vectors, then the pairs' values.
+template <int M2R>
+__host__ __device__ constexpr int image_floats() {
+  constexpr int pairs = 32 * 97 + 32 * 33 + 32 * 65, vectors = kTile * (M2R + 4);
+  return vectors > pairs ? vectors : pairs;
+}
+
 // Image unit of block q: the 24 tiles of 16 x 16 pairs it needs among the
 // samples of blocks q - 2, q - 1, q and the entries evicted by its steps,
 // three per wave, then the image gathered from them.
@@ -175,19 +184,21 @@ template <int M2R>
 __device__ __forceinline__ void image_unit(const BlockJob& j, const TrainCommon& cm, const Source& src, int q,
                                            float* lds) {
   constexpr int Q = M2R / 4, STR = M2R + 4;
+  // the pairs' values take the vectors' place once every wave has its products
   float* xs = lds;
-  float* xn = xs + kTile * STR;
-  float* k1 = xn + kTile;                  // [32][97] members of q against blocks q - 2, q - 1, q
+  float* xn = lds + image_floats<M2R>();
+  float* k1 = lds;                         // [32][97] members of q against blocks q - 2, q - 1, q
   float* k2 = k1 + 32 * 97;                // [32][33] block q - 1 against itself
   float* ev = k2 + 32 * 33;                // [32][65] evicted entries against the lanes' samples
   const int n0 = src.n0, cap = src.cap, base = kBlk * (q - 2);
   stage_vectors<M2R>(src, [&](int r) { return r < 96 ? base + r : kBlk * q + (r - 96) - cap; }, xs, xn);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, c = lane & 15, g = lane >> 4;
+  auto row_tile = [](int t) { return t < 12 ? 4 + t / 6 : t < 16 ? 2 + ((t - 12) >> 1) : 6 + ((t - 16) >> 2); };
+  auto col_tile = [](int t) { return t < 12 ? t % 6 : t < 16 ? 2 + (t & 1) : 2 + (t & 3); };
+  floatx4 accs[3];
 #pragma unroll
   for (int u = 0; u < 3; ++u) {
-    const int t = 3 * w + u;
-    const int rt = t < 12 ? 4 + t / 6 : t < 16 ? 2 + ((t - 12) >> 1) : 6 + ((t - 16) >> 2);
-    const int ct = t < 12 ? t % 6 : t < 16 ? 2 + (t & 1) : 2 + (t & 3);
+    const int rt = row_tile(3 * w + u), ct = col_tile(3 * w + u);
     floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int s0 = 0; s0 < Q; s0 += 4) {
@@ -196,6 +207,13 @@ __device__ __forceinline__ void image_unit(const BlockJob& j, const TrainCommon&
 #pragma unroll
       for (int x = 0; x < 4; ++x) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[x], b4[x], acc, 0, 0, 0);
     }
+    accs[u] = acc;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 3; ++u) {
+    const int t = 3 * w + u, rt = row_tile(t), ct = col_tile(t);
+    const floatx4 acc = accs[u];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int ra = 16 * rt + 4 * g + i, rb = 16 * ct + c;
@@ -253,7 +271,7 @@ __device__ __forceinline__ void image_unit(const BlockJob& j, const TrainCommon&
 
 template <int M2R>
 __host__ __device__ constexpr int prep_floats() {
-  return kTile * (M2R + 4) + kTile + 32 * 97 + 32 * 33 + 32 * 65;
+  return image_floats<M2R>() + kTile;
 }
 __host__ __device__ inline int m2r_of(int M2) { return M2 <= 16 ? 16 : M2 <= 32 ? 32 : M2 <= 64 ? 64 : 128; }
 inline int prep_floats_of(int M2) {
