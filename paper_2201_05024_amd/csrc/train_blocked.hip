@@ -383,27 +383,27 @@ struct Lane {
 
 // The steps whose newest members lie in row A of the wave, t0 the place of
 // the first in its block, n0 its number: 16, or the cnt of the sequence's
-// end.  FULL: all 16, with the window full.  GEN: any set weights, relaxation
-// and set kinds; else position weights and hyperslabs.
-// Bound by the issue of one wave (5 cycles an instruction): with a window of
-// 17 to 32 samples 32 FMAs of the matrix-vector product and about 16 more, 3
-// with evictions.  Unrolled, as the product's registers depend on the place.
-template <bool GEN, int NRW, int A, bool FULL, bool EV>
+// end.  FULL: all 16, with the window full.  Position weights and hyperslabs.
+// Bound by the issue of one wave (about 6 cycles an instruction): with a
+// window of 17 to 32 samples 32 FMAs of the matrix-vector product and 14 more,
+// 3 with evictions; 290 cycles a step at W = 32 (375 with three rows of
+// products).  Unrolled, as the product's registers depend on the place.
+template <int NRW, int A, bool FULL, bool EV>
 __device__ __forceinline__ void steps(Lane& s, const float* kreg, int n0, int t0, int cnt, const TrainCommon& cm,
-                                      bool typed, float qsW, const float* om, const float* qs, const float* ev,
-                                      float aev, int lane) {
+                                      float qsW, const float* om, const float* qs, const float* ev, float aev,
+                                      int lane) {
 #pragma clang fp contract(off)
   const int W = cm.W;
   float w = om[(16 * A - lane) & 63];       // weight of the lane's member (0 outside the window)
   const float iq = s.ikn * qsW;
-  const float inv_mu = 1.0f / cm.mu;
   const float* e0 = ev + t0 * 64 + lane;
   float kv = EV ? e0[0] : 0.0f;
 #pragma unroll
   for (int it = 0; it < 16; ++it) {
     if (!FULL && it >= cnt) continue;
     const int n = n0 + it;
-    const float wc = w;
+    // weight, mu / (omega_0 + .. + omega_{L-1}), -1 / kappa
+    const float t = FULL || n + 1 >= W ? w * iq : w * (s.ikn * qs[n + 1]);
     w = from_below(w);                      // every member is one step older
     if constexpr (EV) {
       // the members in the window lose the entry that leaves; the next
@@ -412,61 +412,102 @@ __device__ __forceinline__ void steps(Lane& s, const float* kreg, int n0, int t0
       s.x = fmaf(-a, kv, s.x);
       kv = e0[(it + 1) * 64];
     }
-    float c;
-    if constexpr (!GEN) {
-      // weight, mu / (omega_0 + .. + omega_{L-1}), -1 / kappa
-      const float t = FULL || n + 1 >= W ? wc * iq : wc * (s.ikn * qs[n + 1]);
-      c = slab_residual_pos(s.x, cm.eps) * t;
-      s.C += c;
-      s.x += window_sum<A, NRW>(window_gather<A, NRW>(c, it, lane), kreg, it);
-    } else {
-      const float x = s.x;
-      float res = slab_residual_pos(x, cm.eps);
-      if (typed) {
-        res = s.kind == kSetPlane   ? x
-              : s.kind == kSetUpper ? fmaxf(x - cm.eps, 0.0f)
-              : s.kind == kSetLower ? fminf(x + cm.eps, 0.0f)
-                                    : res;
-      }
-      const float beta = res * s.ikn;
-      float u;                              // q_j beta_j
-      if (cm.weights != kWeightsPosition) {
-        // proportional to the distance, or uniform over the members violated
-        // by more than 1e-5 (a member that its own projection left on the
-        // boundary stays out, whatever the rounding)
-        const float dist = cm.weights == kWeightsActive ? (fabsf(res) > 1e-5f ? 1.0f : 0.0f) : fabsf(res);
-        const float v = wc > 0.0f && s.d >= 0 ? dist : 0.0f;
-        const float tot = wave_sum(v);
-        u = tot > 0.0f ? v / tot * beta : 0.0f;
-      } else {
-        u = wc * (FULL || n + 1 >= W ? qsW : qs[n + 1]) * inv_mu * beta;
-      }
-      const float ku = window_sum<A, NRW>(window_gather<A, NRW>(u, it, lane), kreg, it);
-      float step = cm.mu;
-      if (cm.extrapolate) {
-        // M = sum_j q_j beta_j^2 K_jj / sum_jl u_j K_jl u_l (beta_j K_jj = -residual)
-        const float num = wave_sum(s.ikn != 0.0f ? -u * res : 0.0f);
-        const float den = wave_sum(u != 0.0f ? u * ku : 0.0f);
-        step = cm.mu * (den > 0.0f ? num / den : 1.0f);
-      }
-      s.C += step * u;
-      s.x += step * ku;
-    }
+    const float c = slab_residual_pos(s.x, cm.eps) * t;
+    s.C += c;
+    s.x += window_sum<A, NRW>(window_gather<A, NRW>(c, it, lane), kreg, it);
   }
+}
+
+// The same with any set weights, relaxation and set kinds, one loop per
+// choice that is alike for all steps (EV: entries leave; POS: position
+// weights; EX: extrapolated), no branch inside: about 110 instructions a step
+// of W = 20 with weights by violation and mixed kinds.  Not unrolled: 16 such
+// steps in one body, branches and all, were 29 KB of code a row and 1100
+// cycles a step.
+template <int NRW, int A, bool EV, bool POS, bool EX>
+__device__ __forceinline__ void general_loop(Lane& s, const float* kreg, int n0, int t0, int cnt,
+                                             const TrainCommon& cm, float qsW, const float* om, const float* qs,
+                                             const float* ev, float aev, int lane) {
+#pragma clang fp contract(off)
+  const int W = cm.W;
+  float wv = om[(16 * A - lane) & 63];
+  const float inv_mu = 1.0f / cm.mu;
+  const float* e0 = ev + t0 * 64 + lane;
+  float kv = EV ? e0[0] : 0.0f;
+  float qn = POS ? qs[min(n0 + 1, W)] : 0.0f;
+  const bool plane = s.kind == kSetPlane, above = s.kind != kSetLower, below = s.kind != kSetUpper;
+  const bool active = cm.weights == kWeightsActive, held = s.d >= 0;
+#pragma unroll 1
+  for (int it = 0; it < cnt; ++it) {
+    const float w = wv, q = qn;
+    wv = from_below(wv);
+    if constexpr (POS) qn = qs[min(n0 + it + 2, W)];
+    if constexpr (EV) {
+      const float a = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(aev), t0 + it));
+      s.x = fmaf(-a, kv, s.x);
+      kv = e0[(it + 1) * 64];
+    }
+    // residual to the member's set: hyperslab, its upper or lower side alone,
+    // or the plane (a NaN is no violation of a slab or a side)
+    const float x = s.x, over = fmaxf(x - cm.eps, 0.0f), under = fminf(x + cm.eps, 0.0f);
+    const float side = (above ? over : 0.0f) + (below ? under : 0.0f);
+    const float res = plane ? x : side;
+    const float beta = res * s.ikn;
+    float u;                                // q_j beta_j
+    if constexpr (!POS) {
+      // proportional to the distance, or uniform over the members violated
+      // by more than 1e-5 (a member that its own projection left on the
+      // boundary stays out, whatever the rounding)
+      const float dist = fabsf(res), flag = dist > 1e-5f ? 1.0f : 0.0f;
+      const float v = w > 0.0f && held ? (active ? flag : dist) : 0.0f;
+      const float tot = wave_sum(v), part = v / tot * beta;
+      u = tot > 0.0f ? part : 0.0f;
+    } else {
+      u = w * q * inv_mu * beta;
+    }
+    const float ku = window_sum_rows<A, NRW>(u, kreg);
+    float step = cm.mu;
+    if constexpr (EX) {
+      // M = sum_j q_j beta_j^2 K_jj / sum_jl u_j K_jl u_l (beta_j K_jj = -residual)
+      const float num = wave_sum(s.ikn != 0.0f ? -u * res : 0.0f);
+      const float den = wave_sum(u != 0.0f ? u * ku : 0.0f);
+      const float r = num / den;
+      step = cm.mu * (den > 0.0f ? r : 1.0f);
+    }
+    s.C += step * u;
+    s.x += step * ku;
+  }
+}
+template <int NRW, int A>
+__device__ __forceinline__ void general_steps(Lane& s, const float* kreg, int n0, int t0, int cnt,
+                                              const TrainCommon& cm, float qsW, const float* om, const float* qs,
+                                              bool evict, const float* ev, float aev, int lane) {
+#define APSM_GENERAL(EV, POS, EX) general_loop<NRW, A, EV, POS, EX>(s, kreg, n0, t0, cnt, cm, qsW, om, qs, ev, aev, lane)
+  const bool pos = cm.weights == kWeightsPosition, ex = cm.extrapolate != 0;
+  if (evict) {
+    if (pos) { if (ex) APSM_GENERAL(true, true, true); else APSM_GENERAL(true, true, false); }
+    else { if (ex) APSM_GENERAL(true, false, true); else APSM_GENERAL(true, false, false); }
+  } else {
+    if (pos) { if (ex) APSM_GENERAL(false, true, true); else APSM_GENERAL(false, true, false); }
+    else { if (ex) APSM_GENERAL(false, false, true); else APSM_GENERAL(false, false, false); }
+  }
+#undef APSM_GENERAL
 }
 
 template <bool GEN, int NRW, int A>
 __device__ __forceinline__ void train_row(Lane& s, const float* kreg, int n0, int t0, int cnt, const TrainCommon& cm,
-                                          bool typed, float qsW, const float* om, const float* qs, bool evict,
-                                          const float* ev, float aev, int lane) {
+                                          float qsW, const float* om, const float* qs, bool evict, const float* ev,
+                                          float aev, int lane) {
   if (cnt <= 0) return;
-  if (!GEN && cnt == 16 && n0 + 1 >= cm.W) {
-    if (evict) steps<GEN, NRW, A, true, true>(s, kreg, n0, t0, 16, cm, typed, qsW, om, qs, ev, aev, lane);
-    else steps<GEN, NRW, A, true, false>(s, kreg, n0, t0, 16, cm, typed, qsW, om, qs, ev, aev, lane);
+  if constexpr (GEN) {
+    general_steps<NRW, A>(s, kreg, n0, t0, cnt, cm, qsW, om, qs, evict, ev, aev, lane);
+  } else if (cnt == 16 && n0 + 1 >= cm.W) {
+    if (evict) steps<NRW, A, true, true>(s, kreg, n0, t0, 16, cm, qsW, om, qs, ev, aev, lane);
+    else steps<NRW, A, true, false>(s, kreg, n0, t0, 16, cm, qsW, om, qs, ev, aev, lane);
   } else if (evict) {
-    steps<GEN, NRW, A, false, true>(s, kreg, n0, t0, cnt, cm, typed, qsW, om, qs, ev, aev, lane);
+    steps<NRW, A, false, true>(s, kreg, n0, t0, cnt, cm, qsW, om, qs, ev, aev, lane);
   } else {
-    steps<GEN, NRW, A, false, false>(s, kreg, n0, t0, cnt, cm, typed, qsW, om, qs, ev, aev, lane);
+    steps<NRW, A, false, false>(s, kreg, n0, t0, cnt, cm, qsW, om, qs, ev, aev, lane);
   }
 }
 
@@ -750,9 +791,8 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
       if (active) {
         const int nb = kBlk * q, rem = T - nb;
         const float* ev = evict_lds + (q & 1) * kEviction;
-        train_row<GEN, NRW, 2>(s, kreg, nb, 0, rem < 16 ? rem : 16, cm, typed, qsW, om, qs, evict, ev, aev, lane);
-        train_row<GEN, NRW, 3>(s, kreg, nb + 16, 16, rem < 32 ? rem - 16 : 16, cm, typed, qsW, om, qs, evict, ev, aev,
-                               lane);
+        train_row<GEN, NRW, 2>(s, kreg, nb, 0, rem < 16 ? rem : 16, cm, qsW, om, qs, evict, ev, aev, lane);
+        train_row<GEN, NRW, 3>(s, kreg, nb + 16, 16, rem < 32 ? rem - 16 : 16, cm, qsW, om, qs, evict, ev, aev, lane);
         s.bad = fmaf(s.x, 0.0f, s.bad);     // a residual that was not finite leaves its prediction so
       }
     }

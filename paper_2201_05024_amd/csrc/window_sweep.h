@@ -134,6 +134,20 @@ __device__ __forceinline__ float window_sum(const WindowRows& w, const float* k,
   return e;
 }
 
+// The same sum whatever the place in row A, through whole rows: 16 FMAs more,
+// for steps that are not unrolled.
+template <int A, int NRW>
+__device__ __forceinline__ float window_sum_rows(float c, const float* k) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(c), __float_as_uint(c), false, false);
+  const auto p = __builtin_amdgcn_permlane32_swap(a[0], a[0], false, false);
+  const auto q = __builtin_amdgcn_permlane32_swap(a[1], a[1], false, false);
+  const float r[4] = {__uint_as_float(p[0]), __uint_as_float(q[0]), __uint_as_float(p[1]), __uint_as_float(q[1])};
+  constexpr int B = (A + 3) & 3, C = (A + 2) & 3;
+  float e = two_row_sum(r[A], r[B], k + 16 * A, k + 16 * B);
+  if constexpr (NRW != kOneRow) e += row_sum(r[C], k + 16 * C);
+  return e;
+}
+
 // x of the lane one below (lane 0: of lane 63), of the lane one above.
 __device__ __forceinline__ float from_below(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x13C, 0xF, 0xF, true));
