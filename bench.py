@@ -76,9 +76,9 @@ MEASURED_TRAFFIC = {
     # FETCH_SIZE + WRITE_SIZE of detect_wide_batch_kernel<128> per dispatch,
     # both x1.000 by the 256 MiB copy of the same runs
     # (profiles/detect_wide_large_array_counters.md)
-    "bytes": int((57266160.2 * 1.0 + 14680064.2 * 1.0) * 1024),
-    "sources": {"paper_2201_05024_amd/csrc/detect_wide.h": "c4466cec43db01aaded2f9d1e5d12b7c8ce86ff1",
-                "paper_2201_05024_amd/csrc/detect_wide.hip": "8ed459dc5ba8dc9f93072750609e6a1b67afc71f"},
+    "bytes": int((57790446.4 * 1.0 + 15728640.2 * 1.0) * 1024),
+    "sources": {"paper_2201_05024_amd/csrc/detect_wide.h": "c389ac1db2d982c0685199c2e700e30b89e60446",
+                "paper_2201_05024_amd/csrc/detect_wide.hip": "1fa21d1c5d93e52a0b61e6fd7b968546b2f1360d"},
 }
 
 
