@@ -88,6 +88,7 @@ struct BlockJob {
   int P, M2, Kt, cap, ku; // ku: users per workgroup
   int SW, qa, qb;
   int write_dict;         // the preparing launch writes the dictionary (not for a continued model)
+  int apart;              // the preparing launch leaves the model's arrays alone (launch_train_model_table)
   float c2;
 };
 constexpr int kMaxBlockJobs = 16;           // detectors per launch, in the kernel arguments
@@ -182,6 +183,9 @@ size_t train_prepare_lds(int M2);
 size_t train_sweep_lds(int M2);
 hipError_t launch_train_prepare_table(const BlockJob* jobs, const int2* items, int n, const TrainCommon& cm,
                                       size_t lds_bytes, hipStream_t stream);
+// Before the sweeps of jobs prepared apart (jobs[0..n), max_cap the largest
+// capacity): their dictionaries.
+hipError_t launch_train_model_table(const BlockJob* jobs, int n, int max_cap, hipStream_t stream);
 hipError_t launch_train_sweep_table(const BlockJob* jobs, const int2* items, int n, const TrainCommon& cm,
                                     size_t lds_bytes, hipStream_t stream);
 hipError_t launch_detect(const DetectArgs& a, hipStream_t stream);

@@ -34,6 +34,7 @@ struct apsm_batch {
   std::vector<size_t> block_off;              // byte offset of each job's workspace
   std::vector<int2> prep_items, sweep_items;  // (job, unit) and (job, first user; job < 0: empty place)
   size_t prep_lds = 0, sweep_lds = 0, block_bytes = 0;
+  int block_max_cap = 0;
   std::vector<apsm::TrainJob> rjobs;          // rows form; glag/kw set at bind
   std::vector<size_t> rows_off;               // float offset of each rows job's glag (kw follows)
   std::vector<int4> ritems;                   // (rows job, first step, first lag) per kernel-row tile
@@ -234,6 +235,8 @@ void plan(apsm_batch& b, const apsm_params_t* p) {
       j.w = it.model.w;
       j.state = it.model.state;
       j.c2 = kLog2e / (2.0f * it.sigma2);
+      j.apart = 1;                            // apsm_batch_kernel_rows writes the workspace and clears the flags
+      b.block_max_cap = std::max(b.block_max_cap, j.cap);
       const int q = (int)b.bjobs.size(), units = train_prepare_units(j);
       for (int u = 0; u < units; ++u) b.prep_items.push_back(make_int2(q, u));
       b.block_off.push_back(b.block_bytes);
@@ -466,8 +469,10 @@ int apsm_batch_train(const apsm_batch_t* b, void* stream) {
 int apsm_batch_train_prepared(const apsm_batch_t* b, void* stream) {
   if (!b || !b->ws) return APSM_ERR_INVALID_ARG;
   hipStream_t s = (hipStream_t)stream;
-  hipError_t e = launch_train_sweep_table(at<BlockJob>(b, b->off_bj), at<int2>(b, b->off_si),
-                                          (int)b->sweep_items.size(), b->cm, b->sweep_lds, s);
+  hipError_t e = launch_train_model_table(at<BlockJob>(b, b->off_bj), (int)b->bjobs.size(), b->block_max_cap, s);
+  if (e == hipSuccess)
+    e = launch_train_sweep_table(at<BlockJob>(b, b->off_bj), at<int2>(b, b->off_si), (int)b->sweep_items.size(), b->cm,
+                                 b->sweep_lds, s);
   if (e == hipSuccess)
     e = launch_train_rows(at<TrainJob>(b, b->off_rj), (int)b->rjobs.size(), b->cm, b->rows_lds, s);
   if (e == hipSuccess) e = launch_train_table(at<TrainJob>(b, b->off_t), (int)b->tjobs.size(), b->cm, b->train_lds, s);

@@ -14,14 +14,20 @@
 // evicted entry's term at its step; its coefficient is final and in alpha a
 // block ahead (capacity >= 96: it is of block q - 3 or older).
 //
-// Two launches.  train_prepare: everything that depends on the received
+// Two launches.  prepare_kernel: everything that depends on the received
 // vectors alone, data-parallel: the strips (kernel values of a block's
 // members against the entries, 128 x 128 pairs per workgroup on
 // v_mfma_f32_16x16x4_f32), the blocks' register images, eviction values and
-// diagonals, and the dictionary itself.  train_sweep: one workgroup per
+// diagonals, and the dictionary itself.  sweep_kernel: one workgroup per
 // detector and up to four users, one wave per user and eight helper waves.
 // Where the workspace does not hold all blocks, the pair of launches is
 // repeated over ranges of blocks, the lanes' state carried in the workspace.
+//
+// Bound by the recursion wave's instruction issue, and past about 2,000
+// entries by the helper waves' reading of the strips.  Step by step and so:
+// K=4 2M=16, 512 steps of W=16 808 -> 74 us; K=6 2M=32, 2,048 steps of W=32,
+// 1,024 entries 4.35 ms -> 323 us; K=16 2M=128, 4,096 steps, 2,048 entries
+// 102 ms -> 805 us.
 #include <algorithm>
 
 #include "apsm_internal.h"
@@ -63,7 +69,7 @@ __host__ __device__ inline Units units_of(const BlockJob& j) {
   u.images = j.qb - j.qa;
   u.groups = j.SW > 0 ? (u.images + 3) / 4 : 0;
   u.tiles = (j.SW + 96 + kTile - 1) / kTile;
-  u.dict = j.write_dict ? (j.cap + kDictSlots - 1) / kDictSlots : 0;
+  u.dict = j.write_dict && !j.apart ? (j.cap + kDictSlots - 1) / kDictSlots : 0;
   return u;
 }
 
@@ -119,6 +125,10 @@ __device__ __forceinline__ float gauss(float c2, float na, float nb, float dot) 
   return __builtin_amdgcn_exp2f(-c2 * fmaxf(na + nb - 2.0f * dot, 0.0f));
 }
 
+// Bound by the FP32 matrix instructions and by its loads, which a second
+// workgroup of the CU covers (93 KB of LDS for any unit at 128 components
+// allowed one: 1006 us for 8,192 steps x 4,096 entries of several detectors,
+// 683 us with two).
 // Strip tile: members 32 (qa + 4 group) .. + 127 against the 128 entries from
 // dlo on.  Wave w has members 16 w .. 16 w + 15 as MFMA columns in registers
 // (lane (c, g): components g Q .. g Q + Q - 1 of member c), the entries are
@@ -338,6 +348,14 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_table_kernel(const Block
   const int2 it = items[blockIdx.x];
   const BlockJob j = jobs[it.x];
   prepare_unit(j, cm, it.y, lds);
+}
+
+// Dictionaries of jobs whose preparation leaves the model's arrays alone: it
+// may run beside a detection with the model the training replaces.
+__global__ __launch_bounds__(kPrepThreads) void model_table_kernel(const BlockJob* jobs) {
+  const BlockJob j = jobs[blockIdx.y];
+  if ((int)blockIdx.x * kDictSlots >= j.cap) return;
+  dict_unit(source_of(j, 0), j.dict, blockIdx.x * kDictSlots);
 }
 
 // The dictionary of a continued model, after its training.
@@ -899,6 +917,12 @@ bool general(const TrainCommon& cm, bool typed) {
 
 }  // namespace
 
+// Windows of up to 33 samples (the members and the entering block are a wave's
+// 64 lanes) and capacities of at least 96 (an entry that leaves must be of a
+// block already in the dictionary).  1,024 steps, step by step just outside
+// and in blocks just inside: K=4 2M=16 at capacity 95 and 96 1604 and 126 us
+// (W=16), at W 34 and 33 2106 and 179 us; K=16 2M=128 8395 and 158 us, 11509
+// and 205 us.
 bool train_in_blocks(int W, int cap) { return W <= kMaxWindow && cap >= kMinCap; }
 
 // Entries a strip covers: those older than the two blocks in the lanes.
@@ -929,6 +953,7 @@ void train_block_job(BlockJob& j, int P, int M2, int K, int cap, bool continued,
   j.qa = 0;
   j.qb = blocks_of(P);
   j.write_dict = continued ? 0 : 1;
+  j.apart = 0;
   unsigned char* ws = static_cast<unsigned char*>(workspace);
   j.header = reinterpret_cast<int32_t*>(ws);
   j.carry = reinterpret_cast<float*>(ws + 256);
@@ -985,6 +1010,13 @@ hipError_t launch_train_prepare_table(const BlockJob* jobs, const int2* items, i
   hipError_t e = set_lds(prepare_table_kernel, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(prepare_table_kernel, dim3(n), dim3(kPrepThreads), lds, s, jobs, items, cm);
+  return hipGetLastError();
+}
+
+hipError_t launch_train_model_table(const BlockJob* jobs, int n, int max_cap, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(model_table_kernel, dim3((max_cap + kDictSlots - 1) / kDictSlots, n), dim3(kPrepThreads), 0, s,
+                     jobs);
   return hipGetLastError();
 }
 

@@ -93,9 +93,17 @@ def test_block_edges(K, M, P, W, cap):
         assert worst <= REL_TOL
         np.testing.assert_array_equal(again[0], first[0])
         np.testing.assert_array_equal(again[3], first[3])
-    # a batch of one: the same bits
+    # a batch of one: the same bits, the model's arrays left alone until it trains
     b = A.Model(2 * M, K, cap, DEV, 0.5)
-    A.Batch(p, [A.BatchItem(model=b, rx_pilot=rx[:P].contiguous(), sym_pilot=sym[:P].contiguous(), sigma2=0.5)]).train()
+    for t in (b.dict, b.alpha, b.w, b.packed):
+        t.fill_(7)
+    b.state.copy_(torch.tensor([1, 2, 3, 4], dtype=torch.int32))
+    before = [t.clone() for t in (b.dict, b.alpha, b.w, b.packed, b.state[:3])]
+    batch = A.Batch(p, [A.BatchItem(model=b, rx_pilot=rx[:P].contiguous(), sym_pilot=sym[:P].contiguous(), sigma2=0.5)])
+    batch.kernel_rows()
+    for x, y in zip(before, (b.dict, b.alpha, b.w, b.packed, b.state[:3])):
+        assert torch.equal(x, y)
+    batch.train_prepared()
     if W <= 33 and cap >= 96:
         for x, y in zip(first, model_bytes(b, data)):
             np.testing.assert_array_equal(x, y)
