@@ -356,9 +356,7 @@ def pocs(rx_pilot, sym_pilot, params: Params, radius: float, cycles: int, model:
             cp.init = init
             sizes.append(library().apsm_train_scratch_bytes(ctypes.byref(cp), M2, K, P, 1))
         cp.init = first
-        workspace = torch.empty(max(sizes), dtype=torch.uint8, device=model.dict.device)
-        if stream is not None:
-            workspace.record_stream(stream)
+        workspace = _device_bytes(max(sizes), model.dict.device, stream)
     m = model._c()
     rc = library().apsm_pocs(ctypes.byref(cp), M2, K, P, rx_pilot.data_ptr(), sym_pilot.data_ptr(),
                              ctypes.byref(m), float(radius), int(cycles), workspace.data_ptr(), workspace.numel(),
@@ -400,17 +398,23 @@ def shutdown() -> None:
     library().apsm_shutdown()
 
 
-def _train_scratch(p: _CParams, M2: int, K: int, P: int, n: int, device, stream):
-    """Scratch for apsm_train_scratch from torch's allocator (None where the
-    shape has no use for one), held until `stream` has passed its use."""
+def _device_bytes(nbytes: int, device, stream):
+    """Uninitialised device memory for work on `stream` (None: the current
+    one), from that stream's pool of torch's allocator: a later owner's work
+    is ordered after it."""
     torch = _torch()
+    if stream is None:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(int(stream.cuda_stream), device=device)
+    with torch.cuda.stream(stream):
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+
+
+def _train_scratch(p: _CParams, M2: int, K: int, P: int, n: int, device, stream):
+    """Scratch for apsm_train_scratch (None where the shape has no use for one)."""
     nbytes = library().apsm_train_scratch_bytes(ctypes.byref(p), M2, K, P, n)
-    if not nbytes:
-        return None
-    t = torch.empty(nbytes, dtype=torch.uint8, device=device)
-    if stream is not None:
-        t.record_stream(stream)
-    return t
+    return _device_bytes(nbytes, device, stream) if nbytes else None
 
 
 def train(rx_pilot, sym_pilot, params: Params, model: Optional[Model] = None, stream=None) -> Model:
