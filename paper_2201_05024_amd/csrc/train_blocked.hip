@@ -43,6 +43,12 @@ constexpr int kThreads = 64 * (kSerial + kHelpers);
 constexpr int kPartFloats = kHelpers * kBlk * kSerial;
 constexpr int kMinCap = 96;
 
+// Carried from one range of blocks to the next, per user: C [64], x [32] and
+// -1 / kappa [32] of the lanes, then v [M2] of every user.  No two workgroups
+// share a word of it: the groups of a launch start and end in any order, so
+// what one writes at its end another may not have read yet.
+constexpr int kCarryX = 64, kCarryIkn = 96, kCarry = 128;
+
 // A block's image in the workspace: matrix and pending image, -1 / kappa(r, r)
 // of its members, then the [step][lane] eviction values (whole KiB each).
 constexpr int kIknAt = kImage, kEvAt = kIknAt + 256;
@@ -719,12 +725,13 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
   // ones, else none and w / wL or 0
   if (first && cm.init != kInitContinue)
     for (size_t e = tid; e < (size_t)cap * nu; e += kThreads) alpha[e / nu * Kt + k0 + e % nu] = 0.0f;
-  float* const carry = j.carry;             // per user C [64], x [32]; v [Kt][M2]; -1 / kappa of the last block
+  auto carry_of = [&](int u) { return j.carry + (size_t)(k0 + u) * kCarry; };
+  float* const carry_v = j.carry + (size_t)Kt * kCarry;
   for (int e = tid; e < kSerial * M2P; e += kThreads) {
     const int u = e / M2P, m = e - u * M2P;
     float v = 0.0f;
     if (u < nu && m < M2) {
-      if (!first) v = carry[(size_t)Kt * 96 + (k0 + u) * M2 + m];
+      if (!first) v = carry_v[(size_t)(k0 + u) * M2 + m];
       else if (cm.init != kInitZero) v = gmem(j.w)[(size_t)(k0 + u) * M2 + m] / cm.wl;
     }
     vlin[e] = v;
@@ -763,15 +770,16 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
     s.d = kBlk * (j.qa - 2) + lane;
     if (active) {
       if (!first) {
-        s.C = carry[(k0 + u) * 96 + lane];
-        s.x = upper ? carry[(k0 + u) * 96 + 64 + il] : 0.0f;
+        const float* carry = carry_of(u);
+        s.C = carry[lane];
+        s.x = upper ? carry[kCarryX + il] : 0.0f;
+        s.ikn = upper ? carry[kCarryIkn + il] : 0.0f;
         if constexpr (GEN)
           if (upper && s.d >= 0 && s.d < T)
             s.kind = typed ? gmem(j.st)[((size_t)(s.d >> 1) * Kt + k0 + u) * 2 + (s.d & 1)] : 0;
       } else if (n0 + s.d >= 0) {
         s.C = cval((n0 + s.d) % cap, u);
       }
-      if (!first && upper) s.ikn = carry[(size_t)Kt * (96 + M2) + il];
     }
     for (int q = j.qa; q < j.qb; ++q) {
       __syncthreads();
@@ -816,9 +824,10 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
     }
     if (active) {
       if (!last) {
-        carry[(k0 + u) * 96 + lane] = s.C;
-        if (upper) carry[(k0 + u) * 96 + 64 + il] = s.x;
-        if (upper && k0 + u == 0) carry[(size_t)Kt * (96 + M2) + il] = s.ikn;
+        float* carry = carry_of(u);
+        carry[lane] = s.C;
+        if (upper) carry[kCarryX + il] = s.x;
+        if (upper) carry[kCarryIkn + il] = s.ikn;
       }
       if (__ballot(!(s.bad == 0.0f)) != 0 && lane == 0) atomicOr(j.state + 3, APSM_FLAG_TRAIN_NONFINITE);
     }
@@ -857,7 +866,7 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
     const int u = e / M2, m = e - u * M2;
     const float v = vlin[u * M2P + m];
     if (last) gmem(j.w)[(size_t)(k0 + u) * M2 + m] = cm.wl * v;
-    else carry[(size_t)Kt * 96 + (k0 + u) * M2 + m] = v;
+    else carry_v[(size_t)(k0 + u) * M2 + m] = v;
   }
   if (last && k0 == 0 && tid == 0) {
     const int Tg = n0 + T;                  // samples seen in all
@@ -899,7 +908,7 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Workspace of one detector: header, carried lanes, then per block its image
 // and strip.
-size_t head_bytes(int M2, int K) { return align256(256 + ((size_t)K * (96 + M2) + kBlk) * sizeof(float)); }
+size_t head_bytes(int M2, int K) { return align256(256 + (size_t)K * (kCarry + M2) * sizeof(float)); }
 size_t block_bytes(int SW) { return ((size_t)kTrainImage + (size_t)SW * kBlk) * sizeof(float); }
 
 template <int NRW>
