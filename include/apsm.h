@@ -419,9 +419,10 @@ int apsm_batch_train(const apsm_batch_t* batch, void* stream);
 
 /* The two parts of apsm_batch_train, for callers that schedule them on
  * different streams.  apsm_batch_kernel_rows computes the kernel values of
- * the batch's pilots into the workspace (data-parallel, over the whole GPU;
- * of the models it clears the flags alone, so that it may run beside a
- * detection); apsm_batch_train_prepared trains and packs from them and must be
+ * the batch's pilots into the workspace (data-parallel, over the whole GPU).
+ * It leaves the models alone and may run beside a detection with them; only
+ * for a detector with window > 33 or dict_cap < 96 does it clear the flags
+ * word as well.  apsm_batch_train_prepared trains and packs from them and must be
  * ordered after that launch (same stream, or an event), with the pilots
  * unchanged in between.  Calls of one batch must not overlap. */
 int apsm_batch_kernel_rows(const apsm_batch_t* batch, void* stream);

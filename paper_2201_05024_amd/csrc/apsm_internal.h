@@ -184,7 +184,7 @@ size_t train_sweep_lds(int M2);
 hipError_t launch_train_prepare_table(const BlockJob* jobs, const int2* items, int n, const TrainCommon& cm,
                                       size_t lds_bytes, hipStream_t stream);
 // Before the sweeps of jobs prepared apart (jobs[0..n), max_cap the largest
-// capacity): their dictionaries.
+// capacity): their dictionaries, and their flags words cleared.
 hipError_t launch_train_model_table(const BlockJob* jobs, int n, int max_cap, hipStream_t stream);
 hipError_t launch_train_sweep_table(const BlockJob* jobs, const int2* items, int n, const TrainCommon& cm,
                                     size_t lds_bytes, hipStream_t stream);

@@ -235,7 +235,7 @@ void plan(apsm_batch& b, const apsm_params_t* p) {
       j.w = it.model.w;
       j.state = it.model.state;
       j.c2 = kLog2e / (2.0f * it.sigma2);
-      j.apart = 1;                            // apsm_batch_kernel_rows writes the workspace and clears the flags
+      j.apart = 1;                            // apsm_batch_kernel_rows writes the workspace alone
       b.block_max_cap = std::max(b.block_max_cap, j.cap);
       const int q = (int)b.bjobs.size(), units = train_prepare_units(j);
       for (int u = 0; u < units; ++u) b.prep_items.push_back(make_int2(q, u));

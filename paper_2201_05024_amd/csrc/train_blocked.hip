@@ -322,7 +322,7 @@ __device__ __forceinline__ void prepare_unit_w(const BlockJob& j, const TrainCom
   const Units u = units_of(j);
   const Source src = source_of(j, cm.init == kInitContinue ? __builtin_amdgcn_readfirstlane(gmem(j.state)[2]) : 0);
   if (unit == 0 && j.qa == 0 && threadIdx.x == 0) {
-    gmem(j.state)[3] = 0;                   // collects what the users' sweeps find
+    if (!j.apart) gmem(j.state)[3] = 0;     // collects what the users' sweeps find
     gmem(j.header)[0] = src.n0;             // for the sweeps: the first to end writes the new count
   }
   if (unit < u.images) {
@@ -356,10 +356,13 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_table_kernel(const Block
   prepare_unit(j, cm, it.y, lds);
 }
 
-// Dictionaries of jobs whose preparation leaves the model's arrays alone: it
-// may run beside a detection with the model the training replaces.
+// Dictionaries of jobs whose preparation leaves the model's arrays alone (it
+// may run beside a detection with the model the training replaces), and their
+// flags words, cleared right before the sweeps: what a detection raised since
+// the preparation is not this training's.
 __global__ __launch_bounds__(kPrepThreads) void model_table_kernel(const BlockJob* jobs) {
   const BlockJob j = jobs[blockIdx.y];
+  if (blockIdx.x == 0 && threadIdx.x == 0) gmem(j.state)[3] = 0;
   if ((int)blockIdx.x * kDictSlots >= j.cap) return;
   dict_unit(source_of(j, 0), j.dict, blockIdx.x * kDictSlots);
 }
