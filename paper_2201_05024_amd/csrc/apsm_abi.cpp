@@ -138,28 +138,31 @@ namespace apsm {
 namespace {
 
 // Training in blocks of detectors of one shape: each with its share of the
-// scratch buffer, or in its model's packed buffer.  False (nothing launched)
-// where a share does not hold one block.
+// scratch buffer, or (none, or a share too small for a block) in its model's
+// packed buffer.  False (nothing launched) where that does not hold one
+// block either.
 bool train_blocks(const apsm_params_t* p, const TrainCommon& cm, int M2, int K, int P, int n_inst,
                   const float* rx_pilot, const float* sym_pilot, const apsm_model_t* models, hipStream_t stream,
                   void* scratch, size_t scratch_bytes, hipError_t* err) {
   const int cap = p->dict_cap;
   const bool continued = p->init == APSM_INIT_CONTINUE;
   auto up = [](uintptr_t x) { return (x + 255) & ~uintptr_t(255); };
-  auto base = [&](int i) {
-    return scratch ? up(reinterpret_cast<uintptr_t>(scratch)) + (size_t)i * (scratch_bytes / n_inst & ~size_t(255))
-                   : up(reinterpret_cast<uintptr_t>(models[i].packed));
-  };
   size_t share = scratch_bytes / n_inst & ~size_t(255);
-  if (!scratch) {
+  int blocks = scratch ? train_blocks_in(M2, K, P, cap, continued, share) : 0;
+  const bool own = blocks >= 1;              // the scratch buffer is used
+  auto base = [&](int i) {
+    return own ? up(reinterpret_cast<uintptr_t>(scratch)) + (size_t)i * share
+               : up(reinterpret_cast<uintptr_t>(models[i].packed));
+  };
+  if (!own) {
     const size_t packed = packed_model_bytes(M2, K, cap);
     share = packed;
     for (int i = 0; i < n_inst; ++i) {
       const size_t skip = base(i) - reinterpret_cast<uintptr_t>(models[i].packed);
       share = std::min(share, packed - std::min(packed, skip));
     }
+    blocks = train_blocks_in(M2, K, P, cap, continued, share);
   }
-  const int blocks = train_blocks_in(M2, K, P, cap, continued, share);
   if (blocks < 1) return false;
   *err = hipSuccess;
   for (int b0 = 0; b0 < n_inst && *err == hipSuccess; b0 += kMaxBlockJobs) {

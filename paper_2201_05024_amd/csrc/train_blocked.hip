@@ -44,10 +44,12 @@ constexpr int kPartFloats = kHelpers * kBlk * kSerial;
 constexpr int kMinCap = 96;
 
 // Carried from one range of blocks to the next, per user: C [64], x [32] and
-// -1 / kappa [32] of the lanes, then v [M2] of every user.  No two workgroups
+// -1 / kappa [32] of the lanes and the C [32] of the block flushed last (the
+// next range's helper waves take it into v as inside a range, so that every
+// sum is in the same order wherever the ranges end), then v [M2] of every user.  No two workgroups
 // share a word of it: the groups of a launch start and end in any order, so
 // what one writes at its end another may not have read yet.
-constexpr int kCarryX = 64, kCarryIkn = 96, kCarry = 128;
+constexpr int kCarryX = 64, kCarryIkn = 96, kCarryFlushed = 128, kCarry = 160;
 
 // A block's image in the workspace: matrix and pending image, -1 / kappa(r, r)
 // of its members, then the [step][lane] eviction values (whole KiB each).
@@ -626,7 +628,7 @@ __device__ __forceinline__ void helper_role(const HelperArgs& h, const TrainComm
     // block q - 3, then v . r of the members joins the wave's sums (the wave
     // reads what its own lanes wrote: LDS operations of a wave are in order).
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    if (q > j.qa && q >= 3) {
+    if (q >= 3) {
       // lane: output o = (user, VW components), samples i = group, group + G, ..
       constexpr int OUT = kSerial * MR / VW, G = 64 / OUT;
       const int o = lane % OUT, uo = o / (MR / VW), mo = mlo + VW * (o % (MR / VW));
@@ -739,6 +741,10 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
     }
     vlin[e] = v;
   }
+  if (!first && tid < kBlk * kSerial) {
+    const int u = tid & 3;
+    flushed[tid] = u < nu ? carry_of(u)[kCarryFlushed + (tid >> 2)] : 0.0f;
+  }
   __syncthreads();
   const float qsW = qs[W];
 
@@ -835,7 +841,9 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
       if (__ballot(!(s.bad == 0.0f)) != 0 && lane == 0) atomicOr(j.state + 3, APSM_FLAG_TRAIN_NONFINITE);
     }
     __syncthreads();
-    take_linear(j.qb - 3, 0, tid);          // flushed at the last block's start
+    // flushed at the last block's start
+    if (last) take_linear(j.qb - 3, 0, tid);
+    else if (active && !upper) carry_of(u)[kCarryFlushed + il] = flushed[il * kSerial + u];
     __syncthreads();
     if (last && active) {
       // what is pending goes into the expansion
@@ -853,7 +861,7 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
       default: helper_role<GEN, 16>(h, cm); break;
     }
     __syncthreads();
-    take_linear(j.qb - 3, 0, tid);
+    if (last) take_linear(j.qb - 3, 0, tid);
     __syncthreads();
     __syncthreads();
   }
