@@ -302,7 +302,7 @@ inline int prep_floats_of(int M2) {
 }
 
 // Dictionary slots [s0, s0 + 256): the newest sample of each, zero for
-// unused slots (a continued model keeps what the block did not replace).
+// unused slots (a continued model keeps the entries that stay in use).
 __device__ __forceinline__ void dict_unit(const Source& src, float* dict, int s0) {
   const int cap = src.cap, T = src.T;
   const int slot = s0 + (threadIdx.x & (kDictSlots - 1));
@@ -310,7 +310,7 @@ __device__ __forceinline__ void dict_unit(const Source& src, float* dict, int s0
   int lag = (src.n0 + T - 1) % cap - slot;
   if (lag < 0) lag += cap;
   const int i = T - 1 - lag;
-  if (i < 0 && src.n0 > 0) return;
+  if (i < 0 && src.n0 + i >= 0) return;
   for (int m = threadIdx.x / kDictSlots; m < src.M2; m += kPrepThreads / kDictSlots)
     gmem(dict)[(size_t)m * cap + slot] = i >= 0 ? src.at(i, m) : 0.0f;
 }
@@ -728,8 +728,11 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
   }
   // coefficients and linear part at the start: the continued (or carried)
   // ones, else none and w / wL or 0
-  if (first && cm.init != kInitContinue)
-    for (size_t e = tid; e < (size_t)cap * nu; e += kThreads) alpha[e / nu * Kt + k0 + e % nu] = 0.0f;
+  // (slots that a continued model has not used yet are cleared as well: the
+  // strips read them, with kernel values of zero)
+  if (first)
+    for (size_t e = tid + (size_t)nold * nu; e < (size_t)cap * nu; e += kThreads)
+      alpha[e / nu * Kt + k0 + e % nu] = 0.0f;
   auto carry_of = [&](int u) { return j.carry + (size_t)(k0 + u) * kCarry; };
   float* const carry_v = j.carry + (size_t)Kt * kCarry;
   for (int e = tid; e < kSerial * M2P; e += kThreads) {

@@ -154,3 +154,29 @@ def test_noalloc_in_two_ranges_is_a_batch_of_one():
     A.Batch(p, [A.BatchItem(model=b, rx_pilot=rx, sym_pilot=sym)]).train()
     for x, y in zip(arrays(a), arrays(b)):
         np.testing.assert_array_equal(x, y)
+
+
+@pytest.mark.parametrize("cap", [96, 300])
+@pytest.mark.parametrize("seen", [0, 40])
+def test_unused_slots_are_not_read(cap, seen):
+    """A continued training does not read the slots that the model has not
+    used yet, and leaves them zero."""
+    print(f"[case] cap={cap} seen={seen}", flush=True)
+    K, M, W = 5, 8, 8
+    inst = synth.make_instance(synth.InstanceSpec(K=K, M=M, P=70, S=16, snr_db=12, seed=6400 + cap))
+    rx, sym = cuda(inst.rx_pilot), cuda(inst.sym_pilot)
+    p = A.Params(sigma2=0.5, eps=0.05, mu=1.0, window=W, dict_cap=cap)
+    q = A.Params(sigma2=0.5, eps=0.05, mu=1.0, window=W, dict_cap=cap, init="continue")
+    models = []
+    for fill in (0.0, float("nan")):
+        m = A.Model(2 * M, K, cap, DEV, 0.5)
+        if seen:
+            A.train(rx[:seen // 2].contiguous(), sym[:seen // 2].contiguous(), p, model=m)
+        m.alpha[seen:] = fill
+        m.dict[:, seen:] = fill
+        A.train(rx[20:30].contiguous(), sym[20:30].contiguous(), q, model=m)
+        models.append(arrays(m))
+        A.train(rx[30:].contiguous(), sym[30:].contiguous(), q, model=m)
+        models.append(arrays(m))
+    for a, b in zip(models[0] + models[1], models[2] + models[3]):
+        np.testing.assert_array_equal(a, b)
