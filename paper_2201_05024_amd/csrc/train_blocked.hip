@@ -280,7 +280,9 @@ __device__ __forceinline__ void image_unit(const BlockJob& j, const TrainCommon&
       for (int x = 0; x < 4; ++x) {
         const int il = 4 * e - kIknAt + x;
         const float kjj = k1[il * 97 + 64 + il];
-        v[x] = kBlk * q + il < src.T && kjj > 0.0f ? -1.0f / kjj : 0.0f;
+        // (-0 where it is not finite)
+        const bool in = kBlk * q + il < src.T;
+        v[x] = in && !__builtin_isfinite(kjj) ? -0.0f : in && kjj > 0.0f ? -1.0f / kjj : 0.0f;
       }
     }
     *reinterpret_cast<floatx4*>(out + 4 * e) = v;
@@ -402,37 +404,41 @@ __host__ __device__ inline SweepLds sweep_lds(int M2) {
 }
 
 struct Lane {
-  float x;         // running prediction less the target
+  float x;         // running prediction less the target (0 while it is held, see train_row)
   float C;         // pending coefficient
-  float ikn;       // -1 / kappa(r, r) (0 where that is not positive)
-  float bad;       // not finite once a prediction or a target was not
+  float ikn;       // -1 / kappa(r, r) (0 where that is not positive, -0 where it is not finite)
+  float held;      // that value as the member came in
+  float bad;       // not zero once a prediction, a target or a coefficient was not finite
   int kind;        // set kind
   int d;           // sample, negative for none
 };
 
 // The steps whose newest members lie in row A of the wave, t0 the place of
-// the first in its block, n0 its number: 16, or the cnt of the sequence's
-// end.  FULL: all 16, with the window full.  Position weights and hyperslabs.
+// the first in its block, n0 its number: 16, or those from lo to cnt (the
+// sequence's end, a held member's step).  FULL: all 16, with the window full.
+// Position weights and hyperslabs.  wild: members outside the window are
+// masked, not multiplied by a weight of zero (see train_row; not FULL).
 // Bound by the issue of one wave (about 6 cycles an instruction): with a
 // window of 17 to 32 samples 32 FMAs of the matrix-vector product and 14 more,
 // 3 with evictions; 290 cycles a step at W = 32 (375 with three rows of
 // products).  Unrolled, as the product's registers depend on the place.
 template <int NRW, int A, bool FULL, bool EV>
-__device__ __forceinline__ void steps(Lane& s, const float* kreg, int n0, int t0, int cnt, const TrainCommon& cm,
-                                      float qsW, const float* om, const float* qs, const float* ev, float aev,
-                                      int lane) {
+__device__ __forceinline__ void steps(Lane& s, const float* kreg, int n0, int t0, int lo, int cnt, bool wild,
+                                      const TrainCommon& cm, float qsW, const float* om, const float* qs,
+                                      const float* ev, float aev, int lane) {
 #pragma clang fp contract(off)
   const int W = cm.W;
-  float w = om[(16 * A - lane) & 63];       // weight of the lane's member (0 outside the window)
+  float w = om[(16 * A + lo - lane) & 63];  // weight of the lane's member (0 outside the window)
   const float iq = s.ikn * qsW;
   const float* e0 = ev + t0 * 64 + lane;
-  float kv = EV ? e0[0] : 0.0f;
+  float kv = EV ? e0[lo * 64] : 0.0f;
 #pragma unroll
   for (int it = 0; it < 16; ++it) {
-    if (!FULL && it >= cnt) continue;
+    if (!FULL && (it < lo || it >= cnt)) continue;
     const int n = n0 + it;
     // weight, mu / (omega_0 + .. + omega_{L-1}), -1 / kappa
     const float t = FULL || n + 1 >= W ? w * iq : w * (s.ikn * qs[n + 1]);
+    const bool out = !FULL && wild && w == 0.0f;
     w = from_below(w);                      // every member is one step older
     if constexpr (EV) {
       // the members in the window lose the entry that leaves; the next
@@ -441,7 +447,8 @@ __device__ __forceinline__ void steps(Lane& s, const float* kreg, int n0, int t0
       s.x = fmaf(-a, kv, s.x);
       kv = e0[(it + 1) * 64];
     }
-    const float c = slab_residual_pos(s.x, cm.eps) * t;
+    float c = slab_residual_pos(s.x, cm.eps) * t;
+    if constexpr (!FULL) c = out ? 0.0f : c;
     s.C += c;
     s.x += window_sum<A, NRW>(window_gather<A, NRW>(c, it, lane), kreg, it);
   }
@@ -449,25 +456,25 @@ __device__ __forceinline__ void steps(Lane& s, const float* kreg, int n0, int t0
 
 // The same with any set weights, relaxation and set kinds, one loop per
 // choice that is alike for all steps (EV: entries leave; POS: position
-// weights; EX: extrapolated), no branch inside: about 110 instructions a step
+// weights; EX: extrapolated; WILD: see train_row), no branch inside: about 110 instructions a step
 // of W = 20 with weights by violation and mixed kinds.  Not unrolled: 16 such
 // steps in one body, branches and all, were 29 KB of code a row and 1100
 // cycles a step.
-template <int NRW, int A, bool EV, bool POS, bool EX>
-__device__ __forceinline__ void general_loop(Lane& s, const float* kreg, int n0, int t0, int cnt,
+template <int NRW, int A, bool EV, bool POS, bool EX, bool WILD>
+__device__ __forceinline__ void general_loop(Lane& s, const float* kreg, int n0, int t0, int lo, int cnt,
                                              const TrainCommon& cm, float qsW, const float* om, const float* qs,
                                              const float* ev, float aev, int lane) {
 #pragma clang fp contract(off)
   const int W = cm.W;
-  float wv = om[(16 * A - lane) & 63];
+  float wv = om[(16 * A + lo - lane) & 63];
   const float inv_mu = 1.0f / cm.mu;
   const float* e0 = ev + t0 * 64 + lane;
-  float kv = EV ? e0[0] : 0.0f;
-  float qn = POS ? qs[min(n0 + 1, W)] : 0.0f;
+  float kv = EV ? e0[lo * 64] : 0.0f;
+  float qn = POS ? qs[min(n0 + lo + 1, W)] : 0.0f;
   const bool plane = s.kind == kSetPlane, above = s.kind != kSetLower, below = s.kind != kSetUpper;
   const bool active = cm.weights == kWeightsActive, held = s.d >= 0;
 #pragma unroll 1
-  for (int it = 0; it < cnt; ++it) {
+  for (int it = lo; it < cnt; ++it) {
     const float w = wv, q = qn;
     wv = from_below(wv);
     if constexpr (POS) qn = qs[min(n0 + it + 2, W)];
@@ -489,16 +496,18 @@ __device__ __forceinline__ void general_loop(Lane& s, const float* kreg, int n0,
       // boundary stays out, whatever the rounding)
       const float dist = fabsf(res), flag = dist > 1e-5f ? 1.0f : 0.0f;
       const float v = w > 0.0f && held ? (active ? flag : dist) : 0.0f;
-      const float tot = wave_sum(v), part = v / tot * beta;
-      u = tot > 0.0f ? part : 0.0f;
+      const float tot = wave_sum(v), share = v / tot;
+      if constexpr (WILD && EX) u = w > 0.0f ? (tot > 0.0f ? share : 0.0f) * beta : 0.0f;
+      else u = tot > 0.0f && (!WILD || w > 0.0f) ? share * beta : 0.0f;
     } else {
-      u = w * q * inv_mu * beta;
+      const float part = w * q * inv_mu * beta;
+      u = !WILD || w > 0.0f ? part : 0.0f;
     }
     const float ku = window_sum_rows<A, NRW>(u, kreg);
     float step = cm.mu;
     if constexpr (EX) {
       // M = sum_j q_j beta_j^2 K_jj / sum_jl u_j K_jl u_l (beta_j K_jj = -residual)
-      const float num = wave_sum(s.ikn != 0.0f ? -u * res : 0.0f);
+      const float num = wave_sum(s.ikn != 0.0f && (!WILD || w > 0.0f) ? -u * res : 0.0f);
       const float den = wave_sum(u != 0.0f ? u * ku : 0.0f);
       const float r = num / den;
       step = cm.mu * (den > 0.0f ? r : 1.0f);
@@ -507,11 +516,12 @@ __device__ __forceinline__ void general_loop(Lane& s, const float* kreg, int n0,
     s.x += step * ku;
   }
 }
-template <int NRW, int A>
-__device__ __forceinline__ void general_steps(Lane& s, const float* kreg, int n0, int t0, int cnt,
+template <int NRW, int A, bool WILD>
+__device__ __forceinline__ void general_steps(Lane& s, const float* kreg, int n0, int t0, int lo, int cnt,
                                               const TrainCommon& cm, float qsW, const float* om, const float* qs,
                                               bool evict, const float* ev, float aev, int lane) {
-#define APSM_GENERAL(EV, POS, EX) general_loop<NRW, A, EV, POS, EX>(s, kreg, n0, t0, cnt, cm, qsW, om, qs, ev, aev, lane)
+#define APSM_GENERAL(EV, POS, EX) \
+  general_loop<NRW, A, EV, POS, EX, WILD>(s, kreg, n0, t0, lo, cnt, cm, qsW, om, qs, ev, aev, lane)
   const bool pos = cm.weights == kWeightsPosition, ex = cm.extrapolate != 0;
   if (evict) {
     if (pos) { if (ex) APSM_GENERAL(true, true, true); else APSM_GENERAL(true, true, false); }
@@ -523,20 +533,52 @@ __device__ __forceinline__ void general_steps(Lane& s, const float* kreg, int n0
 #undef APSM_GENERAL
 }
 
+// A member whose target or prediction is not finite when it comes in is held
+// (x = 0) until its own step, so that the steps before are those of a
+// sequence that ends there.  What it makes infinite then must not reach the
+// members outside the window through a weight of zero: those older are masked
+// (`wild`), those to come get the NaN that the spoilt filter predicts for
+// them.  Where its own kernel value is not finite (-1 / kappa is -0), products
+// over whole rows (GEN) must not meet its kernel values before its step, so
+// these are out of kreg, and one register stands for them from then on (the
+// places that steps() multiplies have all come in).
+// All this once something was not finite (trouble); what it needs is derived
+// from the lanes then, as masks kept in scalar registers over the block cost
+// spills: K=16 2M=128, 4,096 steps 805 us without any of this, 820 so, 811 now.
 template <bool GEN, int NRW, int A>
-__device__ __forceinline__ void train_row(Lane& s, const float* kreg, int n0, int t0, int cnt, const TrainCommon& cm,
+__device__ __forceinline__ void train_row(Lane& s, float* kreg, int n0, int t0, int cnt, const TrainCommon& cm,
                                           float qsW, const float* om, const float* qs, bool evict, const float* ev,
-                                          float aev, int lane) {
-  if (cnt <= 0) return;
-  if constexpr (GEN) {
-    general_steps<NRW, A>(s, kreg, n0, t0, cnt, cm, qsW, om, qs, evict, ev, aev, lane);
-  } else if (cnt == 16 && n0 + 1 >= cm.W) {
-    if (evict) steps<NRW, A, true, true>(s, kreg, n0, t0, 16, cm, qsW, om, qs, ev, aev, lane);
-    else steps<NRW, A, true, false>(s, kreg, n0, t0, 16, cm, qsW, om, qs, ev, aev, lane);
-  } else if (evict) {
-    steps<NRW, A, false, true>(s, kreg, n0, t0, cnt, cm, qsW, om, qs, ev, aev, lane);
-  } else {
-    steps<NRW, A, false, false>(s, kreg, n0, t0, cnt, cm, qsW, om, qs, ev, aev, lane);
+                                          float aev, bool trouble, int lane) {
+  if (GEN && !trouble) {
+    if (cnt > 0) general_steps<NRW, A, false>(s, kreg, n0, t0, 0, cnt, cm, qsW, om, qs, evict, ev, aev, lane);
+    return;
+  }
+  if (!GEN && !trouble && cnt == 16 && n0 + 1 >= cm.W) {
+    if (evict) steps<NRW, A, true, true>(s, kreg, n0, t0, 0, 16, false, cm, qsW, om, qs, ev, aev, lane);
+    else steps<NRW, A, true, false>(s, kreg, n0, t0, 0, 16, false, cm, qsW, om, qs, ev, aev, lane);
+    return;
+  }
+  bool wild = false;
+  unsigned held = 0, spoilt = 0;            // members of the row, by place
+  if (trouble) {
+    wild = __ballot(!__builtin_isfinite(s.x)) != 0;
+    held = (unsigned)(__ballot(!__builtin_isfinite(s.held)) >> 16 * A) & 0xffffu;
+    spoilt = (unsigned)(__ballot(__float_as_uint(s.ikn) == 0x80000000u) >> 16 * A) & held;
+  }
+  for (int lo = 0; lo < cnt;) {
+    const bool released = held >> lo & 1;
+    const unsigned later = held >> lo >> 1;
+    const int next = released ? lo + 1 : later ? lo + 1 + __builtin_ctz(later) : cnt, hi = next < cnt ? next : cnt;
+    if (released) s.x = lane == 16 * A + lo ? s.held : s.x;
+    if (GEN && (spoilt >> lo & 1)) kreg[16 * A] = __builtin_nanf("");
+    if constexpr (GEN) general_steps<NRW, A, true>(s, kreg, n0, t0, lo, hi, cm, qsW, om, qs, evict, ev, aev, lane);
+    else if (evict) steps<NRW, A, false, true>(s, kreg, n0, t0, lo, hi, wild, cm, qsW, om, qs, ev, aev, lane);
+    else steps<NRW, A, false, false>(s, kreg, n0, t0, lo, hi, wild, cm, qsW, om, qs, ev, aev, lane);
+    if (released && __ballot(!__builtin_isfinite(s.C)) != 0) {
+      wild = true;
+      s.x = lane > 16 * A + lo ? __builtin_nanf("") : s.x;
+    }
+    lo = hi;
   }
 }
 
@@ -711,7 +753,9 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
   const bool first = j.qa == 0, last = j.qb == NB;
   // coefficient of user u of the group in a slot
   auto cval = [&](int slot, int u) { return u < nu ? alpha[(unsigned)(slot * Kt + k0 + u)] : 0.0f; };
-  auto set_coef = [&](int d, int u, float C) { alpha[(size_t)((n0 + d) % cap) * Kt + k0 + u] = cm.wg * C; };
+  float wg = cm.wg;
+  asm("" : "+v"(wg));                       // in a vector register: as a scalar it is reloaded, and waited for, in every block
+  auto set_coef = [&](int d, int u, float C) { alpha[(size_t)((n0 + d) % cap) * Kt + k0 + u] = wg * C; };
 
   if (tid < 64) {
     // weights past the window are 0; read at constant indices, straight from
@@ -796,6 +840,7 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
     for (int q = j.qa; q < j.qb; ++q) {
       __syncthreads();
       float aev = 0.0f;
+      bool trouble = false;
       const bool evict = n0 + kBlk * q + kBlk - 1 >= cap;
       if (active) {
         // the lower half's block goes into the expansion, the upper half
@@ -814,23 +859,36 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
         const int du = __float_as_int(upper_half(__int_as_float(s.d)));
         const float b = target[il * kSerial + u], ik = image[kIknAt + il];
         s.x = upper ? e - b : xu;
+        s.bad = fmaf(s.x, 0.0f, fmaf(s.C, 0.0f, s.bad));
         s.C = upper ? 0.0f : Cu;
         s.ikn = upper ? ik : iu;
         s.d = upper ? kBlk * q + il : du;
-        s.bad = fmaf(b, 0.0f, s.bad);
         if constexpr (GEN) {
           const int ku = __float_as_int(upper_half(__int_as_float(s.kind)));
           s.kind = upper ? kind[il * kSerial + u] : ku;
         }
         load_image<64>(image, lane, kreg);
         aev = aevict[il * kSerial + u];     // lane t: coefficient of the entry step t evicts
+        trouble = __ballot(!(s.bad == 0.0f)) != 0;
+        if (trouble) {
+          // something is not finite: see train_row
+          const bool lost = __ballot(!__builtin_isfinite(s.C) || !__builtin_isfinite(flushed[il * kSerial + u])) != 0;
+          s.held = lost ? __builtin_nanf("") : s.x;
+          if (upper) s.x = __builtin_isfinite(s.held) ? s.held : 0.0f;
+          if constexpr (GEN) {
+#pragma unroll
+            for (int r = 0; r < 64; ++r) kreg[r] = __builtin_isfinite(kreg[r]) ? kreg[r] : 0.0f;
+          }
+        }
       }
       __syncthreads();
       if (active) {
         const int nb = kBlk * q, rem = T - nb;
         const float* ev = evict_lds + (q & 1) * kEviction;
-        train_row<GEN, NRW, 2>(s, kreg, nb, 0, rem < 16 ? rem : 16, cm, qsW, om, qs, evict, ev, aev, lane);
-        train_row<GEN, NRW, 3>(s, kreg, nb + 16, 16, rem < 32 ? rem - 16 : 16, cm, qsW, om, qs, evict, ev, aev, lane);
+        train_row<GEN, NRW, 2>(s, kreg, nb, 0, rem < 16 ? rem : 16, cm, qsW, om, qs, evict, ev, aev, trouble,
+                               lane);
+        train_row<GEN, NRW, 3>(s, kreg, nb + 16, 16, rem < 32 ? rem - 16 : 16, cm, qsW, om, qs, evict, ev, aev,
+                               trouble, lane);
         s.bad = fmaf(s.x, 0.0f, s.bad);     // a residual that was not finite leaves its prediction so
       }
     }
