@@ -381,8 +381,10 @@ int apsm_batch_create(const apsm_params_t* params, const apsm_batch_item_t* item
  * lists of detection, claim counters and the kernel values of training (the
  * values of every pilot step against the dictionary entries it sees, computed
  * by one data-parallel launch before training: about 2P x (dict_cap + 256)
- * floats for each detector with window <= 33 and dict_cap >= 96, else for
- * dict_cap <= 8192 2P x (dict_cap + window)). */
+ * floats for each detector with window <= 33 and 96 <= dict_cap <= 8192; with
+ * window <= 33 and larger capacities APSM_TRAIN_SCRATCH_MAX bytes for all of
+ * them together, or room for a block of 32 steps each if that is more; else
+ * for dict_cap <= 8192 2P x (dict_cap + window) floats). */
 size_t apsm_batch_workspace_bytes(const apsm_batch_t* batch);
 
 /* Write the batch's tables into `workspace` (DEVICE, at least

@@ -173,8 +173,9 @@ int train_blocks_of(int P);
 int train_blocks_in(int M2, int K, int P, int cap, bool continued, size_t bytes);   // blocks a workspace holds
 size_t train_blocks_bytes(int M2, int K, int P, int cap, bool continued, int blocks);
 void train_block_job(BlockJob& j, int P, int M2, int K, int cap, bool continued, void* workspace);
+void train_block_range(BlockJob& j, int qa, int qb);   // blocks [qa, qb) of the job, in the same workspace
 hipError_t launch_train_blocks(BlockArgs& a, int blocks, hipStream_t stream);
-// The same for a device table of jobs (all blocks at once): items of the
+// The same for a device table of jobs: items of the
 // preparing launch are (job, unit < train_prepare_units), those of the sweep
 // (job, first user in steps of train_group_users), job < 0 for an empty place.
 int train_prepare_units(const BlockJob& j);
@@ -183,6 +184,9 @@ size_t train_prepare_lds(int M2);
 size_t train_sweep_lds(int M2);
 hipError_t launch_train_prepare_table(const BlockJob* jobs, const int2* items, int n, const TrainCommon& cm,
                                       size_t lds_bytes, hipStream_t stream);
+// Every unit of jobs[0..n), max_units the largest train_prepare_units.
+hipError_t launch_train_prepare_jobs(const BlockJob* jobs, int n, int max_units, const TrainCommon& cm,
+                                     size_t lds_bytes, hipStream_t stream);
 // Before the sweeps of jobs prepared apart (jobs[0..n), max_cap the largest
 // capacity): their dictionaries, and their flags words cleared.
 hipError_t launch_train_model_table(const BlockJob* jobs, int n, int max_cap, hipStream_t stream);

@@ -30,7 +30,14 @@ struct apsm_batch {
   apsm::TrainCommon cm{};
   std::vector<apsm::TrainJob> tjobs;
   size_t train_lds = 0;
-  std::vector<apsm::BlockJob> bjobs;          // training in blocks; workspace pointers set at bind
+  // training in blocks (workspace pointers set at bind): the jobs prepared
+  // apart, then round by round those of large capacities
+  std::vector<apsm::BlockJob> bjobs;
+  int apart = 0, apart_sweeps = 0;
+  struct Round {
+    int job, jobs, units, sweep, sweeps;      // first job and their number, largest unit count, sweep items
+  };
+  std::vector<Round> rounds;
   std::vector<size_t> block_off;              // byte offset of each job's workspace
   std::vector<int2> prep_items, sweep_items;  // (job, unit) and (job, first user; job < 0: empty place)
   size_t prep_lds = 0, sweep_lds = 0, block_bytes = 0;
@@ -208,6 +215,82 @@ void assign_detection(apsm_batch& b) {
   }
 }
 
+BlockJob block_job(const apsm_batch_item_t& it) {
+  BlockJob j{};
+  train_block_job(j, it.P, it.model.M2, it.model.K, it.model.dict_cap, false, nullptr);
+  j.rx = it.rx_pilot;
+  j.sym = it.sym_pilot;
+  j.dict = it.model.dict;
+  j.alpha = it.model.alpha;
+  j.w = it.model.w;
+  j.state = it.model.state;
+  j.c2 = kLog2e / (2.0f * it.sigma2);
+  return j;
+}
+
+// Sweeps of bjobs[q0 .. end), longest first; workgroups go round the eight
+// XCDs, so the user groups of a detector, which read the same kernel values,
+// are placed eight apart (places a detector with fewer groups leaves are
+// empty).
+void add_sweeps(apsm_batch& b, size_t begin) {
+  for (size_t q0 = begin; q0 < b.bjobs.size(); q0 += 8) {
+    const size_t q1 = std::min(q0 + 8, b.bjobs.size());
+    bool any = true;
+    for (int g = 0; any; ++g) {
+      any = false;
+      for (size_t q = q0; q < q1; ++q) any = any || g * b.bjobs[q].ku < b.bjobs[q].Kt;
+      if (!any) break;
+      for (size_t q = q0; q < q0 + 8; ++q) {
+        const bool in = q < q1 && g * b.bjobs[q].ku < b.bjobs[q].Kt;
+        b.sweep_items.push_back(make_int2(in ? (int)q : -1, in ? g * b.bjobs[q].ku : 0));
+      }
+    }
+  }
+}
+
+// Capacities up to which a detector's kernel values are all computed ahead,
+// apart from the training.  They take 2P x (capacity + 256) floats; past it
+// (100,000 pilots of capacity 65,536: 50 GB) the detectors share
+// APSM_TRAIN_SCRATCH_MAX bytes, or have room for a block each if that is
+// more, and train in rounds of as many blocks as fit.
+constexpr int kApartCap = 8192;
+
+void plan_rounds(apsm_batch& b, const std::vector<int>& large) {
+  if (large.empty()) return;
+  const size_t room = (size_t)APSM_TRAIN_SCRATCH_MAX / large.size();
+  struct Plan {
+    BlockJob j;
+    int blocks, all;
+    size_t off;
+  };
+  std::vector<Plan> plans;
+  for (int i : large) {
+    const auto& it = b.items[i];
+    Plan l{block_job(it), 0, train_blocks_of(it.P), b.block_bytes};
+    l.blocks = std::max(1, train_blocks_in(l.j.M2, l.j.Kt, it.P, l.j.cap, false, room));
+    b.block_bytes += align256(train_blocks_bytes(l.j.M2, l.j.Kt, it.P, l.j.cap, false, l.blocks));
+    b.prep_lds = std::max(b.prep_lds, train_prepare_lds(l.j.M2));
+    b.sweep_lds = std::max(b.sweep_lds, train_sweep_lds(l.j.M2));
+    plans.push_back(l);
+  }
+  for (int r = 0;; ++r) {
+    apsm_batch::Round d{(int)b.bjobs.size(), 0, 0, (int)b.sweep_items.size(), 0};
+    for (Plan& l : plans) {
+      if ((long long)r * l.blocks >= l.all) continue;
+      BlockJob j = l.j;
+      train_block_range(j, r * l.blocks, (r + 1) * l.blocks);
+      d.units = std::max(d.units, train_prepare_units(j));
+      b.bjobs.push_back(j);
+      b.block_off.push_back(l.off);
+    }
+    d.jobs = (int)b.bjobs.size() - d.job;
+    if (d.jobs == 0) break;
+    add_sweeps(b, d.job);
+    d.sweeps = (int)b.sweep_items.size() - d.sweep;
+    b.rounds.push_back(d);
+  }
+}
+
 void plan(apsm_batch& b, const apsm_params_t* p) {
   const int n = (int)b.items.size();
   fill_common(p, b.cm);
@@ -223,18 +306,15 @@ void plan(apsm_batch& b, const apsm_params_t* p) {
   std::vector<int> order(n);
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(), [&](int a, int c) { return tcost[a] > tcost[c]; });
+  std::vector<int> large;
   for (int i : order) {
     const auto& it = b.items[i];
     if (train_in_blocks(p->window, it.model.dict_cap)) {
-      BlockJob j{};
-      train_block_job(j, it.P, it.model.M2, it.model.K, it.model.dict_cap, false, nullptr);
-      j.rx = it.rx_pilot;
-      j.sym = it.sym_pilot;
-      j.dict = it.model.dict;
-      j.alpha = it.model.alpha;
-      j.w = it.model.w;
-      j.state = it.model.state;
-      j.c2 = kLog2e / (2.0f * it.sigma2);
+      if (it.model.dict_cap > kApartCap) {
+        large.push_back(i);
+        continue;
+      }
+      BlockJob j = block_job(it);
       j.apart = 1;                            // apsm_batch_kernel_rows writes the workspace alone
       b.block_max_cap = std::max(b.block_max_cap, j.cap);
       const int q = (int)b.bjobs.size(), units = train_prepare_units(j);
@@ -292,22 +372,10 @@ void plan(apsm_batch& b, const apsm_params_t* p) {
     b.train_lds = std::max(b.train_lds, train_lds_bytes(p->window, j.M2, j.K, j.cap));
   }
 
-  // Sweeps, longest first; workgroups go round the eight XCDs, so the user
-  // groups of a detector, which read the same kernel values, are placed eight
-  // apart (places a detector with fewer groups leaves are empty).
-  for (size_t q0 = 0; q0 < b.bjobs.size(); q0 += 8) {
-    const size_t q1 = std::min(q0 + 8, b.bjobs.size());
-    bool any = true;
-    for (int g = 0; any; ++g) {
-      any = false;
-      for (size_t q = q0; q < q1; ++q) any = any || g * b.bjobs[q].ku < b.bjobs[q].Kt;
-      if (!any) break;
-      for (size_t q = q0; q < q0 + 8; ++q) {
-        const bool in = q < q1 && g * b.bjobs[q].ku < b.bjobs[q].Kt;
-        b.sweep_items.push_back(make_int2(in ? (int)q : -1, in ? g * b.bjobs[q].ku : 0));
-      }
-    }
-  }
+  add_sweeps(b, 0);
+  b.apart = (int)b.bjobs.size();
+  b.apart_sweeps = (int)b.sweep_items.size();
+  plan_rounds(b, large);
 
   // packing: dual shapes get both packed images
   for (int i = 0; i < n; ++i) {
@@ -397,7 +465,7 @@ int apsm_batch_create(const apsm_params_t* params, const apsm_batch_item_t* item
   b->items.assign(items, items + n);
   plan(*b, &pc);
   if (b->ditems.size() > (size_t)INT32_MAX || b->witems.size() > (size_t)INT32_MAX ||
-      b->prep_items.size() > (size_t)INT32_MAX) {
+      b->prep_items.size() > (size_t)INT32_MAX || b->sweep_items.size() > (size_t)INT32_MAX) {
     delete b;
     return APSM_ERR_UNSUPPORTED;
   }
@@ -418,6 +486,7 @@ int apsm_batch_bind(apsm_batch_t* b, void* workspace, size_t bytes, void* stream
       BlockJob at{};
       train_block_job(at, bj[q].P, bj[q].M2, bj[q].Kt, bj[q].cap, false,
                       static_cast<unsigned char*>(workspace) + b->off_blocks + b->block_off[q]);
+      train_block_range(at, bj[q].qa, bj[q].qb);
       bj[q].header = at.header;
       bj[q].carry = at.carry;
       bj[q].images = at.images;
@@ -469,10 +538,15 @@ int apsm_batch_train(const apsm_batch_t* b, void* stream) {
 int apsm_batch_train_prepared(const apsm_batch_t* b, void* stream) {
   if (!b || !b->ws) return APSM_ERR_INVALID_ARG;
   hipStream_t s = (hipStream_t)stream;
-  hipError_t e = launch_train_model_table(at<BlockJob>(b, b->off_bj), (int)b->bjobs.size(), b->block_max_cap, s);
-  if (e == hipSuccess)
-    e = launch_train_sweep_table(at<BlockJob>(b, b->off_bj), at<int2>(b, b->off_si), (int)b->sweep_items.size(), b->cm,
-                                 b->sweep_lds, s);
+  const BlockJob* jobs = at<BlockJob>(b, b->off_bj);
+  const int2* sweeps = at<int2>(b, b->off_si);
+  hipError_t e = launch_train_model_table(jobs, b->apart, b->block_max_cap, s);
+  if (e == hipSuccess) e = launch_train_sweep_table(jobs, sweeps, b->apart_sweeps, b->cm, b->sweep_lds, s);
+  for (size_t r = 0; r < b->rounds.size() && e == hipSuccess; ++r) {
+    const apsm_batch::Round& d = b->rounds[r];
+    e = launch_train_prepare_jobs(jobs + d.job, d.jobs, d.units, b->cm, b->prep_lds, s);
+    if (e == hipSuccess) e = launch_train_sweep_table(jobs, sweeps + d.sweep, d.sweeps, b->cm, b->sweep_lds, s);
+  }
   if (e == hipSuccess)
     e = launch_train_rows(at<TrainJob>(b, b->off_rj), (int)b->rjobs.size(), b->cm, b->rows_lds, s);
   if (e == hipSuccess) e = launch_train_table(at<TrainJob>(b, b->off_t), (int)b->tjobs.size(), b->cm, b->train_lds, s);

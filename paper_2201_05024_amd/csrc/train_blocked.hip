@@ -360,6 +360,13 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_table_kernel(const Block
   prepare_unit(j, cm, it.y, lds);
 }
 
+// Workgroup (x, y): unit x of job y.
+__global__ __launch_bounds__(kPrepThreads) void prepare_jobs_kernel(const BlockJob* jobs, TrainCommon cm) {
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  const BlockJob j = jobs[blockIdx.y];
+  prepare_unit(j, cm, blockIdx.x, lds);
+}
+
 // Dictionaries of jobs whose preparation leaves the model's arrays alone (it
 // may run beside a detection with the model the training replaces), and their
 // flags words, cleared right before the sweeps: what a detection raised since
@@ -1042,6 +1049,13 @@ void train_block_job(BlockJob& j, int P, int M2, int K, int cap, bool continued,
   j.strips = j.images + (size_t)(j.qb - j.qa) * kTrainImage;
 }
 
+void train_block_range(BlockJob& j, int qa, int qb) {
+  j.qa = qa;
+  j.qb = std::min(qb, blocks_of(j.P));
+  j.strips = j.images + (size_t)(j.qb - j.qa) * kTrainImage;
+  if (qa > 0) j.write_dict = 0;
+}
+
 int train_prepare_units(const BlockJob& j) {
   const Units u = units_of(j);
   return u.images + u.groups * u.tiles + u.dict;
@@ -1061,13 +1075,7 @@ hipError_t launch_train_blocks(BlockArgs& a, int blocks, hipStream_t s) {
   a.groups = (j0.Kt + kSerial - 1) / kSerial;
   hipError_t e = set_lds(prepare_kernel, plds);
   for (int q = 0; q < NB && e == hipSuccess; q += blocks) {
-    for (int i = 0; i < a.n; ++i) {
-      BlockJob& j = a.jobs[i];
-      j.qa = q;
-      j.qb = std::min(q + blocks, NB);
-      j.strips = j.images + (size_t)(j.qb - j.qa) * kTrainImage;
-      if (q > 0) j.write_dict = 0;
-    }
+    for (int i = 0; i < a.n; ++i) train_block_range(a.jobs[i], q, q + blocks);
     hipLaunchKernelGGL(prepare_kernel, dim3(train_prepare_units(a.jobs[0]), a.n), dim3(kPrepThreads), plds, s, a);
     e = hipGetLastError();
     if (e != hipSuccess) break;
@@ -1091,6 +1099,15 @@ hipError_t launch_train_prepare_table(const BlockJob* jobs, const int2* items, i
   hipError_t e = set_lds(prepare_table_kernel, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(prepare_table_kernel, dim3(n), dim3(kPrepThreads), lds, s, jobs, items, cm);
+  return hipGetLastError();
+}
+
+hipError_t launch_train_prepare_jobs(const BlockJob* jobs, int n, int max_units, const TrainCommon& cm, size_t lds,
+                                     hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  hipError_t e = set_lds(prepare_jobs_kernel, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(prepare_jobs_kernel, dim3(max_units, n), dim3(kPrepThreads), lds, s, jobs, cm);
   return hipGetLastError();
 }
 
