@@ -299,14 +299,19 @@ def linear_mmse(h, n0: float, w=None, stream=None):
 _BALL_TRAIN_MAX = 64 << 20
 
 
+def _ball_bytes(model: "Model") -> int:
+    n = library().apsm_ball_workspace_bytes(model.M2, model.K, model.dict_cap)
+    if n == 0:
+        raise APSMError(ERR_UNSUPPORTED, "apsm_ball_workspace_bytes")
+    return n
+
+
 def ball_workspace(model: "Model"):
     """A device workspace for project_ball / pocs with this model's shape, with
     room for pocs to train about two dictionaries of samples in one launch
     (up to 64 MiB: more samples take more launches)."""
     torch = _torch()
-    n = library().apsm_ball_workspace_bytes(model.M2, model.K, model.dict_cap)
-    if n == 0:
-        raise APSMError(ERR_UNSUPPORTED, "apsm_ball_workspace_bytes")
+    n = _ball_bytes(model)
     p, keep = Params(sigma2=model.sigma2, window=1, dict_cap=model.dict_cap, init="continue")._c()
     t = library().apsm_train_scratch_bytes(ctypes.byref(p), model.M2, model.K, model.dict_cap, 1)
     del keep
@@ -318,8 +323,8 @@ def project_ball(model: "Model", radius: float, params: Params, workspace=None, 
     (apsm_project_ball, with params' sigma2, w_lin and w_gauss).  Returns the
     norms before the projection, a [K] float32 device tensor."""
     torch = _torch()
-    if workspace is None:
-        workspace = ball_workspace(model)
+    if workspace is None:                   # no training here: the projection's own room
+        workspace = torch.empty(_ball_bytes(model), dtype=torch.uint8, device=model.dict.device)
     if norms is None:
         norms = torch.empty(model.K, dtype=torch.float32, device=model.dict.device)
     _check(norms, torch.float32, (model.K,), "norms")
@@ -348,9 +353,7 @@ def pocs(rx_pilot, sym_pilot, params: Params, radius: float, cycles: int, model:
     cp, keep = params._c()
     if workspace is None:
         # room for the training of each cycle as well, the later ones continued
-        sizes = [library().apsm_ball_workspace_bytes(model.M2, model.K, model.dict_cap)]
-        if sizes[0] == 0:
-            raise APSMError(ERR_UNSUPPORTED, "apsm_ball_workspace_bytes")
+        sizes = [_ball_bytes(model)]
         first = cp.init
         for init in {first, INIT["continue"]} if cycles > 1 else {first}:
             cp.init = init
