@@ -359,7 +359,9 @@ def pocs(rx_pilot, sym_pilot, params: Params, radius: float, cycles: int, model:
             cp.init = init
             sizes.append(library().apsm_train_scratch_bytes(ctypes.byref(cp), M2, K, P, 1))
         cp.init = first
-        workspace = _device_bytes(max(sizes), model.dict.device, stream)
+        workspace = _scratch(max(sizes), model.dict.device, stream)
+        if workspace is None:
+            workspace = _device_bytes(sizes[0], model.dict.device, stream)
     m = model._c()
     rc = library().apsm_pocs(ctypes.byref(cp), M2, K, P, rx_pilot.data_ptr(), sym_pilot.data_ptr(),
                              ctypes.byref(m), float(radius), int(cycles), workspace.data_ptr(), workspace.numel(),
@@ -414,10 +416,19 @@ def _device_bytes(nbytes: int, device, stream):
         return torch.empty(nbytes, dtype=torch.uint8, device=device)
 
 
+def _scratch(nbytes: int, device, stream):
+    """Device memory that a training can do without (it works in the models'
+    own buffers then, in more launches): None where the device has no room."""
+    try:
+        return _device_bytes(nbytes, device, stream)
+    except _torch().cuda.OutOfMemoryError:
+        return None
+
+
 def _train_scratch(p: _CParams, M2: int, K: int, P: int, n: int, device, stream):
     """Scratch for apsm_train_scratch (None where the shape has no use for one)."""
     nbytes = library().apsm_train_scratch_bytes(ctypes.byref(p), M2, K, P, n)
-    return _device_bytes(nbytes, device, stream) if nbytes else None
+    return _scratch(nbytes, device, stream) if nbytes else None
 
 
 def train(rx_pilot, sym_pilot, params: Params, model: Optional[Model] = None, stream=None) -> Model:
