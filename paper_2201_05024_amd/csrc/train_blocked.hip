@@ -421,31 +421,33 @@ struct Lane {
 };
 
 // The steps whose newest members lie in row A of the wave, t0 the place of
-// the first in its block, n0 its number: 16, or those from lo to cnt (the
-// sequence's end, a held member's step).  FULL: all 16, with the window full.
-// Position weights and hyperslabs.  wild: members outside the window are
-// masked, not multiplied by a weight of zero (see train_row; not FULL).
+// the first in its block, n0 its number; position weights and hyperslabs.
+// kFull: all 16, with the window full.  kPart: up to cnt, the sequence's end.
+// kRare (see train_row): those from lo to cnt; wild: members outside the
+// window are masked, not multiplied by a weight of zero.
 // Bound by the issue of one wave (about 6 cycles an instruction): with a
 // window of 17 to 32 samples 32 FMAs of the matrix-vector product and 14 more,
 // 3 with evictions; 290 cycles a step at W = 32 (375 with three rows of
 // products).  Unrolled, as the product's registers depend on the place.
-template <int NRW, int A, bool FULL, bool EV>
+enum { kFull, kPart, kRare };
+template <int NRW, int A, int MODE, bool EV>
 __device__ __forceinline__ void steps(Lane& s, const float* kreg, int n0, int t0, int lo, int cnt, bool wild,
                                       const TrainCommon& cm, float qsW, const float* om, const float* qs,
                                       const float* ev, float aev, int lane) {
 #pragma clang fp contract(off)
+  constexpr bool FULL = MODE == kFull, RARE = MODE == kRare;
   const int W = cm.W;
-  float w = om[(16 * A + lo - lane) & 63];  // weight of the lane's member (0 outside the window)
+  float w = om[(16 * A + (RARE ? lo : 0) - lane) & 63];  // weight of the lane's member (0 outside the window)
   const float iq = s.ikn * qsW;
   const float* e0 = ev + t0 * 64 + lane;
-  float kv = EV ? e0[lo * 64] : 0.0f;
+  float kv = EV ? e0[RARE ? lo * 64 : 0] : 0.0f;
 #pragma unroll
   for (int it = 0; it < 16; ++it) {
-    if (!FULL && (it < lo || it >= cnt)) continue;
+    if (!FULL && it >= cnt || RARE && it < lo) continue;
     const int n = n0 + it;
     // weight, mu / (omega_0 + .. + omega_{L-1}), -1 / kappa
     const float t = FULL || n + 1 >= W ? w * iq : w * (s.ikn * qs[n + 1]);
-    const bool out = !FULL && wild && w == 0.0f;
+    const bool out = RARE && wild && w == 0.0f;
     w = from_below(w);                      // every member is one step older
     if constexpr (EV) {
       // the members in the window lose the entry that leaves; the next
@@ -455,7 +457,7 @@ __device__ __forceinline__ void steps(Lane& s, const float* kreg, int n0, int t0
       kv = e0[(it + 1) * 64];
     }
     float c = slab_residual_pos(s.x, cm.eps) * t;
-    if constexpr (!FULL) c = out ? 0.0f : c;
+    if constexpr (RARE) c = out ? 0.0f : c;
     s.C += c;
     s.x += window_sum<A, NRW>(window_gather<A, NRW>(c, it, lane), kreg, it);
   }
@@ -556,22 +558,24 @@ template <bool GEN, int NRW, int A>
 __device__ __forceinline__ void train_row(Lane& s, float* kreg, int n0, int t0, int cnt, const TrainCommon& cm,
                                           float qsW, const float* om, const float* qs, bool evict, const float* ev,
                                           float aev, bool trouble, int lane) {
-  if (GEN && !trouble) {
-    if (cnt > 0) general_steps<NRW, A, false>(s, kreg, n0, t0, 0, cnt, cm, qsW, om, qs, evict, ev, aev, lane);
+  if (cnt <= 0) return;
+  if (!trouble) {
+    if constexpr (GEN) {
+      general_steps<NRW, A, false>(s, kreg, n0, t0, 0, cnt, cm, qsW, om, qs, evict, ev, aev, lane);
+    } else if (cnt == 16 && n0 + 1 >= cm.W) {
+      if (evict) steps<NRW, A, kFull, true>(s, kreg, n0, t0, 0, 16, false, cm, qsW, om, qs, ev, aev, lane);
+      else steps<NRW, A, kFull, false>(s, kreg, n0, t0, 0, 16, false, cm, qsW, om, qs, ev, aev, lane);
+    } else if (evict) {
+      steps<NRW, A, kPart, true>(s, kreg, n0, t0, 0, cnt, false, cm, qsW, om, qs, ev, aev, lane);
+    } else {
+      steps<NRW, A, kPart, false>(s, kreg, n0, t0, 0, cnt, false, cm, qsW, om, qs, ev, aev, lane);
+    }
     return;
   }
-  if (!GEN && !trouble && cnt == 16 && n0 + 1 >= cm.W) {
-    if (evict) steps<NRW, A, true, true>(s, kreg, n0, t0, 0, 16, false, cm, qsW, om, qs, ev, aev, lane);
-    else steps<NRW, A, true, false>(s, kreg, n0, t0, 0, 16, false, cm, qsW, om, qs, ev, aev, lane);
-    return;
-  }
-  bool wild = false;
-  unsigned held = 0, spoilt = 0;            // members of the row, by place
-  if (trouble) {
-    wild = __ballot(!__builtin_isfinite(s.x)) != 0;
-    held = (unsigned)(__ballot(!__builtin_isfinite(s.held)) >> 16 * A) & 0xffffu;
-    spoilt = (unsigned)(__ballot(__float_as_uint(s.ikn) == 0x80000000u) >> 16 * A) & held;
-  }
+  bool wild = __ballot(!__builtin_isfinite(s.x)) != 0;
+  // members of the row, by place
+  const unsigned held = (unsigned)(__ballot(!__builtin_isfinite(s.held)) >> 16 * A) & 0xffffu;
+  const unsigned spoilt = (unsigned)(__ballot(__float_as_uint(s.ikn) == 0x80000000u) >> 16 * A) & held;
   for (int lo = 0; lo < cnt;) {
     const bool released = held >> lo & 1;
     const unsigned later = held >> lo >> 1;
@@ -579,8 +583,8 @@ __device__ __forceinline__ void train_row(Lane& s, float* kreg, int n0, int t0, 
     if (released) s.x = lane == 16 * A + lo ? s.held : s.x;
     if (GEN && (spoilt >> lo & 1)) kreg[16 * A] = __builtin_nanf("");
     if constexpr (GEN) general_steps<NRW, A, true>(s, kreg, n0, t0, lo, hi, cm, qsW, om, qs, evict, ev, aev, lane);
-    else if (evict) steps<NRW, A, false, true>(s, kreg, n0, t0, lo, hi, wild, cm, qsW, om, qs, ev, aev, lane);
-    else steps<NRW, A, false, false>(s, kreg, n0, t0, lo, hi, wild, cm, qsW, om, qs, ev, aev, lane);
+    else if (evict) steps<NRW, A, kRare, true>(s, kreg, n0, t0, lo, hi, wild, cm, qsW, om, qs, ev, aev, lane);
+    else steps<NRW, A, kRare, false>(s, kreg, n0, t0, lo, hi, wild, cm, qsW, om, qs, ev, aev, lane);
     if (released && __ballot(!__builtin_isfinite(s.C)) != 0) {
       wild = true;
       s.x = lane > 16 * A + lo ? __builtin_nanf("") : s.x;
