@@ -223,8 +223,8 @@ int apsm_train_batched(const apsm_params_t* params, int M2, int K, int P, int n_
  * training computes the kernel values of its steps ahead into it.  Without
  * one (apsm_train, apsm_train_batched), or with one that does not hold a block
  * of 32 steps of every detector, it works in the models' packed buffers, a few
- * blocks at a time; where those do not hold a block either (small shapes), the
- * steps run one by one.  The results are the same bits wherever the steps run
+ * blocks at a time; where those do not hold a block either (small shapes), and
+ * for a single pilot of a small shape, the steps run one by one.  The results are the same bits wherever the steps run
  * in blocks, and the same up to rounding one by one; a
  * buffer of apsm_train_scratch_bytes (pure host function; at most about
  * APSM_TRAIN_SCRATCH_MAX unless one block of steps needs more; 0 where the

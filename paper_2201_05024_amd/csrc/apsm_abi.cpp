@@ -193,7 +193,7 @@ bool train_blocks(const apsm_params_t* p, const TrainCommon& cm, int M2, int K, 
 // happens before the first launch.
 int train_impl(const apsm_params_t* p, int M2, int K, int P, int n_inst, const float* rx_pilot,
                const float* sym_pilot, const apsm_model_t* models, void* stream, void* scratch,
-               size_t scratch_bytes) {
+               size_t scratch_bytes, bool short_too) {
   if (int rc = check_params(p)) return rc;
   if (!rx_pilot || !sym_pilot || !models) return APSM_ERR_INVALID_ARG;
   if (P < 1 || M2 < 2 || (M2 & 1) || K < 1 || n_inst < 0) return APSM_ERR_SHAPE;
@@ -216,6 +216,7 @@ int train_impl(const apsm_params_t* p, int M2, int K, int P, int n_inst, const f
 
   hipError_t eb = hipSuccess;
   const bool in_blocks = n_inst > 0 && train_in_blocks(p->window, p->dict_cap) &&
+                         (short_too || !train_step_by_step(M2, K, p->dict_cap, P)) &&
                          train_blocks(p, a.cm, M2, K, P, n_inst, rx_pilot, sym_pilot, models, (hipStream_t)stream,
                                       scratch, scratch_bytes, &eb);
   if (eb != hipSuccess) return hip_status(eb);
@@ -263,7 +264,8 @@ int apsm_train_batched(const apsm_params_t* p, int M2, int K, int P, int n_inst,
 
 size_t apsm_train_scratch_bytes(const apsm_params_t* p, int M2, int K, int P, int n_inst) {
   if (check_params(p) != APSM_OK || P < 1 || M2 < 2 || (M2 & 1) || K < 1 || n_inst < 1 || M2 > APSM_MAX_M2 ||
-      K > APSM_MAX_K || (long long)P * 2 > (long long)INT32_MAX / 2 || !train_in_blocks(p->window, p->dict_cap))
+      K > APSM_MAX_K || (long long)P * 2 > (long long)INT32_MAX / 2 || !train_in_blocks(p->window, p->dict_cap) ||
+      train_step_by_step(M2, K, p->dict_cap, P))
     return 0;
   // all blocks at once where that stays within the bound, else as many as do
   const bool continued = p->init == APSM_INIT_CONTINUE;

@@ -169,6 +169,7 @@ hipError_t launch_train_rows(const TrainJob* jobs, int n, const TrainCommon& cm,
 // (256-byte aligned) for `blocks` blocks at a time, of train_blocks_of(P);
 // launch_train_blocks runs detectors of one shape, all ranges of blocks.
 bool train_in_blocks(int W, int cap);
+bool train_step_by_step(int M2, int K, int cap, int P);   // trainings too short for it
 int train_blocks_of(int P);
 int train_blocks_in(int M2, int K, int P, int cap, bool continued, size_t bytes);   // blocks a workspace holds
 size_t train_blocks_bytes(int M2, int K, int P, int cap, bool continued, int blocks);
@@ -310,9 +311,10 @@ DetectArgs detect_args(const apsm_model_t* model, float sigma2, int S, const flo
 // entry points: n_inst detectors of one shape, pilots contiguous per detector.
 // scratch: device workspace shared by the detectors, or null (training in
 // blocks then works in the models' packed buffers, which packing rewrites
-// afterwards, in as many ranges of blocks as their size asks for).
+// afterwards, in as many ranges of blocks as their size asks for).  short_too:
+// in blocks however short (the results are then those of a batch).
 int train_impl(const apsm_params_t* p, int M2, int K, int P, int n_inst, const float* rx_pilot,
                const float* sym_pilot, const apsm_model_t* models, void* stream, void* scratch = nullptr,
-               size_t scratch_bytes = 0);
+               size_t scratch_bytes = 0, bool short_too = false);
 
 }  // namespace apsm

@@ -1017,6 +1017,16 @@ bool general(const TrainCommon& cm, bool typed) {
 // and 205 us.
 bool train_in_blocks(int W, int cap) { return W <= kMaxWindow && cap >= kMinCap; }
 
+// A single pilot (two steps) of a detector whose dictionary the step-by-step
+// kernel holds in registers is trained faster by that one launch than by two
+// or three.  Training and packing of one pilot, in blocks and step by step,
+// from zero and continued: K=4 2M=16 capacity 256 21.4 and 15.2, 26.5 and
+// 15.9 us; K=6 2M=32 capacity 1,024 23.1 and 20.5, 31.8 and 22.6 us; K=16 of
+// that 24.1 and 28.0, 32.8 and 33.5 us; K=16 2M=128 capacity 2,048 33.7 and
+// 43.7, 58.5 and 73.9 us.  Two pilots from zero, the first two shapes: 21.6
+// and 18.3, 23.4 and 24.7 us.
+bool train_step_by_step(int M2, int K, int cap, int P) { return P == 1 && M2 <= 32 && K <= 8 && cap <= 1024; }
+
 // Entries a strip covers: those older than the two blocks in the lanes.
 static int strip_width(int P, int cap, bool continued) {
   const int by_cap = (std::max(cap - 2 * kBlk - 1, 0) + 15) / 16 * 16;

@@ -91,7 +91,7 @@ int apsm_train_noalloc(const apsm_params_t* p, int M2, int K, int P, const float
   if (hipError_t e = scratch_ptr(&base); e != hipSuccess) return hip_status(e);
 
   if (train_in_blocks(W, cap))              // in the array, as many blocks at a time as it holds
-    return train_impl(p, M2, K, P, 1, rx_pilot, sym_pilot, model, stream, base, kScratchBytes);
+    return train_impl(p, M2, K, P, 1, rx_pilot, sym_pilot, model, stream, base, kScratchBytes, true);
 
   TrainCommon cm{};
   fill_common(p, cm);
