@@ -498,10 +498,10 @@ int apsm_unrolled_backward(const apsm_unrolled_t* u, const float* theta, const f
  * For callers that cannot allocate device memory or pass a workspace: code
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * allocation.  Trains one detector exactly as apsm_batch_train trains a
- * one-item batch (the kernel rows of every pilot step, then training from
- * them, then packing: bit-identical results), with the job table and the
- * kernel rows in a static device array of the library instead of a
- * workspace.  Arguments, validation and results as for apsm_train; the
+ * one-item batch (the kernel values of the pilot steps, then training from
+ * them, then packing: bit-identical results), with the kernel values in a
+ * static device array of the library instead of a workspace; what the array
+ * does not hold at once is trained some blocks of steps at a time.  Arguments, validation and results as for apsm_train; the
  * shape must have dict_cap <= 4096 (else APSM_ERR_UNSUPPORTED) and need at
  * most APSM_NOALLOC_SCRATCH_BYTES of scratch: about 2P * (dict_cap + window)
  * * 4 bytes (else APSM_ERR_WORKSPACE).  Allocates nothing (no hipMalloc or

@@ -178,9 +178,8 @@ void train_block_range(BlockJob& j, int qa, int qb);   // blocks [qa, qb) of the
 hipError_t launch_train_blocks(BlockArgs& a, int blocks, hipStream_t stream);
 // The same for a device table of jobs: items of the
 // preparing launch are (job, unit < train_prepare_units), those of the sweep
-// (job, first user in steps of train_group_users), job < 0 for an empty place.
+// (job, first user in steps of its ku), job < 0 for an empty place.
 int train_prepare_units(const BlockJob& j);
-int train_group_users(int K);
 size_t train_prepare_lds(int M2);
 size_t train_sweep_lds(int M2);
 hipError_t launch_train_prepare_table(const BlockJob* jobs, const int2* items, int n, const TrainCommon& cm,

@@ -1077,7 +1077,6 @@ int train_prepare_units(const BlockJob& j) {
 
 size_t train_prepare_lds(int M2) { return (size_t)prep_floats_of(M2) * sizeof(float); }
 size_t train_sweep_lds(int M2) { return (size_t)sweep_lds(M2).total * sizeof(float); }
-int train_group_users(int K) { return (K + (K + kSerial - 1) / kSerial - 1) / ((K + kSerial - 1) / kSerial); }
 
 // Detectors of one shape, `blocks` of each held by their workspaces at a
 // time.

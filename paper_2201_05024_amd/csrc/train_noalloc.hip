@@ -1,10 +1,10 @@
-// Allocation-free training of one detector from precomputed kernel rows.
-//
-// The same two launches as the batch path (kernel rows of every pilot step
-// against the dictionary entries it sees, then the training kernel reading
-// one row per step) and the packing launch, with the job table, the tile
-// list and the rows in a static device array of this library instead of a
-// caller-provided workspace.  Each GPU the library runs on holds its own copy
+// Allocation-free training of one detector, by the launches that a batch of
+// one takes, with their workspace in a static device array of this library
+// instead of a caller-provided one: in blocks, as many at a time as the array
+// holds, for windows of up to 33 samples and capacities of at least 96; else
+// from precomputed kernel rows (every pilot step against the dictionary
+// entries it sees, then the training kernel reading one row per step), with
+// the job table and the tile list in the array too.  Each GPU the library runs on holds its own copy
 // of the array (kScratchBytes) until the process ends; every call on a GPU
 // uses that GPU's copy, so calls that overlap in time on one GPU race.
 #include <map>
