@@ -10,6 +10,8 @@
 // claims them one at a time from an atomic counter, so expensive tiles start
 // first and the short ones fill the tail; in the plain form workgroup b runs
 // item b and the hardware dispatcher hands out workgroups in that same order.
+#include <atomic>
+
 #include "detect_f16.h"
 
 namespace apsm {
@@ -130,12 +132,18 @@ int detect_tiles(int S) { return (S + f16::kWaves * 16 - 1) / (f16::kWaves * 16)
 // Compute units of the current device (256 if it cannot be queried).  The
 // persistent form of this kernel runs two workgroups per CU: the
 // specialisations use up to 256 VGPRs (two waves per SIMD) and two copies of
-// the largest LDS footprint fit a CU.
+// the largest LDS footprint fit a CU.  Asked for by every detection call, so
+// a device is queried once (threads that do so at once store the same number).
 int device_cus() {
+  constexpr int kDevices = 64;
+  static std::atomic<int> known[kDevices];
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 256;
+  const bool kept = dev >= 0 && dev < kDevices;
+  if (kept && (cus = known[dev].load(std::memory_order_relaxed)) > 0) return cus;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
     return 256;
+  if (kept) known[dev].store(cus, std::memory_order_relaxed);
   return cus;
 }
 
