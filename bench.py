@@ -76,8 +76,8 @@ MEASURED_TRAFFIC = {
     # FETCH_SIZE + WRITE_SIZE of detect_wide_batch_kernel<128> per dispatch,
     # both x1.000 by the 256 MiB copy of the same runs
     # (profiles/detect_wide_large_array_counters.md)
-    "bytes": int((57790446.4 * 1.0 + 15728640.2 * 1.0) * 1024),
-    "sources": {"paper_2201_05024_amd/csrc/detect_wide.h": "c389ac1db2d982c0685199c2e700e30b89e60446",
+    "bytes": int((57790555.7 * 1.0 + 15728640.2 * 1.0) * 1024),
+    "sources": {"paper_2201_05024_amd/csrc/detect_wide.h": "2e29ecc6886c739f09a12b019e8b5961077b3093",
                 "paper_2201_05024_amd/csrc/detect_wide.hip": "1fa21d1c5d93e52a0b61e6fd7b968546b2f1360d"},
 }
 

@@ -169,7 +169,7 @@ struct StageRegs {
 
 // x - h[0], y - h[1]: the mixed-precision FMA takes the half as it is (a
 // conversion and a subtraction otherwise, 8 of about 32 issue cycles a kernel
-// value: 676 -> 622 us at 1024 entries of 32 components, 2 M real vectors),
+// value: 679 -> 639 us at 1024 entries of 32 components, 2 M real vectors),
 // in one rounding, the same one.
 __device__ __forceinline__ float2v less_halves(float x, float y, const half2v& h) {
   float2v r;
@@ -226,6 +226,8 @@ __device__ __forceinline__ void detect_wide_tile(const A& a, const unsigned char
   const int e_d = __builtin_amdgcn_readfirstlane(hdr[0]);
   const int e_a = __builtin_amdgcn_readfirstlane(hdr[1]);
   const int e_w = __builtin_amdgcn_readfirstlane(hdr[2]);
+  // (counted into after a barrier; with one wave after this store, as the LDS
+  // operations of a wave are in order)
   if (tid < 16) werr[tid] = 0;
 
   // ---- the wave's tiles: B operands of its 16 vectors (vector col holds
