@@ -26,8 +26,8 @@
 // Bound by the recursion wave's instruction issue, and past about 2,000
 // entries by the helper waves' reading of the strips.  Step by step and so:
 // K=4 2M=16, 512 steps of W=16 808 -> 74 us; K=6 2M=32, 2,048 steps of W=32,
-// 1,024 entries 4.35 ms -> 323 us; K=16 2M=128, 4,096 steps, 2,048 entries
-// 102 ms -> 805 us.
+// 1,024 entries 4.35 ms -> 325 us; K=16 2M=128, 4,096 steps, 2,048 entries
+// 102 ms -> 811 us.
 #include <algorithm>
 
 #include "apsm_internal.h"
