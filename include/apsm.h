@@ -427,9 +427,10 @@ int apsm_batch_train(const apsm_batch_t* batch, void* stream);
  * the batch's pilots into the workspace (data-parallel, over the whole GPU).
  * It leaves the models alone and may run beside a detection with them; only
  * for a detector with window > 33 or dict_cap < 96 does it clear the flags
- * word as well.  apsm_batch_train_prepared trains and packs from them and must be
- * ordered after that launch (same stream, or an event), with the pilots
- * unchanged in between.  Calls of one batch must not overlap. */
+ * word as well.  apsm_batch_train_prepared trains and packs from them
+ * (detectors whose values are not all held at once compute them there) and
+ * must be ordered after that launch (same stream, or an event), with the
+ * pilots unchanged in between.  Calls of one batch must not overlap. */
 int apsm_batch_kernel_rows(const apsm_batch_t* batch, void* stream);
 int apsm_batch_train_prepared(const apsm_batch_t* batch, void* stream);
 
