@@ -26,8 +26,8 @@
 // Bound by the recursion wave's instruction issue, and past about 2,000
 // entries by the helper waves' reading of the strips.  Step by step and so:
 // K=4 2M=16, 512 steps of W=16 808 -> 74 us; K=6 2M=32, 2,048 steps of W=32,
-// 1,024 entries 4.35 ms -> 325 us; K=16 2M=128, 4,096 steps, 2,048 entries
-// 102 ms -> 811 us.
+// 1,024 entries 4.35 ms -> 323 us; K=16 2M=128, 4,096 steps, 2,048 entries
+// 102 ms -> 809 us.
 #include <algorithm>
 
 #include "apsm_internal.h"
@@ -421,33 +421,28 @@ struct Lane {
 };
 
 // The steps whose newest members lie in row A of the wave, t0 the place of
-// the first in its block, n0 its number; position weights and hyperslabs.
-// kFull: all 16, with the window full.  kPart: up to cnt, the sequence's end.
-// kRare (see train_row): those from lo to cnt; wild: members outside the
-// window are masked, not multiplied by a weight of zero.
+// the first in its block, n0 its number: 16, or the cnt of the sequence's
+// end.  FULL: all 16, with the window full.  Position weights and hyperslabs.
 // Bound by the issue of one wave (about 6 cycles an instruction): with a
 // window of 17 to 32 samples 32 FMAs of the matrix-vector product and 14 more,
 // 3 with evictions; 290 cycles a step at W = 32 (375 with three rows of
 // products).  Unrolled, as the product's registers depend on the place.
-enum { kFull, kPart, kRare };
-template <int NRW, int A, int MODE, bool EV>
-__device__ __forceinline__ void steps(Lane& s, const float* kreg, int n0, int t0, int lo, int cnt, bool wild,
-                                      const TrainCommon& cm, float qsW, const float* om, const float* qs,
-                                      const float* ev, float aev, int lane) {
+template <int NRW, int A, bool FULL, bool EV>
+__device__ __forceinline__ void steps(Lane& s, const float* kreg, int n0, int t0, int cnt, const TrainCommon& cm,
+                                      float qsW, const float* om, const float* qs, const float* ev, float aev,
+                                      int lane) {
 #pragma clang fp contract(off)
-  constexpr bool FULL = MODE == kFull, RARE = MODE == kRare;
   const int W = cm.W;
-  float w = om[(16 * A + (RARE ? lo : 0) - lane) & 63];  // weight of the lane's member (0 outside the window)
+  float w = om[(16 * A - lane) & 63];       // weight of the lane's member (0 outside the window)
   const float iq = s.ikn * qsW;
   const float* e0 = ev + t0 * 64 + lane;
-  float kv = EV ? e0[RARE ? lo * 64 : 0] : 0.0f;
+  float kv = EV ? e0[0] : 0.0f;
 #pragma unroll
   for (int it = 0; it < 16; ++it) {
-    if (!FULL && it >= cnt || RARE && it < lo) continue;
+    if (!FULL && it >= cnt) continue;
     const int n = n0 + it;
     // weight, mu / (omega_0 + .. + omega_{L-1}), -1 / kappa
     const float t = FULL || n + 1 >= W ? w * iq : w * (s.ikn * qs[n + 1]);
-    const bool out = RARE && wild && w == 0.0f;
     w = from_below(w);                      // every member is one step older
     if constexpr (EV) {
       // the members in the window lose the entry that leaves; the next
@@ -456,8 +451,7 @@ __device__ __forceinline__ void steps(Lane& s, const float* kreg, int n0, int t0
       s.x = fmaf(-a, kv, s.x);
       kv = e0[(it + 1) * 64];
     }
-    float c = slab_residual_pos(s.x, cm.eps) * t;
-    if constexpr (RARE) c = out ? 0.0f : c;
+    const float c = slab_residual_pos(s.x, cm.eps) * t;
     s.C += c;
     s.x += window_sum<A, NRW>(window_gather<A, NRW>(c, it, lane), kreg, it);
   }
@@ -546,33 +540,29 @@ __device__ __forceinline__ void general_steps(Lane& s, const float* kreg, int n0
 // (x = 0) until its own step, so that the steps before are those of a
 // sequence that ends there.  What it makes infinite then must not reach the
 // members outside the window through a weight of zero: those older are masked
-// (`wild`), those to come get the NaN that the spoilt filter predicts for
-// them.  Where its own kernel value is not finite (-1 / kappa is -0), products
-// over whole rows (GEN) must not meet its kernel values before its step, so
-// these are out of kreg, and one register stands for them from then on (the
-// places that steps() multiplies have all come in).
-// All this once something was not finite (trouble); what it needs is derived
-// from the lanes then, as masks kept in scalar registers over the block cost
-// spills: K=16 2M=128, 4,096 steps 805 us without any of this, 820 so, 811 now.
+// (WILD), those to come get the NaN that the spoilt filter predicts for them.
+// Where its own kernel value is not finite (-1 / kappa is -0), the products
+// must not meet its kernel values before its step, so these are out of kreg,
+// and one register stands for them from then on.  All this once something was
+// not finite (trouble), in the rolled loop, and derived from the lanes then:
+// masks kept in scalar registers over the block cost spills (K=16 2M=128,
+// 4,096 steps: 806 us without any of this, 820 so, 809 now), and unrolled steps
+// of their own 30 KB of code.
 template <bool GEN, int NRW, int A>
 __device__ __forceinline__ void train_row(Lane& s, float* kreg, int n0, int t0, int cnt, const TrainCommon& cm,
                                           float qsW, const float* om, const float* qs, bool evict, const float* ev,
                                           float aev, bool trouble, int lane) {
   if (cnt <= 0) return;
-  if (!trouble) {
+  if (__builtin_expect(!trouble, 1)) {
     if constexpr (GEN) {
       general_steps<NRW, A, false>(s, kreg, n0, t0, 0, cnt, cm, qsW, om, qs, evict, ev, aev, lane);
-    } else if (cnt == 16 && n0 + 1 >= cm.W) {
-      if (evict) steps<NRW, A, kFull, true>(s, kreg, n0, t0, 0, 16, false, cm, qsW, om, qs, ev, aev, lane);
-      else steps<NRW, A, kFull, false>(s, kreg, n0, t0, 0, 16, false, cm, qsW, om, qs, ev, aev, lane);
     } else if (evict) {
-      steps<NRW, A, kPart, true>(s, kreg, n0, t0, 0, cnt, false, cm, qsW, om, qs, ev, aev, lane);
+      steps<NRW, A, false, true>(s, kreg, n0, t0, cnt, cm, qsW, om, qs, ev, aev, lane);
     } else {
-      steps<NRW, A, kPart, false>(s, kreg, n0, t0, 0, cnt, false, cm, qsW, om, qs, ev, aev, lane);
+      steps<NRW, A, false, false>(s, kreg, n0, t0, cnt, cm, qsW, om, qs, ev, aev, lane);
     }
     return;
   }
-  bool wild = __ballot(!__builtin_isfinite(s.x)) != 0;
   // members of the row, by place
   const unsigned held = (unsigned)(__ballot(!__builtin_isfinite(s.held)) >> 16 * A) & 0xffffu;
   const unsigned spoilt = (unsigned)(__ballot(__float_as_uint(s.ikn) == 0x80000000u) >> 16 * A) & held;
@@ -581,14 +571,11 @@ __device__ __forceinline__ void train_row(Lane& s, float* kreg, int n0, int t0, 
     const unsigned later = held >> lo >> 1;
     const int next = released ? lo + 1 : later ? lo + 1 + __builtin_ctz(later) : cnt, hi = next < cnt ? next : cnt;
     if (released) s.x = lane == 16 * A + lo ? s.held : s.x;
-    if (GEN && (spoilt >> lo & 1)) kreg[16 * A] = __builtin_nanf("");
+    if (spoilt >> lo & 1) kreg[16 * A] = __builtin_nanf("");
     if constexpr (GEN) general_steps<NRW, A, true>(s, kreg, n0, t0, lo, hi, cm, qsW, om, qs, evict, ev, aev, lane);
-    else if (evict) steps<NRW, A, kRare, true>(s, kreg, n0, t0, lo, hi, wild, cm, qsW, om, qs, ev, aev, lane);
-    else steps<NRW, A, kRare, false>(s, kreg, n0, t0, lo, hi, wild, cm, qsW, om, qs, ev, aev, lane);
-    if (released && __ballot(!__builtin_isfinite(s.C)) != 0) {
-      wild = true;
-      s.x = lane > 16 * A + lo ? __builtin_nanf("") : s.x;
-    }
+    else if (evict) general_loop<NRW, A, true, true, false, true>(s, kreg, n0, t0, lo, hi, cm, qsW, om, qs, ev, aev, lane);
+    else general_loop<NRW, A, false, true, false, true>(s, kreg, n0, t0, lo, hi, cm, qsW, om, qs, ev, aev, lane);
+    if (released && __ballot(!__builtin_isfinite(s.C)) != 0) s.x = lane > 16 * A + lo ? __builtin_nanf("") : s.x;
     lo = hi;
   }
 }
@@ -785,9 +772,9 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
   // ones, else none and w / wL or 0
   // (slots that a continued model has not used yet are cleared as well: the
   // strips read them, with kernel values of zero)
-  if (first)
-    for (size_t e = tid + (size_t)nold * nu; e < (size_t)cap * nu; e += kThreads)
-      alpha[e / nu * Kt + k0 + e % nu] = 0.0f;
+  if (first && (tid & 3) < nu)
+    for (int slot = nold + (tid >> 2); slot < cap; slot += kThreads / kSerial)
+      alpha[(unsigned)(slot * Kt + k0 + (tid & 3))] = 0.0f;
   auto carry_of = [&](int u) { return j.carry + (size_t)(k0 + u) * kCarry; };
   float* const carry_v = j.carry + (size_t)Kt * kCarry;
   for (int e = tid; e < kSerial * M2P; e += kThreads) {
@@ -856,6 +843,7 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
       if (active) {
         // the lower half's block goes into the expansion, the upper half
         // moves down, q's members come in
+        const float b = target[il * kSerial + u], ik = image[kIknAt + il];
         const float f = pending_sum(image + kMatrixImage, s.C, lane);
         float sum = 0.0f;
 #pragma unroll
@@ -868,7 +856,6 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
         // (swaps outside the selects: they need every lane)
         const float xu = upper_half(s.x), Cu = upper_half(s.C), iu = upper_half(s.ikn);
         const int du = __float_as_int(upper_half(__int_as_float(s.d)));
-        const float b = target[il * kSerial + u], ik = image[kIknAt + il];
         s.x = upper ? e - b : xu;
         s.bad = fmaf(s.x, 0.0f, fmaf(s.C, 0.0f, s.bad));
         s.C = upper ? 0.0f : Cu;
@@ -881,25 +868,34 @@ __device__ __forceinline__ void sweep_body(const BlockJob& j, const TrainCommon&
         load_image<64>(image, lane, kreg);
         aev = aevict[il * kSerial + u];     // lane t: coefficient of the entry step t evicts
         trouble = __ballot(!(s.bad == 0.0f)) != 0;
-        if (trouble) {
+        if (__builtin_expect(trouble, 0)) {
           // something is not finite: see train_row
           const bool lost = __ballot(!__builtin_isfinite(s.C) || !__builtin_isfinite(flushed[il * kSerial + u])) != 0;
           s.held = lost ? __builtin_nanf("") : s.x;
           if (upper) s.x = __builtin_isfinite(s.held) ? s.held : 0.0f;
-          if constexpr (GEN) {
 #pragma unroll
-            for (int r = 0; r < 64; ++r) kreg[r] = __builtin_isfinite(kreg[r]) ? kreg[r] : 0.0f;
-          }
+          for (int r = 0; r < 64; ++r) kreg[r] = __builtin_isfinite(kreg[r]) ? kreg[r] : 0.0f;
         }
       }
       __syncthreads();
       if (active) {
         const int nb = kBlk * q, rem = T - nb;
         const float* ev = evict_lds + (q & 1) * kEviction;
-        train_row<GEN, NRW, 2>(s, kreg, nb, 0, rem < 16 ? rem : 16, cm, qsW, om, qs, evict, ev, aev, trouble,
-                               lane);
-        train_row<GEN, NRW, 3>(s, kreg, nb + 16, 16, rem < 32 ? rem - 16 : 16, cm, qsW, om, qs, evict, ev, aev,
-                               trouble, lane);
+        // full rows with the window full straight on, each in the code once
+        // (a body that only the first block runs is a microsecond of cold code)
+        if (!GEN && __builtin_expect(!trouble && rem >= 16 && nb + 1 >= W, 1)) {
+          if (evict) steps<NRW, 2, true, true>(s, kreg, nb, 0, 16, cm, qsW, om, qs, ev, aev, lane);
+          else steps<NRW, 2, true, false>(s, kreg, nb, 0, 16, cm, qsW, om, qs, ev, aev, lane);
+        } else {
+          train_row<GEN, NRW, 2>(s, kreg, nb, 0, rem < 16 ? rem : 16, cm, qsW, om, qs, evict, ev, aev, trouble, lane);
+        }
+        if (!GEN && __builtin_expect(!trouble && rem >= 32 && nb + 17 >= W, 1)) {
+          if (evict) steps<NRW, 3, true, true>(s, kreg, nb + 16, 16, 16, cm, qsW, om, qs, ev, aev, lane);
+          else steps<NRW, 3, true, false>(s, kreg, nb + 16, 16, 16, cm, qsW, om, qs, ev, aev, lane);
+        } else {
+          train_row<GEN, NRW, 3>(s, kreg, nb + 16, 16, rem < 32 ? rem - 16 : 16, cm, qsW, om, qs, evict, ev, aev,
+                                 trouble, lane);
+        }
         s.bad = fmaf(s.x, 0.0f, s.bad);     // a residual that was not finite leaves its prediction so
       }
     }
