@@ -4,8 +4,8 @@ Headline workload (the largest single-GPU configuration): the large array,
 batched.  16 detector instances, each with 16 users (16-QAM, Rapp PA p = 2,
 A_sat = 1, 20 dB) received on 64 antennas (2M = 128), 8192 pilot symbols
 (16,384 real training steps, window 32, dictionary capacity 8192) and
-4,194,304 data symbols.  One step trains the 16 detectors (kernel rows in one
-launch, training in one launch, packing) and detects all 16 x 4,194,304
+4,194,304 data symbols.  One step trains the 16 detectors (one launch that
+prepares the kernel values, one that trains, packing) and detects all 16 x 4,194,304
 received vectors with decisions and symbol-error counts (one launch, a
 workgroup per 128 received vectors).  Steps are pipelined over two model sets on two streams (the
 training of step k runs beside the detection of step k - 1); every step still
@@ -276,7 +276,7 @@ def run_large(args, dev, s_train, s_det):
         "train_ms_16_instances": {"kernel_rows": rows_ms, "training_and_packing": train_ms},
         "ms_per_step_serialized": serial_ms,
         "detect_ms_serialized_run": det1_ms,
-        "schedule": ("pipelined: the kernel rows of step k (one launch) precede the detection launch on the "
+        "schedule": ("pipelined: the preparation of step k (its kernel values, one launch) precedes the detection launch on the "
                      "detection stream; the training of step k (one launch, 64 four-user jobs) runs beside the "
                      "detection of step k-1 (one launch over all 16 instances, one workgroup per 128 received "
                      "vectors) on a second stream"),
@@ -629,7 +629,7 @@ def run_batched_mixed(args, dev, s_train, s_det):
     det_s = float(np.mean([a.elapsed_time(b) for a, b in ev])) / 1e3
 
     # Pipelined as the headline: a second model set detecting into the same
-    # outputs; the kernel rows of step k and the detection of step k - 1 on
+    # outputs; the preparation of step k and the detection of step k - 1 on
     # one stream, the training of step k on the other.  Plain-form detection,
     # so the trainings get CUs as detection workgroups retire.
     items2 = [A.BatchItem(model=A.Model(it.model.M2, it.model.K, it.model.dict_cap, dev, 0.5),
@@ -684,7 +684,7 @@ def run_batched_mixed(args, dev, s_train, s_det):
         "ms_per_step_batched": t_batched * 1e3,
         "pipelined_user_symbols_per_s": syms / t_pipe,
         "ms_per_step_pipelined": t_pipe * 1e3,
-        "schedule_pipelined": ("training of step k (kernel rows, then one training launch) beside the "
+        "schedule_pipelined": ("training of step k (preparation launches, then the training launches) beside the "
                                "plain-form detection of step k - 1 on a second stream, two model sets"),
         "graph_replay_ms": t_graph * 1e3,
         "train_ms_one_batch": e[0].elapsed_time(e[1]),

@@ -637,7 +637,7 @@ class Batch:
         return self
 
     def kernel_rows(self, stream=None) -> "Batch":
-        """First part of train(): the kernel rows of the pilots (whole GPU)."""
+        """First part of train(): the pilots' kernel values, as strips of blocks or as rows (whole GPU)."""
         rc = library().apsm_batch_kernel_rows(self._h, _stream_handle(stream))
         if rc:
             raise APSMError(rc, "apsm_batch_kernel_rows")
